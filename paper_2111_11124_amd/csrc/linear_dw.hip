@@ -417,10 +417,188 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
     }
 }
 
+// ---- binary32 tensors ------------------------------------------------------------------------------------------
+// The matrix cores multiply binary32 at a sixteenth of their bfloat16 rate, and a binary32 value is exactly the sum of
+// three bfloat16 values (its significand cut into three runs of eight bits, each with its own exponent).  The codes are
+// exact in bfloat16, a product of two bfloat16 values is exact in binary32, so three bfloat16 MFMAs against the three
+// parts add the same exact products as one binary32 MFMA, sixteen contraction steps per rounding of the sum instead of two.
+//
+// The parts are cut as the tile goes to LDS: three planes of bfloat16 in the tensor's own orientation, read back by the
+// transposing reads like the 16-bit kernel's.  128 x 128 tile of dW per workgroup, four waves of 64 x 64 (64 accumulator
+// registers: two workgroups per CU, one cutting and storing while the other multiplies), 32 contraction rows per stage,
+// two LDS buffers, the next stage's loads in flight while a stage is multiplied.
+//
+// Whole call, one-element-at-a-time binary32 MFMA kernel -> this one: 394 x (192 -> 768) 101 -> 17 us (latency of its
+// two stages and of the two launches), 2494 x (2880 -> 1392) 786 -> 92 us (217 TFLOP/s; a third of the bfloat16 rate is the
+// ceiling), 25216 x (384 -> 1536) 1354 -> 125 us.  Error against 64 bits as before or smaller (tiny block: 3.4e-6 -> 2.3e-6).
+struct DsCfg {
+    static constexpr int BN = 128, BK = 128;
+    static constexpr int PA = BN * 2 + 64, PB = BK + 32;   // LDS row pitches (bytes) of a plane of dy and of the codes
+    static constexpr int PLANE = kDwBM * PA;
+    static constexpr int STAGE = 3 * PLANE + kDwBM * PB;
+    static constexpr int ROWS_A = kThreads / (BN / 4);     // rows that the workgroup's threads cover with one 16-byte load each
+    static constexpr int A_VECS = kDwBM / ROWS_A;
+    static_assert(kDwBM * (BK / 16) == kThreads, "one 16-byte vector of codes per thread and stage");
+    static_assert(2 * STAGE <= 80 * 1024, "two workgroups per CU");
+};
+
+// x = a + b + c with a, b, c bfloat16 values in the upper halves of the results: the leading eight bits of what is left,
+// three times.  Cut, not rounded: no part can overflow, and each difference is exact.  An infinity is its own first part.
+__device__ __forceinline__ void cut_f32(float x, uint32_t &a, uint32_t &b, uint32_t &c)
+{
+    a = __float_as_uint(x) & 0xFFFF0000u;
+    const float r = __builtin_isinf(x) ? 0.0f : x - __uint_as_float(a);
+    b = __float_as_uint(r) & 0xFFFF0000u;
+    c = __float_as_uint(r - __uint_as_float(b));
+}
+
+// four signed codes -> four bfloat16 values q
+__device__ __forceinline__ v4s signed_codes_to_bf4(int raw)
+{
+    const uint32_t f0 = __float_as_uint(float(int(int8_t(raw)))), f1 = __float_as_uint(float(int(int8_t(raw >> 8))));
+    const uint32_t f2 = __float_as_uint(float(int(int8_t(raw >> 16)))), f3 = __float_as_uint(float(raw >> 24));
+    const v2i w = {int(__builtin_amdgcn_perm(f1, f0, 0x07060302u)), int(__builtin_amdgcn_perm(f3, f2, 0x07060302u))};
+    return __builtin_bit_cast(v4s, w);
+}
+
+__global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict__ xq, const float *__restrict__ dy, int64_t M, int K,
+                                                        int N, int tiles_n, int tiles_k, int splits, int64_t rows_per_split,
+                                                        float *__restrict__ P, float *__restrict__ S0)
+{
+    typedef DsCfg C;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int total = gridDim.x;                          // a multiple of 8
+    const int logical = int(blockIdx.x % kDwXcd) * (total / kDwXcd) + int(blockIdx.x / kDwXcd);
+    const int ntiles = tiles_n * tiles_k;
+    if (logical >= ntiles * splits) return;               // padding workgroups; uniform, before any barrier
+    const int split = logical / ntiles;
+    const int t = logical - split * ntiles;
+    const int tn = t / tiles_k, tk = t - tn * tiles_k;
+    const int n0 = tn * C::BN, kk0 = tk * C::BK;
+    const int64_t m_begin = int64_t(split) * rows_per_split;
+    const int64_t m_end = (m_begin + rows_per_split < M) ? m_begin + rows_per_split : M;
+
+    // loads: columns outside N or K are read from column 0 (they only reach results that are never written), rows at
+    // and behind m_end from the slice's last row, and go to LDS as zeros
+    const int row_a = tid >> 5, ca = (tid & 31) * 4, row_b = tid >> 3, cb = (tid & 7) * 16;
+    const int col_a = n0 + ca < N ? n0 + ca : 0, col_b = kk0 + cb < K ? kk0 + cb : 0;   // N % 4 == 0, K % 16 == 0
+    float4 va[C::A_VECS];
+    u32x4 vb;
+    auto load_stage = [&](int64_t m) {
+#pragma unroll
+        for (int i = 0; i < C::A_VECS; ++i) {
+            const int64_t r = m + row_a + i * C::ROWS_A;
+            va[i] = *reinterpret_cast<const float4 *>(dy + (r < m_end ? r : m_end - 1) * N + col_a);
+        }
+        const int64_t r = m + row_b;
+        vb = *reinterpret_cast<const u32x4 *>(xq + (r < m_end ? r : m_end - 1) * K + col_b);
+    };
+    float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);     // this thread's share of the row sums of its four columns of dy
+    auto store_stage = [&](int64_t m, unsigned char *st) {
+#pragma unroll
+        for (int i = 0; i < C::A_VECS; ++i) {
+            const int r = row_a + i * C::ROWS_A;
+            float4 v = va[i];
+            if (m + r >= m_end) v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+            const float x[4] = {v.x, v.y, v.z, v.w};
+            uint32_t p[3][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) cut_f32(x[j], p[0][j], p[1][j], p[2][j]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const u32x2 w = {__builtin_amdgcn_perm(p[q][1], p[q][0], 0x07060302u), __builtin_amdgcn_perm(p[q][3], p[q][2], 0x07060302u)};
+                *reinterpret_cast<u32x2 *>(st + q * C::PLANE + r * C::PA + ca * 2) = w;
+            }
+        }
+        const u32x4 zero4 = {0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4 *>(st + 3 * C::PLANE + row_b * C::PB + cb) = m + row_b < m_end ? vb : zero4;
+    };
+
+    const int wn = wave >> 1, wk = wave & 1;              // 2 x 2 waves of 64 x 64
+    const int blk = lane >> 4, sl = lane & 15;
+    const int a_off = ((blk >> 1) * 8 + (sl >> 2)) * C::PA + (wn * 64 + (blk & 1) * 16 + (sl & 3) * 4) * 2;
+    const int b_off = 3 * C::PLANE + ((blk >> 1) * 8 + (sl >> 1)) * C::PB + wk * 64 + (blk & 1) * 16 + (sl & 1) * 8;
+    v16f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    const int nst = m_end > m_begin ? int((m_end - m_begin + kDwBM - 1) / kDwBM) : 0;
+    if (nst > 0) {
+        load_stage(m_begin);
+        store_stage(m_begin, smem);
+        if (nst > 1) load_stage(m_begin + kDwBM);
+        __syncthreads();
+    }
+    for (int s = 0; s < nst; ++s) {
+        const unsigned char *cur = smem + (s & 1) * C::STAGE;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            v4s b[2][2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const v2i raw = __builtin_amdgcn_ds_read_tr8_b64_v2i32(MESA_LDS3(v2i, cur + b_off + ks * 16 * C::PB + j * 32));
+                b[j][0] = signed_codes_to_bf4(raw[0]);
+                b[j][1] = signed_codes_to_bf4(raw[1]);
+            }
+#pragma unroll
+            for (int q = 2; q >= 0; --q)                  // the smallest parts first
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const unsigned char *p = cur + q * C::PLANE + a_off + ks * 16 * C::PA + i * 64;
+                    const v4s a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(MESA_LDS3(v4s, p));
+                    const v4s a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(MESA_LDS3(v4s, p + 4 * C::PA));
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = DwElem<__bf16>::mfma(a0, a1, b[j][0], b[j][1], acc[i][j]);
+                }
+        }
+        if (s + 1 < nst) {
+            // the other buffer's last readers passed the barrier that ended stage s - 1
+            store_stage(m_begin + int64_t(s + 1) * kDwBM, smem + ((s + 1) & 1) * C::STAGE);
+            if (s + 2 < nst) load_stage(m_begin + int64_t(s + 2) * kDwBM);
+            __syncthreads();
+        }
+    }
+
+    float *Ps = P + int64_t(split) * N * K;
+    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int kk = kk0 + wk * 64 + j * 32 + col_l;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int n = n0 + wn * 64 + i * 32 + (v >> 2) * 8 + row_l + (v & 3);
+                if (n < N && kk < K) Ps[int64_t(n) * K + kk] = acc[i][j][v];
+            }
+        }
+    if (tk == 0) {                                        // uniform: the eight threads of a column group, in order
+        __syncthreads();                                  // the last stage's fragments have been read
+        float4 *part = reinterpret_cast<float4 *>(smem);
+        part[tid] = sum;
+        __syncthreads();
+        if (tid < C::BN / 4 && n0 + ca < N) {
+            float4 tot = part[tid];
+#pragma unroll
+            for (int r = 1; r < C::ROWS_A; ++r) {
+                const float4 v = part[tid + r * (C::BN / 4)];
+                tot.x += v.x; tot.y += v.y; tot.z += v.z; tot.w += v.w;
+            }
+            *reinterpret_cast<float4 *>(S0 + int64_t(split) * N + n0 + ca) = tot;
+        }
+    }
+}
+
 // The plain path: 32x32x2 binary32 MFMA, operands straight from global memory, one element at a time (a lane
 // needs a single value per operand, so no transposition and no alignment is involved).  Kept simple: it serves
-// binary32 tensors (the binary32 configuration is far too small to be a throughput case) and, for the 16-bit
-// types, widths that the vector loads of the kernel above cannot take (K not a multiple of 16, N not of 8).
+// widths that the vector loads of the kernels above cannot take (K not a multiple of 16, N not a multiple of 8, of 4
+// for binary32 tensors).
 constexpr int kDw32BN = 128, kDw32BK = 128;
 
 template <typename T>
@@ -578,12 +756,13 @@ __global__ __launch_bounds__(kThreads) void k_dw_reduce_any(const float *__restr
 }
 
 struct DwPlan {
-    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128; 2: the plain path
+    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128; 4: binary32, 128 x 128; 2: the plain path
     int bn, bk, tiles_n, tiles_k, splits, grid;
     int64_t rows_per_split;
 };
 
-static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
+// few: binary32 tensors with the slices of the 16-bit kernels (a workspace that holds no more)
+static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few = false)
 {
     DwPlan p;
     if (dt != MESA_F32 && K % 16 == 0 && N % 8 == 0) {
@@ -592,6 +771,8 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
         if (K % 256 == 0 || K > 1024) { p.variant = 0; p.bn = 256; p.bk = 256; }
         else if ((K <= 128 || N <= 128) && N % 256 != 0 && N % 256 <= 128) { p.variant = 3; p.bn = 128; p.bk = 128; }   // narrow K or N: no empty half tile in N
         else { p.variant = 1; p.bn = 256; p.bk = 128; }
+    } else if (dt == MESA_F32 && K % 16 == 0 && N % 4 == 0) {
+        p.variant = 4; p.bn = DsCfg::BN; p.bk = DsCfg::BK;
     } else {
         p.variant = 2;
         p.bn = kDw32BN;
@@ -600,10 +781,13 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
     p.tiles_n = int(ceil_div(N, p.bn));
     p.tiles_k = int(ceil_div(K, p.bk));
     const int64_t tiles = int64_t(p.tiles_n) * p.tiles_k;
-    // one workgroup per CU and round; slices of at least 256 contraction rows
-    int64_t splits = 256 / tiles;
+    // one workgroup per CU and round; slices of at least 256 contraction rows.  The binary32 kernel: two workgroups per
+    // CU, and slices down to two stages (the whole matrix is a few tiles at the widths it meets, and a stage's latency,
+    // not the matrix cores, is what a short slice costs).
+    const bool many = p.variant == 4 && !few;
+    int64_t splits = (many ? 512 : 256) / tiles;
     if (splits < 1) splits = 1;
-    int64_t max_splits = M / 256;
+    int64_t max_splits = M / (many ? 2 * kDwBM : 256);
     if (max_splits < 1) max_splits = 1;
     if (splits > max_splits) splits = max_splits;
     if (splits > 256) splits = 256;   // one workgroup per CU also where there is a single tile
@@ -615,11 +799,15 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
     return p;
 }
 
+static size_t dw_plan_bytes(const DwPlan &p, int64_t K, int64_t N)
+{
+    return size_t(p.splits) * (size_t(N) * size_t(K) + size_t(N)) * sizeof(float) + 16;
+}
+
 size_t linear_dw_ws_bytes(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
 {
     if (K <= 0 || N <= 0 || M < 0) return 16;
-    DwPlan p = dw_plan(M, K, N, dt);
-    return size_t(p.splits) * (size_t(N) * size_t(K) + size_t(N)) * sizeof(float) + 16;
+    return dw_plan_bytes(dw_plan(M, K, N, dt), K, N);
 }
 
 }  // namespace mesa
@@ -639,8 +827,9 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     // a thread's byte offsets inside a stage of 32 rows are 32-bit (32*K and 64*N_out), the reduction indexes N_out*K/4 in 32 bits
     if (K >= (int64_t(1) << 26) || N_out >= (int64_t(1) << 25) || (long double)K * (long double)N_out >= 2147483648.0L)
         return MESA_ERR_UNSUPPORTED;
-    if (!ws || !aligned16(ws) || ws_bytes < linear_dw_ws_bytes(M, K, N_out, dt)) return MESA_ERR_WORKSPACE;
     DwPlan p = dw_plan(M, K, N_out, dt);
+    if (p.variant == 4 && ws_bytes < dw_plan_bytes(p, K, N_out)) p = dw_plan(M, K, N_out, dt, true);
+    if (!ws || !aligned16(ws) || ws_bytes < dw_plan_bytes(p, K, N_out)) return MESA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *P = static_cast<float *>(ws);
     float *S0 = P + size_t(p.splits) * size_t(N_out) * size_t(K);
@@ -659,6 +848,9 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
                        p.rows_per_split, P, S0)
         MESA_FOR_DTYPE(dt, MESA_LAUNCH_DW_PLAIN);
 #undef MESA_LAUNCH_DW_PLAIN
+    } else if (p.variant == 4) {   // signed codes too
+        hipLaunchKernelGGL(k_dw_cut, dim3(p.grid), dim3(kThreads), 0, s, xq, static_cast<const float *>(dy), M, Ki, Ni, p.tiles_n,
+                           p.tiles_k, p.splits, p.rows_per_split, P, S0);
     } else if (dt == MESA_F16) {
         if (p.variant == 0) MESA_LAUNCH_DW(_Float16, 256, 256); else if (p.variant == 1) MESA_LAUNCH_DW(_Float16, 256, 128); else MESA_LAUNCH_DW(_Float16, 128, 128);
     } else {
