@@ -18,7 +18,7 @@
 // kept in the operand's own orientation; where that is not the orientation the MFMA wants, the
 // fragments come from the LDS transpose reads.  The next stage's loads are in flight while a stage
 // is multiplied.  binary16 or bfloat16 tensors (every kernel here takes the number type as a parameter);
-// binary32 tensors through one plain kernel (k_bmm_q_f32).
+// binary32 tensors run the general kernel on their three bfloat16 parts.
 //
 // That general kernel (k_bmm_q) serves every shape; dedicated kernels take the shapes that matter: k_attn_da,
 // k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths included, and
@@ -135,10 +135,36 @@ template <> struct BmNum<__bf16> {
     }
 };
 
+// binary32 tensors: a binary32 value is exactly the sum of three bfloat16 values (its significand cut into runs of eight
+// bits), a code q is exact in bfloat16 and a product of the two in binary32, so three bfloat16 MFMAs add the same exact
+// products as the binary32 MFMA, at sixteen times its rate and with one rounding of the sum per sixteen steps instead of
+// per two.  The contracted value is the signed code, as in the plain binary32 kernel.  Against that kernel (one element
+// per lane and load, straight from memory, a dependent load per two contraction steps) the four products and softmax's
+// backward took 140 -> 45 us at (2, 3, 197, 64), 257 -> 62 at (1, 12, 324, 64) and 312 -> 93 at (32, 6, 197, 64).
+template <> struct BmNum<float> {
+    static constexpr float kCentre = 128.0f;
+    static constexpr uint16_t kOne = 0x3F80u;
+    __device__ static __forceinline__ bm_v8h codes8(bm_v2i raw)
+    {
+        bm_v4u out;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const int x = raw[w];
+            const uint32_t f0 = __float_as_uint(float(int(int8_t(x)))), f1 = __float_as_uint(float(int(int8_t(x >> 8))));
+            const uint32_t f2 = __float_as_uint(float(int(int8_t(x >> 16)))), f3 = __float_as_uint(float(x >> 24));
+            out[2 * w] = __builtin_amdgcn_perm(f1, f0, 0x07060302u);
+            out[2 * w + 1] = __builtin_amdgcn_perm(f3, f2, 0x07060302u);
+        }
+        return __builtin_bit_cast(bm_v8h, out);
+    }
+    __device__ static __forceinline__ bm_v16f mfma(bm_v8h a, bm_v8h b, bm_v16f c) { return BmNum<__bf16>::mfma(a, b, c); }
+    __device__ static __forceinline__ float round(float v) { return v; }
+};
+
 struct BmmArgs {
-    const _Float16 *x;          // the plain operand (16-bit container: binary16 or bfloat16 bits)
+    const _Float16 *x;          // the plain operand (16-bit container: binary16 or bfloat16 bits; k_bmm_q<float>: binary32)
     const int8_t *y;            // the coded operand
-    _Float16 *c;                // output, row-major R x Cn per batch
+    _Float16 *c;                // output, row-major R x Cn per batch (of the plain operand's type)
     int64_t x_batch, y_batch, c_batch;   // elements per (sample, head)
     int R, Cn, Tn;              // output rows, output columns, contraction extent
     int64_t p_rs, p_ts;         // element strides of the view P(r, t)
@@ -163,18 +189,46 @@ struct BmmArgs {
 //          supply row k, and lane i receives column i).
 // `line` is the row of P or the column of Q.  Codes stay bytes in LDS and become binary16 (the signed
 // code itself, exact) in the fragment.  Row pitches are padded so that neither access conflicts.
-template <bool CODED> struct BmRaw;
-template <> struct BmRaw<false> { u32x4 w; };   // eight binary16
-template <> struct BmRaw<true> { u32x2 w; };    // eight codes
-
-template <bool CODED> struct BmElem;
-template <> struct BmElem<false> {
-    typedef _Float16 type;
-    static constexpr int kBytes = 2;
+//
+// binary32 (ET = float): eight elements are two 16-byte loads; the store cuts them into kPlanes = 3 bfloat16 parts, each a
+// tile of its own in LDS that is read like a 16-bit operand's.
+template <bool CODED, typename ET> struct BmElem {   // plain 16-bit operand
+    typedef _Float16 global_t, lds_t;
+    typedef u32x4 raw_t;        // eight elements as loaded
+    typedef u32x4 word_t;       // and as they lie in LDS
+    static constexpr int kEb = 2, kPlanes = 1;
+    __device__ static __forceinline__ void cut(const raw_t &v, word_t (&w)[kPlanes]) { w[0] = v; }
 };
-template <> struct BmElem<true> {
-    typedef int8_t type;
-    static constexpr int kBytes = 1;
+template <typename ET> struct BmElem<true, ET> {     // codes
+    typedef int8_t global_t, lds_t;
+    typedef u32x2 raw_t, word_t;
+    static constexpr int kEb = 1, kPlanes = 1;
+    __device__ static __forceinline__ void cut(const raw_t &v, word_t (&w)[kPlanes]) { w[0] = v; }
+};
+template <> struct BmElem<false, float> {
+    typedef float global_t;
+    typedef _Float16 lds_t;     // bfloat16 bits
+    struct raw_t { u32x4 lo, hi; };
+    typedef u32x4 word_t;
+    static constexpr int kEb = 2, kPlanes = 3;
+    // cut, not rounded: no part can overflow and every difference is exact; an infinity is its own first part
+    __device__ static __forceinline__ void cut(const raw_t &v, word_t (&w)[kPlanes])
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t part[3][2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float x = __uint_as_float(k < 2 ? v.lo[2 * k + j] : v.hi[2 * k - 4 + j]);
+                part[0][j] = __float_as_uint(x) & 0xFFFF0000u;
+                const float r = __builtin_isinf(x) ? 0.0f : x - __uint_as_float(part[0][j]);
+                part[1][j] = __float_as_uint(r) & 0xFFFF0000u;
+                part[2][j] = __float_as_uint(r - __uint_as_float(part[1][j]));
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) w[q][k] = __builtin_amdgcn_perm(part[q][1], part[q][0], 0x07060302u);
+        }
+    }
 };
 
 // Edges.  Rows of P / columns of Q beyond the extents produce output rows / columns that are never
@@ -184,13 +238,17 @@ template <> struct BmElem<true> {
 // other values: nothing waits on a load before its stage is due); a vector that was moved back to stay
 // inside the extent is written to LDS at the position it really came from (element by element: the
 // slots overlap the neighbouring vector's, with the same values), and zeros are written where required.
-template <bool CODED, bool TFAST> struct BmOperand {
-    typedef typename BmElem<CODED>::type E;
-    static constexpr int kEb = BmElem<CODED>::kBytes;
+template <bool CODED, bool TFAST, typename ET> struct BmOperand {
+    typedef BmElem<CODED, ET> Elem;
+    typedef typename Elem::global_t E;
+    typedef typename Elem::lds_t L;
+    typedef typename Elem::raw_t Raw;
+    typedef typename Elem::word_t W;
+    static constexpr int kEb = Elem::kEb, kPlanes = Elem::kPlanes;
     // bytes per LDS row: [line][t]: kBmT elements + 8 of padding; [t][line]: 64 elements + 32 of padding
     static constexpr int kPitch = TFAST ? (kBmT + 8) * kEb : (kBmTile + 32) * kEb;
-    static constexpr int kBytes = TFAST ? kBmTile * kPitch : kBmT * kPitch;
-    typedef decltype(BmRaw<CODED>::w) W;
+    static constexpr int kPlane = TFAST ? kBmTile * kPitch : kBmT * kPitch;
+    static constexpr int kBytes = kPlanes * kPlane;
 
     // tile-relative coordinates of vector idx: (line, t) of its first element
     __device__ static __forceinline__ void coord(int idx, int &line, int &t)
@@ -199,36 +257,42 @@ template <bool CODED, bool TFAST> struct BmOperand {
         else { t = idx / 8; line = (idx % 8) * 8; }
     }
     // lines >= 8 and tn >= 8 (checked by the entry points)
-    __device__ static __forceinline__ BmRaw<CODED> load(const E *base, int64_t line_stride, int64_t t_stride, int line0, int t0,
+    __device__ static __forceinline__ Raw load(const E *base, int64_t line_stride, int64_t t_stride, int line0, int t0,
                                                         int lines, int tn, int idx)
     {
         int line, t;
         coord(idx, line, t);
         line += line0;
         t += t0;
-        BmRaw<CODED> v;
+        Raw v;
         if (TFAST) {
             line = line < lines ? line : lines - 1;
             t = t + 8 <= tn ? t : tn - 8;
-            __builtin_memcpy(&v.w, base + int64_t(line) * line_stride + t, 8 * kEb);       // t_stride == 1
+            __builtin_memcpy(&v, base + int64_t(line) * line_stride + t, 8 * sizeof(E));       // t_stride == 1
         } else {
             t = t < tn ? t : tn - 1;
             line = line + 8 <= lines ? line : lines - 8;
-            __builtin_memcpy(&v.w, base + int64_t(t) * t_stride + line, 8 * kEb);          // line_stride == 1
+            __builtin_memcpy(&v, base + int64_t(t) * t_stride + line, 8 * sizeof(E));          // line_stride == 1
         }
         return v;
     }
-    __device__ static __forceinline__ void store(unsigned char *lds, const BmRaw<CODED> &v, int line0, int t0, int lines, int tn,
-                                                 int idx)
+    __device__ static __forceinline__ void store(unsigned char *lds, const Raw &v, int line0, int t0, int lines, int tn, int idx)
+    {
+        W w[kPlanes];
+        Elem::cut(v, w);
+#pragma unroll
+        for (int q = 0; q < kPlanes; ++q) store_plane(lds + q * kPlane, w[q], line0, t0, lines, tn, idx);
+    }
+    __device__ static __forceinline__ void store_plane(unsigned char *lds, const W &w, int line0, int t0, int lines, int tn, int idx)
     {
         int line, t;
         coord(idx, line, t);
         if (line0 + kBmTile <= lines && t0 + kBmT <= tn) {   // uniform: the whole tile lies inside the extents
-            *reinterpret_cast<W *>(lds + (TFAST ? line * kPitch + t * kEb : t * kPitch + line * kEb)) = v.w;
+            *reinterpret_cast<W *>(lds + (TFAST ? line * kPitch + t * kEb : t * kPitch + line * kEb)) = w;
             return;
         }
-        E e[8];
-        __builtin_memcpy(e, &v.w, 8 * kEb);
+        L e[8];
+        __builtin_memcpy(e, &w, sizeof(W));
         W zero;
 #pragma unroll
         for (int k = 0; k < int(sizeof(W) / 4); ++k) zero[k] = 0u;
@@ -236,15 +300,15 @@ template <bool CODED, bool TFAST> struct BmOperand {
             unsigned char *row = lds + line * kPitch;
             const int tg = t0 + t;                                   // global contraction index of slot t
             if (tg + 8 <= tn) {
-                *reinterpret_cast<W *>(row + t * kEb) = v.w;
+                *reinterpret_cast<W *>(row + t * kEb) = w;
             } else if (tg < tn) {                                    // the vector was moved back to tn - 8
                 const int tc = tn - 8 - t0;                          // tile-relative slot of its first element (>= -7)
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (tc + i >= t) reinterpret_cast<E *>(row)[tc + i] = e[i];
+                    if (tc + i >= t) reinterpret_cast<L *>(row)[tc + i] = e[i];
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    if (tg + j >= tn) reinterpret_cast<E *>(row)[t + j] = E(0);
+                    if (tg + j >= tn) reinterpret_cast<L *>(row)[t + j] = L(0);
             } else {
                 *reinterpret_cast<W *>(row + t * kEb) = zero;
             }
@@ -253,18 +317,18 @@ template <bool CODED, bool TFAST> struct BmOperand {
             const bool t_ok = t0 + t < tn;
             const int lg = line0 + line;
             if (lg + 8 <= lines || lg >= lines) {                    // whole vector inside, or wholly outside (anything will do)
-                *reinterpret_cast<W *>(row + line * kEb) = t_ok ? v.w : zero;
+                *reinterpret_cast<W *>(row + line * kEb) = t_ok ? w : zero;
             } else {                                                 // moved back to lines - 8
                 const int lc = lines - 8 - line0;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (lc + i >= line) reinterpret_cast<E *>(row)[lc + i] = t_ok ? e[i] : E(0);
+                    if (lc + i >= line) reinterpret_cast<L *>(row)[lc + i] = t_ok ? e[i] : L(0);
             }
         }
     }
     // the MFMA operand of a wave's 32 lines starting at l0, contraction slots 16*ks ..+15: lane l holds line
     // l%32 and the eight slots 8*(l/32) ..+7
-    template <typename ET> __device__ static __forceinline__ bm_v8h frag(const unsigned char *lds, int l0, int ks, int lane)
+    __device__ static __forceinline__ bm_v8h frag(const unsigned char *lds, int l0, int ks, int lane)
     {
         if (TFAST) {
             const unsigned char *p = lds + (l0 + (lane & 31)) * kPitch + (ks * 16 + (lane >> 5) * 8) * kEb;
@@ -284,13 +348,14 @@ template <bool CODED, bool TFAST> struct BmOperand {
 };
 
 // P_CODED: P is the coded operand (else Q).  P_TFAST / Q_TFAST: the contraction index is the unit-stride
-// index of that operand in memory.  ET: _Float16 or __bf16 (the tensors' 16-bit type; BmmArgs carries them as
-// 16-bit containers).
+// index of that operand in memory.  ET: the tensors' type (BmmArgs carries their pointers as 16-bit containers'; a
+// binary32 operand is three bfloat16 planes, see BmElem).
 template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET>
-__global__ __launch_bounds__(kThreads, 6) void k_bmm_q(BmmArgs a)
+__global__ __launch_bounds__(kThreads, (std::is_same<ET, float>::value ? 4 : 6)) void k_bmm_q(BmmArgs a)
 {
-    typedef BmOperand<P_CODED, P_TFAST> OP;
-    typedef BmOperand<!P_CODED, Q_TFAST> OQ;
+    typedef BmOperand<P_CODED, P_TFAST, ET> OP;
+    typedef BmOperand<!P_CODED, Q_TFAST, ET> OQ;
+    typedef typename BmElem<false, ET>::global_t X;       // the plain operand's and the result's element type in memory
     __shared__ __attribute__((aligned(16))) unsigned char LP[OP::kBytes];
     __shared__ __attribute__((aligned(16))) unsigned char LQ[OQ::kBytes];
 
@@ -300,7 +365,7 @@ __global__ __launch_bounds__(kThreads, 6) void k_bmm_q(BmmArgs a)
     const int r0 = int(blockIdx.y) * kBmTile, c0 = int(blockIdx.x) * kBmTile;
     const uint32_t h = (b + uint32_t(a.head0)) % uint32_t(a.heads);
 
-    const _Float16 *xb = a.x + int64_t(b) * a.x_batch + a.batch0 * a.x_batch;
+    const X *xb = reinterpret_cast<const X *>(a.x) + int64_t(b) * a.x_batch + a.batch0 * a.x_batch;
     const int8_t *yb = a.y + int64_t(b) * a.y_batch + a.batch0 * a.y_batch;
     auto load_p = [&](int t0, int part) {
         if constexpr (P_CODED) return OP::load(yb, a.p_rs, a.p_ts, r0, t0, a.R, a.Tn, tid + part * kThreads);
@@ -319,8 +384,8 @@ __global__ __launch_bounds__(kThreads, 6) void k_bmm_q(BmmArgs a)
 #pragma unroll
     for (int j = 0; j < 8; ++j) ones[j] = __builtin_bit_cast(_Float16, BmNum<ET>::kOne);
 
-    BmRaw<P_CODED> pv[kBmParts];
-    BmRaw<!P_CODED> qv[kBmParts];
+    typename OP::Raw pv[kBmParts];
+    typename OQ::Raw qv[kBmParts];
 #pragma unroll
     for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(0, k); qv[k] = load_q(0, k); }
     for (int t0 = 0; t0 < a.Tn; t0 += kBmT) {
@@ -337,10 +402,14 @@ __global__ __launch_bounds__(kThreads, 6) void k_bmm_q(BmmArgs a)
         }
 #pragma unroll
         for (int ks = 0; ks < kBmT / 16; ++ks) {
-            const bm_v8h fa = OP::template frag<ET>(LP, wr * 32, ks, lane);
-            const bm_v8h fb = OQ::template frag<ET>(LQ, wc * 32, ks, lane);
-            acc = BmNum<ET>::mfma(fa, fb, acc);
-            acc1 = BmNum<ET>::mfma(P_CODED ? ones : fa, P_CODED ? fb : ones, acc1);
+            const bm_v8h coded = P_CODED ? OP::frag(LP, wr * 32, ks, lane) : OQ::frag(LQ, wc * 32, ks, lane);
+            constexpr int kPlanes = OP::kPlanes * OQ::kPlanes;
+#pragma unroll
+            for (int q = kPlanes - 1; q >= 0; --q) {      // binary32: the smallest parts first
+                const bm_v8h plain = P_CODED ? OQ::frag(LQ + q * OQ::kPlane, wc * 32, ks, lane) : OP::frag(LP + q * OP::kPlane, wr * 32, ks, lane);
+                acc = BmNum<ET>::mfma(P_CODED ? coded : plain, P_CODED ? plain : coded, acc);
+                acc1 = BmNum<ET>::mfma(P_CODED ? ones : plain, P_CODED ? plain : ones, acc1);
+            }
         }
     }
 
@@ -350,7 +419,7 @@ __global__ __launch_bounds__(kThreads, 6) void k_bmm_q(BmmArgs a)
     const int col = c0 + wc * 32 + (lane & 31);
     const int row_l = r0 + wr * 32 + (lane >> 5) * 4;
     // R * Cn < 2^31 (checked by the entry points): 32-bit offsets from the batch's base
-    _Float16 *cb = a.c + (int64_t(b) + a.batch0) * a.c_batch;
+    X *cb = reinterpret_cast<X *>(a.c) + (int64_t(b) + a.batch0) * a.c_batch;
     const uint32_t o0 = uint32_t(row_l) * uint32_t(a.Cn) + uint32_t(col);
     if (col < a.Cn) {
 #pragma unroll
@@ -378,10 +447,9 @@ static void launch_bmm(BmmArgs a, int64_t batches, hipStream_t s)
 
 // The plain kernel: 32x32x2 binary32 MFMA with operands straight from global memory, one element at a time (a lane
 // needs one value per operand and step: lane l holds row / column l%32 at contraction slot l/32).  Kept simple: it
-// serves binary32 tensors (the binary32 configuration is far too small to be a throughput case) and, for the 16-bit
-// types, extents shorter than one load vector.  T: the tensors' element type (BmmArgs' pointers are reinterpreted).
+// serves extents shorter than one load vector.  T: the tensors' element type (BmmArgs' pointers are reinterpreted).
 template <bool P_CODED, typename T>
-__global__ __launch_bounds__(kThreads) void k_bmm_q_f32(BmmArgs a)
+__global__ __launch_bounds__(kThreads) void k_bmm_plain(BmmArgs a)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t b = blockIdx.z;
@@ -418,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void k_bmm_q_f32(BmmArgs a)
     }
 }
 
-template <bool P_CODED> static void launch_bmm_f32(BmmArgs a, int64_t batches, mesa_dtype dt, hipStream_t s)
+template <bool P_CODED> static void launch_bmm_plain(BmmArgs a, int64_t batches, mesa_dtype dt, hipStream_t s)
 {
     a.tiles_r = int(ceil_div(a.R, kBmTile));
     a.tiles_c = int(ceil_div(a.Cn, kBmTile));
@@ -427,7 +495,7 @@ template <bool P_CODED> static void launch_bmm_f32(BmmArgs a, int64_t batches, m
         a.head0 = int(b0 % a.heads);
         const int64_t nb = batches - b0 < 65535 ? batches - b0 : 65535;
 #define MESA_LAUNCH_PLAIN(T) \
-    hipLaunchKernelGGL((k_bmm_q_f32<P_CODED, T>), dim3(unsigned(a.tiles_c), unsigned(a.tiles_r), unsigned(nb)), dim3(kThreads), 0, s, a)
+    hipLaunchKernelGGL((k_bmm_plain<P_CODED, T>), dim3(unsigned(a.tiles_c), unsigned(a.tiles_r), unsigned(nb)), dim3(kThreads), 0, s, a)
         MESA_FOR_DTYPE(dt, MESA_LAUNCH_PLAIN);
 #undef MESA_LAUNCH_PLAIN
     }
@@ -768,7 +836,7 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
 {
     typedef TnCfg<DT, JB, WIDE_CODED, NW> C;
     constexpr int kNt = C::kNt;
-    typedef typename BmElem<WIDE_CODED>::type WideT;        // element of the N x N operand
+    typedef typename BmElem<WIDE_CODED, ET>::global_t WideT;       // element of the N x N operand
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_tn[];
     constexpr int Dh = C::Dh;
     constexpr int kEw = 16 / C::kWideEb;                   // elements of the N x N operand per 16-byte vector
@@ -1594,14 +1662,14 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     a.R = int(N); a.Cn = int(N); a.Tn = int(Dh);
     a.p_rs = Dh; a.p_ts = 1; a.q_ts = 1; a.q_cs = Dh;
     a.alpha = alpha_v; a.beta = beta_v;
-    if (dt == MESA_F32 || N < 8 || Dh < 8) {   // binary32, or an extent shorter than one load vector: the plain kernel
-        launch_bmm_f32<false>(a, batches, dt, s);
+    if (N < 8 || Dh < 8) {   // an extent shorter than one load vector: the plain kernel
+        launch_bmm_plain<false>(a, batches, dt, s);
         a.y = aq; a.c = static_cast<_Float16 *>(dV);
         a.y_batch = N * N; a.c_batch = N * Dh;
         a.R = int(N); a.Cn = int(Dh); a.Tn = int(N);
         a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
         a.alpha = alpha_a; a.beta = beta_a;
-        launch_bmm_f32<true>(a, batches, dt, s);
+        launch_bmm_plain<true>(a, batches, dt, s);
         return launch_status();
     }
     // aligned rows (N a multiple of 8): the column-tile kernel, at every length -- k_attn_da keeps its 32 x N block at a
@@ -1616,7 +1684,8 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         else if (Dh == 128 && da_fits<8>(batches, N)) launch_da<8, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
         else launch_bmm<false, true, true, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
+    if (dt == MESA_F32) launch_bmm<false, true, true, float>(a, batches, s);
+    else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
 #undef MESA_AV_DA
     // dV[j,d] = sum_i A_hat[i,j] * dO[i,d]:  P = A (r = j, t = i),  Q = dO (t = i, c = d)
     a.y = aq; a.c = static_cast<_Float16 *>(dV);
@@ -1635,7 +1704,8 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         else \
             launch_bmm<true, false, false, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
+    if (dt == MESA_F32) launch_bmm<true, false, false, float>(a, batches, s);
+    else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
 #undef MESA_AV_DV
     return launch_status();
 }
@@ -1665,12 +1735,12 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
     a.y = kq; a.c = static_cast<_Float16 *>(dQ);
     a.p_rs = N; a.p_ts = 1; a.q_ts = Dh; a.q_cs = 1;
     a.alpha = alpha_k; a.beta = beta_k;
-    if (dt == MESA_F32 || N < 8 || Dh < 8) {
-        launch_bmm_f32<false>(a, batches, dt, s);
+    if (N < 8 || Dh < 8) {
+        launch_bmm_plain<false>(a, batches, dt, s);
         a.y = qq; a.c = static_cast<_Float16 *>(dK);
         a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
         a.alpha = alpha_q; a.beta = beta_q;
-        launch_bmm_f32<false>(a, batches, dt, s);
+        launch_bmm_plain<false>(a, batches, dt, s);
         return launch_status();
     }
     // k_attn_nn (K codes resident) where it fits, except for N a multiple of 32 (its rows' reads meet on the same banks)
@@ -1687,7 +1757,8 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
         else \
             launch_bmm<false, true, false, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
+    if (dt == MESA_F32) launch_bmm<false, true, false, float>(a, batches, s);
+    else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
 #undef MESA_QK_DQ
     // dK[j,d] = scale * sum_i dS[i,j] * Q_hat[i,d]:  P = dS (r = j, t = i),  Q = Q codes (t = i, c = d)
     a.y = qq; a.c = static_cast<_Float16 *>(dK);
@@ -1702,7 +1773,8 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
         else \
             launch_bmm<false, false, false, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
+    if (dt == MESA_F32) launch_bmm<false, false, false, float>(a, batches, s);
+    else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
 #undef MESA_QK_DK
     return launch_status();
 }
