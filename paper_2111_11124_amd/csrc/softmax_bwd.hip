@@ -4,10 +4,12 @@
 // Rows of 197 or 49 elements start at odd byte offsets, so a wave (or, for long rows, a workgroup) takes a
 // tile of R consecutive rows with R*cols a multiple of 8: the tile is then a run of whole 8-element vectors
 // that start 16-byte aligned in dy / dx and 8-byte aligned in the codes, and is read and written flat with
-// full-width accesses.  One HBM read of codes and dy, one write of dx.  Two kernels:
-//   rows of up to 256 elements: k_softmax_bwd_rows, at the end of this file -- the tile staged through LDS, a
-//   row per group of lanes;
-//   longer rows: k_softmax_bwd -- codes and dy stay in registers between the two passes; only two partial
+// full-width accesses.  One HBM read of codes and dy, one write of dx.  The kernels:
+//   rows of up to 256 elements: k_softmax_bwd_rows -- the tile staged through LDS, a row per group of lanes;
+//   longer rows of 8k elements, up to 4096: k_softmax_bwd_wave -- a row per group of lanes, in registers;
+//   longer rows that start anywhere, up to 2048 elements of a 16-bit type: k_softmax_bwd_long -- a tile per workgroup in
+//   LDS, a row per half wave or wave;
+//   other rows of which a tile's worth fits the registers: k_softmax_bwd -- codes and dy stay in registers between the two passes; only two partial
 //   sums per vector (a vector touches at most two rows when cols >= 8) go through LDS, where 16 lanes per row
 //   add them in a fixed order.
 #include <hip/hip_runtime.h>
@@ -402,6 +404,158 @@ __global__ __launch_bounds__(kThreads, kSbRowWaves) void k_softmax_bwd_rows(cons
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Long rows that start anywhere (softmax_rows.hpp: sl_plan): the same phases with a workgroup per tile and a row per
+// half wave or wave.  dx may be dy, as above.  16 x 12 maps of 577 columns, against the flat kernel (whose tile of eight
+// rows leaves 44 % of its threads without a vector): 91 -> 63 us in bfloat16, 73 -> 62 in binary16; 322 columns 104 -> 76;
+// 1127 columns, formerly the plain kernel, 103 -> 59.  Four waves up to 1024 columns, eight beyond (1999 columns: 98
+// against 126 us).  binary32 stays with the flat and the plain kernel: 150 against 122 us at 577, 144 against 126 at 1127.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int LPR, int EPL>
+__global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__restrict__ yq, const void *dy, void *dx, int64_t total_rows,
+                                                                  uint32_t cols, uint32_t R, FastDiv div_rows,
+                                                                  FastDiv div_heads, const float *__restrict__ alpha,
+                                                                  const float *__restrict__ beta)
+{
+    constexpr int kB = Store<T>::kBytes;
+    constexpr int RPP = 64 / LPR;                        // rows per pass
+    constexpr int kBatch = kB == 4 ? 2 : 3;              // vectors a lane requests together
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t sub = lane / LPR, l = lane % LPR;
+    const uint32_t tid = threadIdx.x, nt = blockDim.x;
+    unsigned char *gs = smem;                                         // dy, then dx
+    unsigned char *cs = gs + R * cols * kB;                           // codes
+    const int64_t row0 = int64_t(blockIdx.x) * R;
+    const uint32_t nrows = uint32_t((total_rows - row0 < int64_t(R)) ? (total_rows - row0) : int64_t(R));
+    const uint32_t nelem = nrows * cols;
+    const int64_t e0 = row0 * cols;                      // a multiple of 8
+    const uint32_t nfull = nelem / kVec, tail = nelem % kVec;         // a tail: only at the end of the whole tensor
+
+    for (uint32_t v0 = 0; v0 < nfull; v0 += nt * kBatch) {
+        typename Store<T>::raw_t raw[kBatch];
+        u32x2 rawq[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t v = v0 + u * nt + tid;
+            if (v < nfull) {
+                raw[u] = Nt<T>::load(dy, e0 + int64_t(v) * kVec);
+                rawq[u] = nt_load<u32x2>(yq + e0 + int64_t(v) * kVec);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t v = v0 + u * nt + tid;
+            if (v < nfull) {
+                Store<T>::store(gs, int64_t(v) * kVec, raw[u]);
+                *reinterpret_cast<u32x2 *>(cs + v * kVec) = rawq[u];
+            }
+        }
+    }
+    if (tid < tail) {
+        const uint32_t le = nfull * kVec + tid;
+        LdsElem<T>::put(gs + le * kB, Store<T>::load1(dy, e0 + le));
+        cs[le] = uint8_t(yq[e0 + le]);
+    }
+    __syncthreads();
+
+    for (uint32_t p0 = wave * RPP; p0 < nrows; p0 += (nt >> 6) * RPP) {
+        const uint32_t r = p0 + sub;
+        const bool live = r < nrows;
+        const uint32_t rr = live ? r : p0;                            // a group without a row repeats the pass's first
+        const uint32_t eb = rr * cols + l;
+        unsigned char *gp = gs + eb * kB;
+        const unsigned char *cp = cs + eb;
+        const uint32_t slab = fastdiv(uint32_t(row0) + rr, div_rows);
+        const uint32_t h = slab - fastdiv(slab, div_heads) * div_heads.d;
+        const float s = alpha[h] / 255.0f, off = fmaf(128.0f, s, beta[h]);   // y_hat = s * q + off with q the signed code
+        float g[EPL], yh[EPL];
+        float d = 0.0f;
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) {
+            const float gv = LdsElem<T>::get(gp + k * LPR * kB);
+            const float qv = float(int(*reinterpret_cast<const int8_t *>(cp + k * LPR)));
+            g[k] = (k < sl_full(EPL) || l + k * LPR < cols) ? gv : 0.0f;     // unused slots add nothing
+            yh[k] = fmaf(qv, s, off);
+            d = fmaf(g[k], yh[k], d);
+        }
+        d = lanes_sum_dpp<LPR>(d);
+        if (live) {
+#pragma unroll
+            for (int k = 0; k < EPL; ++k)
+                if (k < sl_full(EPL) || l + k * LPR < cols) LdsElem<T>::put(gp + k * LPR * kB, yh[k] * (g[k] - d));
+        }
+    }
+    __syncthreads();
+
+    for (uint32_t v = tid; v < nfull; v += nt) Nt<T>::store(dx, e0 + int64_t(v) * kVec, Store<T>::load(gs, int64_t(v) * kVec));
+    if (tid < tail) {
+        const uint32_t le = nfull * kVec + tid;
+        Store<T>::store1(dx, e0 + le, LdsElem<T>::get(gs + le * kB));        // exact: the value is already of type T
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Rows of 8k elements, 256 < cols <= 4096: a row per group of LPR lanes, NV whole vectors of that row in each lane's
+// registers, all requested before the first is used; d is one reduction inside the group.  No LDS.  Against the tiled
+// kernel, whose bookkeeping of which element belongs to which row such rows do not need: (1, 16, 4096, 4096) 303 -> 225 us
+// in bfloat16 (6.0 TB/s) and 231 -> 221 in binary16, (4, 16, 1024, 1024) 78 -> 60 in bfloat16 and 126 -> 120 in binary32.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSwMaxCols = 4096;
+
+template <typename T, int LPR, int NV>
+__global__ __launch_bounds__(kThreads, 4) void k_softmax_bwd_wave(const int8_t *__restrict__ yq, const void *dy, void *dx, int64_t total_rows,
+                                                                  uint32_t cols, FastDiv div_rows, FastDiv div_heads,
+                                                                  const float *__restrict__ alpha, const float *__restrict__ beta)
+{
+    constexpr int RPW = 64 / LPR;              // rows a wave takes at a time
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t sub = lane / LPR, lr = lane % LPR;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nvec = cols >> 3;
+    const int64_t row = (int64_t(blockIdx.x) * (kThreads / 64) + wave) * RPW + sub;
+    const bool live = row < total_rows;
+    const int64_t rr = live ? row : total_rows - 1;
+    const int64_t e0 = rr * int64_t(cols);
+    typename Store<T>::raw_t raw[NV];
+    u32x2 rawq[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const uint32_t v = u * LPR + lr;
+        if (v < nvec) {
+            raw[u] = Nt<T>::load(dy, e0 + int64_t(v) * kVec);
+            rawq[u] = nt_load<u32x2>(yq + e0 + int64_t(v) * kVec);
+        }
+    }
+    const uint32_t slab = fastdiv(uint32_t(rr), div_rows);
+    const uint32_t h = slab - fastdiv(slab, div_heads) * div_heads.d;
+    const float s = alpha[h] / 255.0f, b = beta[h];
+    float d = 0.0f;
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+        if (u * LPR + lr < nvec) {
+            float g[8], y[8];
+            Store<T>::unpack(raw[u], g);
+            codes_to_float(rawq[u], y);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) d = fmaf(g[j], fmaf(y[j], s, b), d);
+        }
+    d = lanes_sum_dpp<LPR>(d);
+    // the unpacked values are rebuilt from the packed ones: holding them would halve the waves in flight
+#pragma unroll
+    for (int u = 0; u < NV; ++u) opaque(rawq[u], raw[u]);
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+        if (live && u * LPR + lr < nvec) {
+            float g[8], y[8], o[8];
+            Store<T>::unpack(raw[u], g);
+            codes_to_float(rawq[u], y);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = fmaf(y[j], s, b) * (g[j] - d);
+            Nt<T>::store(dx, e0 + int64_t(u * LPR + lr) * kVec, Store<T>::pack(o));
+        }
+}
+
 // Rows the tiled kernels cannot take (eight rows of an odd length above 1024 do not fit a tile, more than
 // kSmMaxHeads heads, rows shorter than a vector next to many heads): one workgroup per row, the row read twice --
 // once for d = sum_j dy_j * y_hat_j (per-thread sums in a fixed order, then the wave's lanes, then the four waves),
@@ -535,6 +689,47 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
         return launch_status();
     }
     if (cols < kVec) return plain();
+    const SlPlan lp = sl_plan(total_rows, cols, 0, dtype_bytes(dt) + 1, cols > 1024 ? 8 : 4, 32);
+    if (lp.ok && dt != MESA_F32) {
+        FastDiv drl = make_fastdiv(uint32_t(rows)), dhl = make_fastdiv(uint32_t(H));
+        hipStream_t sl = static_cast<hipStream_t>(stream);
+        auto go = [&](auto zero) {
+            typedef decltype(zero) T;
+#define MESA_LAUNCH_SL(LPR_, EPL_) \
+    hipLaunchKernelGGL((k_softmax_bwd_long<T, LPR_, EPL_>), dim3(unsigned(lp.tiles)), dim3(64 * lp.waves), lp.lds, sl, yq, dy, dx, \
+                       total_rows, uint32_t(cols), uint32_t(lp.R), drl, dhl, alpha, beta)
+            MESA_FOR_SL_SHAPE(lp, MESA_LAUNCH_SL);
+#undef MESA_LAUNCH_SL
+        };
+#define MESA_LAUNCH_SL_T(T) go(T(0))
+        MESA_FOR_DTYPE(dt, MESA_LAUNCH_SL_T);
+#undef MESA_LAUNCH_SL_T
+        return launch_status();
+    }
+    if (cols % kVec == 0 && cols > kSrMaxCols && cols <= kSwMaxCols) {
+        const int64_t nvec = cols / kVec;
+        FastDiv drw = make_fastdiv(uint32_t(rows)), dhw = make_fastdiv(uint32_t(H));
+        hipStream_t sw = static_cast<hipStream_t>(stream);
+        auto go = [&](auto zero) {
+            typedef decltype(zero) T;
+#define MESA_LAUNCH_SW(LPR_, NV_) \
+    hipLaunchKernelGGL((k_softmax_bwd_wave<T, LPR_, NV_>), dim3(unsigned(ceil_div(total_rows, 64 / LPR_ * (kThreads / 64)))), dim3(kThreads), 0, sw, \
+                       yq, dy, dx, total_rows, uint32_t(cols), drw, dhw, alpha, beta)
+            if (nvec <= 48) MESA_LAUNCH_SW(16, 3);
+            else if (nvec <= 64) MESA_LAUNCH_SW(16, 4);
+            else if (nvec <= 96) MESA_LAUNCH_SW(32, 3);
+            else if (nvec <= 128) MESA_LAUNCH_SW(32, 4);
+            else if (nvec <= 192) MESA_LAUNCH_SW(64, 3);
+            else if (nvec <= 256) MESA_LAUNCH_SW(64, 4);
+            else if (nvec <= 384) MESA_LAUNCH_SW(64, 6);
+            else MESA_LAUNCH_SW(64, 8);
+#undef MESA_LAUNCH_SW
+        };
+#define MESA_LAUNCH_SW_T(T) go(T(0))
+        MESA_FOR_DTYPE(dt, MESA_LAUNCH_SW_T);
+#undef MESA_LAUNCH_SW_T
+        return launch_status();
+    }
     // rows per tile: a multiple of 8/gcd(cols, 8) so that every tile starts on a vector boundary.
     // Short rows: one wave per tile (2048 elements); long rows: the whole workgroup (8192 elements).
     int64_t gc = cols, b8 = 8;

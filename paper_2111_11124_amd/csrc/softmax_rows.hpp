@@ -35,16 +35,22 @@ constexpr int kSrSlack = 1024;                        // bytes past the last reg
 
 template <int WIDTH, bool MAX> __device__ __forceinline__ float lanes_extreme_dpp(float v)
 {
-    static_assert(WIDTH == 8 || WIDTH == 16, "lane groups inside a DPP row");
+    static_assert(WIDTH == 8 || WIDTH == 16 || WIDTH == 32 || WIDTH == 64, "aligned power-of-two lane groups");
     v = MAX ? vmax(v, dpp_move<0xB1>(v)) : vmin(v, dpp_move<0xB1>(v));      // quad_perm [1,0,3,2]
     v = MAX ? vmax(v, dpp_move<0x4E>(v)) : vmin(v, dpp_move<0x4E>(v));      // quad_perm [2,3,0,1]
     v = MAX ? vmax(v, dpp_move<0x141>(v)) : vmin(v, dpp_move<0x141>(v));    // row_half_mirror
     if (WIDTH >= 16) v = MAX ? vmax(v, dpp_move<0x140>(v)) : vmin(v, dpp_move<0x140>(v));   // row_mirror
+    if (WIDTH >= 32) { const float o = __shfl_xor(v, 16, 64); v = MAX ? vmax(v, o) : vmin(v, o); }
+    if (WIDTH >= 64) { const float o = __shfl_xor(v, 32, 64); v = MAX ? vmax(v, o) : vmin(v, o); }
     return v;
 }
 
 // one staged element <-> binary32; put() returns the value as stored
 template <typename T> struct LdsElem;
+
+// v rounded to the storage type
+template <typename T> __device__ __forceinline__ float as_stored(float v) { return float(T(v)); }
+template <> __device__ __forceinline__ float as_stored<float>(float v) { return v; }
 template <> struct LdsElem<_Float16> {
     __device__ static __forceinline__ float get(const unsigned char *p) { return float(*reinterpret_cast<const _Float16 *>(p)); }
     __device__ static __forceinline__ float put(unsigned char *p, float v)
@@ -102,5 +108,70 @@ inline SrShape sr_shape(int64_t total_rows, int64_t cols)
     p.tiles = (total_rows + p.R - 1) / p.R;
     return p;
 }
+
+// ---------------------------------------------------------------------------------------------
+// Long rows that start anywhere (256 < cols <= 2048, cols no multiple of 8).  The same three phases, but a tile is as
+// large as its alignment asks for -- eight rows of an odd length, 4616 elements at 577 columns -- and belongs to a
+// workgroup of two or four waves, which share out its vectors, then its rows, then its vectors; a row takes half a wave
+// or a whole one.  A tile is fetched when its turn comes: the other workgroups of the CU cover the latency.  (A tile per
+// wave was measured first: half the waves per CU fit their LDS, and a small tensor's few tiles take four times as long
+// each -- 30 against 19 us at three maps of 587 columns.)
+// ---------------------------------------------------------------------------------------------
+constexpr int64_t kSlMaxCols = 2048;
+constexpr int64_t kSlTileElems = 6144;                 // several units of rows per tile up to here
+
+// slots that every row of a shape fills (the shape before it ends there)
+constexpr int sl_full(int epl) { return epl == 12 ? 8 : epl == 16 ? 12 : epl == 20 ? 16 : epl == 24 ? 20 : 24; }
+
+struct SlPlan {
+    bool ok;
+    int lpr, epl;
+    int64_t R, tiles;
+    int waves;               // per workgroup
+    int per_cu;              // workgroups that fit a CU
+    uint32_t tab_bytes;
+    size_t lds;
+};
+
+// tab: bytes of the workgroup's tables; elem: bytes of a tile per element
+inline SlPlan sl_plan(int64_t total_rows, int64_t cols, int64_t tab, int64_t elem, int waves, int max_waves_per_cu)
+{
+    SlPlan p{};
+    if (cols <= kSrMaxCols || cols > kSlMaxCols || cols % kVec == 0) return p;
+    p.lpr = cols <= 1024 ? 32 : 64;
+    const int64_t slots = (cols + p.lpr - 1) / p.lpr;
+    p.epl = slots <= 12 ? 12 : slots <= 16 ? 16 : slots <= 20 ? 20 : slots <= 24 ? 24 : 32;
+    const int64_t unit = cols % 4 == 0 ? 2 : cols % 2 == 0 ? 4 : 8;   // rows until a row starts on a vector boundary again
+    const int64_t units = kSlTileElems / (unit * cols);
+    p.R = unit * (units > 1 ? units : 1);
+    if (p.R > total_rows) p.R = (total_rows + unit - 1) / unit * unit;
+    p.tiles = (total_rows + p.R - 1) / p.R;
+    p.tab_bytes = uint32_t((tab + 15) / 16 * 16);
+    // behind the tile: what the last row's unused slots may read
+    p.lds = size_t(p.tab_bytes) + size_t((p.R * cols * elem + 15) / 16 * 16) + size_t(p.lpr) * p.epl * 4;
+    if (p.lds > 64 * 1024) return p;
+    p.waves = waves;
+    int64_t n = int64_t(160 * 1024) / int64_t(p.lds);
+    if (n * p.waves > max_waves_per_cu) n = max_waves_per_cu / p.waves;
+    p.per_cu = int(n > 1 ? n : 1);
+    p.ok = true;
+    return p;
+}
+
+// expands X(LPR, EPL) with the shape of plan p
+#define MESA_FOR_SL_SHAPE(p, X) \
+    do { \
+        if ((p).lpr == 32) { \
+            if ((p).epl == 12) X(32, 12); \
+            else if ((p).epl == 16) X(32, 16); \
+            else if ((p).epl == 20) X(32, 20); \
+            else if ((p).epl == 24) X(32, 24); \
+            else X(32, 32); \
+        } else { \
+            if ((p).epl == 20) X(64, 20); \
+            else if ((p).epl == 24) X(64, 24); \
+            else X(64, 32); \
+        } \
+    } while (0)
 
 }  // namespace mesa

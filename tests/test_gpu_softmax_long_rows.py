@@ -1,0 +1,96 @@
+"""Softmax forward and backward over rows longer than 256 elements: the kernels that keep a tile of unaligned rows in LDS and
+the one that keeps an aligned row in a wave's registers, at the edges of their shapes, against the CPU oracle.
+
+Bounds: those of the other softmax tests (1e-5, 2e-3, 1.6e-2 of the largest result by storage type); codes and running
+estimates bit for bit on the stored map.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mesa_ref as R
+from tests.test_gpu_parity import DTYPE_IDS, DTYPES, TOL, _mid_of_frame, npy, relerr, ws_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import paper_2111_11124_amd as m
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    m.lib()
+    return m
+
+
+# unaligned: both ends of every slot count, one, two and four rows to a vector boundary; aligned: both ends of every lane
+# group.  Maps of one, three and seven rows put several heads into a tile, the odd row counts leave a ragged last one.
+SHAPES = [(1, 2, 3, 257), (1, 3, 7, 258), (2, 3, 5, 260), (1, 2, 9, 383), (1, 2, 9, 385), (1, 1, 17, 511), (1, 2, 9, 513), (1, 3, 11, 577),
+          (1, 2, 5, 641), (1, 5, 1, 700), (1, 2, 9, 769), (2, 1, 7, 1023), (1, 2, 5, 1025), (1, 2, 3, 1281), (1, 1, 9, 1537), (1, 1, 8, 2046),
+          (1, 1, 9, 2047),
+          (1, 3, 5, 264), (1, 2, 7, 384), (1, 2, 6, 392), (1, 2, 5, 512), (1, 3, 3, 520), (1, 1, 7, 768), (1, 2, 3, 776), (1, 1, 5, 1024), (1, 1, 3, 1032),
+          (1, 1, 5, 1536), (1, 1, 3, 2048), (1, 1, 3, 2056), (1, 1, 2, 3080), (1, 1, 3, 4096)]
+
+
+def _params(H, g):
+    return 0.05 + 0.2 * torch.rand(H, device="cuda", generator=g), 0.01 * torch.rand(H, device="cuda", generator=g)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("B,H,rows,cols", SHAPES)
+def test_softmax_backward_long_rows(M, B, H, rows, cols, dtype):
+    g = torch.Generator(device="cuda").manual_seed(rows * 5000 + cols)
+    n = B * H * rows * cols
+    q = _mid_of_frame(torch.randint(-128, 128, (n,), dtype=torch.int8, device="cuda", generator=g), 127)
+    dy = _mid_of_frame(torch.randn(n, device="cuda", generator=g).to(dtype), float("nan"))
+    a, b = _params(H, g)
+    out = torch.full((n + 128,), 7.0, dtype=dtype, device="cuda")
+    M.mesa_softmax_bwd_q(q, B, H, rows, cols, a, b, dy, out[64:64 + n])
+    ref = R.softmax_bwd_q(npy(q), B, H, rows, cols, npy(a), npy(b), npy(dy))
+    got = npy(out)
+    assert np.all(got[:64] == 7) and np.all(got[64 + n:] == 7)
+    assert relerr(got[64:64 + n].reshape(np.shape(ref)), ref) <= TOL[dtype]
+    M.mesa_softmax_bwd_q(q, B, H, rows, cols, a, b, dy, dy)       # in place
+    assert np.array_equal(npy(dy), got[64:64 + n])
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("B,H,rows,cols", [s for s in SHAPES if s[3] % 8])
+def test_softmax_forward_long_rows(M, B, H, rows, cols, dtype):
+    """Masked logits among them: -infinity, and rows of nothing but the type's lowest value, which come out even."""
+    g = torch.Generator(device="cuda").manual_seed(rows * 7000 + cols)
+    n = B * H * rows * cols
+    s = torch.randn((B, H, rows, cols), device="cuda", generator=g) * 3
+    s[torch.rand(s.shape, device="cuda", generator=g) < 0.1] = -float("inf")
+    s = s.to(dtype)
+    s[0, 0, rows - 1] = torch.finfo(dtype).min
+    s = _mid_of_frame(s, float("nan"))
+    ws = ws_for(M, M.OP_SOFTMAX_FWD_Q, B * H * rows, H, cols, dtype)
+    for mode in (M.ROUND_STOCHASTIC, M.ROUND_NEAREST_EVEN):
+        a, b = _params(H, torch.Generator(device="cuda").manual_seed(5))
+        a0, b0 = npy(a).copy(), npy(b).copy()
+        y = torch.full((n + 128,), 7.0, dtype=dtype, device="cuda")
+        q = torch.full((n + 128,), 99, dtype=torch.int8, device="cuda")
+        M.mesa_softmax_fwd_q(s, B, H, rows, cols, a, b, 0.9, y[64:64 + n], q[64:64 + n], ws, mode, 77, 1000)
+        ref = R.softmax_fwd(npy(s), B * H * rows, cols)
+        got = npy(y)
+        assert np.all(got[:64] == 7) and np.all(got[64 + n:] == 7) and torch.all(q[:64] == 99) and torch.all(q[64 + n:] == 99)
+        assert relerr(got[64:64 + n].reshape(np.shape(ref)), ref) <= TOL[dtype]
+        rq, ra, rb = R.quantize_update_fused(got[64:64 + n].copy(), (B, H, rows * cols), a0, b0, 0.9, mode, 77, 1000)
+        assert np.array_equal(npy(q)[64:64 + n], rq.reshape(-1))
+        assert np.array_equal(npy(a), ra) and np.array_equal(npy(b) + np.float32(0), rb + np.float32(0))
+
+
+def test_softmax_forward_long_rows_in_the_smallest_workspace(M):
+    """One workgroup's worth of extrema less than a resident round: fewer workgroups, the same bits."""
+    B, H, rows, cols = 2, 2, 577, 577
+    g = torch.Generator(device="cuda").manual_seed(3)
+    s = torch.randn((B, H, rows, cols), device="cuda", generator=g).half()
+    full = ws_for(M, M.OP_SOFTMAX_FWD_Q, B * H * rows, H, cols, torch.float16)
+    got = []
+    for ws in (full, full[:768 * 2 * H * 4 + 16] if full.numel() > 768 * 2 * H * 4 + 16 else full):
+        a, b = torch.full((H,), 0.1, device="cuda"), torch.zeros(H, device="cuda")
+        y, q = torch.empty_like(s), torch.empty(s.numel(), dtype=torch.int8, device="cuda")
+        M.mesa_softmax_fwd_q(s, B, H, rows, cols, a, b, 0.9, y, q, ws, M.ROUND_STOCHASTIC, 9, 0)
+        got.append((npy(y), npy(q), npy(a), npy(b)))
+    for u, v in zip(*got):
+        assert np.array_equal(u, v)
