@@ -84,9 +84,44 @@ __device__ __forceinline__ u32x2 pack_codes(const float w[8])
     return c;
 }
 
+// Eq. (3)-(4) for eight elements and their codes in one go: v[] as in quantize_one, before its rounding to an integer.
+// The conversion to a byte rounds by the wave's rounding mode and saturates: to the nearest integer, ties to even, as it
+// stands, and downwards with the mode set so for the eight conversions -- the same integers as rintf / floorf followed by
+// the conversion, without the eight instructions (the quantizers whose producing layer computes much are bound by
+// instruction issue).  One asm statement, so that nothing else is rounded in between.
+template <bool SR> __device__ __forceinline__ u32x2 round_pack_codes(const float v[8])
+{
+    if (!SR) return pack_codes(v);
+    uint32_t lo, hi;
+    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2\n\t"
+        "v_cvt_pk_u8_f32 %0, %2, 0, 0\n\t"
+        "v_cvt_pk_u8_f32 %1, %6, 0, 0\n\t"
+        "v_cvt_pk_u8_f32 %0, %3, 1, %0\n\t"
+        "v_cvt_pk_u8_f32 %1, %7, 1, %1\n\t"
+        "v_cvt_pk_u8_f32 %0, %4, 2, %0\n\t"
+        "v_cvt_pk_u8_f32 %1, %8, 2, %1\n\t"
+        "v_cvt_pk_u8_f32 %0, %5, 3, %0\n\t"
+        "v_cvt_pk_u8_f32 %1, %9, 3, %1\n\t"
+        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
+        : "=&v"(lo), "=&v"(hi)
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+    u32x2 c;
+    c[0] = lo ^ 0x80808080u;  // -128 on each byte
+    c[1] = hi ^ 0x80808080u;
+    return c;
+}
+// v of quantize_one: (x - b) * r, plus the random fraction
+template <bool SR> __device__ __forceinline__ float quantize_real(float x, float r, float b, float bits)
+{
+    const float v = (x - b) * r;
+    return SR ? __builtin_fmaf(bits, 1.52587890625e-05f, v) : v;
+}
+
 // plain selection instructions: the data holds no NaN by contract, so no canonicalisation is wanted
 __device__ __forceinline__ float vmin(float a, float b) { float r; asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
 __device__ __forceinline__ float vmax(float a, float b) { float r; asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ float vmin3(float a, float b, float c) { float r; asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
+__device__ __forceinline__ float vmax3(float a, float b, float c) { float r; asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 __device__ __forceinline__ uint32_t pkmin(uint32_t a, uint32_t b) { uint32_t r; asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
 __device__ __forceinline__ uint32_t pkmax(uint32_t a, uint32_t b) { uint32_t r; asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
 

@@ -4,10 +4,11 @@
 //   then for the stored y: codes with the running estimates as they are on entry and this batch's
 //   per-head extrema, from which the estimates are moved afterwards (the single-pass forward).
 //
-// Three kernels.  Rows of up to 256 elements (the attention maps of the paper's models: 197, 49): k_softmax_fwd_rows,
-// further down -- tiles staged flat through LDS, a row per group of lanes.  Longer rows of 8k elements, up to 4096:
-// k_softmax_fwd_wave, after it -- a row per group of lanes, in registers.  Other long rows: k_softmax_fwd, tiled as
-// the backward kernel: rows start at odd byte offsets, so a team (one wave, or the workgroup for long rows) takes
+// Four kernels.  Rows of up to 256 elements (the attention maps of the paper's models: 197, 49): k_softmax_fwd_rows,
+// further down -- tiles staged flat through LDS, a row per group of lanes.  Longer rows: of 8k elements, up to 4096,
+// k_softmax_fwd_wave -- a row per group of lanes, in registers; of any other length up to 2048, k_softmax_fwd_long -- a tile
+// per workgroup in LDS, a row per half wave or wave.  What is left (rows of 4k elements beyond 2048, more heads than the
+// row kernels' tables leave room for): k_softmax_fwd, tiled: rows start at odd byte offsets, so a team (one wave, or the workgroup for long rows) takes
 // R consecutive rows with R*cols a multiple of 8 -- a run of whole, aligned 8-element vectors, read and written
 // flat.  A vector touches at most two rows; its two partial maxima, then its two partial sums, go through LDS,
 // where a group of lanes per row combines them.  The exponentials stay in registers between the passes.
@@ -441,6 +442,224 @@ __global__ __launch_bounds__(kThreads, kSfRowWaves) void k_softmax_fwd_rows(cons
 }
 
 // ---------------------------------------------------------------------------------------------
+// Longer rows that start anywhere (sl_plan: 256 < cols <= 2048, no multiple of 8): the same phases with the workgroup as the
+// team that owns a tile, and the codes taken elsewhere.  Flat phase: the tile's vectors, requested while the tile before
+// was worked on, go to LDS as they lie.  Row phase: y, rounded to its storage type, goes back over the logits.  Flat phase:
+// a vector of y is read, its Philox block generated and its codes taken there -- eight consecutive elements of the tensor
+// are exactly a block's, so neither bits nor codes pass through LDS.  (For the short rows above, whose tiles mostly
+// straddle two heads, taking the codes per element in the row phase is as fast: 82 against 85 us at 8192 x 3 x 49 x 49.)
+//
+// The extrema of the stored values are taken per row: rounding and the multiplication by 1 / sum are monotonic, so they
+// are the rounded products of the row's smallest and largest exponential.
+//
+// Bound by instruction issue.  577 columns (16 x 12 maps, stochastic rounding), against the flat kernel: 157 -> 84 us in
+// bfloat16, 160 -> 78 in binary16, 170 -> 141 in binary32; 322 columns 172 -> 98; 1127 columns, formerly two steps, 248 -> 75.
+// Workgroups of two waves up to 1024 columns (four: 97 against 91 us at 577), of four beyond (two: 126 against 89 at 1127).
+// ---------------------------------------------------------------------------------------------
+// waves per SIMD the kernel's register budget is set for
+constexpr int sf_long_waves(int elem_bytes, int epl) { return elem_bytes == 2 && epl <= 20 ? 5 : 4; }
+constexpr int kSfLongTeam = 2;      // waves of a workgroup that shares a tile of rows up to 1024 elements; else twice as many
+
+template <typename T, int LPR, int EPL, bool SR>
+__global__ __launch_bounds__(kThreads, (sf_long_waves(Store<T>::kBytes, EPL))) void k_softmax_fwd_long(const void *__restrict__ s_in, void *__restrict__ y,
+                                                                  int8_t *__restrict__ q, int64_t total_rows, uint32_t cols,
+                                                                  uint32_t R, int64_t tiles, FastDiv div_cols, FastDiv div_rows,
+                                                                  FastDiv div_heads, const float *__restrict__ alpha,
+                                                                  const float *__restrict__ beta, uint64_t seed, uint64_t offset,
+                                                                  float *__restrict__ part, uint32_t tab_bytes)
+{
+    constexpr int kB = Store<T>::kBytes;
+    constexpr int RPP = 64 / LPR;                        // rows a wave takes per pass
+    constexpr int FULL = sl_full(EPL);                   // slots that every row fills
+    constexpr int kAhead = 4;                            // vectors a thread requests one tile ahead
+    constexpr bool kFma = std::is_same<T, _Float16>::value;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const uint32_t heads = div_heads.d;
+    float2 *head_tab = reinterpret_cast<float2 *>(smem);              // (255 / alpha, beta) per head
+    int *lmn = reinterpret_cast<int *>(smem + heads * sizeof(float2));
+    int *lmx = lmn + heads;
+    for (uint32_t h = threadIdx.x; h < heads; h += blockDim.x) {
+        const float a = alpha[h];
+        head_tab[h] = make_float2(a > 0.0f ? 255.0f / a : 0.0f, beta[h]);
+        lmn[h] = order_key(__builtin_inff());
+        lmx[h] = order_key(-__builtin_inff());
+    }
+    __syncthreads();
+
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    const uint32_t sub = lane / LPR, l = lane % LPR;
+    const uint32_t nt = blockDim.x, tid = threadIdx.x;
+    unsigned char *xs = smem + tab_bytes;                             // logits, then y
+
+    uint32_t cur_h = 0;
+    float mn = __builtin_inff(), mx = -__builtin_inff();              // extrema of this lane's rows of head cur_h
+    auto flush = [&]() {                                              // a whole lane group at a time
+        const float a = lanes_extreme_dpp<LPR, false>(mn), b = lanes_extreme_dpp<LPR, true>(mx);
+        if (l == 0 && a <= b) {
+            atomicMin(&lmn[cur_h], order_key(a));
+            atomicMax(&lmx[cur_h], order_key(b));
+        }
+    };
+
+    typename Store<T>::raw_t raw[kAhead];
+    auto fetch = [&](int64_t t) {
+        const int64_t row0 = t * R;
+        const uint32_t nfull = uint32_t((total_rows - row0 < int64_t(R)) ? (total_rows - row0) : int64_t(R)) * cols / kVec;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t v = u * nt + tid;
+            if (v < nfull) raw[u] = Nt<T>::load(s_in, row0 * cols + int64_t(v) * kVec);
+        }
+    };
+    if (blockIdx.x < tiles) fetch(blockIdx.x);
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t row0 = tile * R;
+        const uint32_t nrows = uint32_t((total_rows - row0 < int64_t(R)) ? (total_rows - row0) : int64_t(R));
+        const uint32_t nelem = nrows * cols;
+        const int64_t e0 = row0 * cols;                  // a multiple of 8
+        const uint32_t nfull = nelem / kVec, tail = nelem % kVec;    // a tail: only at the end of the whole tensor
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t v = u * nt + tid;
+            if (v < nfull) Store<T>::store(xs, int64_t(v) * kVec, raw[u]);
+        }
+        for (uint32_t v = kAhead * nt + tid; v < nfull; v += nt) Store<T>::store(xs, int64_t(v) * kVec, Nt<T>::load(s_in, e0 + int64_t(v) * kVec));
+        if (tid < tail) LdsElem<T>::put(xs + (nfull * kVec + tid) * kB, Store<T>::load1(s_in, e0 + nfull * kVec + tid));
+        __syncthreads();
+        if (tile + gridDim.x < tiles) fetch(tile + gridDim.x);
+
+        // rows
+        for (uint32_t p0 = wave * RPP; p0 < nrows; p0 += waves * RPP) {
+            const uint32_t r = p0 + sub;
+            const bool live = r < nrows;
+            // slot k is a constant distance from the lane's first element; a group without a row repeats the pass's first
+            unsigned char *xp = xs + ((live ? r : p0) * cols + l) * kB;
+            float x[EPL];
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) {
+                const float v = LdsElem<T>::get(xp + k * LPR * kB);
+                x[k] = (k < FULL || l + k * LPR < cols) ? v : -__builtin_inff();
+            }
+            float m = x[0];
+#pragma unroll
+            for (int k = 1; k + 1 < EPL; k += 2) m = vmax3(m, x[k], x[k + 1]);
+            if (EPL % 2 == 0) m = vmax(m, x[EPL - 1]);
+            m = lanes_extreme_dpp<LPR, true>(m);
+            // binary16: one fused operation -- the rounding of m * log2(e) is a factor common to the row.  The wider types'
+            // lowest values, as masks use them, would overflow there: a row of nothing else has to come out even.
+            const float ml = m * 1.4426950408889634f;
+            float sum = 0.0f;
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) {
+                x[k] = __builtin_amdgcn_exp2f(kFma ? __builtin_fmaf(x[k], 1.4426950408889634f, -ml) : (x[k] - m) * 1.4426950408889634f);
+                sum += x[k];                             // 0 in unused slots
+            }
+            sum = lanes_sum_dpp<LPR>(sum);
+            const float inv = 1.0f / sum;
+            if (live) {
+                const uint32_t slab = fastdiv(uint32_t(row0) + r, div_rows);
+                const uint32_t h = slab - fastdiv(slab, div_heads) * heads;
+                if (h != cur_h) {
+                    flush();
+                    cur_h = h;
+                    mn = __builtin_inff();
+                    mx = -__builtin_inff();
+                }
+                float xmn = x[0], xmx = x[0];
+#pragma unroll
+                for (int k = 1; k + 1 < EPL; k += 2) {
+                    xmn = vmin3(xmn, (k < FULL || l + k * LPR < cols) ? x[k] : __builtin_inff(),
+                                (k + 1 < FULL || l + (k + 1) * LPR < cols) ? x[k + 1] : __builtin_inff());
+                    xmx = vmax3(xmx, x[k], x[k + 1]);
+                }
+                if (EPL % 2 == 0) {
+                    xmn = vmin(xmn, (EPL - 1 < FULL || l + (EPL - 1) * LPR < cols) ? x[EPL - 1] : __builtin_inff());
+                    xmx = vmax(xmx, x[EPL - 1]);
+                }
+#pragma unroll
+                for (int k = 0; k < EPL; ++k)
+                    if (k < FULL || l + k * LPR < cols) LdsElem<T>::put(xp + k * LPR * kB, x[k] * inv);
+                mn = vmin(mn, as_stored<T>(xmn * inv));
+                mx = vmax(mx, as_stored<T>(xmx * inv));
+            }
+        }
+        __syncthreads();
+
+        // codes
+        const uint32_t slab_first = fastdiv(uint32_t(row0), div_rows);
+        const uint32_t slab_last = fastdiv(uint32_t(row0) + nrows - 1, div_rows);
+        if (slab_last - slab_first <= 1) {
+            // at most two heads: element `edge` of the tile is the first of the second one
+            const uint32_t h0 = slab_first - fastdiv(slab_first, div_heads) * heads;
+            const uint32_t h1 = slab_last - fastdiv(slab_last, div_heads) * heads;
+            const float2 prm0 = head_tab[h0], prm1 = head_tab[h1];
+            const uint32_t edge = slab_last == slab_first ? 0xFFFFFFFFu : (slab_last * div_rows.d - uint32_t(row0)) * cols;
+            for (uint32_t v = tid; v < nfull; v += nt) {
+                const uint32_t le = v * kVec;
+                const int64_t e = e0 + le;
+                const typename Store<T>::raw_t out = Store<T>::load(xs, le);
+                float f[8], bits[8], w[8];
+                if (SR) sr_bits(seed, offset + uint64_t(e >> 3), bits);
+                Store<T>::unpack(out, f);                // y as stored
+                const bool second = le >= edge;
+                const float2 prm = make_float2(second ? prm1.x : prm0.x, second ? prm1.y : prm0.y);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = quantize_real<SR>(f[j], prm.x, prm.y, SR ? bits[j] : 0.0f);
+                if (le < edge && le + 7 >= edge) {       // the one vector that straddles two maps
+#pragma unroll
+                    for (int j = 1; j < 8; ++j)
+                        if (le + j >= edge) w[j] = quantize_real<SR>(f[j], prm1.x, prm1.y, SR ? bits[j] : 0.0f);
+                }
+                Nt<T>::store(y, e, out);
+                nt_store<u32x2>(q + e, round_pack_codes<SR>(w));
+            }
+        }
+        // maps of fewer rows than a tile, and the tensor's last few elements: the head of each element's row
+#pragma unroll 1
+        for (uint32_t v = (slab_last - slab_first <= 1 ? nfull : 0u) + tid; v * kVec < nelem; v += nt) {
+            const uint32_t le = v * kVec;
+            const int64_t e = e0 + le;
+            float f[8], bits[8], w[8];
+            if (SR) sr_bits(seed, offset + uint64_t(e >> 3), bits);
+            uint32_t r = fastdiv(le, div_cols), next = (r + 1) * cols;
+            uint32_t slab = fastdiv(uint32_t(row0) + r, div_rows);
+            float2 prm = head_tab[slab - fastdiv(slab, div_heads) * heads];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (le + j == next) {
+                    ++r;
+                    next += cols;
+                    slab = fastdiv(uint32_t(row0) + r, div_rows);
+                    prm = head_tab[slab - fastdiv(slab, div_heads) * heads];
+                }
+                f[j] = le + j < nelem ? LdsElem<T>::get(xs + (le + j) * kB) : 0.0f;
+                w[j] = quantize_real<SR>(f[j], prm.x, prm.y, SR ? bits[j] : 0.0f);
+            }
+            const u32x2 codes = round_pack_codes<SR>(w);
+            if (le + kVec <= nelem) {
+                Nt<T>::store(y, e, Store<T>::load(xs, le));
+                nt_store<u32x2>(q + e, codes);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (le + j < nelem) {
+                        Store<T>::store1(y, e + j, f[j]);   // exact: the value is already of type T
+                        q[e + j] = int8_t(codes[j >> 2] >> (8 * (j & 3)));
+                    }
+            }
+        }
+        __syncthreads();   // the next tile rewrites the region
+    }
+    flush();
+    __syncthreads();
+    float *out = part + int64_t(blockIdx.x) * 2 * heads;
+    for (uint32_t h = threadIdx.x; h < heads; h += blockDim.x) {
+        out[h] = order_val(lmn[h]);
+        out[heads + h] = order_val(lmx[h]);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Rows of 8k elements, 256 < cols <= 4096 (long sequences): a row per group of LPR lanes (a wave, or half or a quarter
 // of one where that fills the lanes better).  Such rows start on vector boundaries, so a lane holds NV whole vectors of
 // ONE row (vector u*LPR + its index in the group), all requested before the first is used; maximum and sum are
@@ -562,6 +781,19 @@ __global__ __launch_bounds__(kThreads, NV <= 4 ? 4 : 3) void k_softmax_fwd_wave(
         out[h] = order_val(lmn[h]);
         out[heads + h] = order_val(lmx[h]);
     }
+}
+
+static SlPlan sf_long_plan(int64_t total_rows, int64_t H, int64_t cols, int elem_bytes)
+{
+    const int64_t lanes = cols <= 1024 ? 32 : 64;
+    return sl_plan(total_rows, cols, H * 16, elem_bytes, cols <= 1024 ? kSfLongTeam : 2 * kSfLongTeam,
+                   4 * sf_long_waves(elem_bytes, int(ceil_div(cols, lanes))));
+}
+// one resident round of workgroups, as far as the workspace has room for their extrema
+static int sl_grid(const SlPlan &p)
+{
+    const int64_t resident = 256 * int64_t(p.per_cu);
+    return int(p.tiles < resident ? p.tiles : resident);
 }
 
 static bool sw_fits(int64_t cols) { return cols % kVec == 0 && cols > kSrMaxCols && cols <= kSwMaxCols; }
@@ -689,6 +921,7 @@ struct SfRoute {
     bool two_step, wave_rows;
     SrPlan rp;
     SfPlan p;
+    SlPlan lp;               // where it is ok, its kernel runs; two_step or p then only say what workspace suffices
 };
 static SfRoute sf_route(int64_t total_rows, int64_t H, int64_t cols, int elem_bytes, bool sr)
 {
@@ -699,13 +932,15 @@ static SfRoute sf_route(int64_t total_rows, int64_t H, int64_t cols, int elem_by
     r.wave_rows = sw_fits(cols);
     if (r.wave_rows) return r;
     if (cols < kVec) { r.two_step = true; return r; }
+    r.lp = sf_long_plan(total_rows, H, cols, elem_bytes);
     r.p = sf_plan(total_rows, cols);
     r.two_step = !r.p.ok;
     return r;
 }
 
-// enough for whichever kernel, storage type and rounding mode the call will use
-size_t softmax_fwd_ws_bytes(int64_t total_rows, int64_t H, int64_t cols)
+// enough for whichever kernel, storage type and rounding mode the call will use; full: for a whole round of
+// k_softmax_fwd_long's workgroups, which also runs with fewer
+static size_t sf_ws_bytes(int64_t total_rows, int64_t H, int64_t cols, bool full)
 {
     if (total_rows <= 0 || H <= 0 || cols <= 0 || total_rows >= (int64_t(1) << 31)) return 16;
     int grid = 0;
@@ -716,6 +951,7 @@ size_t softmax_fwd_ws_bytes(int64_t total_rows, int64_t H, int64_t cols)
             two_step = two_step || r.two_step;
             if (r.rp.ok && r.rp.grid > grid) grid = r.rp.grid;
             if (r.p.ok && r.p.grid > grid) grid = r.p.grid;
+            if (full && r.lp.ok && sl_grid(r.lp) > grid) grid = sl_grid(r.lp);
             if (r.wave_rows && sw_grid_bound(total_rows) > grid) grid = sw_grid_bound(total_rows);
         }
     size_t need = grid == 0 ? 16 : size_t(grid) * 2 * size_t(H) * sizeof(float) + 16;
@@ -725,6 +961,7 @@ size_t softmax_fwd_ws_bytes(int64_t total_rows, int64_t H, int64_t cols)
     }
     return need;
 }
+size_t softmax_fwd_ws_bytes(int64_t total_rows, int64_t H, int64_t cols) { return sf_ws_bytes(total_rows, H, cols, true); }
 
 }  // namespace mesa
 
@@ -757,16 +994,39 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_fwd_q(const void *s_in, int64_t 
         const mesa_status st = check_layout(L);
         if (st != MESA_OK) return st;
         if (!ws || !aligned16(ws) || ws_bytes < update_ws_bytes(L.outer, L.groups, L.inner)) return MESA_ERR_WORKSPACE;
+    } else if (!ws || !aligned16(ws) || ws_bytes < sf_ws_bytes(total_rows, H, cols, false)) {
+        return MESA_ERR_WORKSPACE;
+    }
+    FastDiv dc = make_fastdiv(uint32_t(cols)), dr = make_fastdiv(uint32_t(rows)), dh = make_fastdiv(uint32_t(H));
+    float *part = static_cast<float *>(ws);
+    const int64_t room = int64_t((ws_bytes < (size_t(1) << 40) ? ws_bytes : (size_t(1) << 40)) / (size_t(H) * 2 * sizeof(float)));
+    if (route.lp.ok && room > 0) {
+        const SlPlan &lp = route.lp;
+        const int full = sl_grid(lp), grid = room < full ? int(room) : full;
+        auto go = [&](auto zero, auto stochastic) {
+            typedef decltype(zero) T;
+            constexpr bool SR = decltype(stochastic)::value;
+#define MESA_LAUNCH_SL(LPR_, EPL_) \
+    hipLaunchKernelGGL((k_softmax_fwd_long<T, LPR_, EPL_, SR>), dim3(grid), dim3(64 * lp.waves), lp.lds, s, s_in, y, q, total_rows, \
+                       uint32_t(cols), uint32_t(lp.R), lp.tiles, dc, dr, dh, alpha, beta, seed, offset, part, lp.tab_bytes)
+            MESA_FOR_SL_SHAPE(lp, MESA_LAUNCH_SL);
+#undef MESA_LAUNCH_SL
+        };
+#define MESA_LAUNCH_SL_T(T) do { if (sr) go(T(0), std::true_type()); else go(T(0), std::false_type()); } while (0)
+        MESA_FOR_DTYPE(dt, MESA_LAUNCH_SL_T);
+#undef MESA_LAUNCH_SL_T
+        if (launch_status() != MESA_OK) return MESA_ERR_LAUNCH;   // the consumer must not run on a workspace nobody wrote
+        launch_ema_finalize(part, grid, uint32_t(H), alpha, beta, lambda, 0, 0, 0.0f, s);
+        return launch_status();
+    }
+    if (route.two_step) {
         const unsigned grid = unsigned(total_rows < (int64_t(1) << 20) ? total_rows : (int64_t(1) << 20));
 #define MESA_LAUNCH_SP(T) hipLaunchKernelGGL((k_softmax_fwd_plain_y<T>), dim3(grid), dim3(kThreads), 0, s, s_in, y, total_rows, uint32_t(cols))
         MESA_FOR_DTYPE(dt, MESA_LAUNCH_SP);
 #undef MESA_LAUNCH_SP
         if (launch_status() != MESA_OK) return MESA_ERR_LAUNCH;
-        return mesa_quantize_update_fused(y, dt, L, alpha, beta, lambda, q, mode, seed, offset, ws, ws_bytes, stream);
+        return mesa_quantize_update_fused(y, dt, mesa_layout{B, H, rows * cols}, alpha, beta, lambda, q, mode, seed, offset, ws, ws_bytes, stream);
     }
-    if (!ws || !aligned16(ws) || ws_bytes < softmax_fwd_ws_bytes(total_rows, H, cols)) return MESA_ERR_WORKSPACE;
-    FastDiv dc = make_fastdiv(uint32_t(cols)), dr = make_fastdiv(uint32_t(rows)), dh = make_fastdiv(uint32_t(H));
-    float *part = static_cast<float *>(ws);
     if (rp.ok) {
 #define MESA_LAUNCH_SR(T, LPR_, EPL_, TIGHT_, SR_) \
     hipLaunchKernelGGL((k_softmax_fwd_rows<T, LPR_, EPL_, TIGHT_, SR_>), dim3(rp.grid), dim3(kThreads), rp.lds, s, s_in, y, q, total_rows, \
