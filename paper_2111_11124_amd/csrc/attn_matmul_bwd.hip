@@ -1026,10 +1026,14 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
 // The workgroups of a head's column tiles are neighbours in the grid: they read adjacent segments of the same rows at
 // about the same time and share the N x Dh chunks in the L2.  The N x N operand is read exactly once.
 // As in k_attn_tn the N x Dh operand sits on the M side: a lane ends up with one output row j and runs of four d.
-template <int DT, bool WIDE_CODED> struct TcCfg {
+//
+// RS: groups of four waves that share out the workgroup's chunks (group g takes chunks g, g + RS, ...), each with LDS buffers
+// of its own; their sums are added through LDS at the end, in group order.  Few heads leave a CU one or two workgroups,
+// and one workgroup of four waves has a single chunk of 4 to 8 KB on its way: latency, not HBM, is what it waits for.
+template <int DT, bool WIDE_CODED, int RS> struct TcCfg {
     static constexpr int Dh = 32 * DT;
     static constexpr int kJW = 256;                        // columns of the N x N operand per workgroup
-    static constexpr int kNt = kJW;                        // threads: a wave per 64 columns (two blocks of 32)
+    static constexpr int kNt = kJW;                        // threads of a group: a wave per 64 columns (two blocks of 32)
     static constexpr int kJB = 2;
     static constexpr int kCR = 16;                         // rows per chunk (N is a multiple of 16: no ragged chunk)
     static constexpr int kAhead = WIDE_CODED ? 2 : 1;      // chunks in registers ahead of the one in LDS: the codes' chunks are
@@ -1042,18 +1046,23 @@ template <int DT, bool WIDE_CODED> struct TcCfg {
     static constexpr int kVecRowN = Dh * (WIDE_CODED ? 2 : 1) / 16;
     static constexpr int kNarrowVecs = (kCR * kVecRowN + kNt - 1) / kNt;
     static constexpr int kStage = kCR * kPitchW + kCR * kRowN;
-    static constexpr int kLds = 2 * kStage;
+    static constexpr int kSum = (kJB * DT * 16 + kJB + DT) * kNt * 4;   // a group's sums
+    static constexpr int kLds = RS * 2 * kStage > (RS > 1 ? kSum : 0) ? RS * 2 * kStage : kSum;
+    static constexpr int kWaves = RS > 1 ? RS : 2;         // per SIMD, for the register budget
 };
 
-template <int DT, bool WIDE_CODED, typename ET>
-__global__ __launch_bounds__((TcCfg<DT, WIDE_CODED>::kNt), DT == 4 ? 1 : 2) void k_attn_tn_cols(const void *__restrict__ wide_, const void *__restrict__ narrow_,
+template <int DT, bool WIDE_CODED, int RS, typename ET>
+__global__ __launch_bounds__((TcCfg<DT, WIDE_CODED, RS>::kNt * RS), (TcCfg<DT, WIDE_CODED, RS>::kWaves)) void k_attn_tn_cols(const void *__restrict__ wide_, const void *__restrict__ narrow_,
                                                               _Float16 *__restrict__ out, int N, int heads, int tiles_j, float scale,
                                                               const float *__restrict__ alpha, const float *__restrict__ beta)
 {
-    typedef TcCfg<DT, WIDE_CODED> C;
-    __shared__ __attribute__((aligned(16))) unsigned char lds_tc[C::kLds];
+    typedef TcCfg<DT, WIDE_CODED, RS> C;
+    __shared__ __attribute__((aligned(16))) unsigned char lds_all[C::kLds];
     constexpr int Dh = C::Dh;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int group = RS > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / C::kNt) : 0;
+    const int tid = RS > 1 ? int(threadIdx.x) % C::kNt : int(threadIdx.x);   // within the group
+    const int lane = tid & 63, wave = tid >> 6;
+    unsigned char *lds_tc = lds_all + group * 2 * C::kStage;
     const int64_t bh = blockIdx.x / unsigned(tiles_j);
     const int j0 = int(blockIdx.x % unsigned(tiles_j)) * C::kJW;
     const unsigned char *wide = static_cast<const unsigned char *>(wide_) + (bh * N * int64_t(N) + j0) * C::kWideEb;
@@ -1073,7 +1082,7 @@ __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED>::kNt), DT == 4 ? 1 : 2) void
     }
     auto load_chunk = [&](int c, auto set_) {
         constexpr int S = decltype(set_)::value;
-        constexpr int rows = C::kCR;
+        const int rows = c < nchunks ? C::kCR : 0;         // a chunk past the end (RS > 1): zeros
         const unsigned char *src = wide + int64_t(c) * C::kCR * N * C::kWideEb;
 #pragma unroll
         for (int k = 0; k < C::kWideVecs; ++k) {
@@ -1120,11 +1129,13 @@ __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED>::kNt), DT == 4 ? 1 : 2) void
                                      : ((blk >> 1) * 8 + (sl >> 1)) * C::kRowN + (blk & 1) * 16 + (sl & 1) * 8;
     const bool wave_live = wave * 64 < cols;               // uniform per wave
 
-    // chunk c waits in register set c % kAhead; it goes to LDS buffer c % 2 when chunk c - 1 is being multiplied
+    // the group's chunk c is the head's chunk c * RS + group; it waits in register set c % kAhead and goes to LDS buffer
+    // c % 2 when chunk c - 1 is being multiplied
+    const int steps = (nchunks + RS - 1) / RS;             // the same for every group: they meet at the barriers
     auto chunk_step = [&](int c, auto set_) {
         const int b = c & 1;
         store_chunk(b, set_);
-        if (c + C::kAhead < nchunks) load_chunk(c + C::kAhead, set_);
+        if (c + C::kAhead < steps) load_chunk((c + C::kAhead) * RS + group, set_);
         __syncthreads();   // chunk c is in LDS; every wave has finished with chunk c - 1 (the other buffer)
         const unsigned char *lw = lds_tc + b * C::kStage, *ln = lw + C::kCR * C::kPitchW;
         if (!wave_live) return;                          // its columns lie past N (the barrier above is still met)
@@ -1163,21 +1174,45 @@ __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED>::kNt), DT == 4 ? 1 : 2) void
             }
         }
     };
-    load_chunk(0, std::integral_constant<int, 0>());
-    if (C::kAhead == 2 && nchunks > 1) load_chunk(1, std::integral_constant<int, C::kAhead - 1>());
-    for (int c = 0; c < nchunks; c += C::kAhead) {
+    load_chunk(group, std::integral_constant<int, 0>());
+    if (C::kAhead == 2 && steps > 1) load_chunk(RS + group, std::integral_constant<int, C::kAhead - 1>());
+    for (int c = 0; c < steps; c += C::kAhead) {
         chunk_step(c, std::integral_constant<int, 0>());
-        if (C::kAhead == 2 && c + 1 < nchunks) chunk_step(c + 1, std::integral_constant<int, C::kAhead - 1>());
+        if (C::kAhead == 2 && c + 1 < steps) chunk_step(c + 1, std::integral_constant<int, C::kAhead - 1>());
+    }
+    if constexpr (RS > 1) {
+        // the groups' sums, one group after the other: a value per lane at a stride of the group's threads
+        float *sums = reinterpret_cast<float *>(lds_all) + tid;
+        auto each = [&](auto f) {
+            int n = 0;
+#pragma unroll
+            for (int jb = 0; jb < C::kJB; ++jb)
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) { float t = acc[jb][dt][v]; f(t, n++); acc[jb][dt][v] = t; }
+#pragma unroll
+            for (int jb = 0; jb < C::kJB; ++jb) f(csum[jb], n++);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) f(dsum[dt], n++);
+        };
+#pragma unroll 1
+        for (int g = 1; g < RS; ++g) {
+            __syncthreads();   // every wave is done with the chunks, or with the sums before
+            if (group == g) each([&](float &x, int n) { sums[n * C::kNt] = x; });
+            __syncthreads();
+            if (group == 0) each([&](float &x, int n) { x += sums[n * C::kNt]; });
+        }
     }
 
     // ---- epilogue: lane l, register v of a tile: d = 32*dt + 8*(v/4) + 4*(l/32) + v%4, row j = (tile's first) + l%32 ----
     const int h = int(bh % heads);
     const float s = alpha[h] / 255.0f;
     const float off = fmaf(BmNum<ET>::kCentre, s, beta[h]);
-    float *dsums = reinterpret_cast<float *>(lds_tc);      // dV: the sums of dO per d, for every lane to pick its four
+    float *dsums = reinterpret_cast<float *>(lds_all);     // dV: the sums of dO per d, for every lane to pick its four
     if (WIDE_CODED) {
         __syncthreads();                                   // every wave is done with the chunks
-        if (wave == 0) {                                   // (a live wave: column 0 of the tile always exists)
+        if (group == 0 && wave == 0) {                     // (a live wave: column 0 of the tile always exists)
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
                 const float t = dsum[dt] + __shfl_xor(dsum[dt], 32);   // both halves of the rows
@@ -1186,6 +1221,7 @@ __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED>::kNt), DT == 4 ? 1 : 2) void
         }
         __syncthreads();
     }
+    if (group != 0) return;
 #pragma unroll
     for (int jb = 0; jb < C::kJB; ++jb) {
         const int j = j0 + wave * 64 + jb * 32 + fl;
@@ -1595,16 +1631,19 @@ template <bool WIDE_CODED, typename ET>
 static void launch_tn_cols(const void *wide, const void *narrow, _Float16 *out, int64_t batches, int N, int Dh, int heads, float scale,
                            const float *alpha, const float *beta, hipStream_t s)
 {
-#define MESA_LAUNCH_TC(DT_) \
-    do { \
-        typedef TcCfg<DT_, WIDE_CODED> C; \
-        const int tiles_j = int(ceil_div(N, C::kJW)); \
-        hipLaunchKernelGGL((k_attn_tn_cols<DT_, WIDE_CODED, ET>), dim3(unsigned(batches * tiles_j)), dim3(C::kNt), 0, s, wide, narrow, out, N, \
-                           heads, tiles_j, scale, alpha, beta); \
-    } while (0)
-    if (Dh == 32) MESA_LAUNCH_TC(1);
-    else if (Dh == 64) MESA_LAUNCH_TC(2);
-    else MESA_LAUNCH_TC(4);
+    const int tiles_j = int(ceil_div(N, 256));
+    const int64_t wgs = batches * tiles_j;
+    // groups per workgroup, by the workgroups there are: (1, 16, 4096, 64), 256 of them, 759 / 644 / 630 us for the whole
+    // attention backward with 1 / 2 / 4 groups; (2, 16, 4096, 64), 512: 1269 / 1235 / 1251; (8, 12, 1024, 64), 384:
+    // 261 / 254 / 265; (16, 12, 576, 64), 576: 188 / 200 / 210; short columns pay the adding sooner: (16, 12, 256, 64),
+    // 192: 61.0 / 57.9 / 60.7
+    const int rs = wgs > 512 ? 1 : wgs <= 256 && N >= 1024 && Dh <= 64 ? 4 : 2;
+#define MESA_LAUNCH_TC(DT_, RS_) \
+    hipLaunchKernelGGL((k_attn_tn_cols<DT_, WIDE_CODED, RS_, ET>), dim3(unsigned(wgs)), dim3(TcCfg<DT_, WIDE_CODED, RS_>::kNt * (RS_)), 0, s, wide, narrow, \
+                       out, N, heads, tiles_j, scale, alpha, beta)
+    if (Dh == 32) { if (rs == 4) MESA_LAUNCH_TC(1, 4); else if (rs == 2) MESA_LAUNCH_TC(1, 2); else MESA_LAUNCH_TC(1, 1); }
+    else if (Dh == 64) { if (rs == 4) MESA_LAUNCH_TC(2, 4); else if (rs == 2) MESA_LAUNCH_TC(2, 2); else MESA_LAUNCH_TC(2, 1); }
+    else { if (rs == 2) MESA_LAUNCH_TC(4, 2); else MESA_LAUNCH_TC(4, 1); }
 #undef MESA_LAUNCH_TC
 }
 
