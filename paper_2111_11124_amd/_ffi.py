@@ -3,16 +3,20 @@
 Every function below has the name and the argument order of the C entry point it calls
 (include/mesa.h); tensors are torch tensors on the GPU, whose data pointers and current stream are
 passed through.  No arithmetic of the method happens in Python, and there is no fallback: if the
-shared library is missing or a call fails, an exception is raised.
+shared library is missing or a call fails, an exception is raised.  The ordinary form of a compute call is
+marshalled natively (csrc/marshal.c: 1 to 2 us of the host instead of 6 to 8); what that does not know -- and
+every argument error -- goes through ctypes.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 from pathlib import Path
 
 import torch  # noqa: F401  (first, so that libmesa binds to the HIP runtime torch has loaded)
 
 _LIB_PATH = Path(__file__).resolve().parent / "libmesa.so"
+_FAST_PATH = Path(__file__).resolve().parent / "_marshal.so"
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_LAUNCH = range(5)
 F32, F16, BF16 = 0, 1, 2
@@ -49,11 +53,24 @@ class Conv2d(C.Structure):
 
 
 _lib = None
+_fast = None   # the native marshalling (csrc/marshal.c), there once _lib is
 _vp, _i64, _u64, _int, _f32, _sz = C.c_void_p, C.c_int64, C.c_uint64, C.c_int, C.c_float, C.c_size_t
 
 
+def _load_fast():
+    """The compute calls' ordinary form, marshalled natively: each function returns the status, or None for a call that
+    the general path below has to judge."""
+    spec = importlib.util.spec_from_file_location("paper_2111_11124_amd._marshal", _FAST_PATH)
+    if not _FAST_PATH.exists():
+        raise RuntimeError(f"{_FAST_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
+    fast = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fast)
+    fast.setup(torch.float16, torch.float32, torch.bfloat16, Conv2d, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    return fast
+
+
 def lib() -> C.CDLL:
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not _LIB_PATH.exists():
             raise RuntimeError(f"{_LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
@@ -107,6 +124,8 @@ def lib() -> C.CDLL:
             if name not in ("mesa_workspace_bytes", "mesa_status_string", "mesa_version", "mesa_static_scratch_bytes",
                             "mesa_conv2d_dw_q_workspace_bytes"):
                 fn.restype = _int
+        if _fast is None:
+            _fast = _load_fast()
         _lib = L
     return _lib
 
@@ -157,42 +176,70 @@ def _ws_args(ws):
 
 
 def mesa_update_running_params(x, layout, alpha, beta, lam, first_call, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_update_running_params(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
-                                            int(bool(first_call)), p, n, _stream()), "mesa_update_running_params")
+    st = _fast.update_running_params(x, layout, alpha, beta, lam, first_call, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_update_running_params(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
+                                                int(bool(first_call)), p, n, _stream()), "mesa_update_running_params")
+    elif st:
+        _check(st, "mesa_update_running_params")
 
 
 def mesa_update_running_params_sym(x, layout, alpha, beta, lam, first_call, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_update_running_params_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
-                                                int(bool(first_call)), p, n, _stream()), "mesa_update_running_params_sym")
+    st = _fast.update_running_params_sym(x, layout, alpha, beta, lam, first_call, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_update_running_params_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
+                                                    int(bool(first_call)), p, n, _stream()), "mesa_update_running_params_sym")
+    elif st:
+        _check(st, "mesa_update_running_params_sym")
 
 
 def mesa_update_running_params_fixed_beta(x, layout, alpha, beta, lam, first_call, beta_fixed, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_update_running_params_fixed_beta(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
-                                                       int(bool(first_call)), float(beta_fixed), p, n, _stream()),
-           "mesa_update_running_params_fixed_beta")
+    st = _fast.update_running_params_fixed_beta(x, layout, alpha, beta, lam, first_call, beta_fixed, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_update_running_params_fixed_beta(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
+                                                           int(bool(first_call)), float(beta_fixed), p, n, _stream()),
+               "mesa_update_running_params_fixed_beta")
+    elif st:
+        _check(st, "mesa_update_running_params_fixed_beta")
 
 
 def mesa_update_running_scale_sym(x, layout, m, lam, first_call, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_update_running_scale_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(m), float(lam), int(bool(first_call)), p, n,
-                                               _stream()), "mesa_update_running_scale_sym")
+    st = _fast.update_running_scale_sym(x, layout, m, lam, first_call, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_update_running_scale_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(m), float(lam), int(bool(first_call)), p, n,
+                                                   _stream()), "mesa_update_running_scale_sym")
+    elif st:
+        _check(st, "mesa_update_running_scale_sym")
 
 
 def mesa_quantize_sym(x, layout, m, q, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    _check(lib().mesa_quantize_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(m), _ptr(q), int(mode), int(seed), int(offset),
-                                   _stream()), "mesa_quantize_sym")
+    st = _fast.quantize_sym(x, layout, m, q, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_quantize_sym(_ptr(x), _dt(x), Layout(*layout), _ptr(m), _ptr(q), int(mode), int(seed), int(offset),
+                                       _stream()), "mesa_quantize_sym")
+    elif st:
+        _check(st, "mesa_quantize_sym")
 
 
 def mesa_dequantize_sym(q, layout, m, x_hat):
-    _check(lib().mesa_dequantize_sym(_ptr(q), Layout(*layout), _ptr(m), _ptr(x_hat), _dt(x_hat), _stream()), "mesa_dequantize_sym")
+    st = _fast.dequantize_sym(q, layout, m, x_hat) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_dequantize_sym(_ptr(q), Layout(*layout), _ptr(m), _ptr(x_hat), _dt(x_hat), _stream()), "mesa_dequantize_sym")
+    elif st:
+        _check(st, "mesa_dequantize_sym")
 
 
 def mesa_update_running_params_static(x, layout, alpha, beta, lam, first_call):
-    _check(lib().mesa_update_running_params_static(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
-                                                   int(bool(first_call)), _stream()), "mesa_update_running_params_static")
+    st = _fast.update_running_params_static(x, layout, alpha, beta, lam, first_call) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_update_running_params_static(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam),
+                                                       int(bool(first_call)), _stream()), "mesa_update_running_params_static")
+    elif st:
+        _check(st, "mesa_update_running_params_static")
 
 
 def static_scratch_bytes() -> int:
@@ -200,101 +247,165 @@ def static_scratch_bytes() -> int:
 
 
 def mesa_quantize_headwise(x, layout, alpha, beta, q, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    _check(lib().mesa_quantize_headwise(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(q), int(mode),
-                                        int(seed), int(offset), _stream()), "mesa_quantize_headwise")
+    st = _fast.quantize_headwise(x, layout, alpha, beta, q, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_quantize_headwise(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(q), int(mode),
+                                            int(seed), int(offset), _stream()), "mesa_quantize_headwise")
+    elif st:
+        _check(st, "mesa_quantize_headwise")
 
 
 def mesa_quantize_update_fused(x, layout, alpha, beta, lam, q, ws, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_quantize_update_fused(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam), _ptr(q),
-                                            int(mode), int(seed), int(offset), p, n, _stream()), "mesa_quantize_update_fused")
+    st = _fast.quantize_update_fused(x, layout, alpha, beta, lam, q, ws, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_quantize_update_fused(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam), _ptr(q),
+                                                int(mode), int(seed), int(offset), p, n, _stream()), "mesa_quantize_update_fused")
+    elif st:
+        _check(st, "mesa_quantize_update_fused")
 
 
 def mesa_gelu_fwd_q(x, layout, alpha, beta, lam, y, q, ws, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    assert y.dtype == x.dtype
-    p, n = _ws_args(ws)
-    _check(lib().mesa_gelu_fwd_q(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam), _ptr(y), _ptr(q),
-                                 int(mode), int(seed), int(offset), p, n, _stream()), "mesa_gelu_fwd_q")
+    st = _fast.gelu_fwd_q(x, layout, alpha, beta, lam, y, q, ws, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        assert y.dtype == x.dtype
+        p, n = _ws_args(ws)
+        _check(lib().mesa_gelu_fwd_q(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), float(lam), _ptr(y), _ptr(q),
+                                     int(mode), int(seed), int(offset), p, n, _stream()), "mesa_gelu_fwd_q")
+    elif st:
+        _check(st, "mesa_gelu_fwd_q")
 
 
 def mesa_softmax_fwd_q(s, B, H, rows, cols, alpha, beta, lam, y, q, ws, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    assert y.dtype == s.dtype
-    p, n = _ws_args(ws)
-    _check(lib().mesa_softmax_fwd_q(_ptr(s), B, H, rows, cols, _ptr(alpha), _ptr(beta), float(lam), _ptr(y), _ptr(q), int(mode),
-                                    int(seed), int(offset), p, n, _dt(s), _stream()), "mesa_softmax_fwd_q")
+    st = _fast.softmax_fwd_q(s, B, H, rows, cols, alpha, beta, lam, y, q, ws, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        assert y.dtype == s.dtype
+        p, n = _ws_args(ws)
+        _check(lib().mesa_softmax_fwd_q(_ptr(s), B, H, rows, cols, _ptr(alpha), _ptr(beta), float(lam), _ptr(y), _ptr(q), int(mode),
+                                        int(seed), int(offset), p, n, _dt(s), _stream()), "mesa_softmax_fwd_q")
+    elif st:
+        _check(st, "mesa_softmax_fwd_q")
 
 
 def mesa_layernorm_fwd_q(x, M, D, G, gamma, bias, eps, alpha, beta, lam, y, mean, rstd, q, ws, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    assert y.dtype == x.dtype == gamma.dtype == bias.dtype
-    p, n = _ws_args(ws)
-    _check(lib().mesa_layernorm_fwd_q(_ptr(x), M, D, G, _ptr(gamma), _ptr(bias), float(eps), _ptr(alpha), _ptr(beta), float(lam),
-                                      _ptr(y), _ptr(mean), _ptr(rstd), _ptr(q), int(mode), int(seed), int(offset), p, n, _dt(x),
-                                      _stream()), "mesa_layernorm_fwd_q")
+    st = _fast.layernorm_fwd_q(x, M, D, G, gamma, bias, eps, alpha, beta, lam, y, mean, rstd, q, ws, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        assert y.dtype == x.dtype == gamma.dtype == bias.dtype
+        p, n = _ws_args(ws)
+        _check(lib().mesa_layernorm_fwd_q(_ptr(x), M, D, G, _ptr(gamma), _ptr(bias), float(eps), _ptr(alpha), _ptr(beta), float(lam),
+                                          _ptr(y), _ptr(mean), _ptr(rstd), _ptr(q), int(mode), int(seed), int(offset), p, n, _dt(x),
+                                          _stream()), "mesa_layernorm_fwd_q")
+    elif st:
+        _check(st, "mesa_layernorm_fwd_q")
 
 
 def mesa_dequantize(q, layout, alpha, beta, x_hat):
-    _check(lib().mesa_dequantize(_ptr(q), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(x_hat), _dt(x_hat), _stream()),
-           "mesa_dequantize")
+    st = _fast.dequantize(q, layout, alpha, beta, x_hat) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_dequantize(_ptr(q), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(x_hat), _dt(x_hat), _stream()),
+               "mesa_dequantize")
+    elif st:
+        _check(st, "mesa_dequantize")
 
 
 def mesa_quantize_headwise_b4(x, layout, alpha, beta, q4, mode=ROUND_STOCHASTIC, seed=0, offset=0):
-    _check(lib().mesa_quantize_headwise_b4(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(q4), int(mode),
-                                           int(seed), int(offset), _stream()), "mesa_quantize_headwise_b4")
+    st = _fast.quantize_headwise_b4(x, layout, alpha, beta, q4, mode, seed, offset) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_quantize_headwise_b4(_ptr(x), _dt(x), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(q4), int(mode),
+                                               int(seed), int(offset), _stream()), "mesa_quantize_headwise_b4")
+    elif st:
+        _check(st, "mesa_quantize_headwise_b4")
 
 
 def mesa_dequantize_b4(q4, layout, alpha, beta, x_hat):
-    _check(lib().mesa_dequantize_b4(_ptr(q4), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(x_hat), _dt(x_hat), _stream()),
-           "mesa_dequantize_b4")
+    st = _fast.dequantize_b4(q4, layout, alpha, beta, x_hat) if _lib is not None else None
+    if st is None:
+        _check(lib().mesa_dequantize_b4(_ptr(q4), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(x_hat), _dt(x_hat), _stream()),
+               "mesa_dequantize_b4")
+    elif st:
+        _check(st, "mesa_dequantize_b4")
 
 
 def mesa_gelu_bwd_q_b4(q4, layout, alpha, beta, dy, dx):
-    assert dx.dtype == dy.dtype
-    _check(lib().mesa_gelu_bwd_q_b4(_ptr(q4), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
-           "mesa_gelu_bwd_q_b4")
+    st = _fast.gelu_bwd_q_b4(q4, layout, alpha, beta, dy, dx) if _lib is not None else None
+    if st is None:
+        assert dx.dtype == dy.dtype
+        _check(lib().mesa_gelu_bwd_q_b4(_ptr(q4), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
+               "mesa_gelu_bwd_q_b4")
+    elif st:
+        _check(st, "mesa_gelu_bwd_q_b4")
 
 
 def mesa_softmax_bwd_q(yq, B, H, rows, cols, alpha, beta, dy, dx):
-    assert dx.dtype == dy.dtype
-    _check(lib().mesa_softmax_bwd_q(_ptr(yq), B, H, rows, cols, _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy),
-                                    _stream()), "mesa_softmax_bwd_q")
+    st = _fast.softmax_bwd_q(yq, B, H, rows, cols, alpha, beta, dy, dx) if _lib is not None else None
+    if st is None:
+        assert dx.dtype == dy.dtype
+        _check(lib().mesa_softmax_bwd_q(_ptr(yq), B, H, rows, cols, _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy),
+                                        _stream()), "mesa_softmax_bwd_q")
+    elif st:
+        _check(st, "mesa_softmax_bwd_q")
 
 
 def mesa_gelu_bwd_q(xq, layout, alpha, beta, dy, dx):
-    assert dx.dtype == dy.dtype
-    _check(lib().mesa_gelu_bwd_q(_ptr(xq), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
-           "mesa_gelu_bwd_q")
+    st = _fast.gelu_bwd_q(xq, layout, alpha, beta, dy, dx) if _lib is not None else None
+    if st is None:
+        assert dx.dtype == dy.dtype
+        _check(lib().mesa_gelu_bwd_q(_ptr(xq), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
+               "mesa_gelu_bwd_q")
+    elif st:
+        _check(st, "mesa_gelu_bwd_q")
 
 
 def mesa_relu_bwd_q(xq, layout, alpha, beta, dy, dx):
-    assert dx.dtype == dy.dtype
-    _check(lib().mesa_relu_bwd_q(_ptr(xq), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
-           "mesa_relu_bwd_q")
+    st = _fast.relu_bwd_q(xq, layout, alpha, beta, dy, dx) if _lib is not None else None
+    if st is None:
+        assert dx.dtype == dy.dtype
+        _check(lib().mesa_relu_bwd_q(_ptr(xq), Layout(*layout), _ptr(alpha), _ptr(beta), _ptr(dy), _ptr(dx), _dt(dy), _stream()),
+               "mesa_relu_bwd_q")
+    elif st:
+        _check(st, "mesa_relu_bwd_q")
 
 
 def mesa_attn_av_bwd_q(aq, vq, B, H, N, Dh, alpha_a, beta_a, alpha_v, beta_v, dO, dA, dV):
-    assert dA.dtype == dO.dtype == dV.dtype
-    _check(lib().mesa_attn_av_bwd_q(_ptr(aq), _ptr(vq), B, H, N, Dh, _ptr(alpha_a), _ptr(beta_a), _ptr(alpha_v), _ptr(beta_v),
-                                    _ptr(dO), _ptr(dA), _ptr(dV), _dt(dO), _stream()), "mesa_attn_av_bwd_q")
+    st = _fast.attn_av_bwd_q(aq, vq, B, H, N, Dh, alpha_a, beta_a, alpha_v, beta_v, dO, dA, dV) if _lib is not None else None
+    if st is None:
+        assert dA.dtype == dO.dtype == dV.dtype
+        _check(lib().mesa_attn_av_bwd_q(_ptr(aq), _ptr(vq), B, H, N, Dh, _ptr(alpha_a), _ptr(beta_a), _ptr(alpha_v), _ptr(beta_v),
+                                        _ptr(dO), _ptr(dA), _ptr(dV), _dt(dO), _stream()), "mesa_attn_av_bwd_q")
+    elif st:
+        _check(st, "mesa_attn_av_bwd_q")
 
 
 def mesa_attn_qk_bwd_q(qq, kq, B, H, N, Dh, alpha_q, beta_q, alpha_k, beta_k, dS, scale, dQ, dK):
-    assert dQ.dtype == dS.dtype == dK.dtype
-    _check(lib().mesa_attn_qk_bwd_q(_ptr(qq), _ptr(kq), B, H, N, Dh, _ptr(alpha_q), _ptr(beta_q), _ptr(alpha_k), _ptr(beta_k),
-                                    _ptr(dS), float(scale), _ptr(dQ), _ptr(dK), _dt(dS), _stream()), "mesa_attn_qk_bwd_q")
+    st = _fast.attn_qk_bwd_q(qq, kq, B, H, N, Dh, alpha_q, beta_q, alpha_k, beta_k, dS, scale, dQ, dK) if _lib is not None else None
+    if st is None:
+        assert dQ.dtype == dS.dtype == dK.dtype
+        _check(lib().mesa_attn_qk_bwd_q(_ptr(qq), _ptr(kq), B, H, N, Dh, _ptr(alpha_q), _ptr(beta_q), _ptr(alpha_k), _ptr(beta_k),
+                                        _ptr(dS), float(scale), _ptr(dQ), _ptr(dK), _dt(dS), _stream()), "mesa_attn_qk_bwd_q")
+    elif st:
+        _check(st, "mesa_attn_qk_bwd_q")
 
 
 def mesa_layernorm_bwd_q(xq, M, D, G, alpha, beta, mean, rstd, gamma, dy, dx, dgamma, dbeta, ws):
-    assert dx.dtype == dy.dtype == gamma.dtype
-    p, n = _ws_args(ws)
-    _check(lib().mesa_layernorm_bwd_q(_ptr(xq), M, D, G, _ptr(alpha), _ptr(beta), _ptr(mean), _ptr(rstd), _ptr(gamma),
-                                      _ptr(dy), _ptr(dx), _ptr(dgamma), _ptr(dbeta), _dt(dy), p, n, _stream()),
-           "mesa_layernorm_bwd_q")
+    st = _fast.layernorm_bwd_q(xq, M, D, G, alpha, beta, mean, rstd, gamma, dy, dx, dgamma, dbeta, ws) if _lib is not None else None
+    if st is None:
+        assert dx.dtype == dy.dtype == gamma.dtype
+        p, n = _ws_args(ws)
+        _check(lib().mesa_layernorm_bwd_q(_ptr(xq), M, D, G, _ptr(alpha), _ptr(beta), _ptr(mean), _ptr(rstd), _ptr(gamma),
+                                          _ptr(dy), _ptr(dx), _ptr(dgamma), _ptr(dbeta), _dt(dy), p, n, _stream()),
+               "mesa_layernorm_bwd_q")
+    elif st:
+        _check(st, "mesa_layernorm_bwd_q")
 
 
 def mesa_linear_dw_q(xq, M, K, G, alpha, beta, dy, N_out, dW, db, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_linear_dw_q(_ptr(xq), M, K, G, _ptr(alpha), _ptr(beta), _ptr(dy), N_out, _dt(dy), _ptr(dW), _ptr(db),
-                                  p, n, _stream()), "mesa_linear_dw_q")
+    st = _fast.linear_dw_q(xq, M, K, G, alpha, beta, dy, N_out, dW, db, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_linear_dw_q(_ptr(xq), M, K, G, _ptr(alpha), _ptr(beta), _ptr(dy), N_out, _dt(dy), _ptr(dW), _ptr(db),
+                                      p, n, _stream()), "mesa_linear_dw_q")
+    elif st:
+        _check(st, "mesa_linear_dw_q")
 
 
 def conv2d_dw_q_workspace_bytes(cv: Conv2d, dtype: int = F16) -> int:
@@ -302,9 +413,13 @@ def conv2d_dw_q_workspace_bytes(cv: Conv2d, dtype: int = F16) -> int:
 
 
 def mesa_conv2d_dw_q(xq, cv: Conv2d, G, alpha, beta, dy, dW, db, ws):
-    p, n = _ws_args(ws)
-    _check(lib().mesa_conv2d_dw_q(_ptr(xq), cv, G, _ptr(alpha), _ptr(beta), _ptr(dy), _dt(dy), _ptr(dW), _ptr(db), p, n, _stream()),
-           "mesa_conv2d_dw_q")
+    st = _fast.conv2d_dw_q(xq, cv, G, alpha, beta, dy, dW, db, ws) if _lib is not None else None
+    if st is None:
+        p, n = _ws_args(ws)
+        _check(lib().mesa_conv2d_dw_q(_ptr(xq), cv, G, _ptr(alpha), _ptr(beta), _ptr(dy), _dt(dy), _ptr(dW), _ptr(db), p, n, _stream()),
+               "mesa_conv2d_dw_q")
+    elif st:
+        _check(st, "mesa_conv2d_dw_q")
 
 
 def mesa_stream_copy(src, dst, nbytes):

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -11,6 +12,7 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 LIB = PKG / "libmesa.so"
+FAST = PKG / "_marshal.so"
 OBJ = PKG / "_build"
 SOURCES = ["stream_kernels.hip", "softmax_fwd.hip", "softmax_bwd.hip", "layernorm_fwd.hip", "layernorm_bwd.hip", "linear_dw.hip", "attn_matmul_bwd.hip", "lowbit.hip", "conv_dw.hip", "mfma_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -45,6 +47,12 @@ def build(verbose: bool = True) -> Path:
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
+    # the binding's native marshalling: plain C against the Python headers, bound to the library beside it
+    tmp = FAST.with_suffix(f".tmp{os.getpid()}.so")
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", f"-I{INCLUDE}", f"-I{sysconfig.get_path('include')}",
+           str(CSRC / "marshal.c"), "-o", str(tmp), f"-L{PKG}", "-l:libmesa.so", "-Wl,-rpath,$ORIGIN"]
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, FAST)
     if verbose:
         print(f"built {LIB}")
     return LIB
