@@ -43,6 +43,8 @@ constexpr int kDwPF = 3;         // stages prefetched into registers ahead of th
 
 // BN x BK tile of dW per workgroup, WGN x WGK waves, each wave (BN/WGN) x (BK/WGK) as 32x32 MFMA tiles
 template <int BN, int BK, int WGN, int WGK> struct DwCfg {
+    static constexpr bool SIGNED = BN * BK <= 128 * 128;                  // which value of the code is contracted (DwElem)
+    static constexpr bool DIRECT = BN * BK <= 128 * 128;                  // one slice: finishes dW itself (large tiles have many, or fill the chip)
     static constexpr int PF = BN * BK <= 128 * 128 ? 2 * kDwPF : kDwPF;   // small tiles: less per stage, so more stages in flight
     static constexpr int NW = WGN * WGK;
     static constexpr int THREADS = NW * 64;
@@ -91,12 +93,34 @@ __device__ __forceinline__ v4s codes_to_bf4(int raw)
     return __builtin_bit_cast(v4s, w);
 }
 
+// four signed codes -> four bfloat16 values q
+__device__ __forceinline__ v4s signed_codes_to_bf4(int raw)
+{
+    const uint32_t f0 = __float_as_uint(float(int(int8_t(raw)))), f1 = __float_as_uint(float(int(int8_t(raw >> 8))));
+    const uint32_t f2 = __float_as_uint(float(int(int8_t(raw >> 16)))), f3 = __float_as_uint(float(raw >> 24));
+    const v2i w = {int(__builtin_amdgcn_perm(f1, f0, 0x07060302u)), int(__builtin_amdgcn_perm(f3, f2, 0x07060302u))};
+    return __builtin_bit_cast(v4s, w);
+}
+
+// four signed codes -> four binary16 values q
+__device__ __forceinline__ v4s signed_codes_to_half4(int raw)
+{
+    const v2i w = __builtin_bit_cast(v2i, codes_to_half4(raw));
+    const h2 k1152 = {(_Float16)1152.0f, (_Float16)1152.0f};
+    const v2i q = {int(as_u32(as_h2(uint32_t(w[0])) - k1152)), int(as_u32(as_h2(uint32_t(w[1])) - k1152))};
+    return __builtin_bit_cast(v4s, q);
+}
+
 // What the operand type decides: how codes become matrix-core operands and which value of the code is
-// contracted (kCentre: the offset c in "operand = x_bar - c"), the row sums of dy, and the MFMA itself.
+// contracted (centre: the offset c in "operand = x_bar - c"), the row sums of dy, and the MFMA itself.
+// SIGNED: the signed code, centred.  The small tile takes it: its slices are the longest (one slice of the whole matrix where
+// that is cheapest), and a sum that carries c * S0 loses a bit with every fourfold length; it waits for memory and
+// latency, not for the few instructions (errors against 64 bits at 1604 x (1344 -> 1752): 5e-5 with six slices of
+// 1024 + x_bar, 1e-4 with one slice of them, 1e-6 centred).
 template <typename E> struct DwElem;
 template <> struct DwElem<_Float16> {
-    static constexpr float kCentre = -1024.0f;
-    __device__ static __forceinline__ v4s convert(int raw) { return codes_to_half4(raw); }
+    static constexpr float centre(bool is_signed) { return is_signed ? 128.0f : -1024.0f; }
+    template <bool SIGNED> __device__ static __forceinline__ v4s convert(int raw) { return SIGNED ? signed_codes_to_half4(raw) : codes_to_half4(raw); }
     __device__ static __forceinline__ float dot_ones(uint32_t pair, float acc)
     {
         const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
@@ -110,8 +134,8 @@ template <> struct DwElem<_Float16> {
     }
 };
 template <> struct DwElem<__bf16> {
-    static constexpr float kCentre = 0.0f;
-    __device__ static __forceinline__ v4s convert(int raw) { return codes_to_bf4(raw); }
+    static constexpr float centre(bool is_signed) { return is_signed ? 128.0f : 0.0f; }
+    template <bool SIGNED> __device__ static __forceinline__ v4s convert(int raw) { return SIGNED ? signed_codes_to_bf4(raw) : codes_to_bf4(raw); }
     __device__ static __forceinline__ float dot_ones(uint32_t pair, float acc)
     {
         return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, pair), __builtin_bit_cast(v2b, 0x3F803F80u), acc, false);
@@ -124,13 +148,20 @@ template <> struct DwElem<__bf16> {
     }
 };
 
-// P[split][n][k] = sum over the slice's m of dy[m][n] * (x_bar[m][k] - kCentre)   (x_bar - 128 is the signed code)
+// A single slice needs no second kernel: its workgroups apply the affine map to their own sums (dW non-null).
+struct DwDirect {
+    const float *alpha, *beta;
+    FastDiv div_per;          // columns per channel group
+    float *dW, *db;
+};
+
+// P[split][n][k] = sum over the slice's m of dy[m][n] * (x_bar[m][k] - centre)   (x_bar - 128 is the signed code)
 // S0[split][n]   = sum over the slice's m of dy[m][n]
 template <typename E, int BN, int BK, int WGN, int WGK>
 __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__restrict__ xq, const E *__restrict__ dy,
                                                               int64_t M, int K, int N, int tiles_n, int tiles_k, int splits,
                                                               int64_t rows_per_split, float *__restrict__ P,
-                                                              float *__restrict__ S0)
+                                                              float *__restrict__ S0, DwDirect direct)
 {
     using C = DwCfg<BN, BK, WGN, WGK>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -255,7 +286,7 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
         const int i = d >> 2, k = d & 3;
         s0[i] = DwElem<E>::dot_ones(uint32_t(__builtin_bit_cast(v2i, afr[set][i][k >> 1])[k & 1]), s0[i]);
     };
-    auto conv_item = [&](int c, int set) { bfr[set][c >> 1][c & 1] = DwElem<E>::convert(braw[c >> 1][c & 1]); };
+    auto conv_item = [&](int c, int set) { bfr[set][c >> 1][c & 1] = DwElem<E>::template convert<C::SIGNED>(braw[c >> 1][c & 1]); };
     auto mfma_item = [&](int r, int set) {
         const int i = r / C::TJ, j = r % C::TJ;
         acc[i][j] = DwElem<E>::mfma(afr[set][i][0], afr[set][i][1], bfr[set][j][0], bfr[set][j][1], acc[i][j]);
@@ -396,6 +427,41 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
     // partial sums of this slice: lane l, register v of a 32x32 tile -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
     float *Ps = P + int64_t(split) * N * K;
     const int col_l = lane & 31, row_l = (lane >> 5) * 4;
+    if (C::DIRECT && direct.dW) {
+        float *rows = reinterpret_cast<float *>(smem);    // the row sums of the tile's BN rows of dW
+        __syncthreads();                                  // the last LDS reads of a stage are done
+#pragma unroll
+        for (int i = 0; i < C::TIS; ++i) {
+            const float tot = s0[i] + __shfl_xor(s0[i], 32, 64);
+            if (lane < 32) rows[wn * C::WN + a_block(i) * 32 + col_l] = tot;
+        }
+        __syncthreads();
+        float sg[C::TJ], off[C::TJ];
+#pragma unroll
+        for (int j = 0; j < C::TJ; ++j) {
+            const int kk = kk0 + wk * C::WK + j * 32 + col_l;
+            const uint32_t g = fastdiv(uint32_t(kk < K ? kk : 0), direct.div_per);
+            sg[j] = direct.alpha[g] / 255.0f;
+            off[j] = fmaf(DwElem<E>::centre(C::SIGNED), sg[j], direct.beta[g]);
+        }
+#pragma unroll
+        for (int i = 0; i < C::TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = wn * C::WN + a_block(i) * 32 + (v >> 2) * 8 + row_l + (v & 3);
+                const int n = n0 + r;
+                const float sum = rows[r];
+#pragma unroll
+                for (int j = 0; j < C::TJ; ++j) {
+                    const int kk = kk0 + wk * C::WK + j * 32 + col_l;
+                    if (n < N && kk < K) direct.dW[int64_t(n) * K + kk] = fmaf(sg[j], acc[i][j][v], off[j] * sum);
+                }
+            }
+        if (direct.db && do_s0)
+            for (int r = tid; r < BN; r += C::THREADS)
+                if (n0 + r < N) direct.db[n0 + r] = rows[r];
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < C::TI; ++i)
 #pragma unroll
@@ -452,18 +518,9 @@ __device__ __forceinline__ void cut_f32(float x, uint32_t &a, uint32_t &b, uint3
     c = __float_as_uint(r - __uint_as_float(b));
 }
 
-// four signed codes -> four bfloat16 values q
-__device__ __forceinline__ v4s signed_codes_to_bf4(int raw)
-{
-    const uint32_t f0 = __float_as_uint(float(int(int8_t(raw)))), f1 = __float_as_uint(float(int(int8_t(raw >> 8))));
-    const uint32_t f2 = __float_as_uint(float(int(int8_t(raw >> 16)))), f3 = __float_as_uint(float(raw >> 24));
-    const v2i w = {int(__builtin_amdgcn_perm(f1, f0, 0x07060302u)), int(__builtin_amdgcn_perm(f3, f2, 0x07060302u))};
-    return __builtin_bit_cast(v4s, w);
-}
-
 __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict__ xq, const float *__restrict__ dy, int64_t M, int K,
                                                         int N, int tiles_n, int tiles_k, int splits, int64_t rows_per_split,
-                                                        float *__restrict__ P, float *__restrict__ S0)
+                                                        float *__restrict__ P, float *__restrict__ S0, DwDirect direct)
 {
     typedef DsCfg C;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE];
@@ -565,33 +622,50 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
         }
     }
 
-    float *Ps = P + int64_t(split) * N * K;
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int kk = kk0 + wk * 64 + j * 32 + col_l;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int n = n0 + wn * 64 + i * 32 + (v >> 2) * 8 + row_l + (v & 3);
-                if (n < N && kk < K) Ps[int64_t(n) * K + kk] = acc[i][j][v];
-            }
-        }
-    if (tk == 0) {                                        // uniform: the eight threads of a column group, in order
+    // the row sums of the tile's rows of dW: the eight threads of a column group, in order
+    if (tk == 0 || direct.dW) {                           // uniform
         __syncthreads();                                  // the last stage's fragments have been read
         float4 *part = reinterpret_cast<float4 *>(smem);
         part[tid] = sum;
         __syncthreads();
-        if (tid < C::BN / 4 && n0 + ca < N) {
+        if (tid < C::BN / 4) {
             float4 tot = part[tid];
 #pragma unroll
             for (int r = 1; r < C::ROWS_A; ++r) {
                 const float4 v = part[tid + r * (C::BN / 4)];
                 tot.x += v.x; tot.y += v.y; tot.z += v.z; tot.w += v.w;
             }
-            *reinterpret_cast<float4 *>(S0 + int64_t(split) * N + n0 + ca) = tot;
+            part[tid] = tot;
+            float *to = !direct.dW ? S0 + int64_t(split) * N : tk == 0 ? direct.db : nullptr;
+            if (to && n0 + ca < N) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) to[n0 + ca + j] = j == 0 ? tot.x : j == 1 ? tot.y : j == 2 ? tot.z : tot.w;
+            }
         }
+        __syncthreads();
+    }
+    const float *rows = reinterpret_cast<const float *>(smem);
+    float *Ps = P + int64_t(split) * N * K;
+    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int kk = kk0 + wk * 64 + j * 32 + col_l;
+        float sg = 1.0f, off = 0.0f;
+        if (direct.dW) {
+            const uint32_t g = fastdiv(uint32_t(kk < K ? kk : 0), direct.div_per);
+            sg = direct.alpha[g] / 255.0f;
+            off = fmaf(128.0f, sg, direct.beta[g]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = wn * 64 + i * 32 + (v >> 2) * 8 + row_l + (v & 3), n = n0 + r;
+                if (n < N && kk < K) {
+                    if (direct.dW) direct.dW[int64_t(n) * K + kk] = fmaf(sg, acc[i][j][v], off * rows[r]);
+                    else Ps[int64_t(n) * K + kk] = acc[i][j][v];
+                }
+            }
     }
 }
 
@@ -761,14 +835,41 @@ struct DwPlan {
     int64_t rows_per_split;
 };
 
-// few: binary32 tensors with the slices of the 16-bit kernels (a workspace that holds no more)
+// Slices of m for 128 x 128 tiles, two workgroups per CU at most: the cheapest of a slice's stages (us each; half as long
+// again where two workgroups share a CU), the second kernel's launch and the partial sums' way out and back.  With one
+// slice there is neither.  The constants are fits to a sweep of every split over twenty shapes; what it picks is within 5 %
+// of the sweep's best.
+static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double stage_us)
+{
+    int64_t best = 1;
+    double least = 0.0;
+    for (int64_t s = 1; s <= 256 && (s == 1 || (tiles * s <= 512 && M >= 2 * kDwBM * s)); ++s) {
+        const int64_t stages = ceil_div(ceil_div(M > 0 ? M : 1, s), kDwBM), wgs = tiles * s;
+        double us = double(stages) * stage_us * (wgs <= 256 ? 1.0 : 1.5 * double(ceil_div(wgs, 512)));
+        if (s > 1) us += 4.0 + double(s) * double(N) * double(K) * 2e-6;   // 8 bytes at 4 TB/s
+        if (s == 1 || us < least) { best = s; least = us; }
+    }
+    return best;
+}
+
+// few: the plan of a caller whose workspace holds no more slices than 16-bit matrices of any size once had
 static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few = false)
 {
     DwPlan p;
+    // Up to 20 GFLOP the 128 x 128 tile at any width: a small matrix leaves most CUs without a 256 x 256 tile unless it is
+    // cut into slices, whose partial sums then cost more than the product.  Whole call, former plan -> this one: 505 rows,
+    // 1344 -> 1088: 34 -> 18 us (one slice); 1604, 1344 -> 1752: 41 -> 32; 4096, 768 -> 768: 36 -> 28; 12000, 768 -> 768:
+    // 44 -> 38; even from 22 to 26 (25216, 384 -> 1152: 49 / 50; 4096, 1024 -> 3072: 55 / 56).  Up to 36 GFLOP where 256 x 256
+    // tiles would be at most 16, i.e. 16 slices and more (25216, 1536 -> 384: 62 -> 56).  Beyond, the large tile's half as
+    // many operand bytes win (50432, 768 -> 768: 86 against 90; 768 -> 3072: 251 against 307).
+    const double flops = 2.0 * double(M) * double(K) * double(N);
+    const bool large_k = K % 256 == 0 || K > 1024;
+    const bool small = !few && (flops <= 20e9 || (flops <= 36e9 && large_k && ceil_div(N, 256) * ceil_div(K, 256) <= 16));
     if (dt != MESA_F32 && K % 16 == 0 && N % 8 == 0) {
         // 256-wide k tiles unless they would waste much of the last one.  (A 128 x 384 tile for K = 384 was
         // measured too: no faster per MFMA, and its 21 slices instead of 14 cost more partial-sum traffic.)
-        if (K % 256 == 0 || K > 1024) { p.variant = 0; p.bn = 256; p.bk = 256; }
+        if (small) { p.variant = 3; p.bn = 128; p.bk = 128; }
+        else if (large_k) { p.variant = 0; p.bn = 256; p.bk = 256; }
         else if ((K <= 128 || N <= 128) && N % 256 != 0 && N % 256 <= 128) { p.variant = 3; p.bn = 128; p.bk = 128; }   // narrow K or N: no empty half tile in N
         else { p.variant = 1; p.bn = 256; p.bk = 128; }
     } else if (dt == MESA_F32 && K % 16 == 0 && N % 4 == 0) {
@@ -781,16 +882,15 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few =
     p.tiles_n = int(ceil_div(N, p.bn));
     p.tiles_k = int(ceil_div(K, p.bk));
     const int64_t tiles = int64_t(p.tiles_n) * p.tiles_k;
-    // one workgroup per CU and round; slices of at least 256 contraction rows.  The binary32 kernel: two workgroups per
-    // CU, and slices down to two stages (the whole matrix is a few tiles at the widths it meets, and a stage's latency,
-    // not the matrix cores, is what a short slice costs).
-    const bool many = p.variant == 4 && !few;
-    int64_t splits = (many ? 512 : 256) / tiles;
+    // one workgroup per CU and round; slices of at least 256 contraction rows
+    int64_t splits = 256 / tiles;
     if (splits < 1) splits = 1;
-    int64_t max_splits = M / (many ? 2 * kDwBM : 256);
+    int64_t max_splits = M / 256;
     if (max_splits < 1) max_splits = 1;
     if (splits > max_splits) splits = max_splits;
     if (splits > 256) splits = 256;   // one workgroup per CU also where there is a single tile
+    if (!few && p.variant == 4) splits = dw_slices(M, K, N, tiles, 1.25);
+    else if (small && p.variant == 3) splits = dw_slices(M, K, N, tiles, 0.31);
     int64_t rps = ceil_div(ceil_div(M > 0 ? M : 1, splits), kDwBM) * kDwBM;
     splits = ceil_div(M > 0 ? M : 1, rps);
     p.splits = int(splits);
@@ -828,19 +928,22 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     if (K >= (int64_t(1) << 26) || N_out >= (int64_t(1) << 25) || (long double)K * (long double)N_out >= 2147483648.0L)
         return MESA_ERR_UNSUPPORTED;
     DwPlan p = dw_plan(M, K, N_out, dt);
-    if (p.variant == 4 && ws_bytes < dw_plan_bytes(p, K, N_out)) p = dw_plan(M, K, N_out, dt, true);
+    if (ws_bytes < dw_plan_bytes(p, K, N_out)) p = dw_plan(M, K, N_out, dt, true);
     if (!ws || !aligned16(ws) || ws_bytes < dw_plan_bytes(p, K, N_out)) return MESA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *P = static_cast<float *>(ws);
     float *S0 = P + size_t(p.splits) * size_t(N_out) * size_t(K);
     const int Ki = int(K), Ni = int(N_out);
     float centre = 128.0f;
+    const FastDiv dper = make_fastdiv(uint32_t(K / G));
+    const bool one = p.splits == 1 && p.variant >= 3;    // the others leave their sums to the second kernel
+    const DwDirect direct = {alpha, beta, dper, one ? dW : nullptr, db};
 #define MESA_LAUNCH_DW(E, BN_, BK_) \
     do { \
         using C = DwCfg<BN_, BK_, 2, 2>; \
         hipLaunchKernelGGL((k_dw_f16<E, BN_, BK_, 2, 2>), dim3(p.grid), dim3(C::THREADS), 2 * C::STAGE, s, xq, \
-                           static_cast<const E *>(dy), M, Ki, Ni, p.tiles_n, p.tiles_k, p.splits, p.rows_per_split, P, S0); \
-        centre = DwElem<E>::kCentre; \
+                           static_cast<const E *>(dy), M, Ki, Ni, p.tiles_n, p.tiles_k, p.splits, p.rows_per_split, P, S0, direct); \
+        centre = DwElem<E>::centre(C::SIGNED); \
     } while (0)
     if (p.variant == 2) {   // the plain path contracts with the signed code
 #define MESA_LAUNCH_DW_PLAIN(T) \
@@ -850,14 +953,14 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
 #undef MESA_LAUNCH_DW_PLAIN
     } else if (p.variant == 4) {   // signed codes too
         hipLaunchKernelGGL(k_dw_cut, dim3(p.grid), dim3(kThreads), 0, s, xq, static_cast<const float *>(dy), M, Ki, Ni, p.tiles_n,
-                           p.tiles_k, p.splits, p.rows_per_split, P, S0);
+                           p.tiles_k, p.splits, p.rows_per_split, P, S0, direct);
     } else if (dt == MESA_F16) {
         if (p.variant == 0) MESA_LAUNCH_DW(_Float16, 256, 256); else if (p.variant == 1) MESA_LAUNCH_DW(_Float16, 256, 128); else MESA_LAUNCH_DW(_Float16, 128, 128);
     } else {
         if (p.variant == 0) MESA_LAUNCH_DW(__bf16, 256, 256); else if (p.variant == 1) MESA_LAUNCH_DW(__bf16, 256, 128); else MESA_LAUNCH_DW(__bf16, 128, 128);
     }
     if (launch_status() != MESA_OK) return MESA_ERR_LAUNCH;   // the reduction must not run on partial sums nobody wrote
-    FastDiv dper = make_fastdiv(uint32_t(K / G));
+    if (one) return MESA_OK;
     if (K % 4 == 0) {
         const int64_t nvec = N_out * (K / 4);
         FastDiv dk4 = make_fastdiv(uint32_t(K / 4));

@@ -1,0 +1,43 @@
+"""The weight gradient's tiles and slices: matrices on both sides of the line between the small and the large tiles, one slice
+(whose workgroups finish dW themselves) and several, ragged in every extent.  Reference: the definition in binary64 on the
+GPU (the CPU oracle would take minutes at these sizes; the two agree elsewhere)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# 2e-3 of the largest result: the bound of the 16-bit weight gradient tests (exact products, binary32 sums)
+TOL = 2e-3
+
+
+@pytest.fixture(scope="module")
+def M():
+    import paper_2111_11124_amd as m
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    m.lib()
+    return m
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("Mr,K,N,G", [
+    (50437, 768, 520, 3), (50437, 400, 1000, 1),          # beyond the line: 256 x 256 and 256 x 128 tiles, several slices
+    (300, 8192, 8200, 8), (300, 1008, 65536, 1),          # and one slice
+    (23451, 768, 1000, 3), (23400, 1008, 768, 3),         # below it, close to it
+    (1, 16, 8, 1), (127, 112, 136, 1), (129, 128, 120, 2), (511, 1344, 1088, 6), (4097, 768, 264, 12)])
+def test_linear_dw_tiles_and_slices(M, Mr, K, N, G, dtype):
+    g = torch.Generator(device="cuda").manual_seed(Mr + K)
+    q = torch.randint(-128, 128, (Mr, K), dtype=torch.int8, device="cuda", generator=g)
+    dy = torch.randn((Mr, N), device="cuda", generator=g).to(dtype)
+    a, b = 0.5 + torch.rand(G, device="cuda", generator=g), -torch.rand(G, device="cuda", generator=g)
+    ws = torch.empty(M.workspace_bytes(M.OP_LINEAR_DW_Q, Mr, K, N, M.F16), dtype=torch.uint8, device="cuda")
+    out = torch.full((N * K + 128,), 7.0, device="cuda")
+    dW, db = out[64:64 + N * K].view(N, K), torch.empty(N, device="cuda")
+    M.mesa_linear_dw_q(q, Mr, K, G, a, b, dy, N, dW, db, ws)
+    x_hat = (q.double() + 128) * (a.double() / 255).repeat_interleave(K // G) + b.double().repeat_interleave(K // G)
+    ref = dy.double().t().contiguous() @ x_hat
+    assert (dW - ref).abs().max() <= TOL * ref.abs().max()
+    assert (db - dy.double().sum(0)).abs().max() <= 1e-5 * dy.double().abs().sum(0).max()
+    assert torch.all(out[:64] == 7) and torch.all(out[64 + N * K:] == 7)
+    again = dW.clone()
+    M.mesa_linear_dw_q(q, Mr, K, G, a, b, dy, N, dW, None, ws)      # without the bias gradient: the same bits
+    assert torch.equal(dW, again)
