@@ -454,9 +454,29 @@ __global__ __launch_bounds__(kCvThreads, 2) void k_conv_dw(const int8_t *__restr
 // V[part][co][tap] = sum of dy[b,co,oh,ow] over the part's images and the outputs whose tap (kh, kw) lies inside the
 // input image; tap index KH*KW holds the plain sum (the bias gradient).  One workgroup per (output channel, part);
 // stride_w = dil_w = 1 and OW % 8 == 0 as in the kernel above.  Fixed summation order.
+// A thread's vectors of a part (several images of vpi vectors each): image and place of vector threadIdx.x, then of every
+// kCvThreads-th one after it; two divisions per kernel instead of one per vector.
+struct PartWalk {
+    int img, rem, vpi, step_img, step_rem;
+    __device__ __forceinline__ explicit PartWalk(int vpi_) : vpi(vpi_ > 0 ? vpi_ : 1)
+    {
+        step_img = kCvThreads / vpi;
+        step_rem = kCvThreads - step_img * vpi;
+        img = int(threadIdx.x) / vpi;
+        rem = int(threadIdx.x) - img * vpi;
+    }
+    __device__ __forceinline__ void next()
+    {
+        img += step_img;
+        rem += step_rem;
+        if (rem >= vpi) { rem -= vpi; ++img; }
+    }
+};
+
 template <typename E>
 __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums(const E *__restrict__ dy, ConvGeom cg, int parts, int imgs_per_part,
-                                                                int row_blocks, int rows_per_block, float *__restrict__ V)
+                                                                int row_blocks, int rows_per_block, FastDiv div_vpr,
+                                                                float *__restrict__ V)
 {
     __shared__ float red[kCvThreads / 64][10];
     const int co = blockIdx.x / parts, pt = blockIdx.x - co * parts;
@@ -475,6 +495,7 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums(const E *__restr
     const int vpi = v_end - v_begin;                          // vectors per image
     const int nv = (b1 - b0) * vpi;
     {
+        PartWalk w(vpi);
         for (int base = 0; base < nv; base += 4 * kCvThreads) {
             u32x4 raw[4];
             int at[4];                                        // the vector's index in its plane, -1: none
@@ -484,34 +505,30 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums(const E *__restr
                 raw[u] = u32x4{0u, 0u, 0u, 0u};
                 at[u] = -1;
                 if (v < nv) {
-                    const int bi = v / vpi;
-                    at[u] = v_begin + (v - bi * vpi);
-                    const E *plane = dy + (int64_t(b0 + bi) * cg.Cout + co) * cg.OH * cg.OW;
+                    at[u] = v_begin + w.rem;
+                    const E *plane = dy + (int64_t(b0 + w.img) * cg.Cout + co) * cg.OH * cg.OW;
                     raw[u] = *reinterpret_cast<const u32x4 *>(plane + int64_t(at[u]) * 8);
                 }
+                w.next();
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int idx = at[u];
                 if (idx < 0) continue;
-                const int oh = idx / vec_per_row, ow0 = (idx - oh * vec_per_row) * 8;
+                const int oh = int(fastdiv(uint32_t(idx), div_vpr)), ow0 = (idx - oh * vec_per_row) * 8;
                 float f[8];
                 Store<E>::unpack(raw[u], f);
-                float cs[3] = {0.0f, 0.0f, 0.0f}, all = 0.0f;
+                // a 3 x 3 kernel's outer taps leave out a row's first element, or the last one that has an image column
+                // (and what lies behind it: zeros, in rows padded to eight elements)
+                const int last = cg.Wv - 1 - ow0;
+                float no_first = 0.0f, no_last = 0.0f;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) all += f[j];
-                if (ow0 - cg.pw >= 0 && ow0 + 7 - cg.pw + 2 < cg.Wv) {   // every tap of every element lies inside: all but a row's ends
+                for (int j = 1; j < 8; ++j) no_first += f[j];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) cs[c] = c < cg.KW ? all : 0.0f;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            const int iw = ow0 + j - cg.pw + c;
-                            cs[c] += (c < cg.KW && iw >= 0 && iw < cg.Wv) ? f[j] : 0.0f;
-                        }
-                }
+                for (int j = 0; j < 8; ++j) no_last += j < last ? f[j] : 0.0f;
+                const float all = f[0] + no_first;
+                const bool outer = cg.KW == 3;
+                const float cs[3] = {outer && ow0 == 0 ? no_first : all, outer ? all : 0.0f, outer ? no_last : 0.0f};
                 tot += all;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
@@ -570,6 +587,7 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums_any(const E *__r
     // vectors each)
     const int vpi = (e_end - e_begin + 7) >> 3;               // vectors per image
     const int nv = (b1 - b0) * vpi;
+    PartWalk w(vpi);
     for (int base = 0; base < nv; base += 4 * kCvThreads) {
         u32x4 raw[4];
         int at[4];                                            // the vector's first element in its plane, -1: none
@@ -579,8 +597,8 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums_any(const E *__r
             raw[u] = u32x4{0u, 0u, 0u, 0u};
             at[u] = -1;
             if (v < nv) {
-                const int bi = v / vpi, idx = e_begin + (v - bi * vpi) * 8;
-                const E *plane = dy + (int64_t(b0 + bi) * cg.Cout + co) * per_img;
+                const int idx = e_begin + w.rem * 8;
+                const E *plane = dy + (int64_t(b0 + w.img) * cg.Cout + co) * per_img;
                 at[u] = idx;
                 if (idx + 8 <= e_end) {
                     raw[u] = cv_load_unaligned<u32x4>(reinterpret_cast<const char *>(plane + idx));
@@ -592,6 +610,7 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums_any(const E *__r
                     for (int k = 0; k < 4; ++k) raw[u][k] = uint32_t(h[2 * k]) | (uint32_t(h[2 * k + 1]) << 16);
                 }
             }
+            w.next();
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -602,21 +621,27 @@ __global__ __launch_bounds__(kCvThreads) void k_conv_valid_sums_any(const E *__r
             const int oh = int(fastdiv(uint32_t(idx), div_ow)), ow0 = idx - oh * cg.OW;
             // elements j < n0 lie in row oh, the others in row oh + 1 (OW >= 8: at most one row end inside a vector)
             const int n0 = cg.OW - ow0;
-            float cs[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}}, all[2] = {0.0f, 0.0f};
+            // of either row: its first element, its last one and what lies between, as far as they lie in this vector
+            float first[2] = {0.0f, 0.0f}, last = 0.0f, mid[2] = {0.0f, 0.0f};
+            const float head = ow0 == 0 ? f[0] : 0.0f;
+            if (n0 > 8) {
+                mid[0] = (((f[1] + f[2]) + (f[3] + f[4])) + ((f[5] + f[6]) + f[7])) + (ow0 == 0 ? 0.0f : f[0]);
+                first[0] = head;
+            } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool second = j >= n0;
-                const int ow = second ? j - n0 : ow0 + j;
-                all[0] += second ? 0.0f : f[j];
-                all[1] += second ? f[j] : 0.0f;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const int iw = ow - cg.pw + c;
-                    const float v = (c < cg.KW && iw >= 0 && iw < cg.Wv) ? f[j] : 0.0f;
-                    cs[0][c] += second ? 0.0f : v;
-                    cs[1][c] += second ? v : 0.0f;
+                for (int j = 0; j < 8; ++j) {
+                    mid[0] += j < n0 - 1 && !(j == 0 && ow0 == 0) ? f[j] : 0.0f;
+                    last = j == n0 - 1 ? f[j] : last;
+                    first[1] = j == n0 ? f[j] : first[1];
+                    mid[1] += j > n0 ? f[j] : 0.0f;
                 }
+                first[0] = head;                              // (OW >= 8: not the row's last)
             }
+            const float all[2] = {mid[0] + first[0] + last, mid[1] + first[1]};
+            // a 3 x 3 kernel's outer taps leave out a row's first or last element
+            const bool outer = cg.KW == 3;
+            const float cs[2][3] = {{outer ? mid[0] + last : all[0], outer ? all[0] : 0.0f, outer ? mid[0] + first[0] : 0.0f},
+                                    {outer ? mid[1] : all[1], outer ? all[1] : 0.0f, outer ? all[1] : 0.0f}};
             tot += all[0] + all[1];      // (zeros beyond the part's end)
 #pragma unroll
             for (int r = 0; r < 2; ++r)
@@ -1064,7 +1089,7 @@ extern "C" MESA_EXPORT mesa_status mesa_conv2d_dw_q(const int8_t *xq, mesa_conv2
         if (p.pad) { \
             if (p.taps3) MESA_LAUNCH_CV(E, true, 1, 2); else MESA_LAUNCH_CV(E, false, 1, 2); \
             hipLaunchKernelGGL((k_conv_valid_sums<E>), dim3(unsigned(cg.Cout) * p.parts), dim3(kCvThreads), 0, s, \
-                               static_cast<const E *>(kd), ck, p.parts, p.imgs_per_part, p.row_blocks, p.rows_per_block, V); \
+                               static_cast<const E *>(kd), ck, p.parts, p.imgs_per_part, p.row_blocks, p.rows_per_block, make_fastdiv(uint32_t(ck.OW / 8)), V); \
         } else if (p.rag) { \
             if (p.taps3) MESA_PICK_NKS(E, true, 1); else MESA_PICK_NKS(E, false, 1); \
             hipLaunchKernelGGL((k_conv_valid_sums_any<E>), dim3(unsigned(cg.Cout) * p.parts), dim3(kCvThreads), 0, s, \
@@ -1073,7 +1098,7 @@ extern "C" MESA_EXPORT mesa_status mesa_conv2d_dw_q(const int8_t *xq, mesa_conv2
         } else { \
             if (p.taps3) MESA_PICK_NKS(E, true, 0); else MESA_PICK_NKS(E, false, 0); \
             hipLaunchKernelGGL((k_conv_valid_sums<E>), dim3(unsigned(cg.Cout) * p.parts), dim3(kCvThreads), 0, s, \
-                               static_cast<const E *>(dy), cg, p.parts, p.imgs_per_part, p.row_blocks, p.rows_per_block, V); \
+                               static_cast<const E *>(dy), cg, p.parts, p.imgs_per_part, p.row_blocks, p.rows_per_block, make_fastdiv(uint32_t(cg.OW / 8)), V); \
         } \
     } while (0)
     float centre;
