@@ -453,6 +453,32 @@ __device__ __forceinline__ void ema_update(float mn, float mx, float alpha_old, 
 // variant kEmaFixedBeta: the offset is beta_fixed, only alpha is a running estimate (of max - beta_fixed)
 // variant kEmaScaleOnly: the scale-only symmetric scheme -- alpha is the running estimate of m = max |x|, beta is not touched
 enum { kEmaPlain = 0, kEmaSymmetric = 1, kEmaFixedBeta = 2, kEmaScaleOnly = 3 };
+// one group's estimates moved by its extrema, in whichever variant the call is
+__device__ __forceinline__ void ema_store(float mn, float mx, float alpha_old, float beta_old, float *alpha, float *beta, uint32_t g,
+                                          float lambda, int first_call, int variant, float beta_fixed)
+{
+    if (variant == kEmaSymmetric) {
+        mx = vmax(-mn, mx);
+        mn = -mx;
+    }
+    if (variant == kEmaScaleOnly) {
+        const float m = vmax(-mn, mx) + 0.0f;
+        if (first_call) {
+            alpha[g] = m;
+        } else {
+            float a = lambda * alpha_old;
+            float b = 1.0f - lambda;
+            float c = b * m;
+            alpha[g] = a + c;
+        }
+    } else if (variant == kEmaFixedBeta) {
+        ema_update(beta_fixed, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call);
+        beta[g] = beta_fixed;
+    } else {
+        ema_update(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call);
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void k_ema_finalize(const float *__restrict__ part, int nwg, uint32_t groups,
                                                            float *alpha, float *beta, float lambda, int first_call,
                                                            int variant = kEmaPlain, float beta_fixed = 0.0f)
@@ -475,26 +501,78 @@ __global__ __launch_bounds__(kThreads) void k_ema_finalize(const float *__restri
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int w = 1; w < kThreads / 64; ++w) { mn = vmin(mn, smn[w]); mx = vmax(mx, smx[w]); }
-        if (variant == kEmaSymmetric) {
-            mx = vmax(-mn, mx);
-            mn = -mx;
+        ema_store(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call, variant, beta_fixed);
+    }
+}
+
+// Scan by group: workgroup (g, s) takes every gridDim.y-th piece of group g's slabs, so that no thread ever meets another
+// group.  A slab (the group's `inner` elements of one sample) is covered by vps aligned vectors; where slabs are no whole
+// vectors, the elements of the first and last one that belong to a neighbour are left out.
+// One workgroup per group (small tensors): it updates the estimates itself -- a second, dependent launch costs as much as
+// the whole scan there.  Else partial extrema, as k_minmax_partial leaves them.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallElems = 32768;        // of a group, at most
+
+template <typename T>
+__global__ __launch_bounds__(kSmallThreads) void k_minmax_by_group(const void *__restrict__ x, uint32_t outer, uint32_t groups, uint32_t inner,
+                                                                int64_t numel, uint32_t vps, FastDiv div_vps, float *alpha, float *beta,
+                                                                float lambda, int first_call, int variant, float beta_fixed,
+                                                                float *__restrict__ part)
+{
+    __shared__ float smn[kSmallThreads / 64], smx[kSmallThreads / 64];
+    constexpr int U = 4;
+    const uint32_t g = blockIdx.x, total = outer * vps;
+    const float alpha_old = alpha[g], beta_old = variant == kEmaScaleOnly ? 0.0f : beta[g];
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+    for (uint32_t v0 = blockIdx.y * (U * kSmallThreads) + threadIdx.x; v0 < total; v0 += gridDim.y * (U * kSmallThreads)) {
+        typename Store<T>::raw_t raw[U];
+        int64_t start[U], at[U];                   // of the slab, of the vector
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t v = v0 + u * kSmallThreads;
+            const uint32_t o = v < total ? fastdiv(v, div_vps) : 0u;
+            start[u] = (int64_t(o) * groups + g) * inner;
+            at[u] = v < total ? (start[u] & ~int64_t(7)) + int64_t(v - o * vps) * kVec : start[u] + inner;
+            if (at[u] < start[u] + inner && at[u] + kVec <= numel) raw[u] = Store<T>::load(x, at[u]);
         }
-        if (variant == kEmaScaleOnly) {
-            const float m = vmax(-mn, mx) + 0.0f;
-            if (first_call) {
-                alpha[g] = m;
-            } else {
-                float a = lambda * alpha_old;
-                float b = 1.0f - lambda;
-                float c = b * m;
-                alpha[g] = a + c;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t end = start[u] + inner;
+            if (at[u] >= end) continue;
+            if (at[u] + kVec <= numel) {
+                float f[8];
+                Store<T>::unpack(raw[u], f);
+                const bool whole = at[u] >= start[u] && at[u] + kVec <= end;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool in = whole || (at[u] + j >= start[u] && at[u] + j < end);
+                    mn = vmin(mn, in ? f[j] : __builtin_inff());
+                    mx = vmax(mx, in ? f[j] : -__builtin_inff());
+                }
+            } else {                               // the vector that the tensor ends in
+                for (int64_t e = at[u] > start[u] ? at[u] : start[u]; e < end; ++e) {
+                    const float f = Store<T>::load1(x, e);
+                    mn = vmin(mn, f);
+                    mx = vmax(mx, f);
+                }
             }
-        } else if (variant == kEmaFixedBeta) {
-            ema_update(beta_fixed, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call);
-            beta[g] = beta_fixed;
-        } else {
-            ema_update(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call);
         }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        mn = vmin(mn, __shfl_xor(mn, off, 64));
+        mx = vmax(mx, __shfl_xor(mx, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) { smn[threadIdx.x >> 6] = mn; smx[threadIdx.x >> 6] = mx; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < kSmallThreads / 64; ++w) { mn = vmin(mn, smn[w]); mx = vmax(mx, smx[w]); }
+        if (part) {
+            part[int64_t(blockIdx.y) * 2 * groups + g] = mn;
+            part[int64_t(blockIdx.y) * 2 * groups + groups + g] = mx;
+        } else
+        ema_store(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call, variant, beta_fixed);
     }
 }
 
@@ -1003,6 +1081,31 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
     const size_t need = max_wgs > 0 ? size_t(grid) * 2 * size_t(L.groups) * sizeof(float) : update_ws_bytes(L.outer, L.groups, L.inner);
     if (!ws || !aligned16(ws) || ws_bytes < need) return MESA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // Scan by group: one launch up to 32768 elements of a group (three groups of 394 x 64: 5.7 -> 5.2 us in binary16, 5.8 -> 4.8
+    // in binary32; at 64000 one workgroup per group takes 8.4 against 6.1), and slabs of 64 to 2047 elements that are no
+    // whole vectors, whose lanes the scan by position sends to another group at nearly every step ((64, 8, 441): 21 -> 5.6
+    // us, (725, 8, 341): 16.9 -> 8.1, (1919, 32, 441): 36 -> 24, (50000, 3, 341): 56 -> 35).  Shorter slabs waste the vectors
+    // at their ends ((100000, 12, 20): 21 against 35), longer ones keep a lane's group as it is ((8192, 3, 2401): 29 / 37).
+    const int64_t vps = L.inner / kVec + (L.inner % kVec ? 2 : 0);
+    const bool one = L.outer * L.inner <= kSmallElems;
+    if (L.outer * vps < (int64_t(1) << 31) && (one || (L.groups > 1 && L.inner % kVec != 0 && L.inner >= 64 && L.inner < 2048))) {
+        int64_t pieces = ceil_div(L.outer * vps, int64_t(4) * kSmallThreads), most = ceil_div(1024, L.groups);
+        if (pieces > most) pieces = most;
+        if (pieces > grid) pieces = grid;
+        if (one) pieces = 1;
+        float *part = pieces > 1 ? static_cast<float *>(ws) : nullptr;
+#define MESA_LAUNCH_BG(T) \
+    hipLaunchKernelGGL((k_minmax_by_group<T>), dim3(unsigned(L.groups), unsigned(pieces)), dim3(kSmallThreads), 0, s, x, uint32_t(L.outer), \
+                       uint32_t(L.groups), uint32_t(L.inner), numel, uint32_t(vps), make_fastdiv(uint32_t(vps)), alpha, beta, lambda, first_call, \
+                       variant, beta_fixed, part)
+        MESA_FOR_DTYPE(dt, MESA_LAUNCH_BG);
+#undef MESA_LAUNCH_BG
+        if (launch_status() != MESA_OK) return MESA_ERR_LAUNCH;   // the consumer must not run on partials nobody wrote
+        if (part)
+            hipLaunchKernelGGL(k_ema_finalize, dim3(unsigned(L.groups)), dim3(kThreads), 0, s, part, int(pieces), uint32_t(L.groups), alpha, beta,
+                               lambda, first_call, variant, beta_fixed);
+        return launch_status();
+    }
     GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * kMmU * kVec);
     const size_t lds = size_t(2) * gg.groups * sizeof(int);
     float *part = static_cast<float *>(ws);
