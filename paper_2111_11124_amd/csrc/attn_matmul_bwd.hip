@@ -350,16 +350,21 @@ template <bool CODED, bool TFAST, typename ET> struct BmOperand {
 // P_CODED: P is the coded operand (else Q).  P_TFAST / Q_TFAST: the contraction index is the unit-stride
 // index of that operand in memory.  ET: the tensors' type (BmmArgs carries their pointers as 16-bit containers'; a
 // binary32 operand is three bfloat16 planes, see BmElem).
-template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET>
-__global__ __launch_bounds__(kThreads, (std::is_same<ET, float>::value ? 4 : 6)) void k_bmm_q(BmmArgs a)
+// RS: groups of four waves that share out the contraction's stages (group g takes stages g, g + RS, ...), each with LDS tiles
+// of its own; their sums are added through LDS at the end, in group order.  A stage behind the last one is all zeros
+// (BmOperand::store).  For few workgroups with many stages: one workgroup's next stage is all that a CU has on its way.
+template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET, int RS>
+__global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || RS == 4 ? 4 : 6)) void k_bmm_q(BmmArgs a)
 {
     typedef BmOperand<P_CODED, P_TFAST, ET> OP;
     typedef BmOperand<!P_CODED, Q_TFAST, ET> OQ;
     typedef typename BmElem<false, ET>::global_t X;       // the plain operand's and the result's element type in memory
-    __shared__ __attribute__((aligned(16))) unsigned char LP[OP::kBytes];
-    __shared__ __attribute__((aligned(16))) unsigned char LQ[OQ::kBytes];
+    constexpr int kTiles = (OP::kBytes + OQ::kBytes) * RS, kSums = RS > 1 ? 32 * kThreads * 4 : 0;
+    __shared__ __attribute__((aligned(16))) unsigned char lds_bm[kTiles > kSums ? kTiles : kSums];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int group = RS > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kThreads) : 0;
+    const int tid = RS > 1 ? int(threadIdx.x) % kThreads : int(threadIdx.x), lane = tid & 63, wave = tid >> 6;   // within the group
+    unsigned char *LP = lds_bm + group * (OP::kBytes + OQ::kBytes), *LQ = LP + OP::kBytes;
     // grid: x = column tile, y = row tile, z = (sample, head) in pieces of at most 65535 (32-bit, uniform arithmetic only)
     const uint32_t b = blockIdx.z;
     const int r0 = int(blockIdx.y) * kBmTile, c0 = int(blockIdx.x) * kBmTile;
@@ -387,8 +392,9 @@ __global__ __launch_bounds__(kThreads, (std::is_same<ET, float>::value ? 4 : 6))
     typename OP::Raw pv[kBmParts];
     typename OQ::Raw qv[kBmParts];
 #pragma unroll
-    for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(0, k); qv[k] = load_q(0, k); }
-    for (int t0 = 0; t0 < a.Tn; t0 += kBmT) {
+    for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(group * kBmT, k); qv[k] = load_q(group * kBmT, k); }
+    for (int first = 0; first < a.Tn; first += kBmT * RS) {   // the same count for every group: they meet at the barriers
+        const int t0 = first + group * kBmT;
         __syncthreads();   // the previous stage's fragments have been read
 #pragma unroll
         for (int k = 0; k < kBmParts; ++k) {
@@ -396,9 +402,9 @@ __global__ __launch_bounds__(kThreads, (std::is_same<ET, float>::value ? 4 : 6))
             OQ::store(LQ, qv[k], c0, t0, a.Cn, a.Tn, tid + k * kThreads);
         }
         __syncthreads();
-        if (t0 + kBmT < a.Tn) {   // the next stage's loads fly while this one is multiplied
+        if (first + kBmT * RS < a.Tn) {   // the next stage's loads fly while this one is multiplied
 #pragma unroll
-            for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(t0 + kBmT, k); qv[k] = load_q(t0 + kBmT, k); }
+            for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(t0 + kBmT * RS, k); qv[k] = load_q(t0 + kBmT * RS, k); }
         }
 #pragma unroll
         for (int ks = 0; ks < kBmT / 16; ++ks) {
@@ -413,6 +419,23 @@ __global__ __launch_bounds__(kThreads, (std::is_same<ET, float>::value ? 4 : 6))
         }
     }
 
+    if constexpr (RS > 1) {
+        float *sums = reinterpret_cast<float *>(lds_bm) + tid;
+#pragma unroll 1
+        for (int g = 1; g < RS; ++g) {
+            __syncthreads();   // the last fragments, or the sums before, have been read
+            if (group == g) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { sums[v * kThreads] = acc[v]; sums[(16 + v) * kThreads] = acc1[v]; }
+            }
+            __syncthreads();
+            if (group == 0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) { acc[v] += sums[v * kThreads]; acc1[v] += sums[(16 + v) * kThreads]; }
+            }
+        }
+        if (group != 0) return;
+    }
     // lane l, register v of a 32 x 32 tile: row 8*(v/4) + 4*(l/32) + v%4, column l%32
     const float s = a.alpha[h] / 255.0f;
     const float off = fmaf(BmNum<ET>::kCentre, s, a.beta[h]);
@@ -440,8 +463,15 @@ static void launch_bmm(BmmArgs a, int64_t batches, hipStream_t s)
         a.batch0 = b0;
         a.head0 = int(b0 % a.heads);
         const int64_t nb = batches - b0 < 65535 ? batches - b0 : 65535;
-        hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET>), dim3(unsigned(a.tiles_c), unsigned(a.tiles_r), unsigned(nb)),
-                           dim3(kThreads), 0, s, a);
+        const dim3 grid(unsigned(a.tiles_c), unsigned(a.tiles_r), unsigned(nb));
+        const int64_t wgs = int64_t(a.tiles_c) * a.tiles_r * nb;
+        // groups per workgroup: whole attention backward with 1 / 2 / 4 of them, by the workgroups of dV, dQ and dK: (1, 4, 919,
+        // 32), 60: 90 / 67 / 58 us; (1, 3, 856, 96), 84: 72 / 56 / 56; (4, 8, 577, 64), 320: 76 / 67 / 82; (34, 4, 378, 64),
+        // 816: 93 / 102 / 119; binary32 (1, 12, 324, 64), 72: 63 / 51 / 54
+        const int rs = a.Tn < 128 || wgs > 512 ? 1 : wgs <= 64 && a.Tn >= 512 ? 4 : 2;
+        if (rs == 4) hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 4>), grid, dim3(kThreads * 4), 0, s, a);
+        else if (rs == 2) hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 2>), grid, dim3(kThreads * 2), 0, s, a);
+        else hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 1>), grid, dim3(kThreads), 0, s, a);
     }
 }
 

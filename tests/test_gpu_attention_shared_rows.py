@@ -1,5 +1,6 @@
-"""dK and dV of aligned sequences where a workgroup's groups of waves share out the rows: chunk counts that the groups do and do
-not divide, every head size, against the CPU oracle (the bounds of the other attention tests)."""
+"""Attention products where groups of waves share a contraction: dK and dV of aligned sequences, whose rows a workgroup's groups
+share out, and the general kernel with its stages; chunk counts that the groups do and do not divide, every head size, against
+the CPU oracle (the bounds of the other attention tests)."""
 import pytest
 import torch
 
@@ -20,4 +21,11 @@ def M():
 @pytest.mark.parametrize("B,H,N,Dh", [(1, 1, 64, 64), (1, 2, 80, 32), (1, 1, 272, 64), (1, 1, 336, 128), (1, 1, 1024, 64), (1, 1, 1040, 32), (1, 1, 1072, 64),
                                       (1, 1, 1056, 128)])
 def test_attention_products_rows_shared_among_wave_groups(M, B, H, N, Dh, dtype):
+    _attention_case(M, B, H, N, Dh, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16], ids=["f32", "f16", "bf16"])
+@pytest.mark.parametrize("B,H,N,Dh", [(1, 1, 129, 40), (1, 2, 257, 64), (1, 1, 289, 96), (1, 1, 511, 64), (1, 1, 513, 64), (1, 1, 545, 32), (1, 1, 577, 72)])
+def test_attention_products_stages_shared_among_wave_groups(M, B, H, N, Dh, dtype):
+    """The general kernel: contractions of stages that two and four groups do and do not divide, ragged last ones."""
     _attention_case(M, B, H, N, Dh, dtype)
