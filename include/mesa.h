@@ -206,8 +206,8 @@ mesa_status mesa_gelu_fwd_q(const void *x, mesa_dtype dt, mesa_layout L,
  * s: [B*H*rows*cols] of dt (in).  y: same (out), not aliasing s.  q: int8 (out).
  * alpha, beta: [H] (in/out).  ws: MESA_OP_SOFTMAX_FWD_Q bytes.  Limits: rows, cols and B*H*rows below 2^31, else
  * MESA_ERR_UNSUPPORTED.  One pass over s for H <= 1024 and rows of up to 256 elements (any length), rows of 8k elements
- * up to 4096, and other rows of at least 8 elements as long as 8 / gcd(cols, 8) of them fit a tile of 8192 elements
- * (odd lengths up to 1024, even ones up to 2048, ...).  Every other shape takes two steps inside the call -- y by a
+ * up to 4096, rows of any length up to 2048 as long as 8 / gcd(cols, 8) of them fit 64 KB, and other rows of which as
+ * many fit a tile of 8192 elements.  Every other shape takes two steps inside the call -- y by a
  * plain kernel, one workgroup per row, then mesa_quantize_update_fused on y (which reads y back) -- and that step's
  * limits: H <= 8192, rows*cols < 2^30.
  */
@@ -266,10 +266,9 @@ mesa_status mesa_gelu_bwd_q_b4(const uint8_t *q4, mesa_layout L, const float *al
  * head-wise parameters alpha[H], beta[H].  Per row:  d = sum_j dy_j*y_hat_j,
  * dx_j = y_hat_j * (dy_j - d), accumulated in binary32.
  * yq: int8 (in); dy, dx: [B*H*rows*cols] of dt (in / out); dx may alias dy.
- * Limits: rows, cols, H and B*H*rows below 2^31, else MESA_ERR_UNSUPPORTED.  The tiled kernels take rows of up
- * to 256 elements of any length, and longer rows with R*cols <= 8192 for R = 8/gcd(cols, 8) (cols <= 8192 when
- * cols % 8 == 0, cols <= 1024 when cols is odd), at H <= 1024; every other shape runs a plain kernel, one
- * workgroup per row (rows of 1025 elements: two thirds of the rate of rows of 1024; 4097: 0.96 of 4096).
+ * Limits: rows, cols, H and B*H*rows below 2^31, else MESA_ERR_UNSUPPORTED.  At H <= 1024, kernels of their own take
+ * rows of up to 256 elements, rows of 8k elements up to 4096, rows of a 16-bit type of any length up to 2048, and other
+ * rows with R*cols <= 8192 for R = 8/gcd(cols, 8); every other shape runs a plain kernel, one workgroup per row.
  */
 mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t B, int64_t H, int64_t rows, int64_t cols,
                                const float *alpha, const float *beta, const void *dy, void *dx,
@@ -314,13 +313,15 @@ mesa_status mesa_layernorm_bwd_q(const int8_t *xq, int64_t M, int64_t D, int64_t
  * Linear weight gradient at the de-quantized input, Eq. (2) for y = x W^T, W of shape (N_out, K):
  *   dW[n, k] = sum_m dy[m, n] * x_hat[m, k],   db[n] = sum_m dy[m, n]
  * evaluated as  s_g(k) * sum_m dy[m,n]*(q[m,k]+128+c)  +  (beta_g(k) - c*s_g(k)) * db[n]  on the matrix cores
- * (binary16 products for MESA_F16, bfloat16 products for MESA_BF16, binary32 accumulation; fixed summation order;
- * c = 1024 for MESA_F16, where 1024 + code is the cheapest exact binary16 operand, c = 0 otherwise: the binary32
+ * (binary16 products for MESA_F16, bfloat16 products for MESA_BF16 and for MESA_F32, whose dy is taken apart into three
+ * bfloat16 values that add up to it exactly; binary32 accumulation; fixed summation order).  c = -128, the signed code, for
+ * MESA_F32 and for matrices of up to some 20 GFLOP.  Larger ones: c = 1024 for MESA_F16, where 1024 + code is the cheapest
+ * exact binary16 operand, c = 0 for MESA_BF16: the binary32
  * sums then carry a term c*db[n] that cancels in the result, which costs accuracy when dy has a large mean --
- * about 3e-4 of max|dW| at a mean of half a standard deviation over 50000 rows, 1e-5 at mean zero).
+ * about 3e-4 of max|dW| at a mean of half a standard deviation over 50000 rows, 1e-5 at mean zero.
  * xq: (M, K) int8, K in G channel groups.  dy: (M, N_out) of dt.  dW: (N_out, K) binary32, row-major,
  * overwritten.  db: [N_out] binary32 or NULL.  ws: MESA_OP_LINEAR_DW_Q bytes.
- * K % G == 0.  Widths with K % 16 != 0 or N_out % 8 != 0 (and binary32 tensors) run a plain, slow kernel.
+ * K % G == 0.  Widths with K % 16 != 0 or N_out % 8 != 0 (MESA_F32: N_out % 4 != 0) run a plain, slow kernel.
  * Limits: K * N_out < 2^31, else MESA_ERR_UNSUPPORTED.
  */
 mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M, int64_t K, int64_t G,
@@ -359,8 +360,8 @@ mesa_status mesa_conv2d_dw_q(const int8_t *xq, mesa_conv2d cv, int64_t G, const 
  * Backward of the two matrix products of self-attention at head-wise de-quantized operands, Sec. 3.1
  * Eq. (2) with G_l = the gradient of a matrix product (the "MatMul" rows of the paper's overhead table;
  * Sec. 3.2: the operands are saved as codes with one (alpha, beta) pair per head).  All tensors are
- * (B, H, N, .) contiguous, upstream gradients and results of dt (binary32 tensors run one plain, slow
- * kernel, as do extents below 8), accumulation in binary32; any N and Dh (nothing needs to be aligned).
+ * (B, H, N, .) contiguous, upstream gradients and results of dt (extents below 8 run one plain, slow
+ * kernel; a binary32 operand is taken apart into three bfloat16 values that add up to it exactly), accumulation in binary32; any N and Dh (nothing needs to be aligned).
  *
  * O = A V with A the attention map (B,H,N,N) and V (B,H,N,Dh):
  *   dA[i,j] = sum_d dO[i,d] * V_hat[j,d],    dV[j,d] = sum_i A_hat[i,j] * dO[i,d]

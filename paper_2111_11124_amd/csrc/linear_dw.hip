@@ -6,8 +6,8 @@
 // and centred, so P does not cancel against S0) and the per-column affine map is applied once to
 // the finished sums.
 //
-// (bfloat16 dy: the same kernel with bfloat16 matrix-core operands; there the contracted value is
-// x_bar = q + 128 itself, c = 0 in  dW = s_g (dy^T (x_bar - c)) + (beta_g + c s_g) S0.)
+// (Matrices beyond some 20 GFLOP contract another value of the code, see DwElem: 1024 + x_bar in binary16, x_bar = q + 128
+// in bfloat16, c = -1024 and 0 in  dW = s_g (dy^T (x_bar - c)) + (beta_g + c s_g) S0.  binary32 dy: k_dw_cut.)
 //
 // 16-bit path, gfx950.  Both operands are row-major in the contraction index m, which is the
 // layout the MFMA operands do NOT want (a lane holds 8 consecutive contraction values of one
@@ -16,7 +16,8 @@
 // column of four binary16 / eight int8 values it needs (within 16 lanes, lanes 4k..4k+3 -- resp.
 // 2k, 2k+1 -- supply row k and lane i receives column i).  A workgroup of four waves owns a
 // BN x BK tile of dW (each wave a quarter, as 32x32x16 MFMA tiles) for one slice of m; slices
-// are combined in a fixed order by a second kernel that also applies the affine map.
+// are combined in a fixed order by a second kernel that also applies the affine map (a small tile's
+// only slice applies it itself).
 // Workgroups are numbered so that those sharing a slice of m run on the same XCD (same L2).
 #include <hip/hip_runtime.h>
 
