@@ -6,7 +6,7 @@
 // and centred, so P does not cancel against S0) and the per-column affine map is applied once to
 // the finished sums.
 //
-// (Matrices beyond some 20 GFLOP contract another value of the code, see DwElem: 1024 + x_bar in binary16, x_bar = q + 128
+// (Large and narrow matrices contract another value of the code, see DwElem: 1024 + x_bar in binary16, x_bar = q + 128
 // in bfloat16, c = -1024 and 0 in  dW = s_g (dy^T (x_bar - c)) + (beta_g + c s_g) S0.  binary32 dy: k_dw_cut.)
 //
 // 16-bit path, gfx950.  Both operands are row-major in the contraction index m, which is the
@@ -43,8 +43,8 @@ constexpr int kDwXcd = 8;
 constexpr int kDwPF = 3;         // stages prefetched into registers ahead of the one being multiplied
 
 // BN x BK tile of dW per workgroup, WGN x WGK waves, each wave (BN/WGN) x (BK/WGK) as 32x32 MFMA tiles
-template <int BN, int BK, int WGN, int WGK> struct DwCfg {
-    static constexpr bool SIGNED = BN * BK <= 128 * 128;                  // which value of the code is contracted (DwElem)
+template <int BN, int BK, int WGN, int WGK, bool SIGNED_> struct DwCfg {
+    static constexpr bool SIGNED = SIGNED_;                               // which value of the code is contracted (DwElem)
     static constexpr bool DIRECT = BN * BK <= 128 * 128;                  // one slice: finishes dW itself (large tiles have many, or fill the chip)
     static constexpr int PF = BN * BK <= 128 * 128 ? 2 * kDwPF : kDwPF;   // small tiles: less per stage, so more stages in flight
     static constexpr int NW = WGN * WGK;
@@ -158,13 +158,13 @@ struct DwDirect {
 
 // P[split][n][k] = sum over the slice's m of dy[m][n] * (x_bar[m][k] - centre)   (x_bar - 128 is the signed code)
 // S0[split][n]   = sum over the slice's m of dy[m][n]
-template <typename E, int BN, int BK, int WGN, int WGK>
+template <typename E, int BN, int BK, int WGN, int WGK, bool SIGNED_>
 __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__restrict__ xq, const E *__restrict__ dy,
                                                               int64_t M, int K, int N, int tiles_n, int tiles_k, int splits,
                                                               int64_t rows_per_split, float *__restrict__ P,
                                                               float *__restrict__ S0, DwDirect direct)
 {
-    using C = DwCfg<BN, BK, WGN, WGK>;
+    using C = DwCfg<BN, BK, WGN, WGK, SIGNED_>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -831,7 +831,8 @@ __global__ __launch_bounds__(kThreads) void k_dw_reduce_any(const float *__restr
 }
 
 struct DwPlan {
-    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128; 4: binary32, 128 x 128; 2: the plain path
+    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128, 5: 128 x 128 of signed
+                   // codes; 4: binary32, 128 x 128; 2: the plain path
     int bn, bk, tiles_n, tiles_k, splits, grid;
     int64_t rows_per_split;
 };
@@ -844,7 +845,8 @@ static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double 
 {
     int64_t best = 1;
     double least = 0.0;
-    for (int64_t s = 1; s <= 256 && (s == 1 || (tiles * s <= 512 && M >= 2 * kDwBM * s)); ++s) {
+    // (every count up to 16, then steps of an eighth: some forty candidates, under a microsecond of the host)
+    for (int64_t s = 1; s <= 256 && (s == 1 || (tiles * s <= 512 && M >= 2 * kDwBM * s)); s += s < 16 ? 1 : s / 8) {
         const int64_t stages = ceil_div(ceil_div(M > 0 ? M : 1, s), kDwBM), wgs = tiles * s;
         double us = double(stages) * stage_us * (wgs <= 256 ? 1.0 : 1.5 * double(ceil_div(wgs, 512)));
         if (s > 1) us += 4.0 + double(s) * double(N) * double(K) * 2e-6;   // 8 bytes at 4 TB/s
@@ -857,21 +859,24 @@ static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double 
 static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few = false)
 {
     DwPlan p;
-    // Up to 20 GFLOP the 128 x 128 tile at any width: a small matrix leaves most CUs without a 256 x 256 tile unless it is
-    // cut into slices, whose partial sums then cost more than the product.  Whole call, former plan -> this one: 505 rows,
-    // 1344 -> 1088: 34 -> 18 us (one slice); 1604, 1344 -> 1752: 41 -> 32; 4096, 768 -> 768: 36 -> 28; 12000, 768 -> 768:
-    // 44 -> 38; even from 22 to 26 (25216, 384 -> 1152: 49 / 50; 4096, 1024 -> 3072: 55 / 56).  Up to 36 GFLOP where 256 x 256
-    // tiles would be at most 16, i.e. 16 slices and more (25216, 1536 -> 384: 62 -> 56).  Beyond, the large tile's half as
-    // many operand bytes win (50432, 768 -> 768: 86 against 90; 768 -> 3072: 251 against 307).
+    // Up to 20 GFLOP (10 at widths that the 256 x 128 tile would take) the 128 x 128 tile: a small matrix leaves most CUs
+    // without a 256 x 256 tile unless it is cut into slices, whose partial sums then cost more than the product.  Whole call,
+    // former plan -> this one: 505 rows, 1344 -> 1088: 34 -> 18 us (one slice); 1604, 1344 -> 1752: 41 -> 32; 4096, 768 -> 768:
+    // 36 -> 28; 12000, 768 -> 768: 44 -> 38; 8192, 384 -> 1152: 31 -> 29.  Even or behind above (12608, 384 -> 1536, 15 GFLOP: 38 / 39;
+    // 25216, 384 -> 1152: 49 / 50; 4096, 1024 -> 3072: 55 / 56).  Up to 36 GFLOP where 256 x 256 tiles would be at most 16,
+    // i.e. 16 slices and more (25216, 1536 -> 384: 62 -> 56).  Beyond, the large tile's half as many operand bytes win (50432,
+    // 768 -> 768: 86 against 90; 768 -> 3072: 251 against 307).  Narrow layers have had that tile all along, with a slice per CU
+    // and the cheaper conversion: they are bound by memory.
     const double flops = 2.0 * double(M) * double(K) * double(N);
     const bool large_k = K % 256 == 0 || K > 1024;
-    const bool small = !few && (flops <= 20e9 || (flops <= 36e9 && large_k && ceil_div(N, 256) * ceil_div(K, 256) <= 16));
+    const bool narrow = !large_k && (K <= 128 || N <= 128) && N % 256 != 0 && N % 256 <= 128;   // no empty half tile in N
+    const bool small = !few && !narrow && (flops <= (large_k ? 20e9 : 10e9) || (flops <= 36e9 && large_k && ceil_div(N, 256) * ceil_div(K, 256) <= 16));
     if (dt != MESA_F32 && K % 16 == 0 && N % 8 == 0) {
         // 256-wide k tiles unless they would waste much of the last one.  (A 128 x 384 tile for K = 384 was
         // measured too: no faster per MFMA, and its 21 slices instead of 14 cost more partial-sum traffic.)
-        if (small) { p.variant = 3; p.bn = 128; p.bk = 128; }
+        if (small) { p.variant = 5; p.bn = 128; p.bk = 128; }
         else if (large_k) { p.variant = 0; p.bn = 256; p.bk = 256; }
-        else if ((K <= 128 || N <= 128) && N % 256 != 0 && N % 256 <= 128) { p.variant = 3; p.bn = 128; p.bk = 128; }   // narrow K or N: no empty half tile in N
+        else if (narrow) { p.variant = 3; p.bn = 128; p.bk = 128; }
         else { p.variant = 1; p.bn = 256; p.bk = 128; }
     } else if (dt == MESA_F32 && K % 16 == 0 && N % 4 == 0) {
         p.variant = 4; p.bn = DsCfg::BN; p.bk = DsCfg::BK;
@@ -891,7 +896,7 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few =
     if (splits > max_splits) splits = max_splits;
     if (splits > 256) splits = 256;   // one workgroup per CU also where there is a single tile
     if (!few && p.variant == 4) splits = dw_slices(M, K, N, tiles, 1.25);
-    else if (small && p.variant == 3) splits = dw_slices(M, K, N, tiles, 0.31);
+    else if (p.variant == 5) splits = dw_slices(M, K, N, tiles, 0.31);
     int64_t rps = ceil_div(ceil_div(M > 0 ? M : 1, splits), kDwBM) * kDwBM;
     splits = ceil_div(M > 0 ? M : 1, rps);
     p.splits = int(splits);
@@ -939,12 +944,19 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     const FastDiv dper = make_fastdiv(uint32_t(K / G));
     const bool one = p.splits == 1 && p.variant >= 3;    // the others leave their sums to the second kernel
     const DwDirect direct = {alpha, beta, dper, one ? dW : nullptr, db};
-#define MESA_LAUNCH_DW(E, BN_, BK_) \
+#define MESA_LAUNCH_DW(E, BN_, BK_, SIGNED_) \
     do { \
-        using C = DwCfg<BN_, BK_, 2, 2>; \
-        hipLaunchKernelGGL((k_dw_f16<E, BN_, BK_, 2, 2>), dim3(p.grid), dim3(C::THREADS), 2 * C::STAGE, s, xq, \
+        using C = DwCfg<BN_, BK_, 2, 2, SIGNED_>; \
+        hipLaunchKernelGGL((k_dw_f16<E, BN_, BK_, 2, 2, SIGNED_>), dim3(p.grid), dim3(C::THREADS), 2 * C::STAGE, s, xq, \
                            static_cast<const E *>(dy), M, Ki, Ni, p.tiles_n, p.tiles_k, p.splits, p.rows_per_split, P, S0, direct); \
         centre = DwElem<E>::centre(C::SIGNED); \
+    } while (0)
+#define MESA_PICK_DW(E) \
+    do { \
+        if (p.variant == 0) MESA_LAUNCH_DW(E, 256, 256, false); \
+        else if (p.variant == 1) MESA_LAUNCH_DW(E, 256, 128, false); \
+        else if (p.variant == 3) MESA_LAUNCH_DW(E, 128, 128, false); \
+        else MESA_LAUNCH_DW(E, 128, 128, true); \
     } while (0)
     if (p.variant == 2) {   // the plain path contracts with the signed code
 #define MESA_LAUNCH_DW_PLAIN(T) \
@@ -956,9 +968,9 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
         hipLaunchKernelGGL(k_dw_cut, dim3(p.grid), dim3(kThreads), 0, s, xq, static_cast<const float *>(dy), M, Ki, Ni, p.tiles_n,
                            p.tiles_k, p.splits, p.rows_per_split, P, S0, direct);
     } else if (dt == MESA_F16) {
-        if (p.variant == 0) MESA_LAUNCH_DW(_Float16, 256, 256); else if (p.variant == 1) MESA_LAUNCH_DW(_Float16, 256, 128); else MESA_LAUNCH_DW(_Float16, 128, 128);
+        MESA_PICK_DW(_Float16);
     } else {
-        if (p.variant == 0) MESA_LAUNCH_DW(__bf16, 256, 256); else if (p.variant == 1) MESA_LAUNCH_DW(__bf16, 256, 128); else MESA_LAUNCH_DW(__bf16, 128, 128);
+        MESA_PICK_DW(__bf16);
     }
     if (launch_status() != MESA_OK) return MESA_ERR_LAUNCH;   // the reduction must not run on partial sums nobody wrote
     if (one) return MESA_OK;
@@ -976,6 +988,7 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
         hipLaunchKernelGGL(k_dw_reduce_any, dim3(unsigned(ceil_div(N_out * K, kThreads))), dim3(kThreads), 0, s, P, S0, p.splits, Ni,
                            Ki, dk, dper, alpha, beta, centre, dW, db);
     }
+#undef MESA_PICK_DW
 #undef MESA_LAUNCH_DW
     return launch_status();
 }
