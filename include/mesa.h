@@ -320,7 +320,8 @@ mesa_status mesa_layernorm_bwd_q(const int8_t *xq, int64_t M, int64_t D, int64_t
  * sums then carry a term c*db[n] that cancels in the result, which costs accuracy when dy has a large mean --
  * about 3e-4 of max|dW| at a mean of half a standard deviation over 50000 rows, 1e-5 at mean zero.
  * xq: (M, K) int8, K in G channel groups.  dy: (M, N_out) of dt.  dW: (N_out, K) binary32, row-major,
- * overwritten.  db: [N_out] binary32 or NULL.  ws: MESA_OP_LINEAR_DW_Q bytes.
+ * overwritten.  db: [N_out] binary32 or NULL.  ws: MESA_OP_LINEAR_DW_Q bytes; those of a larger M serve too (the rows
+ * are then cut into as many slices as the workspace holds).
  * K % G == 0.  Widths with K % 16 != 0 or N_out % 8 != 0 (MESA_F32: N_out % 4 != 0) run a plain, slow kernel.
  * Limits: K * N_out < 2^31, else MESA_ERR_UNSUPPORTED.
  */

@@ -835,18 +835,19 @@ struct DwPlan {
                    // codes; 4: binary32, 128 x 128; 2: the plain path
     int bn, bk, tiles_n, tiles_k, splits, grid;
     int64_t rows_per_split;
+    int64_t least;  // the fewest slices that the plan of as many rows, or of more, has
 };
 
 // Slices of m for 128 x 128 tiles, two workgroups per CU at most: the cheapest of a slice's stages (us each; half as long
 // again where two workgroups share a CU), the second kernel's launch and the partial sums' way out and back.  With one
 // slice there is neither.  The constants are fits to a sweep of every split over twenty shapes; what it picks is within 5 %
 // of the sweep's best.
-static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double stage_us)
+static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double stage_us, int64_t room)
 {
     int64_t best = 1;
     double least = 0.0;
     // (every count up to 16, then steps of an eighth: some forty candidates, under a microsecond of the host)
-    for (int64_t s = 1; s <= 256 && (s == 1 || (tiles * s <= 512 && M >= 2 * kDwBM * s)); s += s < 16 ? 1 : s / 8) {
+    for (int64_t s = 1; s <= room && (s == 1 || (tiles * s <= 512 && M >= 2 * kDwBM * s)); s += s < 16 ? 1 : s / 8) {
         const int64_t stages = ceil_div(ceil_div(M > 0 ? M : 1, s), kDwBM), wgs = tiles * s;
         double us = double(stages) * stage_us * (wgs <= 256 ? 1.0 : 1.5 * double(ceil_div(wgs, 512)));
         if (s > 1) us += 4.0 + double(s) * double(N) * double(K) * 2e-6;   // 8 bytes at 4 TB/s
@@ -855,8 +856,12 @@ static int64_t dw_slices(int64_t M, int64_t K, int64_t N, int64_t tiles, double 
     return best;
 }
 
-// few: the plan of a caller whose workspace holds no more slices than 16-bit matrices of any size once had
-static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few = false)
+// room: slices that the workspace holds.  The number of slices is not monotonic in the number of rows -- the slices are whole
+// stages, and where they are chosen by cost a few rows more can make fewer of them the cheapest -- and a workspace sized for
+// a full batch has to serve a shorter one: the slices are then as many as it holds.
+constexpr int64_t kDwMaxSlices = 256;
+
+static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, int64_t room = kDwMaxSlices)
 {
     DwPlan p;
     // Up to 20 GFLOP (10 at widths that the 256 x 128 tile would take) the 128 x 128 tile: a small matrix leaves most CUs
@@ -870,7 +875,7 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few =
     const double flops = 2.0 * double(M) * double(K) * double(N);
     const bool large_k = K % 256 == 0 || K > 1024;
     const bool narrow = !large_k && (K <= 128 || N <= 128) && N % 256 != 0 && N % 256 <= 128;   // no empty half tile in N
-    const bool small = !few && !narrow && (flops <= (large_k ? 20e9 : 10e9) || (flops <= 36e9 && large_k && ceil_div(N, 256) * ceil_div(K, 256) <= 16));
+    const bool small = !narrow && (flops <= (large_k ? 20e9 : 10e9) || (flops <= 36e9 && large_k && ceil_div(N, 256) * ceil_div(K, 256) <= 16));
     if (dt != MESA_F32 && K % 16 == 0 && N % 8 == 0) {
         // 256-wide k tiles unless they would waste much of the last one.  (A 128 x 384 tile for K = 384 was
         // measured too: no faster per MFMA, and its 21 slices instead of 14 cost more partial-sum traffic.)
@@ -894,9 +899,12 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few =
     int64_t max_splits = M / 256;
     if (max_splits < 1) max_splits = 1;
     if (splits > max_splits) splits = max_splits;
-    if (splits > 256) splits = 256;   // one workgroup per CU also where there is a single tile
-    if (!few && p.variant == 4) splits = dw_slices(M, K, N, tiles, 1.25);
-    else if (p.variant == 5) splits = dw_slices(M, K, N, tiles, 0.31);
+    if (splits > kDwMaxSlices) splits = kDwMaxSlices;   // one workgroup per CU also where there is a single tile
+    // made whole stages, slices of 256 rows and more grow by an eighth at most, and their number falls to 8 / 9 at most
+    p.least = p.variant >= 4 ? 1 : (8 * splits + 8) / 9;
+    if (splits > room) splits = room;
+    if (p.variant == 4) splits = dw_slices(M, K, N, tiles, 1.25, room);
+    else if (p.variant == 5) splits = dw_slices(M, K, N, tiles, 0.31, room);
     int64_t rps = ceil_div(ceil_div(M > 0 ? M : 1, splits), kDwBM) * kDwBM;
     splits = ceil_div(M > 0 ? M : 1, rps);
     p.splits = int(splits);
@@ -905,15 +913,12 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, bool few =
     return p;
 }
 
-static size_t dw_plan_bytes(const DwPlan &p, int64_t K, int64_t N)
-{
-    return size_t(p.splits) * (size_t(N) * size_t(K) + size_t(N)) * sizeof(float) + 16;
-}
+static size_t dw_slice_bytes(int64_t K, int64_t N) { return (size_t(N) * size_t(K) + size_t(N)) * sizeof(float); }
 
 size_t linear_dw_ws_bytes(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
 {
     if (K <= 0 || N <= 0 || M < 0) return 16;
-    return dw_plan_bytes(dw_plan(M, K, N, dt), K, N);
+    return size_t(dw_plan(M, K, N, dt).splits) * dw_slice_bytes(K, N) + 16;
 }
 
 }  // namespace mesa
@@ -934,8 +939,9 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     if (K >= (int64_t(1) << 26) || N_out >= (int64_t(1) << 25) || (long double)K * (long double)N_out >= 2147483648.0L)
         return MESA_ERR_UNSUPPORTED;
     DwPlan p = dw_plan(M, K, N_out, dt);
-    if (ws_bytes < dw_plan_bytes(p, K, N_out)) p = dw_plan(M, K, N_out, dt, true);
-    if (!ws || !aligned16(ws) || ws_bytes < dw_plan_bytes(p, K, N_out)) return MESA_ERR_WORKSPACE;
+    const size_t room = ws_bytes >= 16 ? (ws_bytes - 16) / dw_slice_bytes(K, N_out) : 0;
+    if (!ws || !aligned16(ws) || room < size_t(p.least)) return MESA_ERR_WORKSPACE;
+    if (size_t(p.splits) > room) p = dw_plan(M, K, N_out, dt, int64_t(room));
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *P = static_cast<float *>(ws);
     float *S0 = P + size_t(p.splits) * size_t(N_out) * size_t(K);

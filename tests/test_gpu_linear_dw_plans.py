@@ -41,3 +41,28 @@ def test_linear_dw_tiles_and_slices(M, Mr, K, N, G, dtype):
     again = dW.clone()
     M.mesa_linear_dw_q(q, Mr, K, G, a, b, dy, N, dW, None, ws)      # without the bias gradient: the same bits
     assert torch.equal(dW, again)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("Mr,K,N,G,sized_for", [(2961, 384, 384, 6, 3200), (1422, 384, 1152, 1, 1472), (2961, 384, 384, 6, None), (511, 1344, 1088, 6, 511),
+                                                (4097, 768, 264, 12, 4097), (129, 128, 120, 2, 129)])
+def test_linear_dw_of_small_matrices_in_the_workspace_there_is(M, Mr, K, N, G, sized_for, dtype):
+    """The small tile in a workspace sized for more rows, which holds fewer slices than it would take, in one of a single slice (None)
+    and in its own.  1e-5 of the largest result, the binary32 bound: the codes are centred, every product is exact in
+    binary32 (contracting 1024 + code, as the large binary16 tiles do, misses it)."""
+    g = torch.Generator(device="cuda").manual_seed(Mr + K)
+    q = torch.randint(-128, 128, (Mr, K), dtype=torch.int8, device="cuda", generator=g)
+    dy = torch.randn((Mr, N), device="cuda", generator=g).to(dtype)
+    a, b = 0.5 + torch.rand(G, device="cuda", generator=g), -torch.rand(G, device="cuda", generator=g)
+    one = (N * K + N) * 4 + 16
+    need = M.workspace_bytes(M.OP_LINEAR_DW_Q, Mr, K, N, M.F16)
+    n = M.workspace_bytes(M.OP_LINEAR_DW_Q, sized_for, K, N, M.F16) if sized_for else one
+    assert n == need if sized_for == Mr else n < need
+    frame = torch.full((n + 256,), 0x55, dtype=torch.uint8, device="cuda")
+    dW, db = torch.empty((N, K), device="cuda"), torch.empty(N, device="cuda")
+    M.mesa_linear_dw_q(q, Mr, K, G, a, b, dy, N, dW, db, frame[:n])
+    x_hat = (q.double() + 128) * (a.double() / 255).repeat_interleave(K // G) + b.double().repeat_interleave(K // G)
+    ref = dy.double().t().contiguous() @ x_hat
+    assert (dW - ref).abs().max() <= 1e-5 * ref.abs().max()
+    assert (db - dy.double().sum(0)).abs().max() <= 1e-5 * dy.double().abs().sum(0).max()
+    assert torch.all(frame[n:] == 0x55)                     # nothing behind the workspace
