@@ -1064,6 +1064,41 @@ static bool minmax_few_groups(const mesa_layout &L, int grid, int unroll)
     return off > L.inner / 16;
 }
 
+// Aligned vectors that cover a slab, wherever it starts.
+static int64_t slab_vectors(int64_t inner) { return inner / kVec + (inner % kVec ? 2 : 0); }
+
+// Which way the extrema are found: by position, or by group with one workgroup per group (and one launch) or several.
+//
+// One workgroup per group, up to 32768 elements of it: (394, 3, 64) 5.4 us by position, 5.1 by group; (64, 8, 441) 21 and 5.6;
+// (16, 512, 49) 14.4 and 5.0; (8, 768, 4096) 29 and 18.  It loses where its 1024 threads have next to nothing to do -- five
+// hundred workgroups run at once, 8192 take 45 us whatever they hold: (1, 8192, 64) 20 and 46, (1, 4096, 100) 15 and 24,
+// (16, 4096, 128) 21 and 25, hence the elements per group from 512 groups on -- and where a slab is shorter than the vectors that
+// cover it, at a distance from the next: (32768, 768, 1) 64 and 162, (32768, 16, 1) 12 and 47, (4096, 768, 8) 21 and 60,
+// (2048, 384, 7) in binary32 22 and 26, against (394, 384, 1) 13 and 6.7, (512, 1024, 31) 56 and 20, (1024, 16, 20) 9.1 and 5.7.
+//
+// Several, for slabs of 64 to 2047 elements that are no whole vectors, whose lanes the scan by position sends to another
+// group at nearly every step: (725, 8, 341) 16.9 and 8.1, (1919, 32, 441) 36 and 24, (50000, 3, 341) 56 and 35.  Shorter slabs waste
+// the vectors at their ends ((100000, 12, 20): 21 and 35), longer ones keep a lane's group as it is ((8192, 3, 2401): 29 and
+// 37).  Beyond four million elements it takes slabs that are not even multiples of four elements, or a tensor that is large
+// enough: (11184, 2, 1500) 16 and 25, (82241, 3, 68) 16 and 21, (15420, 8, 68) in binary32 12 and 16.  Over 2300 shapes in both types,
+// of one to 8192 groups, none is slower than by position by more than the runs of one side differ (7 %).
+enum MinmaxScan { kByPosition, kByGroup, kByGroupInPieces };
+
+static MinmaxScan minmax_scan(int64_t outer, int64_t groups, int64_t inner)
+{
+    const bool whole = inner % kVec == 0;
+    const int64_t n = outer * inner;                       // of a group
+    if (n <= kSmallElems) {
+        if (inner < 64 && (whole || outer * slab_vectors(inner) > (inner < 16 ? 2047 : 4096))) return kByPosition;
+        return groups <= 512 || n >= (whole ? 4096 : 512) ? kByGroup : kByPosition;
+    }
+    if (groups == 1 || whole || inner < 64 || inner >= 2048) return kByPosition;
+    if (n * groups <= (int64_t(1) << 22)) return groups >= 3 || inner < 512 ? kByGroupInPieces : kByPosition;
+    if (groups >= 512) return kByGroupInPieces;
+    if (inner < 190) return kByPosition;
+    return (groups >= 8 && inner % 4 != 0) || (inner < 600 && n * groups >= 45000000) ? kByGroupInPieces : kByPosition;
+}
+
 // max_wgs > 0: the scan runs on at most that many workgroups and the workspace need only hold their partial values
 static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layout L, float *alpha, float *beta, float lambda,
                                          int first_call, int variant, float beta_fixed, void *ws, size_t ws_bytes, void *stream,
@@ -1081,22 +1116,19 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
     const size_t need = max_wgs > 0 ? size_t(grid) * 2 * size_t(L.groups) * sizeof(float) : update_ws_bytes(L.outer, L.groups, L.inner);
     if (!ws || !aligned16(ws) || ws_bytes < need) return MESA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Scan by group: one launch up to 32768 elements of a group (three groups of 394 x 64: 5.7 -> 5.2 us in binary16, 5.8 -> 4.8
-    // in binary32; at 64000 one workgroup per group takes 8.4 against 6.1), and slabs of 64 to 2047 elements that are no
-    // whole vectors, whose lanes the scan by position sends to another group at nearly every step ((64, 8, 441): 21 -> 5.6
-    // us, (725, 8, 341): 16.9 -> 8.1, (1919, 32, 441): 36 -> 24, (50000, 3, 341): 56 -> 35).  Shorter slabs waste the vectors
-    // at their ends ((100000, 12, 20): 21 against 35), longer ones keep a lane's group as it is ((8192, 3, 2401): 29 / 37).
-    const int64_t vps = L.inner / kVec + (L.inner % kVec ? 2 : 0);
-    const bool one = L.outer * L.inner <= kSmallElems;
-    if (L.outer * vps < (int64_t(1) << 31) && (one || (L.groups > 1 && L.inner % kVec != 0 && L.inner >= 64 && L.inner < 2048))) {
-        int64_t pieces = ceil_div(L.outer * vps, int64_t(4) * kSmallThreads), most = ceil_div(1024, L.groups);
+    // one group is one slab, however its elements are counted
+    const int64_t outer = L.groups == 1 ? 1 : L.outer, inner = L.groups == 1 ? L.outer * L.inner : L.inner;
+    const int64_t vps = slab_vectors(inner);
+    const MinmaxScan scan = minmax_scan(outer, L.groups, inner);
+    if (scan != kByPosition && outer * vps < (int64_t(1) << 31)) {
+        int64_t pieces = ceil_div(outer * vps, int64_t(4) * kSmallThreads), most = ceil_div(1024, L.groups);
         if (pieces > most) pieces = most;
         if (pieces > grid) pieces = grid;
-        if (one) pieces = 1;
+        if (scan == kByGroup) pieces = 1;
         float *part = pieces > 1 ? static_cast<float *>(ws) : nullptr;
 #define MESA_LAUNCH_BG(T) \
-    hipLaunchKernelGGL((k_minmax_by_group<T>), dim3(unsigned(L.groups), unsigned(pieces)), dim3(kSmallThreads), 0, s, x, uint32_t(L.outer), \
-                       uint32_t(L.groups), uint32_t(L.inner), numel, uint32_t(vps), make_fastdiv(uint32_t(vps)), alpha, beta, lambda, first_call, \
+    hipLaunchKernelGGL((k_minmax_by_group<T>), dim3(unsigned(L.groups), unsigned(pieces)), dim3(kSmallThreads), 0, s, x, uint32_t(outer), \
+                       uint32_t(L.groups), uint32_t(inner), numel, uint32_t(vps), make_fastdiv(uint32_t(vps)), alpha, beta, lambda, first_call, \
                        variant, beta_fixed, part)
         MESA_FOR_DTYPE(dt, MESA_LAUNCH_BG);
 #undef MESA_LAUNCH_BG

@@ -38,3 +38,10 @@ def test_running_estimates_scan_by_group(M, layout, dtype):
     M.mesa_update_running_scale_sym(x, layout, s, 0.9, False, ws)
     rs = R.update_running_scale_sym(npy(x), layout, np.full(groups, 3.0, np.float32), 0.9, False)
     assert np.array_equal(npy(s), rs)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("layout", [(32768, 1, 1), (5000, 1, 7), (1023, 2, 1), (1024, 2, 1), (4096, 3, 1), (2047, 1, 9), (819, 2, 31), (1025, 2, 17), (1, 513, 64),
+                                    (64, 513, 64), (7, 513, 73), (8, 513, 73), (40, 1000, 900)])
+def test_running_estimates_on_either_side_of_the_scans_lines(M, layout, dtype):
+    test_running_estimates_scan_by_group(M, layout, dtype)
