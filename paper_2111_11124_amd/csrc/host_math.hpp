@@ -63,4 +63,7 @@ inline GroupGeom make_geom(int64_t groups, int64_t inner, int64_t step)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The most workgroups of so many threads that a launch can have: it counts a dimension's threads in 32 bits.
+inline int64_t most_workgroups(int64_t threads) { return 0xFFFFFFFFll / threads; }
+
 }  // namespace mesa

@@ -689,8 +689,9 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
         return launch_status();
     }
     if (cols < kVec) return plain();
+    // a workgroup per tile, or per so many rows: beyond what one launch holds, the tiled or the plain kernel, which stride
     const SlPlan lp = sl_plan(total_rows, cols, 0, dtype_bytes(dt) + 1, cols > 1024 ? 8 : 4, 32);
-    if (lp.ok && dt != MESA_F32) {
+    if (lp.ok && dt != MESA_F32 && lp.tiles <= most_workgroups(64 * lp.waves)) {
         FastDiv drl = make_fastdiv(uint32_t(rows)), dhl = make_fastdiv(uint32_t(H));
         hipStream_t sl = static_cast<hipStream_t>(stream);
         auto go = [&](auto zero) {
@@ -706,14 +707,15 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
 #undef MESA_LAUNCH_SL_T
         return launch_status();
     }
-    if (cols % kVec == 0 && cols > kSrMaxCols && cols <= kSwMaxCols) {
-        const int64_t nvec = cols / kVec;
+    const int64_t nvec = cols / kVec;
+    const int64_t wave_wgs = ceil_div(total_rows, (nvec <= 64 ? 4 : nvec <= 128 ? 2 : 1) * (kThreads / 64));
+    if (cols % kVec == 0 && cols > kSrMaxCols && cols <= kSwMaxCols && wave_wgs <= most_workgroups(kThreads)) {
         FastDiv drw = make_fastdiv(uint32_t(rows)), dhw = make_fastdiv(uint32_t(H));
         hipStream_t sw = static_cast<hipStream_t>(stream);
         auto go = [&](auto zero) {
             typedef decltype(zero) T;
 #define MESA_LAUNCH_SW(LPR_, NV_) \
-    hipLaunchKernelGGL((k_softmax_bwd_wave<T, LPR_, NV_>), dim3(unsigned(ceil_div(total_rows, 64 / LPR_ * (kThreads / 64)))), dim3(kThreads), 0, sw, \
+    hipLaunchKernelGGL((k_softmax_bwd_wave<T, LPR_, NV_>), dim3(unsigned(wave_wgs)), dim3(kThreads), 0, sw, \
                        yq, dy, dx, total_rows, uint32_t(cols), drw, dhw, alpha, beta)
             if (nvec <= 48) MESA_LAUNCH_SW(16, 3);
             else if (nvec <= 64) MESA_LAUNCH_SW(16, 4);
@@ -748,6 +750,7 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
     const int64_t resident = 256 * kSmWgPerCu;
     int64_t want = ceil_div(wgs, 4);
     if (want < resident) want = resident;
+    if (want > most_workgroups(kThreads)) want = most_workgroups(kThreads);
     const int grid = int(wgs < want ? wgs : want);
     FastDiv dc = make_fastdiv(uint32_t(cols)), dr = make_fastdiv(uint32_t(rows)), dh = make_fastdiv(uint32_t(H));
     hipStream_t s = static_cast<hipStream_t>(stream);
