@@ -5,18 +5,19 @@ Every function below has the name and the argument order of the C entry point it
 passed through.  No arithmetic of the method happens in Python, and there is no fallback: if the
 shared library is missing or a call fails, an exception is raised.  The ordinary form of a compute call is
 marshalled natively (csrc/marshal.c: 1 to 2 us of the host instead of 6 to 8); what that does not know -- and
-every argument error -- goes through ctypes.
+every argument error, and everything where it was not built for the running Python -- goes through ctypes.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
 import importlib.util
 from pathlib import Path
 
 import torch  # noqa: F401  (first, so that libmesa binds to the HIP runtime torch has loaded)
 
 _LIB_PATH = Path(__file__).resolve().parent / "libmesa.so"
-_FAST_PATH = Path(__file__).resolve().parent / "_marshal.so"
+_FAST_PATH = Path(__file__).resolve().parent / ("_marshal" + importlib.machinery.EXTENSION_SUFFIXES[0])   # of this Python
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_LAUNCH = range(5)
 F32, F16, BF16 = 0, 1, 2
@@ -57,16 +58,25 @@ _fast = None   # the native marshalling (csrc/marshal.c), there once _lib is
 _vp, _i64, _u64, _int, _f32, _sz = C.c_void_p, C.c_int64, C.c_uint64, C.c_int, C.c_float, C.c_size_t
 
 
+class _General:
+    """In the native marshalling's place: leaves every call to the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_fast():
     """The compute calls' ordinary form, marshalled natively: each function returns the status, or None for a call that
-    the general path below has to judge."""
-    spec = importlib.util.spec_from_file_location("paper_2111_11124_amd._marshal", _FAST_PATH)
-    if not _FAST_PATH.exists():
-        raise RuntimeError(f"{_FAST_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
-    fast = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(fast)
-    fast.setup(torch.float16, torch.float32, torch.bfloat16, Conv2d, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-    return fast
+    the general path below has to judge.  The general path is complete, so where the extension was not built for this
+    Python, or this torch has no device functions, every call goes there."""
+    try:
+        spec = importlib.util.spec_from_file_location("paper_2111_11124_amd._marshal", _FAST_PATH)
+        fast = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(fast)
+        fast.setup(torch.float16, torch.float32, torch.bfloat16, Conv2d, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        return fast
+    except (ImportError, AttributeError):
+        return _General()
 
 
 def lib() -> C.CDLL:

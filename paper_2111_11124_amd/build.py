@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -12,7 +13,7 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 LIB = PKG / "libmesa.so"
-FAST = PKG / "_marshal.so"
+FAST = PKG / ("_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ = PKG / "_build"
 SOURCES = ["stream_kernels.hip", "softmax_fwd.hip", "softmax_bwd.hip", "layernorm_fwd.hip", "layernorm_bwd.hip", "linear_dw.hip", "attn_matmul_bwd.hip", "lowbit.hip", "conv_dw.hip", "mfma_probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -47,12 +48,17 @@ def build(verbose: bool = True) -> Path:
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
-    # the binding's native marshalling: plain C against the Python headers, bound to the library beside it
-    tmp = FAST.with_suffix(f".tmp{os.getpid()}.so")
-    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", f"-I{INCLUDE}", f"-I{sysconfig.get_path('include')}",
-           str(CSRC / "marshal.c"), "-o", str(tmp), f"-L{PKG}", "-l:libmesa.so", "-Wl,-rpath,$ORIGIN"]
-    subprocess.run(cmd, check=True)
-    os.replace(tmp, FAST)
+    # the binding's native marshalling: plain C against the Python headers, bound to the library beside it.  The binding
+    # does without it, at some 6 us a call, so it asks for nothing that the library does not: no headers, no extension
+    headers, cc = sysconfig.get_path("include"), os.environ.get("CC", "gcc")
+    if (Path(headers) / "Python.h").exists() and shutil.which(cc.split()[0]):
+        tmp = PKG / f"_marshal.tmp{os.getpid()}.so"
+        cmd = [*cc.split(), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", f"-I{INCLUDE}", f"-I{headers}", str(CSRC / "marshal.c"), "-o", str(tmp),
+               f"-L{PKG}", "-l:libmesa.so", "-Wl,-rpath,$ORIGIN"]
+        subprocess.run(cmd, check=True)
+        os.replace(tmp, FAST)
+    else:
+        print(f"no Python headers in {headers}, or no C compiler {cc}: {FAST.name} not built, calls are marshalled by ctypes")
     if verbose:
         print(f"built {LIB}")
     return LIB
