@@ -419,7 +419,7 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
 {
     constexpr int kB = Store<T>::kBytes;
     constexpr int RPP = 64 / LPR;                        // rows per pass
-    constexpr int kBatch = kB == 4 ? 2 : 3;              // vectors a lane requests together
+    constexpr int kBatch = 3;                            // vectors a lane requests together
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t sub = lane / LPR, l = lane % LPR;
@@ -690,7 +690,7 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
     }
     if (cols < kVec) return plain();
     // a workgroup per tile, or per so many rows: beyond what one launch holds, the tiled or the plain kernel, which stride
-    const SlPlan lp = sl_plan(total_rows, cols, 0, dtype_bytes(dt) + 1, cols > 1024 ? 8 : 4, 32);
+    const SlPlan lp = sl_plan(total_rows, cols, 0, dtype_bytes(dt) + 1, cols > 1024 ? 8 : 4);
     if (lp.ok && dt != MESA_F32 && lp.tiles <= most_workgroups(64 * lp.waves)) {
         FastDiv drl = make_fastdiv(uint32_t(rows)), dhl = make_fastdiv(uint32_t(H));
         hipStream_t sl = static_cast<hipStream_t>(stream);
@@ -702,9 +702,8 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_bwd_q(const int8_t *yq, int64_t 
             MESA_FOR_SL_SHAPE(lp, MESA_LAUNCH_SL);
 #undef MESA_LAUNCH_SL
         };
-#define MESA_LAUNCH_SL_T(T) go(T(0))
-        MESA_FOR_DTYPE(dt, MESA_LAUNCH_SL_T);
-#undef MESA_LAUNCH_SL_T
+        if (dt == MESA_F16) go(_Float16(0));
+        else go(__bf16(0));
         return launch_status();
     }
     const int64_t nvec = cols / kVec;

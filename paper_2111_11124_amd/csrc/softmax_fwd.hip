@@ -785,14 +785,15 @@ __global__ __launch_bounds__(kThreads, NV <= 4 ? 4 : 3) void k_softmax_fwd_wave(
 
 static SlPlan sf_long_plan(int64_t total_rows, int64_t H, int64_t cols, int elem_bytes)
 {
-    const int64_t lanes = cols <= 1024 ? 32 : 64;
-    return sl_plan(total_rows, cols, H * 16, elem_bytes, cols <= 1024 ? kSfLongTeam : 2 * kSfLongTeam,
-                   4 * sf_long_waves(elem_bytes, int(ceil_div(cols, lanes))));
+    return sl_plan(total_rows, cols, H * 16, elem_bytes, cols <= 1024 ? kSfLongTeam : 2 * kSfLongTeam);
 }
 // one resident round of workgroups, as far as the workspace has room for their extrema
-static int sl_grid(const SlPlan &p)
+static int sl_grid(const SlPlan &p, int elem_bytes)
 {
-    const int64_t resident = 256 * int64_t(p.per_cu);
+    const int waves_per_cu = 4 * sf_long_waves(elem_bytes, p.epl);
+    int64_t per_cu = int64_t(160 * 1024) / int64_t(p.lds);
+    if (per_cu * p.waves > waves_per_cu) per_cu = waves_per_cu / p.waves;
+    const int64_t resident = 256 * (per_cu > 1 ? per_cu : 1);
     return int(p.tiles < resident ? p.tiles : resident);
 }
 
@@ -951,7 +952,7 @@ static size_t sf_ws_bytes(int64_t total_rows, int64_t H, int64_t cols, bool full
             two_step = two_step || r.two_step;
             if (r.rp.ok && r.rp.grid > grid) grid = r.rp.grid;
             if (r.p.ok && r.p.grid > grid) grid = r.p.grid;
-            if (full && r.lp.ok && sl_grid(r.lp) > grid) grid = sl_grid(r.lp);
+            if (full && r.lp.ok && sl_grid(r.lp, eb) > grid) grid = sl_grid(r.lp, eb);
             if (r.wave_rows && sw_grid_bound(total_rows) > grid) grid = sw_grid_bound(total_rows);
         }
     size_t need = grid == 0 ? 16 : size_t(grid) * 2 * size_t(H) * sizeof(float) + 16;
@@ -1002,7 +1003,7 @@ extern "C" MESA_EXPORT mesa_status mesa_softmax_fwd_q(const void *s_in, int64_t 
     const int64_t room = int64_t((ws_bytes < (size_t(1) << 40) ? ws_bytes : (size_t(1) << 40)) / (size_t(H) * 2 * sizeof(float)));
     if (route.lp.ok && room > 0) {
         const SlPlan &lp = route.lp;
-        const int full = sl_grid(lp), grid = room < full ? int(room) : full;
+        const int full = sl_grid(lp, dtype_bytes(dt)), grid = room < full ? int(room) : full;
         auto go = [&](auto zero, auto stochastic) {
             typedef decltype(zero) T;
             constexpr bool SR = decltype(stochastic)::value;

@@ -112,10 +112,11 @@ inline SrShape sr_shape(int64_t total_rows, int64_t cols)
 // ---------------------------------------------------------------------------------------------
 // Long rows that start anywhere (256 < cols <= 2048, cols no multiple of 8).  The same three phases, but a tile is as
 // large as its alignment asks for -- eight rows of an odd length, 4616 elements at 577 columns -- and belongs to a
-// workgroup of two or four waves, which share out its vectors, then its rows, then its vectors; a row takes half a wave
-// or a whole one.  A tile is fetched when its turn comes: the other workgroups of the CU cover the latency.  (A tile per
-// wave was measured first: half the waves per CU fit their LDS, and a small tensor's few tiles take four times as long
-// each -- 30 against 19 us at three maps of 587 columns.)
+// workgroup (two or four waves in the forward, four or eight in the backward), whose waves share out its vectors, then its
+// rows, then its vectors; a row takes half a wave or a whole one.  The forward's workgroups stride over the tiles and request the
+// next one's first vectors while they work; the backward has a workgroup per tile, and the CU's other workgroups cover
+// the latency.  (A tile per wave was measured first: half the waves per CU fit their LDS, and a small tensor's few tiles take
+// four times as long each -- 30 against 19 us at three maps of 587 columns.)
 // ---------------------------------------------------------------------------------------------
 constexpr int64_t kSlMaxCols = 2048;
 constexpr int64_t kSlTileElems = 6144;                 // several units of rows per tile up to here
@@ -128,13 +129,12 @@ struct SlPlan {
     int lpr, epl;
     int64_t R, tiles;
     int waves;               // per workgroup
-    int per_cu;              // workgroups that fit a CU
     uint32_t tab_bytes;
     size_t lds;
 };
 
 // tab: bytes of the workgroup's tables; elem: bytes of a tile per element
-inline SlPlan sl_plan(int64_t total_rows, int64_t cols, int64_t tab, int64_t elem, int waves, int max_waves_per_cu)
+inline SlPlan sl_plan(int64_t total_rows, int64_t cols, int64_t tab, int64_t elem, int waves)
 {
     SlPlan p{};
     if (cols <= kSrMaxCols || cols > kSlMaxCols || cols % kVec == 0) return p;
@@ -151,9 +151,6 @@ inline SlPlan sl_plan(int64_t total_rows, int64_t cols, int64_t tab, int64_t ele
     p.lds = size_t(p.tab_bytes) + size_t((p.R * cols * elem + 15) / 16 * 16) + size_t(p.lpr) * p.epl * 4;
     if (p.lds > 64 * 1024) return p;
     p.waves = waves;
-    int64_t n = int64_t(160 * 1024) / int64_t(p.lds);
-    if (n * p.waves > max_waves_per_cu) n = max_waves_per_cu / p.waves;
-    p.per_cu = int(n > 1 ? n : 1);
     p.ok = true;
     return p;
 }
