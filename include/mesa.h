@@ -313,8 +313,9 @@ mesa_status mesa_layernorm_bwd_q(const int8_t *xq, int64_t M, int64_t D, int64_t
  * Linear weight gradient at the de-quantized input, Eq. (2) for y = x W^T, W of shape (N_out, K):
  *   dW[n, k] = sum_m dy[m, n] * x_hat[m, k],   db[n] = sum_m dy[m, n]
  * evaluated as  s_g(k) * sum_m dy[m,n]*(q[m,k]+128+c)  +  (beta_g(k) - c*s_g(k)) * db[n]  on the matrix cores
- * (binary16 products for MESA_F16, bfloat16 products for MESA_BF16 and for MESA_F32, whose dy is taken apart into three
- * bfloat16 values that add up to it exactly; binary32 accumulation; fixed summation order).  c = -128, the signed code, for
+ * (binary16 products for MESA_F16, bfloat16 products for MESA_BF16 and for MESA_F32, whose dy is taken apart, 2^23-fold,
+ * into three bfloat16 values that add up to it exactly, subnormal values too; where dy holds values of 2^64 and more,
+ * binary32 products; binary32 accumulation; fixed summation order).  c = -128, the signed code, for
  * MESA_F32 and for small matrices (of up to some 20 GFLOP, narrow ones aside).  Others: c = 1024 for MESA_F16, where 1024 + code is the cheapest
  * exact binary16 operand, c = 0 for MESA_BF16: the binary32
  * sums then carry a term c*db[n] that cancels in the result, which costs accuracy when dy has a large mean --
@@ -362,7 +363,7 @@ mesa_status mesa_conv2d_dw_q(const int8_t *xq, mesa_conv2d cv, int64_t G, const 
  * Eq. (2) with G_l = the gradient of a matrix product (the "MatMul" rows of the paper's overhead table;
  * Sec. 3.2: the operands are saved as codes with one (alpha, beta) pair per head).  All tensors are
  * (B, H, N, .) contiguous, upstream gradients and results of dt (extents below 8 run one plain, slow
- * kernel; a binary32 operand is taken apart into three bfloat16 values that add up to it exactly), accumulation in binary32; any N and Dh (nothing needs to be aligned).
+ * kernel; a binary32 operand is taken apart as in mesa_linear_dw_q), accumulation in binary32; any N and Dh (nothing needs to be aligned).
  *
  * O = A V with A the attention map (B,H,N,N) and V (B,H,N,Dh):
  *   dA[i,j] = sum_d dO[i,d] * V_hat[j,d],    dV[j,d] = sum_i A_hat[i,j] * dO[i,d]

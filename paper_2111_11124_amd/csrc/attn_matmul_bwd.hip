@@ -18,7 +18,7 @@
 // kept in the operand's own orientation; where that is not the orientation the MFMA wants, the
 // fragments come from the LDS transpose reads.  The next stage's loads are in flight while a stage
 // is multiplied.  binary16 or bfloat16 tensors (every kernel here takes the number type as a parameter);
-// binary32 tensors run the general kernel on their three bfloat16 parts.
+// binary32 tensors run the general kernel on three bfloat16 parts.
 //
 // That general kernel (k_bmm_q) serves every shape; dedicated kernels take the shapes that matter: k_attn_da,
 // k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths included, and
@@ -135,10 +135,10 @@ template <> struct BmNum<__bf16> {
     }
 };
 
-// binary32 tensors: a binary32 value is exactly the sum of three bfloat16 values (its significand cut into runs of eight
-// bits), a code q is exact in bfloat16 and a product of the two in binary32, so three bfloat16 MFMAs add the same exact
-// products as the binary32 MFMA, at sixteen times its rate and with one rounding of the sum per sixteen steps instead of
-// per two.  The contracted value is the signed code, as in the plain binary32 kernel.  Against that kernel (one element
+// binary32 tensors: 2^23 times a binary32 value is exactly the sum of three bfloat16 values (cut_f32), a code q is exact in
+// bfloat16 and a product of the two in binary32, so three bfloat16 MFMAs add the same exact products as the binary32
+// MFMA, at sixteen times its rate and with one rounding of the sum per sixteen steps instead of per two.  A workgroup that met
+// a value of 2^64 or more, an infinity or a NaN does its tile again with binary32 MFMAs, as the plain kernel does.  The contracted value is the signed code, as in the plain binary32 kernel.  Against that kernel (one element
 // per lane and load, straight from memory, a dependent load per two contraction steps) the four products and softmax's
 // backward took 140 -> 45 us at (2, 3, 197, 64), 257 -> 62 at (1, 12, 324, 64) and 312 -> 93 at (32, 6, 197, 64).
 template <> struct BmNum<float> {
@@ -211,7 +211,6 @@ template <> struct BmElem<false, float> {
     struct raw_t { u32x4 lo, hi; };
     typedef u32x4 word_t;
     static constexpr int kEb = 2, kPlanes = 3;
-    // cut, not rounded: no part can overflow and every difference is exact; an infinity is its own first part
     __device__ static __forceinline__ void cut(const raw_t &v, word_t (&w)[kPlanes])
     {
 #pragma unroll
@@ -219,15 +218,22 @@ template <> struct BmElem<false, float> {
             uint32_t part[3][2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const float x = __uint_as_float(k < 2 ? v.lo[2 * k + j] : v.hi[2 * k - 4 + j]);
-                part[0][j] = __float_as_uint(x) & 0xFFFF0000u;
-                const float r = __builtin_isinf(x) ? 0.0f : x - __uint_as_float(part[0][j]);
-                part[1][j] = __float_as_uint(r) & 0xFFFF0000u;
-                part[2][j] = __float_as_uint(r - __uint_as_float(part[1][j]));
+                cut_f32(__uint_as_float(k < 2 ? v.lo[2 * k + j] : v.hi[2 * k - 4 + j]), part[0][j], part[1][j], part[2][j]);
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q) w[q][k] = __builtin_amdgcn_perm(part[q][1], part[q][0], 0x07060302u);
         }
+    }
+    // magnitude bits of the largest element
+    __device__ static __forceinline__ uint32_t most(const raw_t &v)
+    {
+        uint32_t m = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t bits = (k < 4 ? v.lo[k] : v.hi[k - 4]) & 0x7FFFFFFFu;
+            m = bits > m ? bits : m;
+        }
+        return m;
     }
 };
 
@@ -347,6 +353,31 @@ template <bool CODED, bool TFAST, typename ET> struct BmOperand {
     }
 };
 
+// One wave's 32 x 32 tile with 32x32x2 binary32 MFMAs, operands straight from global memory, one element at a time (a lane needs
+// one value per operand and step: lane l holds row r / column c, both l%32 of the tile, at contraction slot l/32).
+// acc: the sums with the signed codes, acc1: those of the plain operand alone.  T: the tensors' element type.
+template <bool P_CODED, typename T>
+__device__ __forceinline__ void bmm_plain_sums(const BmmArgs &a, uint32_t b, int r, int c, bm_v16f &acc, bm_v16f &acc1)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t xb0 = (int64_t(b) + a.batch0) * a.x_batch;
+    const int8_t *yb = a.y + (int64_t(b) + a.batch0) * a.y_batch;
+    const bool r_ok = r < a.R, c_ok = c < a.Cn;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { acc[v] = 0.0f; acc1[v] = 0.0f; }
+    for (int t0 = 0; t0 < a.Tn; t0 += 2) {
+        const int t = t0 + (lane >> 5);
+        const bool t_ok = t < a.Tn;
+        float pa = 0.0f, qb = 0.0f;
+        const int64_t po = int64_t(r) * a.p_rs + int64_t(t) * a.p_ts, qo = int64_t(t) * a.q_ts + int64_t(c) * a.q_cs;
+        if (t_ok && r_ok) pa = P_CODED ? float(int(yb[po])) : Store<T>::load1(a.x, xb0 + po);
+        if (t_ok && c_ok) qb = P_CODED ? Store<T>::load1(a.x, xb0 + qo) : float(int(yb[qo]));
+        const float one = t_ok ? 1.0f : 0.0f;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa, qb, acc, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(P_CODED ? one : pa, P_CODED ? qb : one, acc1, 0, 0, 0);   // sums of the plain operand
+    }
+}
+
 // P_CODED: P is the coded operand (else Q).  P_TFAST / Q_TFAST: the contraction index is the unit-stride
 // index of that operand in memory.  ET: the tensors' type (BmmArgs carries their pointers as 16-bit containers'; a
 // binary32 operand is three bfloat16 planes, see BmElem).
@@ -359,8 +390,11 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
     typedef BmOperand<P_CODED, P_TFAST, ET> OP;
     typedef BmOperand<!P_CODED, Q_TFAST, ET> OQ;
     typedef typename BmElem<false, ET>::global_t X;       // the plain operand's and the result's element type in memory
-    constexpr int kTiles = (OP::kBytes + OQ::kBytes) * RS, kSums = RS > 1 ? 32 * kThreads * 4 : 0;
-    __shared__ __attribute__((aligned(16))) unsigned char lds_bm[kTiles > kSums ? kTiles : kSums];
+    constexpr bool kCut = std::is_same<ET, float>::value;
+    constexpr int kTiles = (OP::kBytes + OQ::kBytes) * RS, kSums = RS > 1 ? 32 * kThreads * 4 : 0, kLds = kTiles > kSums ? kTiles : kSums;
+    __shared__ __attribute__((aligned(16))) unsigned char lds_bm[kLds + (kCut ? 16 : 0)];
+    int *large = reinterpret_cast<int *>(lds_bm + (kCut ? kLds : 0));   // binary32: some value is too large to be cut
+    if (kCut && threadIdx.x == 0) *large = 0;
 
     const int group = RS > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kThreads) : 0;
     const int tid = RS > 1 ? int(threadIdx.x) % kThreads : int(threadIdx.x), lane = tid & 63, wave = tid >> 6;   // within the group
@@ -391,6 +425,7 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
 
     typename OP::Raw pv[kBmParts];
     typename OQ::Raw qv[kBmParts];
+    uint32_t most = 0;
 #pragma unroll
     for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(group * kBmT, k); qv[k] = load_q(group * kBmT, k); }
     for (int first = 0; first < a.Tn; first += kBmT * RS) {   // the same count for every group: they meet at the barriers
@@ -400,6 +435,12 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
         for (int k = 0; k < kBmParts; ++k) {
             OP::store(LP, pv[k], r0, t0, a.R, a.Tn, tid + k * kThreads);
             OQ::store(LQ, qv[k], c0, t0, a.Cn, a.Tn, tid + k * kThreads);
+            if constexpr (kCut) {
+                uint32_t m;
+                if constexpr (P_CODED) m = OQ::Elem::most(qv[k]);
+                else m = OP::Elem::most(pv[k]);
+                most = m > most ? m : most;
+            }
         }
         __syncthreads();
         if (first + kBmT * RS < a.Tn) {   // the next stage's loads fly while this one is multiplied
@@ -419,6 +460,10 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
         }
     }
 
+    if constexpr (kCut) {
+        if (most >= kCutMost) *large = 1;
+        __syncthreads();
+    }
     if constexpr (RS > 1) {
         float *sums = reinterpret_cast<float *>(lds_bm) + tid;
 #pragma unroll 1
@@ -435,6 +480,14 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
             }
         }
         if (group != 0) return;
+    }
+    if constexpr (kCut) {
+        if (*large) {                                     // uniform
+            bmm_plain_sums<P_CODED, float>(a, b, r0 + wr * 32 + (lane & 31), c0 + wc * 32 + (lane & 31), acc, acc1);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[v] *= kCutDown; acc1[v] *= kCutDown; }
+        }
     }
     // lane l, register v of a 32 x 32 tile: row 8*(v/4) + 4*(l/32) + v%4, column l%32
     const float s = a.alpha[h] / 255.0f;
@@ -475,9 +528,8 @@ static void launch_bmm(BmmArgs a, int64_t batches, hipStream_t s)
     }
 }
 
-// The plain kernel: 32x32x2 binary32 MFMA with operands straight from global memory, one element at a time (a lane
-// needs one value per operand and step: lane l holds row / column l%32 at contraction slot l/32).  Kept simple: it
-// serves extents shorter than one load vector.  T: the tensors' element type (BmmArgs' pointers are reinterpreted).
+// The plain kernel: bmm_plain_sums alone.  Kept simple: it serves extents shorter than one load vector.  T: the tensors'
+// element type (BmmArgs' pointers are reinterpreted).
 template <bool P_CODED, typename T>
 __global__ __launch_bounds__(kThreads) void k_bmm_plain(BmmArgs a)
 {
@@ -486,23 +538,9 @@ __global__ __launch_bounds__(kThreads) void k_bmm_plain(BmmArgs a)
     const int r = int(blockIdx.y) * kBmTile + (wave >> 1) * 32 + (lane & 31);
     const int c = int(blockIdx.x) * kBmTile + (wave & 1) * 32 + (lane & 31);
     const uint32_t h = (b + uint32_t(a.head0)) % uint32_t(a.heads);
-    const int64_t xb0 = (int64_t(b) + a.batch0) * a.x_batch;
-    const int8_t *yb = a.y + (int64_t(b) + a.batch0) * a.y_batch;
-    const bool r_ok = r < a.R, c_ok = c < a.Cn;
+    const bool c_ok = c < a.Cn;
     bm_v16f acc, acc1;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { acc[v] = 0.0f; acc1[v] = 0.0f; }
-    for (int t0 = 0; t0 < a.Tn; t0 += 2) {
-        const int t = t0 + (lane >> 5);
-        const bool t_ok = t < a.Tn;
-        float pa = 0.0f, qb = 0.0f;
-        const int64_t po = int64_t(r) * a.p_rs + int64_t(t) * a.p_ts, qo = int64_t(t) * a.q_ts + int64_t(c) * a.q_cs;
-        if (t_ok && r_ok) pa = P_CODED ? float(int(yb[po])) : Store<T>::load1(a.x, xb0 + po);
-        if (t_ok && c_ok) qb = P_CODED ? Store<T>::load1(a.x, xb0 + qo) : float(int(yb[qo]));
-        const float one = t_ok ? 1.0f : 0.0f;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa, qb, acc, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(P_CODED ? one : pa, P_CODED ? qb : one, acc1, 0, 0, 0);   // sums of the plain operand
-    }
+    bmm_plain_sums<P_CODED, T>(a, b, r, c, acc, acc1);
     const float s = a.alpha[h] / 255.0f;
     const float off = fmaf(128.0f, s, a.beta[h]);
     const int row_l = int(blockIdx.y) * kBmTile + (wave >> 1) * 32 + (lane >> 5) * 4;

@@ -485,10 +485,11 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
 }
 
 // ---- binary32 tensors ------------------------------------------------------------------------------------------
-// The matrix cores multiply binary32 at a sixteenth of their bfloat16 rate, and a binary32 value is exactly the sum of
-// three bfloat16 values (its significand cut into three runs of eight bits, each with its own exponent).  The codes are
-// exact in bfloat16, a product of two bfloat16 values is exact in binary32, so three bfloat16 MFMAs against the three
-// parts add the same exact products as one binary32 MFMA, sixteen contraction steps per rounding of the sum instead of two.
+// The matrix cores multiply binary32 at a sixteenth of their bfloat16 rate, and 2^23 times a binary32 value is exactly the sum
+// of three bfloat16 values that are no subnormals (cut_f32).  The codes are exact in bfloat16, a product of two bfloat16 values
+// is exact in binary32, so three bfloat16 MFMAs against the three parts add the same exact products as one binary32
+// MFMA, sixteen contraction steps per rounding of the sum instead of two.  A workgroup that met a value of 2^64 or more, an
+// infinity or a NaN does its slice again with binary32 MFMAs, operands straight from memory.
 //
 // The parts are cut as the tile goes to LDS: three planes of bfloat16 in the tensor's own orientation, read back by the
 // transposing reads like the 16-bit kernel's.  128 x 128 tile of dW per workgroup, four waves of 64 x 64 (64 accumulator
@@ -497,7 +498,8 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
 //
 // Whole call, one-element-at-a-time binary32 MFMA kernel -> this one: 394 x (192 -> 768) 101 -> 17 us (latency of its
 // two stages and of the two launches), 2494 x (2880 -> 1392) 786 -> 92 us (217 TFLOP/s; a third of the bfloat16 rate is the
-// ceiling), 25216 x (384 -> 1536) 1354 -> 125 us.  Error against 64 bits as before or smaller (tiny block: 3.4e-6 -> 2.3e-6).
+// ceiling), 25216 x (384 -> 1536) 1354 -> 120 us.  Error against 64 bits as before or smaller at every magnitude (70 to 4099 rows:
+// 2e-7 to 7e-7 -> 1e-7); the factor and the search for large values cost 0.1 us to 1 %.
 struct DsCfg {
     static constexpr int BN = 128, BK = 128;
     static constexpr int PA = BN * 2 + 64, PB = BK + 32;   // LDS row pitches (bytes) of a plane of dy and of the codes
@@ -509,23 +511,15 @@ struct DsCfg {
     static_assert(2 * STAGE <= 80 * 1024, "two workgroups per CU");
 };
 
-// x = a + b + c with a, b, c bfloat16 values in the upper halves of the results: the leading eight bits of what is left,
-// three times.  Cut, not rounded: no part can overflow, and each difference is exact.  An infinity is its own first part.
-__device__ __forceinline__ void cut_f32(float x, uint32_t &a, uint32_t &b, uint32_t &c)
-{
-    a = __float_as_uint(x) & 0xFFFF0000u;
-    const float r = __builtin_isinf(x) ? 0.0f : x - __uint_as_float(a);
-    b = __float_as_uint(r) & 0xFFFF0000u;
-    c = __float_as_uint(r - __uint_as_float(b));
-}
-
 __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict__ xq, const float *__restrict__ dy, int64_t M, int K,
                                                         int N, int tiles_n, int tiles_k, int splits, int64_t rows_per_split,
                                                         float *__restrict__ P, float *__restrict__ S0, DwDirect direct)
 {
     typedef DsCfg C;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE];
+    __shared__ int large;                                 // some value is too large to be cut
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) large = 0;
     const int total = gridDim.x;                          // a multiple of 8
     const int logical = int(blockIdx.x % kDwXcd) * (total / kDwXcd) + int(blockIdx.x / kDwXcd);
     const int ntiles = tiles_n * tiles_k;
@@ -553,6 +547,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
         vb = *reinterpret_cast<const u32x4 *>(xq + (r < m_end ? r : m_end - 1) * K + col_b);
     };
     float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);     // this thread's share of the row sums of its four columns of dy
+    uint32_t most = 0;                                    // magnitude bits
     auto store_stage = [&](int64_t m, unsigned char *st) {
 #pragma unroll
         for (int i = 0; i < C::A_VECS; ++i) {
@@ -563,7 +558,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
             const float x[4] = {v.x, v.y, v.z, v.w};
             uint32_t p[3][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) cut_f32(x[j], p[0][j], p[1][j], p[2][j]);
+            for (int j = 0; j < 4; ++j) {
+                cut_f32(x[j], p[0][j], p[1][j], p[2][j]);
+                const uint32_t bits = magnitude_bits(x[j]);
+                most = bits > most ? bits : most;
+            }
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 const u32x2 w = {__builtin_amdgcn_perm(p[q][1], p[q][0], 0x07060302u), __builtin_amdgcn_perm(p[q][3], p[q][2], 0x07060302u)};
@@ -623,9 +622,36 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
         }
     }
 
+    if (most >= kCutMost) large = 1;
+    __syncthreads();                                      // (and the last stage's fragments have been read)
+    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
+    float down = kCutDown;
+    if (large) {                                          // uniform
+        down = 1.0f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+        for (int64_t m2 = m_begin; m2 < m_end; m2 += 2) {
+            const int64_t m = m2 + (lane >> 5);
+            float a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int n = n0 + wn * 64 + i * 32 + col_l, kk = kk0 + wk * 64 + i * 32 + col_l;
+                a[i] = m < m_end && n < N ? dy[m * N + n] : 0.0f;
+                b[i] = m < m_end && kk < K ? float(int(xq[m * K + kk])) : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+
     // the row sums of the tile's rows of dW: the eight threads of a column group, in order
     if (tk == 0 || direct.dW) {                           // uniform
-        __syncthreads();                                  // the last stage's fragments have been read
         float4 *part = reinterpret_cast<float4 *>(smem);
         part[tid] = sum;
         __syncthreads();
@@ -647,7 +673,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
     }
     const float *rows = reinterpret_cast<const float *>(smem);
     float *Ps = P + int64_t(split) * N * K;
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int kk = kk0 + wk * 64 + j * 32 + col_l;
@@ -663,8 +688,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
             for (int v = 0; v < 16; ++v) {
                 const int r = wn * 64 + i * 32 + (v >> 2) * 8 + row_l + (v & 3), n = n0 + r;
                 if (n < N && kk < K) {
-                    if (direct.dW) direct.dW[int64_t(n) * K + kk] = fmaf(sg, acc[i][j][v], off * rows[r]);
-                    else Ps[int64_t(n) * K + kk] = acc[i][j][v];
+                    const float p = acc[i][j][v] * down;
+                    if (direct.dW) direct.dW[int64_t(n) * K + kk] = fmaf(sg, p, off * rows[r]);
+                    else Ps[int64_t(n) * K + kk] = p;
                 }
             }
     }
