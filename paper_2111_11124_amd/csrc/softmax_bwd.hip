@@ -425,7 +425,7 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
     const uint32_t sub = lane / LPR, l = lane % LPR;
     const uint32_t tid = threadIdx.x, nt = blockDim.x;
     unsigned char *gs = smem;                                         // dy, then dx
-    unsigned char *cs = gs + R * cols * kB;                           // codes
+    unsigned char *cs = gs + R * cols * kB;                           // x_bar, the codes from 0 to 255
     const int64_t row0 = int64_t(blockIdx.x) * R;
     const uint32_t nrows = uint32_t((total_rows - row0 < int64_t(R)) ? (total_rows - row0) : int64_t(R));
     const uint32_t nelem = nrows * cols;
@@ -448,6 +448,8 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
             const uint32_t v = v0 + u * nt + tid;
             if (v < nfull) {
                 Store<T>::store(gs, int64_t(v) * kVec, raw[u]);
+                rawq[u][0] ^= 0x80808080u;
+                rawq[u][1] ^= 0x80808080u;
                 *reinterpret_cast<u32x2 *>(cs + v * kVec) = rawq[u];
             }
         }
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
     if (tid < tail) {
         const uint32_t le = nfull * kVec + tid;
         LdsElem<T>::put(gs + le * kB, Store<T>::load1(dy, e0 + le));
-        cs[le] = uint8_t(yq[e0 + le]);
+        cs[le] = uint8_t(yq[e0 + le]) ^ 0x80u;
     }
     __syncthreads();
 
@@ -468,13 +470,15 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
         const unsigned char *cp = cs + eb;
         const uint32_t slab = fastdiv(uint32_t(row0) + rr, div_rows);
         const uint32_t h = slab - fastdiv(slab, div_heads) * div_heads.d;
-        const float s = alpha[h] / 255.0f, off = fmaf(128.0f, s, beta[h]);   // y_hat = s * q + off with q the signed code
+        // y_hat = s * x_bar + beta: with the signed code and 128 s + beta for the offset, the smallest values -- most of a long
+        // map's -- would be left over from a difference of numbers of the range's size
+        const float s = alpha[h] / 255.0f, off = beta[h];
         float g[EPL], yh[EPL];
         float d = 0.0f;
 #pragma unroll
         for (int k = 0; k < EPL; ++k) {
             const float gv = LdsElem<T>::get(gp + k * LPR * kB);
-            const float qv = float(int(*reinterpret_cast<const int8_t *>(cp + k * LPR)));
+            const float qv = float(uint32_t(cp[k * LPR]));
             g[k] = (k < sl_full(EPL) || l + k * LPR < cols) ? gv : 0.0f;     // unused slots add nothing
             yh[k] = fmaf(qv, s, off);
             d = fmaf(g[k], yh[k], d);

@@ -94,3 +94,30 @@ def test_softmax_forward_long_rows_in_the_smallest_workspace(M):
         got.append((npy(y), npy(q), npy(a), npy(b)))
     for u, v in zip(*got):
         assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("cols", [257, 577, 1000, 1023, 1127, 2047, 2050])
+def test_softmax_backward_long_rows_near_the_smallest_value(M, cols, dtype):
+    """Nearly every element of a long attention map has the smallest codes, and its map's offset is orders of magnitude below the
+    range: x_bar * alpha / 255 + beta is rounded once, element by element, not taken off a number of the range's size.
+    Bound: a unit of the type (the result is rounded to it once, the arithmetic before is binary32) and, for d, 1e-6 of the terms
+    that it adds."""
+    H, rows = 2, 24
+    n = H * rows * cols
+    g = torch.Generator(device="cuda").manual_seed(cols)
+    q = torch.full((n,), -128, dtype=torch.int8, device="cuda")
+    few = torch.rand(n, device="cuda", generator=g) < 0.02
+    q[few] = torch.randint(-128, 128, (int(few.sum()),), dtype=torch.int8, device="cuda", generator=g)
+    dy = (torch.randn(n, device="cuda", generator=g) * 4096).to(dtype)
+    a, b = torch.tensor([0.06, 0.9], device="cuda"), torch.tensor([3e-6, 1e-5], device="cuda")
+    dx = torch.empty(n, dtype=dtype, device="cuda")
+    M.mesa_softmax_bwd_q(q, 1, H, rows, cols, a, b, dy, dx)
+    y = (q.double().view(H, rows, cols) + 128) * (a.double() / 255).view(H, 1, 1) + b.double().view(H, 1, 1)
+    gy = dy.double().view(H, rows, cols)
+    d = (gy * y).sum(-1, keepdim=True)
+    ref = y * (gy - d)
+    slack = y * 1e-6 * ((gy * y).abs().sum(-1, keepdim=True) + gy.abs())
+    unit = 0.5 * torch.finfo(dtype).eps + 2.0 ** -21
+    least = {torch.float32: 2.0 ** -149, torch.float16: 2.0 ** -24, torch.bfloat16: 2.0 ** -133}[dtype]
+    assert ((dx.double().view(H, rows, cols) - ref).abs() <= unit * ref.abs() + slack + least).all()
