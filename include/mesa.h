@@ -315,9 +315,9 @@ mesa_status mesa_layernorm_bwd_q(const int8_t *xq, int64_t M, int64_t D, int64_t
  * evaluated as  s_g(k) * sum_m dy[m,n]*(q[m,k]+128+c)  +  (beta_g(k) - c*s_g(k)) * db[n]  on the matrix cores
  * (binary16 products for MESA_F16, bfloat16 products for MESA_BF16 and for MESA_F32, whose dy is taken apart, 2^23-fold,
  * into three bfloat16 values that add up to it exactly, subnormal values too; where dy holds values of 2^64 and more,
- * binary32 products; binary32 accumulation; fixed summation order).  c = -128, the signed code, for
- * MESA_F32 and for small matrices (of up to some 20 GFLOP, narrow ones aside).  Others: c = 1024 for MESA_F16, where 1024 + code is the cheapest
- * exact binary16 operand, c = 0 for MESA_BF16: the binary32
+ * binary32 products; binary32 accumulation; fixed summation order).  c = -128, the signed code, for MESA_F32 and for small
+ * matrices (of up to some 20 GFLOP, narrow ones aside) in MESA_F16; c = 0 for MESA_BF16.  Other MESA_F16 matrices: c = 1024,
+ * since 1024 + code is the cheapest exact binary16 operand: the binary32
  * sums then carry a term c*db[n] that cancels in the result, which costs accuracy when dy has a large mean --
  * about 3e-4 of max|dW| at a mean of half a standard deviation over 50000 rows, 1e-5 at mean zero.
  * xq: (M, K) int8, K in G channel groups.  dy: (M, N_out) of dt.  dW: (N_out, K) binary32, row-major,

@@ -6,8 +6,8 @@
 // and centred, so P does not cancel against S0) and the per-column affine map is applied once to
 // the finished sums.
 //
-// (Large and narrow matrices contract another value of the code, see DwElem: 1024 + x_bar in binary16, x_bar = q + 128
-// in bfloat16, c = -1024 and 0 in  dW = s_g (dy^T (x_bar - c)) + (beta_g + c s_g) S0.  binary32 dy: k_dw_cut.)
+// (bfloat16, and large and narrow matrices in binary16, contract another value of the code, see DwElem: x_bar = q + 128 and
+// 1024 + x_bar, c = 0 and -1024 in  dW = s_g (dy^T (x_bar - c)) + (beta_g + c s_g) S0.  binary32 dy: k_dw_cut.)
 //
 // 16-bit path, gfx950.  Both operands are row-major in the contraction index m, which is the
 // layout the MFMA operands do NOT want (a lane holds 8 consecutive contraction values of one
@@ -42,11 +42,18 @@ constexpr int kDwBM = 32;        // contraction rows per LDS stage
 constexpr int kDwXcd = 8;
 constexpr int kDwPF = 3;         // stages prefetched into registers ahead of the one being multiplied
 
+// What a kernel contracts and how it adds (the reasons at DwElem): the code as it is cheapest, in one chain of sums per slice; the
+// signed code; or the code as it is cheapest, in chains of 256 rows that are added up beside them.
+enum DwSums { kDwPlain, kDwSigned, kDwSplit };
+
 // BN x BK tile of dW per workgroup, WGN x WGK waves, each wave (BN/WGN) x (BK/WGK) as 32x32 MFMA tiles
-template <int BN, int BK, int WGN, int WGK, bool SIGNED_> struct DwCfg {
-    static constexpr bool SIGNED = SIGNED_;                               // which value of the code is contracted (DwElem)
+template <int BN, int BK, int WGN, int WGK, DwSums SUMS> struct DwCfg {
+    static constexpr bool SIGNED = SUMS == kDwSigned;                     // which value of the code is contracted (DwElem)
+    static constexpr bool SPLIT = SUMS == kDwSplit;
     static constexpr bool DIRECT = BN * BK <= 128 * 128;                  // one slice: finishes dW itself (large tiles have many, or fill the chip)
-    static constexpr int PF = BN * BK <= 128 * 128 ? 2 * kDwPF : kDwPF;   // small tiles: less per stage, so more stages in flight
+    // small tiles: less per stage, so more stages in flight (split sums leave registers for four)
+    static constexpr int PF = SPLIT ? 4 : BN * BK <= 128 * 128 ? 2 * kDwPF : kDwPF;
+    static constexpr int BODY = SPLIT ? 2 * PF : PF;                      // stages of the loop's body
     static constexpr int NW = WGN * WGK;
     static constexpr int THREADS = NW * 64;
     static constexpr int WN = BN / WGN, WK = BK / WGK;  // wave tile
@@ -114,10 +121,14 @@ __device__ __forceinline__ v4s signed_codes_to_half4(int raw)
 
 // What the operand type decides: how codes become matrix-core operands and which value of the code is
 // contracted (centre: the offset c in "operand = x_bar - c"), the row sums of dy, and the MFMA itself.
-// SIGNED: the signed code, centred.  The small tile takes it: its slices are the longest (one slice of the whole matrix where
-// that is cheapest), and a sum that carries c * S0 loses a bit with every fourfold length; it waits for memory and
-// latency, not for the few instructions (errors against 64 bits at 1604 x (1344 -> 1752): 5e-5 with six slices of
-// 1024 + x_bar, 1e-4 with one slice of them, 1e-6 centred).
+// Small matrices have the longest slices (one slice of the whole matrix where that is cheapest), and a chain of sums loses a bit
+// with every fourfold length.  Their tile waits for memory and latency, not for a few more instructions:
+//  - binary16 takes the signed code (SIGNED).  Errors against 64 bits at 1604 x (1344 -> 1752): 5e-5 with six slices of
+//    1024 + x_bar, 1e-4 with one slice of them, 1e-6 centred, and no larger for inputs of one sign.
+//  - bfloat16 keeps x_bar, which is exactly zero where the input is its smallest value: behind a ReLU or a GELU, where most of it
+//    is, the signed code's sums are numbers of the range's size that cancel (12000 x (768 -> 768), 3 % of the inputs not zero:
+//    9e-8 with x_bar, 6e-6 signed; GELU 1.6e-7 and 7.3e-7).  Its chains end after 256 rows, the shortest slice that these
+//    matrices ever had (2000 x (2048 -> 1024), GELU: 1.1e-7 in slices of 288 rows, 3.1e-7 in one chain per slice, 1.1e-7 so).
 template <typename E> struct DwElem;
 template <> struct DwElem<_Float16> {
     static constexpr float centre(bool is_signed) { return is_signed ? 128.0f : -1024.0f; }
@@ -135,8 +146,8 @@ template <> struct DwElem<_Float16> {
     }
 };
 template <> struct DwElem<__bf16> {
-    static constexpr float centre(bool is_signed) { return is_signed ? 128.0f : 0.0f; }
-    template <bool SIGNED> __device__ static __forceinline__ v4s convert(int raw) { return SIGNED ? signed_codes_to_bf4(raw) : codes_to_bf4(raw); }
+    static constexpr float centre(bool) { return 0.0f; }
+    template <bool SIGNED> __device__ static __forceinline__ v4s convert(int raw) { return codes_to_bf4(raw); }
     __device__ static __forceinline__ float dot_ones(uint32_t pair, float acc)
     {
         return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, pair), __builtin_bit_cast(v2b, 0x3F803F80u), acc, false);
@@ -158,13 +169,13 @@ struct DwDirect {
 
 // P[split][n][k] = sum over the slice's m of dy[m][n] * (x_bar[m][k] - centre)   (x_bar - 128 is the signed code)
 // S0[split][n]   = sum over the slice's m of dy[m][n]
-template <typename E, int BN, int BK, int WGN, int WGK, bool SIGNED_>
-__global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__restrict__ xq, const E *__restrict__ dy,
+template <typename E, int BN, int BK, int WGN, int WGK, DwSums SUMS>
+__global__ __launch_bounds__(WGN * WGK * 64, SUMS == kDwSplit ? 2 : 1) void k_dw_f16(const int8_t *__restrict__ xq, const E *__restrict__ dy,
                                                               int64_t M, int K, int N, int tiles_n, int tiles_k, int splits,
                                                               int64_t rows_per_split, float *__restrict__ P,
                                                               float *__restrict__ S0, DwDirect direct)
 {
-    using C = DwCfg<BN, BK, WGN, WGK, SIGNED_>;
+    using C = DwCfg<BN, BK, WGN, WGK, SUMS>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -200,6 +211,28 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
         for (int j = 0; j < C::TJ; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    v16f sum[C::SPLIT ? C::TI : 1][C::SPLIT ? C::TJ : 1];   // of the chains that are finished
+    auto end_chain = [&]() {
+        if constexpr (C::SPLIT) {
+#pragma unroll
+            for (int i = 0; i < C::TI; ++i)
+#pragma unroll
+                for (int j = 0; j < C::TJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        sum[i][j][v] += acc[i][j][v];
+                        acc[i][j][v] = 0.0f;
+                    }
+        }
+    };
+    if constexpr (C::SPLIT) {
+#pragma unroll
+        for (int i = 0; i < C::TI; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[i][j][v] = 0.0f;
+    }
     float s0[C::TIS];
 #pragma unroll
     for (int i = 0; i < C::TIS; ++i) s0[i] = 0.0f;
@@ -382,13 +415,14 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
         // writes -- a third of all stages then run with no prefetch distance at all -- and copies
         // fragment registers at the latch.)
         int sbase = 0;
-        for (; sbase + C::PF <= nfull; sbase += C::PF) {
+        for (; sbase + C::BODY <= nfull; sbase += C::BODY) {
 #pragma unroll
-            for (int d = 0; d < C::PF; ++d) stage(sbase + d, ring_a[d], ring_b[d]);
+            for (int d = 0; d < C::BODY; ++d) stage(sbase + d, ring_a[d % C::PF], ring_b[d % C::PF]);
+            end_chain();
         }
 #pragma unroll
-        for (int d = 0; d < C::PF - 1; ++d) {
-            if (sbase + d < nfull) stage(sbase + d, ring_a[d], ring_b[d]);
+        for (int d = 0; d < C::BODY - 1; ++d) {
+            if (sbase + d < nfull) stage(sbase + d, ring_a[d % C::PF], ring_b[d % C::PF]);
         }
     }
     // The rows left over when the slice is not a whole number of stages (only the slice that ends
@@ -425,6 +459,14 @@ __global__ __launch_bounds__(WGN * WGK * 64, 1) void k_dw_f16(const int8_t *__re
         }
     }
 
+    if constexpr (C::SPLIT) {
+#pragma unroll
+        for (int i = 0; i < C::TI; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] += sum[i][j][v];
+    }
     // partial sums of this slice: lane l, register v of a 32x32 tile -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
     float *Ps = P + int64_t(split) * N * K;
     const int col_l = lane & 31, row_l = (lane >> 5) * 4;
@@ -857,8 +899,8 @@ __global__ __launch_bounds__(kThreads) void k_dw_reduce_any(const float *__restr
 }
 
 struct DwPlan {
-    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128, 5: 128 x 128 of signed
-                   // codes; 4: binary32, 128 x 128; 2: the plain path
+    int variant;   // 16-bit tiles (n x k): 0: 256 x 256, 1: 256 x 128, 3: 128 x 128, 5: 128 x 128 for small matrices (signed
+                   // codes or split sums); 4: binary32, 128 x 128; 2: the plain path
     int bn, bk, tiles_n, tiles_k, splits, grid;
     int64_t rows_per_split;
     int64_t least;  // the fewest slices that the plan of as many rows, or of more, has
@@ -976,19 +1018,19 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     const FastDiv dper = make_fastdiv(uint32_t(K / G));
     const bool one = p.splits == 1 && p.variant >= 3;    // the others leave their sums to the second kernel
     const DwDirect direct = {alpha, beta, dper, one ? dW : nullptr, db};
-#define MESA_LAUNCH_DW(E, BN_, BK_, SIGNED_) \
+#define MESA_LAUNCH_DW(E, BN_, BK_, SUMS_) \
     do { \
-        using C = DwCfg<BN_, BK_, 2, 2, SIGNED_>; \
-        hipLaunchKernelGGL((k_dw_f16<E, BN_, BK_, 2, 2, SIGNED_>), dim3(p.grid), dim3(C::THREADS), 2 * C::STAGE, s, xq, \
+        using C = DwCfg<BN_, BK_, 2, 2, SUMS_>; \
+        hipLaunchKernelGGL((k_dw_f16<E, BN_, BK_, 2, 2, SUMS_>), dim3(p.grid), dim3(C::THREADS), 2 * C::STAGE, s, xq, \
                            static_cast<const E *>(dy), M, Ki, Ni, p.tiles_n, p.tiles_k, p.splits, p.rows_per_split, P, S0, direct); \
         centre = DwElem<E>::centre(C::SIGNED); \
     } while (0)
 #define MESA_PICK_DW(E) \
     do { \
-        if (p.variant == 0) MESA_LAUNCH_DW(E, 256, 256, false); \
-        else if (p.variant == 1) MESA_LAUNCH_DW(E, 256, 128, false); \
-        else if (p.variant == 3) MESA_LAUNCH_DW(E, 128, 128, false); \
-        else MESA_LAUNCH_DW(E, 128, 128, true); \
+        if (p.variant == 0) MESA_LAUNCH_DW(E, 256, 256, kDwPlain); \
+        else if (p.variant == 1) MESA_LAUNCH_DW(E, 256, 128, kDwPlain); \
+        else if (p.variant == 3) MESA_LAUNCH_DW(E, 128, 128, kDwPlain); \
+        else MESA_LAUNCH_DW(E, 128, 128, (std::is_same<E, _Float16>::value ? kDwSigned : kDwSplit)); \
     } while (0)
     if (p.variant == 2) {   // the plain path contracts with the signed code
 #define MESA_LAUNCH_DW_PLAIN(T) \

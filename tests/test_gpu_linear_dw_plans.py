@@ -48,8 +48,8 @@ def test_linear_dw_tiles_and_slices(M, Mr, K, N, G, dtype):
                                                 (4097, 768, 264, 12, 4097), (129, 128, 120, 2, 129)])
 def test_linear_dw_of_small_matrices_in_the_workspace_there_is(M, Mr, K, N, G, sized_for, dtype):
     """The small tile in a workspace sized for more rows, which holds fewer slices than it would take, in one of a single slice (None)
-    and in its own.  1e-5 of the largest result, the binary32 bound: the codes are centred, every product is exact in
-    binary32 (contracting 1024 + code, as the large binary16 tiles do, misses it)."""
+    and in its own.  1e-5 of the largest result, the binary32 bound: every product is exact in binary32, and the sums are of
+    centred codes or in short chains (contracting 1024 + code, as the large binary16 tiles do, misses it)."""
     g = torch.Generator(device="cuda").manual_seed(Mr + K)
     q = torch.randint(-128, 128, (Mr, K), dtype=torch.int8, device="cuda", generator=g)
     dy = torch.randn((Mr, N), device="cuda", generator=g).to(dtype)
@@ -66,3 +66,22 @@ def test_linear_dw_of_small_matrices_in_the_workspace_there_is(M, Mr, K, N, G, s
     assert (dW - ref).abs().max() <= 1e-5 * ref.abs().max()
     assert (db - dy.double().sum(0)).abs().max() <= 1e-5 * dy.double().abs().sum(0).max()
     assert torch.all(frame[n:] == 0x55)                     # nothing behind the workspace
+
+
+@pytest.mark.parametrize("share", [1.0, 0.03], ids=["half-zero", "sparse"])
+@pytest.mark.parametrize("Mr,K,N", [(394, 192, 768), (505, 1344, 1088), (2000, 2048, 1024), (4096, 768, 768), (12000, 768, 768), (25216, 1536, 384)])
+def test_linear_dw_bfloat16_behind_a_rectifier(M, Mr, K, N, share):
+    """Inputs of one sign, at least half of them zero and thus the smallest code, gradients with a mean.  Bound on the 2-norm, against
+    the definition in binary64: a zero adds nothing, and a sum of terms of one sign is off by some 2^-25 of itself for
+    the 16 roundings of a chain of 256 rows and for each chain and slice, at random: under 2e-7."""
+    g = torch.Generator(device="cuda").manual_seed(Mr + K)
+    x = torch.randn((Mr, K), device="cuda", generator=g).clamp(min=0)
+    x[torch.rand((Mr, K), device="cuda", generator=g) >= share] = 0
+    q = (x / 4 * 255).round().clamp(0, 255).sub(128).to(torch.int8)
+    dy = (torch.randn((Mr, N), device="cuda", generator=g) + 0.5).bfloat16()
+    a, b = torch.full((1,), 4.0, device="cuda"), torch.zeros(1, device="cuda")
+    ws = torch.empty(M.workspace_bytes(M.OP_LINEAR_DW_Q, Mr, K, N, M.BF16), dtype=torch.uint8, device="cuda")
+    dW, db = torch.empty((N, K), device="cuda"), torch.empty(N, device="cuda")
+    M.mesa_linear_dw_q(q, Mr, K, 1, a, b, dy, N, dW, db, ws)
+    ref = dy.double().t().contiguous() @ ((q.double() + 128) * (4.0 / 255))
+    assert (dW - ref).norm() <= 2e-7 * ref.norm()
