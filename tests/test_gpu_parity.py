@@ -403,14 +403,14 @@ def test_attention_matmul_backward_long_sequences(M, B, H, N, Dh, dtype):
 
 @pytest.mark.parametrize("B,H,N,Dh", [(2, 3, 19, 8), (2, 3, 197, 64), (1, 2, 65, 40), (2, 2, 49, 32)])
 def test_attention_matmul_backward_binary32(M, B, H, N, Dh):
-    """The same products on binary32 tensors (one plain kernel), to the binary32 bound."""
+    """The same products on binary32 tensors (the general kernel on three bfloat16 parts), to the binary32 bound."""
     _attention_case(M, B, H, N, Dh, torch.float32)
 
 
-@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16], ids=["f32", "f16", "bf16"])
 @pytest.mark.parametrize("B,H,N,Dh", [(2, 3, 3, 5), (1, 2, 7, 64), (2, 1, 40, 4), (1, 1, 1, 1)])
 def test_attention_matmul_backward_short_extents(M, B, H, N, Dh, dtype):
-    """Sequences or heads shorter than one load vector (the plain kernel, in the 16-bit types too)."""
+    """Sequences or heads shorter than one load vector (the plain kernel, in every type)."""
     _attention_case(M, B, H, N, Dh, dtype)
 
 

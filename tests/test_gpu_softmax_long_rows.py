@@ -80,20 +80,28 @@ def test_softmax_forward_long_rows(M, B, H, rows, cols, dtype):
         assert np.array_equal(npy(a), ra) and np.array_equal(npy(b) + np.float32(0), rb + np.float32(0))
 
 
-def test_softmax_forward_long_rows_in_the_smallest_workspace(M):
-    """One workgroup's worth of extrema less than a resident round: fewer workgroups, the same bits."""
-    B, H, rows, cols = 2, 2, 577, 577
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("cols", [577, 1023])
+def test_softmax_forward_long_rows_in_the_smallest_workspace(M, cols, dtype):
+    """Room for the extrema of fewer workgroups than a resident round -- what the tiled kernel's 768 need is accepted: fewer
+    workgroups that take several tiles each, the same bits."""
+    B, H, rows = 16, 12, 577
     g = torch.Generator(device="cuda").manual_seed(3)
-    s = torch.randn((B, H, rows, cols), device="cuda", generator=g).half()
-    full = ws_for(M, M.OP_SOFTMAX_FWD_Q, B * H * rows, H, cols, torch.float16)
+    s = torch.randn((B, H, rows, cols), device="cuda", generator=g).to(dtype)
+    full = ws_for(M, M.OP_SOFTMAX_FWD_Q, B * H * rows, H, cols, dtype)
+    least = 768 * 2 * H * 4 + 16
+    assert full.numel() >= 1024 * 2 * H * 4 + 16            # a resident round is more than that
     got = []
-    for ws in (full, full[:768 * 2 * H * 4 + 16] if full.numel() > 768 * 2 * H * 4 + 16 else full):
+    for ws in (full, full[:least]):
         a, b = torch.full((H,), 0.1, device="cuda"), torch.zeros(H, device="cuda")
         y, q = torch.empty_like(s), torch.empty(s.numel(), dtype=torch.int8, device="cuda")
         M.mesa_softmax_fwd_q(s, B, H, rows, cols, a, b, 0.9, y, q, ws, M.ROUND_STOCHASTIC, 9, 0)
-        got.append((npy(y), npy(q), npy(a), npy(b)))
+        got.append((y, q, a, b))
     for u, v in zip(*got):
-        assert np.array_equal(u, v)
+        assert torch.equal(u, v)
+    with pytest.raises(M.MesaError) as e:
+        M.mesa_softmax_fwd_q(s, B, H, rows, cols, a, b, 0.9, y, q, full[:least - 16], M.ROUND_STOCHASTIC, 9, 0)
+    assert e.value.status == M.ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
