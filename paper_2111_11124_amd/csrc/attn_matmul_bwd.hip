@@ -138,7 +138,7 @@ template <> struct BmNum<__bf16> {
 // binary32 tensors: 2^23 times a binary32 value is exactly the sum of three bfloat16 values (cut_f32), a code q is exact in
 // bfloat16 and a product of the two in binary32, so three bfloat16 MFMAs add the same exact products as the binary32
 // MFMA, at sixteen times its rate and with one rounding of the sum per sixteen steps instead of per two.  A workgroup that met
-// a value of 2^64 or more, an infinity or a NaN does its tile again with binary32 MFMAs, as the plain kernel does.  The contracted value is the signed code, as in the plain binary32 kernel.  Against that kernel (one element
+// a value of 2^64 or more, or an infinity, does its tile again with binary32 MFMAs, as the plain kernel does.  The contracted value is the signed code, as in the plain binary32 kernel.  Against that kernel (one element
 // per lane and load, straight from memory, a dependent load per two contraction steps) the four products and softmax's
 // backward took 140 -> 45 us at (2, 3, 197, 64), 257 -> 62 at (1, 12, 324, 64) and 312 -> 93 at (32, 6, 197, 64).
 template <> struct BmNum<float> {
@@ -224,14 +224,13 @@ template <> struct BmElem<false, float> {
             for (int q = 0; q < 3; ++q) w[q][k] = __builtin_amdgcn_perm(part[q][1], part[q][0], 0x07060302u);
         }
     }
-    // magnitude bits of the largest element
-    __device__ static __forceinline__ uint32_t most(const raw_t &v)
+    // the largest magnitude, of m or an element
+    __device__ static __forceinline__ float most(float m, const raw_t &v)
     {
-        uint32_t m = 0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint32_t bits = (k < 4 ? v.lo[k] : v.hi[k - 4]) & 0x7FFFFFFFu;
-            m = bits > m ? bits : m;
+        for (int k = 0; k < 4; k += 2) {
+            m = max_magnitude(m, __uint_as_float(v.lo[k]), __uint_as_float(v.lo[k + 1]));
+            m = max_magnitude(m, __uint_as_float(v.hi[k]), __uint_as_float(v.hi[k + 1]));
         }
         return m;
     }
@@ -425,7 +424,7 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
 
     typename OP::Raw pv[kBmParts];
     typename OQ::Raw qv[kBmParts];
-    uint32_t most = 0;
+    float most = 0.0f;
 #pragma unroll
     for (int k = 0; k < kBmParts; ++k) { pv[k] = load_p(group * kBmT, k); qv[k] = load_q(group * kBmT, k); }
     for (int first = 0; first < a.Tn; first += kBmT * RS) {   // the same count for every group: they meet at the barriers
@@ -436,10 +435,8 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
             OP::store(LP, pv[k], r0, t0, a.R, a.Tn, tid + k * kThreads);
             OQ::store(LQ, qv[k], c0, t0, a.Cn, a.Tn, tid + k * kThreads);
             if constexpr (kCut) {
-                uint32_t m;
-                if constexpr (P_CODED) m = OQ::Elem::most(qv[k]);
-                else m = OP::Elem::most(pv[k]);
-                most = m > most ? m : most;
+                if constexpr (P_CODED) most = OQ::Elem::most(most, qv[k]);
+                else most = OP::Elem::most(most, pv[k]);
             }
         }
         __syncthreads();
@@ -461,7 +458,7 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
     }
 
     if constexpr (kCut) {
-        if (most >= kCutMost) *large = 1;
+        if (too_large(most)) *large = 1;
         __syncthreads();
     }
     if constexpr (RS > 1) {
@@ -483,7 +480,10 @@ __global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || R
     }
     if constexpr (kCut) {
         if (*large) {                                     // uniform
-            bmm_plain_sums<P_CODED, float>(a, b, r0 + wr * 32 + (lane & 31), c0 + wc * 32 + (lane & 31), acc, acc1);
+            // the arguments are read again here, so that the ordinary path does not hold the strides to its end (it spilled for them)
+            uint64_t args = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+            asm volatile("" : "+s"(args));
+            bmm_plain_sums<P_CODED, float>(*reinterpret_cast<const BmmArgs *>(args), b, r0 + wr * 32 + (lane & 31), c0 + wc * 32 + (lane & 31), acc, acc1);
         } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) { acc[v] *= kCutDown; acc1[v] *= kCutDown; }

@@ -323,10 +323,10 @@ template <int WIDTH> __device__ __forceinline__ float lanes_sum_dpp(float v)
 // three times, cut and not rounded, so that each difference is exact.  The bfloat16 MFMA takes subnormal operands for
 // zero, and a last part lies up to 23 binades below its value: without the factor values below 2^-103 lost bits (an error of 4e-3
 // at 2^-126), with it every part of every value, subnormal ones among them, is a multiple of 2^-126.  The sums are to be
-// multiplied by kCutDown.  For |x| < 2^64; a kernel that meets a larger value (or an infinity, or a NaN: kCutMost and above
-// as a bit pattern without its sign) has to take binary32 products instead.
+// multiplied by kCutDown.  For |x| < 2^64; a kernel that meets a larger value or an infinity has to take binary32 products
+// instead (a NaN may go either way).
 constexpr float kCutUp = 8388608.0f, kCutDown = 1.0f / 8388608.0f;
-constexpr uint32_t kCutMost = 0x5F800000u;   // 2^64: 2^30 such values times a code, 2^23-fold, stay below 2^127 in a sum
+constexpr float kCutMost = 18446744073709551616.0f;   // 2^64: 2^30 such values times a code, 2^23-fold, stay below 2^127 in a sum
 
 __device__ __forceinline__ void cut_f32(float x, uint32_t &a, uint32_t &b, uint32_t &c)
 {
@@ -336,6 +336,13 @@ __device__ __forceinline__ void cut_f32(float x, uint32_t &a, uint32_t &b, uint3
     b = __float_as_uint(r) & 0xFFFF0000u;
     c = __float_as_uint(r - __uint_as_float(b));
 }
-__device__ __forceinline__ uint32_t magnitude_bits(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+// the largest of m, |a| and |b|; one instruction for two values.  With too_large: a NaN that stayed in m counts as too large
+__device__ __forceinline__ float max_magnitude(float m, float a, float b)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ bool too_large(float m) { return !(m < kCutMost); }
 
 }  // namespace mesa

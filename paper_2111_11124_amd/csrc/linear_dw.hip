@@ -530,8 +530,8 @@ __global__ __launch_bounds__(WGN * WGK * 64, SUMS == kDwSplit ? 2 : 1) void k_dw
 // The matrix cores multiply binary32 at a sixteenth of their bfloat16 rate, and 2^23 times a binary32 value is exactly the sum
 // of three bfloat16 values that are no subnormals (cut_f32).  The codes are exact in bfloat16, a product of two bfloat16 values
 // is exact in binary32, so three bfloat16 MFMAs against the three parts add the same exact products as one binary32
-// MFMA, sixteen contraction steps per rounding of the sum instead of two.  A workgroup that met a value of 2^64 or more, an
-// infinity or a NaN does its slice again with binary32 MFMAs, operands straight from memory.
+// MFMA, sixteen contraction steps per rounding of the sum instead of two.  A workgroup that met a value of 2^64 or more, or an
+// infinity, does its slice again with binary32 MFMAs, operands straight from memory.
 //
 // The parts are cut as the tile goes to LDS: three planes of bfloat16 in the tensor's own orientation, read back by the
 // transposing reads like the 16-bit kernel's.  128 x 128 tile of dW per workgroup, four waves of 64 x 64 (64 accumulator
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(WGN * WGK * 64, SUMS == kDwSplit ? 2 : 1) void k_dw
 // Whole call, one-element-at-a-time binary32 MFMA kernel -> this one: 394 x (192 -> 768) 101 -> 17 us (latency of its
 // two stages and of the two launches), 2494 x (2880 -> 1392) 786 -> 92 us (217 TFLOP/s; a third of the bfloat16 rate is the
 // ceiling), 25216 x (384 -> 1536) 1354 -> 120 us.  Error against 64 bits as before or smaller at every magnitude (70 to 4099 rows:
-// 2e-7 to 7e-7 -> 1e-7); the factor and the search for large values cost 0.1 us to 1 %.
+// 2e-7 to 7e-7 -> 1e-7); the factor and the search for large values cost 0.1 us or half a percent.
 struct DsCfg {
     static constexpr int BN = 128, BK = 128;
     static constexpr int PA = BN * 2 + 64, PB = BK + 32;   // LDS row pitches (bytes) of a plane of dy and of the codes
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
         vb = *reinterpret_cast<const u32x4 *>(xq + (r < m_end ? r : m_end - 1) * K + col_b);
     };
     float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);     // this thread's share of the row sums of its four columns of dy
-    uint32_t most = 0;                                    // magnitude bits
+    float most = 0.0f;                                    // magnitude of the largest value
     auto store_stage = [&](int64_t m, unsigned char *st) {
 #pragma unroll
         for (int i = 0; i < C::A_VECS; ++i) {
@@ -600,11 +600,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
             const float x[4] = {v.x, v.y, v.z, v.w};
             uint32_t p[3][4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                cut_f32(x[j], p[0][j], p[1][j], p[2][j]);
-                const uint32_t bits = magnitude_bits(x[j]);
-                most = bits > most ? bits : most;
-            }
+            for (int j = 0; j < 4; ++j) cut_f32(x[j], p[0][j], p[1][j], p[2][j]);
+            most = max_magnitude(max_magnitude(most, v.x, v.y), v.z, v.w);
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 const u32x2 w = {__builtin_amdgcn_perm(p[q][1], p[q][0], 0x07060302u), __builtin_amdgcn_perm(p[q][3], p[q][2], 0x07060302u)};
@@ -664,7 +661,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
         }
     }
 
-    if (most >= kCutMost) large = 1;
+    if (too_large(most)) large = 1;
     __syncthreads();                                      // (and the last stage's fragments have been read)
     const int col_l = lane & 31, row_l = (lane >> 5) * 4;
     float down = kCutDown;

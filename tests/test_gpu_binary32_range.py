@@ -71,3 +71,21 @@ def test_attention_products_over_the_range_of_binary32(M, N, Dh):
     for got, ref in ((dA, dO @ hat[1].transpose(-1, -2).contiguous()), (dV, hat[0].transpose(-1, -2).contiguous() @ dO),
                      (dQ, 0.125 * dS @ hat[3]), (dK, 0.125 * dS.transpose(-1, -2).contiguous() @ hat[2])):
         _check(got.cpu(), ref, 1, 2 + N // 64)
+
+
+@pytest.mark.parametrize("at_nan,at_large", [(0, 1), (1, 0), (0, 2), (3, 1), (2, 3), (5, 4)])
+def test_linear_dw_with_a_nan_beside_a_large_value(M, at_nan, at_large):
+    """Both in one row of dy, in one thread's vector: the NaN stays in its row of dW and hides the large value from nobody."""
+    Mr, K, N = 70, 48, 20
+    g = torch.Generator(device="cuda").manual_seed(8 * at_nan + at_large)
+    q = torch.randint(-128, 128, (Mr, K), dtype=torch.int8, device="cuda", generator=g)
+    dy = torch.randn((Mr, N), device="cuda", generator=g)
+    dy[33, at_nan], dy[33, at_large] = float("nan"), 1e33
+    a, b = torch.full((1,), 0.7, device="cuda"), torch.full((1,), -0.2, device="cuda")
+    ws = torch.empty(M.workspace_bytes(M.OP_LINEAR_DW_Q, Mr, K, N, M.F32), dtype=torch.uint8, device="cuda")
+    dW, db = torch.empty((N, K), device="cuda"), torch.empty(N, device="cuda")
+    M.mesa_linear_dw_q(q, Mr, K, 1, a, b, dy, N, dW, db, ws)
+    ref = dy.double().t().contiguous() @ ((q.double() + 128) * (a.double() / 255) + b.double())
+    assert torch.isnan(dW[at_nan]).all() and torch.isnan(db[at_nan])
+    rest = torch.arange(N, device="cuda") != at_nan
+    assert ((dW - ref)[rest].abs().amax(1) <= 1e-5 * ref[rest].abs().amax(1)).all()
