@@ -538,11 +538,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_softmax_bwd_wave(const int8_t *
 #pragma unroll
     for (int u = 0; u < NV; ++u)
         if (u * LPR + lr < nvec) {
-            float g[8], y[8];
+            float g[8], y[8], dv = 0.0f;                  // a vector's own sum: one chain of all would be up to 64 long
             Store<T>::unpack(raw[u], g);
             codes_to_float(rawq[u], y);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) d = fmaf(g[j], fmaf(y[j], s, b), d);
+            for (int j = 0; j < 8; ++j) dv = fmaf(g[j], fmaf(y[j], s, b), dv);
+            d += dv;
         }
     d = lanes_sum_dpp<LPR>(d);
     // the unpacked values are rebuilt from the packed ones: holding them would halve the waves in flight

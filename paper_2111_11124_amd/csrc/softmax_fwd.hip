@@ -472,6 +472,7 @@ __global__ __launch_bounds__(kThreads, (sf_long_waves(Store<T>::kBytes, EPL))) v
     constexpr int RPP = 64 / LPR;                        // rows a wave takes per pass
     constexpr int FULL = sl_full(EPL);                   // slots that every row fills
     constexpr int kAhead = 4;                            // vectors a thread requests one tile ahead
+    constexpr int kSums = kB == 4 ? 4 : 1;               // chains of a lane's sum: one would show in a binary32 result
     constexpr bool kFma = std::is_same<T, _Float16>::value;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t heads = div_heads.d;
@@ -548,13 +549,13 @@ __global__ __launch_bounds__(kThreads, (sf_long_waves(Store<T>::kBytes, EPL))) v
             // binary16: one fused operation -- the rounding of m * log2(e) is a factor common to the row.  The wider types'
             // lowest values, as masks use them, would overflow there: a row of nothing else has to come out even.
             const float ml = m * 1.4426950408889634f;
-            float sum = 0.0f;
+            float chain[kSums] = {};                          // 0 in unused slots
 #pragma unroll
             for (int k = 0; k < EPL; ++k) {
                 x[k] = __builtin_amdgcn_exp2f(kFma ? __builtin_fmaf(x[k], 1.4426950408889634f, -ml) : (x[k] - m) * 1.4426950408889634f);
-                sum += x[k];                             // 0 in unused slots
+                chain[k % kSums] += x[k];
             }
-            sum = lanes_sum_dpp<LPR>(sum);
+            const float sum = lanes_sum_dpp<LPR>(kSums == 4 ? (chain[0] + chain[1]) + (chain[2 % kSums] + chain[3 % kSums]) : chain[0]);
             const float inv = 1.0f / sum;
             if (live) {
                 const uint32_t slab = fastdiv(uint32_t(row0) + r, div_rows);

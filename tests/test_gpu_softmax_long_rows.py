@@ -129,3 +129,22 @@ def test_softmax_backward_long_rows_near_the_smallest_value(M, cols, dtype):
     unit = 0.5 * torch.finfo(dtype).eps + 2.0 ** -21
     least = {torch.float32: 2.0 ** -149, torch.float16: 2.0 ** -24, torch.bfloat16: 2.0 ** -133}[dtype]
     assert ((dx.double().view(H, rows, cols) - ref).abs() <= unit * ref.abs() + slack + least).all()
+
+
+@pytest.mark.parametrize("cols", [384, 512])
+def test_softmax_backward_long_rows_sums_a_row_in_short_chains(M, cols):
+    """binary32, even rows, a gradient of 100 with noise of 1: what is left of dy - d is 100 times smaller than the terms that d is the
+    sum of.  A sum of all in a balanced tree is off by 3.1e-6 (2^-17 sqrt(1/12) for the last addition, half a square less for
+    each level before); vectors of eight and four of them to a lane before the tree: under 3.9e-6, one chain of all: above."""
+    H, rows = 4, 2048
+    n = H * rows * cols
+    g = torch.Generator(device="cuda").manual_seed(1)
+    y = torch.softmax(torch.randn((H, rows, cols), device="cuda", generator=g).double(), -1)
+    a, b = y.amax((1, 2)).float(), torch.zeros(H, device="cuda")
+    q = (y / a.double().view(H, 1, 1) * 255).round().clamp(0, 255).sub(128).to(torch.int8).contiguous()
+    dy = torch.randn(n, device="cuda", generator=g) + 100
+    dx = torch.empty(n, device="cuda")
+    M.mesa_softmax_bwd_q(q, 1, H, rows, cols, a, b, dy, dx)
+    yh, gy = (q.double() + 128) * (a.double() / 255).view(H, 1, 1), dy.double().view(H, rows, cols)
+    ref = yh * (gy - (gy * yh).sum(-1, keepdim=True))
+    assert (dx.double().view(H, rows, cols) - ref).norm() <= 3.9e-6 * ref.norm()
