@@ -1,4 +1,4 @@
-"""ctypes binding of libmesa.so: argument marshalling only.
+"""Binding of libmesa.so: argument marshalling only.
 
 Every function below has the name and the argument order of the C entry point it calls
 (include/mesa.h); tensors are torch tensors on the GPU, whose data pointers and current stream are
