@@ -34,6 +34,11 @@ constexpr int kU = 2;                            // vectors per thread and itera
 constexpr int kGridCap = 1 << 20;                // one chunk per workgroup up to 2^32 elements: the workgroups in flight then sweep the tensor as one compact window (a grid-stride loop has them at 2^12-element pieces spread over the whole tensor, measured 15 % slower at 2^31 elements)
 constexpr int kMmU = 4;                          // the same two numbers for the min/max scan
 constexpr int kMmGridCap = 1024;
+// Up to 2^24 elements the scan's threads hold two vectors as well: twice the workgroups (as many as the single-pass kernel has, for
+// which the workspace is sized), and half the vectors to hand to LDS at the end.  Whole call, four -> two vectors: (394, 3, 256)
+// in binary32 6.2 -> 5.5 us, (4096, 3, 64) 5.7 -> 5.4, (6304, 6, 64) in binary32 7.8 -> 7.4, (25216, 6, 64) 9.2 -> 9.0; beyond,
+// (50432, 12, 64) 17.2 -> 19.0, (25216, 6, 256) 16.7 -> 17.4.
+constexpr int64_t kMmSmall = int64_t(1) << 24;
 constexpr int kMmFew = 8;                        // groups for which a thread can hold every group's extrema
 constexpr int kFuU = 2;                          // and for the single-pass quantize + min/max
 constexpr int kFuGridCap = 2048;
@@ -124,7 +129,7 @@ template <> struct MinMax<float> {
         float f[8];
         Store<float>::unpack(v, f);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { mn = vmin(mn, f[j]); mx = vmax(mx, f[j]); }
+        for (int j = 0; j < 8; j += 2) { mn = vmin3(mn, f[j], f[j + 1]); mx = vmax3(mx, f[j], f[j + 1]); }
     }
     __device__ __forceinline__ void add1(float f) { mn = vmin(mn, f); mx = vmax(mx, f); }
     __device__ __forceinline__ void merge(const MinMax<float> &o) { mn = vmin(mn, o.mn); mx = vmax(mx, o.mx); }
@@ -141,7 +146,7 @@ template <> struct MinMax<__bf16> {
         float f[8];
         Store<__bf16>::unpack(v, f);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { mn = vmin(mn, f[j]); mx = vmax(mx, f[j]); }
+        for (int j = 0; j < 8; j += 2) { mn = vmin3(mn, f[j], f[j + 1]); mx = vmax3(mx, f[j], f[j + 1]); }
     }
     __device__ __forceinline__ void add1(float f) { mn = vmin(mn, f); mx = vmax(mx, f); }
     __device__ __forceinline__ void merge(const MinMax<__bf16> &o) { mn = vmin(mn, o.mn); mx = vmax(mx, o.mx); }
@@ -174,6 +179,44 @@ template <> struct MinMax<_Float16> {
     __device__ __forceinline__ float lo() const { h2 p = as_h2(mn); return vmin(float(p.x), float(p.y)); }
     __device__ __forceinline__ float hi() const { h2 p = as_h2(mx); return vmax(float(p.x), float(p.y)); }
 };
+
+// The tables of a kernel's extrema in LDS, an ordered key per group.  Lanes of one wave that hold extrema of several groups meet at the
+// same few words, and same-address atomics are served one after the other (some 32 clocks each): with few groups the tables come four
+// times, a lane takes its quarter, and they are folded as they leave.  Sixteen tables measured the same.  Whole
+// call of the two-launch update with one table -> four: (25216, 6, 256) 19.8 -> 16.7 us, (128, 6, 38809) 17.6 -> 15.7,
+// (394, 3, 256) in binary32 6.8 -> 6.2, single-pass GELU forward (2000, 12, 256) 15.5 -> 13.9; within 0.1 us at 600 to 10^5 elements.
+__host__ __device__ __forceinline__ uint32_t extrema_tables(uint32_t groups) { return groups <= 256 ? 4u : 1u; }
+
+__device__ __forceinline__ void clear_tables(int *lmn, int *lmx, uint32_t words)
+{
+    for (uint32_t k = threadIdx.x; k < words; k += kThreads) {
+        lmn[k] = order_key(__builtin_inff());
+        lmx[k] = order_key(-__builtin_inff());
+    }
+}
+__device__ __forceinline__ int quad_min(int v, bool whole)   // of four neighbouring lanes, or the lane's own
+{
+    if (whole) {
+        int w = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+        v = w < v ? w : v;
+        w = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);       // quad_perm [2,3,0,1]
+        v = w < v ? w : v;
+    }
+    return v;
+}
+// the tables, complete behind a barrier, to this workgroup's row of the partial extrema: minima, then maxima
+__device__ __forceinline__ void store_tables(const int *lmn, const int *lmx, uint32_t groups, uint32_t tables, float *__restrict__ part)
+{
+    float *out = part + int64_t(blockIdx.x) * 2 * groups;
+    for (uint32_t k = threadIdx.x; k < groups * tables; k += kThreads) {   // a group's four words in neighbouring lanes: k's last quad is whole
+        const uint32_t g = tables == 4u ? k >> 2 : k, t = tables == 4u ? k & 3u : 0u;
+        const int lo = quad_min(lmn[t * groups + g], tables == 4u), hi = ~quad_min(~lmx[t * groups + g], tables == 4u);
+        if (t == 0) {
+            out[g] = order_val(lo);
+            out[groups + g] = order_val(hi);
+        }
+    }
+}
 
 __device__ __forceinline__ void flush_lane(int *lmn, int *lmx, uint32_t g, float lo, float hi)
 {
@@ -226,10 +269,10 @@ __device__ __forceinline__ void minmax_element(MinMaxState<T> &st, uint32_t g, f
 // End of a kernel that tracked extrema: what the threads still hold goes to the LDS tables, and the
 // tables become this workgroup's partials.  The U accumulators that sit in the same group are folded
 // first, and a wave whose lanes all sit in one group (head-wise tensors) combines in registers
-// before touching LDS.
+// before touching LDS.  (lmn, lmx: the lane's tables; all_mn, all_mx: the first of them)
 template <typename T, int U>
-__device__ __forceinline__ void minmax_finish(MinMaxState<T> (&st)[U], int *lmn, int *lmx, float *__restrict__ part,
-                                              const GroupGeom &gg)
+__device__ __forceinline__ void minmax_finish(MinMaxState<T> (&st)[U], int *lmn, int *lmx, const int *all_mn, const int *all_mx,
+                                              uint32_t groups, uint32_t tables, float *__restrict__ part)
 {
     float lo = st[0].acc.lo(), hi = st[0].acc.hi();
 #pragma unroll
@@ -253,27 +296,23 @@ __device__ __forceinline__ void minmax_finish(MinMaxState<T> (&st)[U], int *lmn,
         flush_lane(lmn, lmx, st[0].cur, lo, hi);
     }
     __syncthreads();
-    float *out = part + int64_t(blockIdx.x) * 2 * gg.groups;
-    for (uint32_t g = threadIdx.x; g < gg.groups; g += kThreads) {
-        out[g] = order_val(lmn[g]);
-        out[gg.groups + g] = order_val(lmx[g]);
-    }
+    store_tables(all_mn, all_mx, groups, tables, part);
 }
 
 // Partial extrema of each workgroup: part[wg][0..G) = min, part[wg][G..2G) = max.  (Letting the last
-// workgroup to finish do the final step in the same launch was tried and dropped: the device-scope
-// fence it needs flushes the per-XCD L2 once per workgroup, which costs far more than a second launch.)
+// workgroup to finish do the final step in the same launch was tried and dropped, twice: the device-scope
+// fence it needs flushes the per-XCD L2 once per workgroup, and without a fence, every partial and a flag per workgroup
+// written and read as device-scope atomics, the last workgroup's polls and loads across the XCDs take 1 us longer than the second
+// launch at a dozen workgroups and 10 us at a thousand.  Requesting the next chunk before this one is worked on: 2 to 8 % slower.)
 template <typename T, int U>
 __global__ __launch_bounds__(kThreads) void k_minmax_partial(const void *__restrict__ x, int64_t numel, GroupGeom gg,
                                                              float *__restrict__ part)
 {
     extern __shared__ int lds_mm[];
-    int *lmn = lds_mm;
-    int *lmx = lds_mm + gg.groups;
-    for (uint32_t g = threadIdx.x; g < gg.groups; g += kThreads) {
-        lmn[g] = order_key(__builtin_inff());
-        lmx[g] = order_key(-__builtin_inff());
-    }
+    const uint32_t tables = extrema_tables(gg.groups), own = (threadIdx.x & (tables - 1)) * gg.groups;
+    int *all_mn = lds_mm, *all_mx = lds_mm + tables * gg.groups;
+    int *lmn = all_mn + own, *lmx = all_mx + own;
+    clear_tables(all_mn, all_mx, tables * gg.groups);
     __syncthreads();
 
     Cursor c[U];
@@ -325,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial(const void *__restr
     int64_t base = int64_t(blockIdx.x) * kChunk;
     for (; base + kChunk <= numel; base += stride) chunk(base, std::false_type());
     if (base < numel) chunk(base, std::true_type());   // the chunk that holds the end of the tensor
-    minmax_finish<T, U>(st, lmn, lmx, part, gg);
+    minmax_finish<T, U>(st, lmn, lmx, all_mn, all_mx, gg.groups, tables, part);
 }
 
 // Few groups (at most GMAX) whose slabs are short and of awkward length -- a 49 x 49 window's attention
@@ -339,10 +378,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial_few(const void *__r
     extern __shared__ int lds_mm[];
     int *lmn = lds_mm;
     int *lmx = lds_mm + gg.groups;
-    for (uint32_t g = threadIdx.x; g < gg.groups; g += kThreads) {
-        lmn[g] = order_key(__builtin_inff());
-        lmx[g] = order_key(-__builtin_inff());
-    }
+    clear_tables(lmn, lmx, gg.groups);
     __syncthreads();
 
     Cursor c[U];
@@ -419,11 +455,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial_few(const void *__r
         }
     }
     __syncthreads();
-    float *out = part + int64_t(blockIdx.x) * 2 * gg.groups;
-    for (uint32_t g = threadIdx.x; g < gg.groups; g += kThreads) {
-        out[g] = order_val(lmn[g]);
-        out[gg.groups + g] = order_val(lmx[g]);
-    }
+    store_tables(lmn, lmx, gg.groups, 1u, part);
 }
 
 // Eq. (6)-(7) for one group from its extrema: each product, difference and sum rounded on its own.
@@ -487,9 +519,29 @@ __global__ __launch_bounds__(kThreads) void k_ema_finalize(const float *__restri
     const uint32_t g = blockIdx.x;
     const float alpha_old = alpha[g], beta_old = variant == kEmaScaleOnly ? 0.0f : beta[g];   // in flight together with the partial extrema
     float mn = __builtin_inff(), mx = -__builtin_inff();
-    for (int w = threadIdx.x; w < nwg; w += kThreads) {
-        mn = vmin(mn, part[int64_t(w) * 2 * groups + g]);
-        mx = vmax(mx, part[int64_t(w) * 2 * groups + groups + g]);
+    if (nwg <= kThreads) {                         // uniform
+        if (int(threadIdx.x) < nwg) {
+            const float *row = part + int64_t(threadIdx.x) * 2 * groups + g;
+            mn = row[0];
+            mx = row[groups];
+        }
+    } else {
+        // eight rows per thread requested together (a row behind the last one: the last one again): 0.2 to 0.5 us of the launch
+        for (int w0 = threadIdx.x; w0 < nwg; w0 += 8 * kThreads) {
+            float lo[8], hi[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int w = w0 + k * kThreads;
+                const float *row = part + int64_t(w < nwg ? w : nwg - 1) * 2 * groups + g;
+                lo[k] = row[0];
+                hi[k] = row[groups];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                mn = vmin(mn, lo[k]);
+                mx = vmax(mx, hi[k]);
+            }
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -510,6 +562,9 @@ __global__ __launch_bounds__(kThreads) void k_ema_finalize(const float *__restri
 // vectors, the elements of the first and last one that belong to a neighbour are left out.
 // One workgroup per group (small tensors): it updates the estimates itself -- a second, dependent launch costs as much as
 // the whole scan there.  Else partial extrema, as k_minmax_partial leaves them.
+// A workgroup alone on its CU: what 1024 threads issue for 32768 elements was longer than the memory's latency, and there were four
+// of those in turn.  Packed or three-operand comparisons where slabs are whole vectors, and all loads at once: (512, 3, 64) 5.5 ->
+// 3.9 us, (16, 512, 49) 5.1 -> 4.1, (8, 768, 4096) 17.8 -> 11.5, (64, 6, 1225) in binary32 8.2 -> 7.2.
 constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmallElems = 32768;        // of a group, at most
 
@@ -522,32 +577,42 @@ __global__ __launch_bounds__(kSmallThreads) void k_minmax_by_group(const void *_
     __shared__ float smn[kSmallThreads / 64], smx[kSmallThreads / 64];
     constexpr int U = 4;
     const uint32_t g = blockIdx.x, total = outer * vps;
-    const float alpha_old = alpha[g], beta_old = variant == kEmaScaleOnly ? 0.0f : beta[g];
+    const float alpha_old = alpha[g], beta_old = (variant == kEmaScaleOnly ? alpha : beta)[g];
+    MinMax<T> acc;
+    acc.init();
     float mn = __builtin_inff(), mx = -__builtin_inff();
+    // Four vectors per thread are requested together, without a test: one behind the last is the last one again, and the one that the
+    // tensor ends in, if it is no whole one, is the tensor's first.  (A load per branch waits for the one before it.)
+    const int64_t whole_end = numel & ~int64_t(7);
     for (uint32_t v0 = blockIdx.y * (U * kSmallThreads) + threadIdx.x; v0 < total; v0 += gridDim.y * (U * kSmallThreads)) {
         typename Store<T>::raw_t raw[U];
         int64_t start[U], at[U];                   // of the slab, of the vector
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t v = v0 + u * kSmallThreads;
-            const uint32_t o = v < total ? fastdiv(v, div_vps) : 0u;
+            const uint32_t v = v0 + u * kSmallThreads < total ? v0 + u * kSmallThreads : total - 1;
+            const uint32_t o = fastdiv(v, div_vps);
             start[u] = (int64_t(o) * groups + g) * inner;
-            at[u] = v < total ? (start[u] & ~int64_t(7)) + int64_t(v - o * vps) * kVec : start[u] + inner;
-            if (at[u] < start[u] + inner && at[u] + kVec <= numel) raw[u] = Store<T>::load(x, at[u]);
+            at[u] = (start[u] & ~int64_t(7)) + int64_t(v - o * vps) * kVec;
+        }
+        if (whole_end > 0) {                       // uniform
+#pragma unroll
+            for (int u = 0; u < U; ++u) raw[u] = Store<T>::load(x, at[u] < whole_end ? at[u] : 0);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (v0 + u * kSmallThreads >= total) continue;
             const int64_t end = start[u] + inner;
-            if (at[u] >= end) continue;
-            if (at[u] + kVec <= numel) {
+            if (inner % kVec == 0) {               // uniform
+                acc.add(raw[u]);
+            } else if (at[u] < whole_end) {        // elements of a neighbour are left out
                 float f[8];
                 Store<T>::unpack(raw[u], f);
-                const bool whole = at[u] >= start[u] && at[u] + kVec <= end;
+                const int lo = at[u] < start[u] ? int(start[u] - at[u]) : 0, hi = end - at[u] < 8 ? int(end - at[u]) : 8;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const bool in = whole || (at[u] + j >= start[u] && at[u] + j < end);
-                    mn = vmin(mn, in ? f[j] : __builtin_inff());
-                    mx = vmax(mx, in ? f[j] : -__builtin_inff());
+                for (int j = 0; j < 8; j += 2) {
+                    const bool in0 = j >= lo && j < hi, in1 = j + 1 >= lo && j + 1 < hi;
+                    mn = vmin3(mn, in0 ? f[j] : __builtin_inff(), in1 ? f[j + 1] : __builtin_inff());
+                    mx = vmax3(mx, in0 ? f[j] : -__builtin_inff(), in1 ? f[j + 1] : -__builtin_inff());
                 }
             } else {                               // the vector that the tensor ends in
                 for (int64_t e = at[u] > start[u] ? at[u] : start[u]; e < end; ++e) {
@@ -558,6 +623,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_minmax_by_group(const void *_
             }
         }
     }
+    mn = vmin(mn, acc.lo());
+    mx = vmax(mx, acc.hi());
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         mn = vmin(mn, __shfl_xor(mn, off, 64));
@@ -571,8 +638,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_minmax_by_group(const void *_
         if (part) {
             part[int64_t(blockIdx.y) * 2 * groups + g] = mn;
             part[int64_t(blockIdx.y) * 2 * groups + groups + g] = mx;
-        } else
-        ema_store(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call, variant, beta_fixed);
+        } else {
+            ema_store(mn, mx, alpha_old, beta_old, alpha, beta, g, lambda, first_call, variant, beta_fixed);
+        }
     }
 }
 
@@ -668,12 +736,10 @@ __global__ __launch_bounds__(kThreads) void k_quantize_minmax(const void *__rest
                                                               float *__restrict__ part, void *__restrict__ y = nullptr)
 {
     extern __shared__ float2 lds_tab[];
-    int *lmn = reinterpret_cast<int *>(lds_tab + gg.groups);
-    int *lmx = lmn + gg.groups;
-    for (uint32_t g = threadIdx.x; g < gg.groups; g += kThreads) {
-        lmn[g] = order_key(__builtin_inff());
-        lmx[g] = order_key(-__builtin_inff());
-    }
+    const uint32_t tables = extrema_tables(gg.groups), own = (threadIdx.x & (tables - 1)) * gg.groups;
+    int *all_mn = reinterpret_cast<int *>(lds_tab + gg.groups), *all_mx = all_mn + tables * gg.groups;
+    int *lmn = all_mn + own, *lmx = all_mx + own;
+    clear_tables(all_mn, all_mx, tables * gg.groups);
     fill_table<Scale::Quant>(lds_tab, alpha, beta, gg.groups);   // ends with a barrier
 
     Cursor c[U];
@@ -751,7 +817,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_minmax(const void *__rest
     int64_t base = int64_t(blockIdx.x) * kChunk;
     for (; base + kChunk <= numel; base += stride) chunk(base, std::false_type());
     if (base < numel) chunk(base, std::true_type());
-    minmax_finish<T, U>(st, lmn, lmx, part, gg);
+    minmax_finish<T, U>(st, lmn, lmx, all_mn, all_mx, gg.groups, tables, part);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1069,19 +1135,19 @@ static int64_t slab_vectors(int64_t inner) { return inner / kVec + (inner % kVec
 
 // Which way the extrema are found: by position, or by group with one workgroup per group (and one launch) or several.
 //
-// One workgroup per group, up to 32768 elements of it: (394, 3, 64) 5.4 us by position, 5.1 by group; (64, 8, 441) 21 and 5.6;
-// (16, 512, 49) 14.4 and 5.0; (8, 768, 4096) 29 and 18.  It loses where its 1024 threads have next to nothing to do -- five
-// hundred workgroups run at once, 8192 take 45 us whatever they hold: (1, 8192, 64) 20 and 46, (1, 4096, 100) 15 and 24,
-// (16, 4096, 128) 21 and 25, hence the elements per group from 512 groups on -- and where a slab is shorter than the vectors that
-// cover it, at a distance from the next: (32768, 768, 1) 64 and 162, (32768, 16, 1) 12 and 47, (4096, 768, 8) 21 and 60,
-// (2048, 384, 7) in binary32 22 and 26, against (394, 384, 1) 13 and 6.7, (512, 1024, 31) 56 and 20, (1024, 16, 20) 9.1 and 5.7.
+// One workgroup per group, up to 32768 elements of it: (394, 3, 64) 5.0 us by position, 3.7 by group; (64, 8, 441) 21 and 5.1;
+// (16, 512, 49) 10.1 and 4.0; (8, 768, 4096) 28 and 11.  It loses where its 1024 threads have next to nothing to do -- five
+// hundred workgroups run at once, 8192 take 27 us whatever they hold: (1, 8192, 64) 18 and 27, in binary32 (2048, 384, 7) 20 and 23 --,
+// hence the elements per group from 512 groups on, and where a slab is shorter than the vectors that
+// cover it, at a distance from the next: (32768, 768, 1) 63 and 261, (32768, 16, 1) 9 and 42, (4096, 768, 8) 20 and 61,
+// against (394, 384, 1) 9.6 and 5.4, (512, 1024, 31) 58 and 18, (1024, 16, 20) 7.1 and 6.1.
 //
 // Several, for slabs of 64 to 2047 elements that are no whole vectors, whose lanes the scan by position sends to another
-// group at nearly every step: (725, 8, 341) 16.9 and 8.1, (1919, 32, 441) 36 and 24, (50000, 3, 341) 56 and 35.  Shorter slabs waste
-// the vectors at their ends ((100000, 12, 20): 21 and 35), longer ones keep a lane's group as it is ((8192, 3, 2401): 29 and
-// 37).  Beyond four million elements it takes slabs that are not even multiples of four elements, or a tensor that is large
-// enough: (11184, 2, 1500) 16 and 25, (82241, 3, 68) 16 and 21, (15420, 8, 68) in binary32 12 and 16.  Over 2300 shapes in both types,
-// of one to 8192 groups, none is slower than by position by more than the runs of one side differ (7 %).
+// group at nearly every step: (725, 8, 341) 16.7 and 7.7, (1919, 32, 441) 29 and 17, (50000, 3, 341) 55 and 25.  Shorter slabs waste
+// the vectors at their ends ((100000, 12, 20): 22 and 35), longer ones keep a lane's group as it is.
+// Beyond four million elements it takes slabs that are not even multiples of four elements, or a tensor that is large
+// enough: (11184, 2, 1500) 17.7 and 18.5, (82241, 3, 68) 14.9 and 16.3, (15420, 8, 68) in binary32 14.4 and 17.6.  The lines were
+// fitted to 2300 shapes in both types, of one to 8192 groups; both scans have become faster since, the one by group by more.
 enum MinmaxScan { kByPosition, kByGroup, kByGroupInPieces };
 
 static MinmaxScan minmax_scan(int64_t outer, int64_t groups, int64_t inner)
@@ -1112,7 +1178,10 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
     if (numel == 0) return MESA_OK;
     if (!x || !alpha || !aligned16(x) || !aligned4(alpha)) return MESA_ERR_INVALID_ARG;
     if (variant != kEmaScaleOnly && (!beta || !aligned4(beta))) return MESA_ERR_INVALID_ARG;
-    const int grid = minmax_grid(L, kMmU, kMmGridCap, max_wgs);
+    int grid = minmax_grid(L, kMmU, kMmGridCap, max_wgs);
+    const bool few = minmax_few_groups(L, grid, kMmU);
+    const int unroll = !few && numel <= kMmSmall ? kFuU : kMmU;
+    if (unroll != kMmU) grid = minmax_grid(L, unroll, kFuGridCap, max_wgs);
     const size_t need = max_wgs > 0 ? size_t(grid) * 2 * size_t(L.groups) * sizeof(float) : update_ws_bytes(L.outer, L.groups, L.inner);
     if (!ws || !aligned16(ws) || ws_bytes < need) return MESA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1138,10 +1207,10 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
                                lambda, first_call, variant, beta_fixed);
         return launch_status();
     }
-    GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * kMmU * kVec);
-    const size_t lds = size_t(2) * gg.groups * sizeof(int);
+    GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * unroll * kVec);
+    const size_t lds = size_t(2) * gg.groups * (few ? 1 : extrema_tables(gg.groups)) * sizeof(int);
     float *part = static_cast<float *>(ws);
-    if (minmax_few_groups(L, grid, kMmU)) {
+    if (few) {
 #define MESA_LAUNCH_FEW(T, GM) \
     hipLaunchKernelGGL((k_minmax_partial_few<T, kMmU, GM>), dim3(grid), dim3(kThreads), lds, s, x, numel, gg, part)
 #define MESA_LAUNCH_FEW_T(T) \
@@ -1156,7 +1225,11 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
 #undef MESA_LAUNCH_FEW_T
 #undef MESA_LAUNCH_FEW
     } else {
-#define MESA_LAUNCH_MM(T) hipLaunchKernelGGL((k_minmax_partial<T, kMmU>), dim3(grid), dim3(kThreads), lds, s, x, numel, gg, part)
+#define MESA_LAUNCH_MM(T) \
+    do { \
+        if (unroll == kMmU) hipLaunchKernelGGL((k_minmax_partial<T, kMmU>), dim3(grid), dim3(kThreads), lds, s, x, numel, gg, part); \
+        else hipLaunchKernelGGL((k_minmax_partial<T, kFuU>), dim3(grid), dim3(kThreads), lds, s, x, numel, gg, part); \
+    } while (0)
         MESA_FOR_DTYPE(dt, MESA_LAUNCH_MM);
 #undef MESA_LAUNCH_MM
     }
@@ -1297,10 +1370,10 @@ static mesa_status quantize_update_fused(const void *x, mesa_dtype dt, mesa_layo
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int grid = minmax_grid(L, kFuU, kFuGridCap);
     GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * kFuU * kVec);
-    const size_t lds = size_t(gg.groups) * (sizeof(float2) + 2 * sizeof(int));
+    const size_t lds = size_t(gg.groups) * (sizeof(float2) + 2 * extrema_tables(gg.groups) * sizeof(int));
     float *part = static_cast<float *>(ws);
     const bool sr = mode == MESA_ROUND_STOCHASTIC;
-    // parameter table and extrema of every group live in LDS, 16 bytes a group: beyond the 64 KiB a launch gets by default
+    // parameter table and extrema of every group live in LDS, 16 bytes a group where there are many: beyond the 64 KiB a launch gets by default
     // (more than 4096 groups, up to the layout's limit of 8192: 128 KiB) the kernel is given leave for more
 #define MESA_LAUNCH_QM(T, SRF, GF) \
     do { \
