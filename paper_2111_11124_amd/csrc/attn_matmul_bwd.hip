@@ -20,11 +20,12 @@
 // is multiplied.  binary16 or bfloat16 tensors (every kernel here takes the number type as a parameter);
 // binary32 tensors run the general kernel on three bfloat16 parts.
 //
-// That general kernel (k_bmm_q) serves every shape; dedicated kernels take the shapes that matter: k_attn_da,
-// k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths included, and
-// k_attn_da_cols, k_attn_tn_cols, k_attn_nn_rows for sequences of any length whose rows are aligned (N a multiple of 8
-// or 16): long ones, and short ones too -- a pitch of N elements with N a multiple of 32 puts the first three kernels'
-// lanes on the same LDS banks.
+// That general kernel (k_bmm_q) serves every shape; dedicated kernels take over where there is work enough for them (da_way, tn_way,
+// nn_way): k_attn_da, k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths
+// included, and k_attn_da_cols, k_attn_tn_cols, k_attn_nn_rows, by tiles, for sequences of any length from 64 on (a pitch of N elements
+// with N a multiple of 32 puts the first three kernels' lanes on the same LDS banks).  The tile kernels' rows may start at any
+// element (ANY): a vector that is not aligned touches one cache line more, and from LDS on everything is aligned.  Whole backward (four
+// products), general kernel -> by tiles: (16, 12, 577, 64) 204 -> 150 us, (8, 8, 919, 64) 162 -> 110, (64, 6, 301, 96) 188 -> 129.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -160,6 +161,24 @@ template <> struct BmNum<float> {
     __device__ static __forceinline__ bm_v16f mfma(bm_v8h a, bm_v8h b, bm_v16f c) { return BmNum<__bf16>::mfma(a, b, c); }
     __device__ static __forceinline__ float round(float v) { return v; }
 };
+
+// Workgroups b, b + 8, .. run on one XCD: the number that gives each XCD a run of neighbouring pieces of work (they share operands in its
+// L2).  A permutation of 0 .. total-1.
+__device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned total)
+{
+    const unsigned x = b % 8u, q = total / 8u, r = total % 8u;
+    return x * q + (x < r ? x : r) + b / 8u;
+}
+
+// the 16 bytes of v moved down by 0 .. 15 bytes, zeros above them
+__device__ __forceinline__ u32x4 move_down(u32x4 v, int bytes)
+{
+    if (bytes & 8) v = u32x4{v[2], v[3], 0u, 0u};
+    if (bytes & 4) v = u32x4{v[1], v[2], v[3], 0u};
+    const uint32_t r = uint32_t(bytes) & 3u;
+    return u32x4{__builtin_amdgcn_alignbyte(v[1], v[0], r), __builtin_amdgcn_alignbyte(v[2], v[1], r), __builtin_amdgcn_alignbyte(v[3], v[2], r),
+                 __builtin_amdgcn_alignbyte(0u, v[3], r)};
+}
 
 struct BmmArgs {
     const _Float16 *x;          // the plain operand (16-bit container: binary16 or bfloat16 bits; k_bmm_q<float>: binary32)
@@ -753,12 +772,13 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 7 : 4) void k_attn_da(const _Fl
     }
 }
 
-// ---- dA for long sequences (N a multiple of 8, beyond what k_attn_da's 32 x N output block can hold in LDS) ----------
+// ---- dA by tiles of columns (long sequences, and aligned ones) ----------
 // A workgroup takes 64 rows i and 256 columns j of one head: the 64 rows of dO and the 256 rows of V codes go to LDS
 // once (the codes only until every wave holds its fragments), wave w multiplies the 64 rows by the code rows 64 w ..+63 (four accumulator tiles, codes on the M side as in
 // k_attn_da: a lane ends up with one row i and runs of four consecutive j), and its 64 x 64 piece of the result leaves
 // through a private LDS region, 32 rows at a time, as aligned 16-byte vectors: 128 contiguous bytes per row and wave,
-// 512 per row and workgroup.  The column tiles of a row block are neighbours in the grid.  Dh == 16 * KS.
+// 512 per row and workgroup.  The column tiles of a row block are neighbours, on one XCD.  Rows that start at any element (ANY) leave by
+// unaligned stores, the last few elements of a row one by one.  Dh == 16 * KS.
 template <int KS> struct DcCfg {
     static constexpr int Dh = 16 * KS;
     static constexpr int kRowO = 2 * Dh + 16, kRowV = Dh + 16;     // bytes per staged row of dO, of codes
@@ -770,7 +790,7 @@ template <int KS> struct DcCfg {
     static constexpr int kLds = kCodesAt + (256 * kRowV > 4 * 32 * kRowOut ? 256 * kRowV : 4 * 32 * kRowOut);
 };
 
-template <int KS, typename ET>
+template <int KS, bool ANY, typename ET>
 __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(const _Float16 *__restrict__ dO, const int8_t *__restrict__ vq,
                                                                             _Float16 *__restrict__ dA, int N, int heads, int tiles_j,
                                                                             int tiles_i, const float *__restrict__ alpha_v,
@@ -781,7 +801,8 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
     constexpr int Dh = C::Dh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fl = lane & 31, fk = (lane >> 5) * 8;
-    const unsigned tj = blockIdx.x % unsigned(tiles_j), rest = blockIdx.x / unsigned(tiles_j);
+    const unsigned bid = xcd_block(blockIdx.x, gridDim.x);
+    const unsigned tj = bid % unsigned(tiles_j), rest = bid / unsigned(tiles_j);
     const int64_t bh = rest / unsigned(tiles_i);
     const int i0 = int(rest % unsigned(tiles_i)) * C::kRows, j0 = int(tj) * 256;
     const int rows = N - i0 < C::kRows ? N - i0 : C::kRows, cols = N - j0 < 256 ? N - j0 : 256;
@@ -858,9 +879,21 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int r = (lane >> 3) + 8 * k;
-                if (rb * 32 + r < rows)
-                    *reinterpret_cast<u32x4 *>(dA + (bh * N + i0 + rb * 32 + r) * int64_t(N) + j0 + wave * 64 + cv * 8) =
-                        *reinterpret_cast<const u32x4 *>(lout + r * C::kRowOut + cv * 16);
+                if (rb * 32 + r < rows) {
+                    _Float16 *to = dA + (bh * N + i0 + rb * 32 + r) * int64_t(N) + j0 + wave * 64 + cv * 8;
+                    const u32x4 w = *reinterpret_cast<const u32x4 *>(lout + r * C::kRowOut + cv * 16);
+                    if constexpr (!ANY) {
+                        *reinterpret_cast<u32x4 *>(to) = w;
+                    } else if (wave * 64 + cv * 8 + 8 <= cols) {
+                        __builtin_memcpy(to, &w, 16);      // rows start at any element
+                    } else {
+                        _Float16 e[8];
+                        __builtin_memcpy(e, &w, 16);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (wave * 64 + cv * 8 + q < cols) to[q] = e[q];
+                    }
+                }
             }
         }
         wave_sync();                                       // the region is free for the next 32 rows
@@ -1084,15 +1117,15 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
     }
 }
 
-// ---- the same two products for long sequences (N a multiple of 16, beyond what one workgroup per head can hold) -----
+// ---- the same two products by tiles of columns -----
 // A workgroup takes 256 columns j of one head and walks down ALL rows i in chunks of 32: per chunk 32 row segments of
-// 256 elements of the N x N operand (512 contiguous bytes of dS, 256 of the A codes: aligned 16-byte vectors, rows a
-// multiple of 16 elements apart) and the chunk's 32 rows of the N x Dh operand.  Both lie in LDS row by row, with a
+// 256 elements of the N x N operand (512 contiguous bytes of dS, 256 of the A codes: 16-byte vectors, aligned where N is
+// a multiple of 16) and the chunk's 32 rows of the N x Dh operand.  Both lie in LDS row by row, with a
 // pitch that keeps the transposing reads of sixteen lanes on different banks; every MFMA operand is one or two
 // transposing reads (lane: column j or d, eight consecutive rows i).  The next chunk's vectors wait in registers
 // while a chunk is multiplied (two LDS buffers, one barrier per chunk).  Wave w takes columns 64 w ..+63 of the tile.
-// The workgroups of a head's column tiles are neighbours in the grid: they read adjacent segments of the same rows at
-// about the same time and share the N x Dh chunks in the L2.  The N x N operand is read exactly once.
+// The workgroups of a head's column tiles are neighbours on one XCD: they read adjacent segments of the same rows at
+// about the same time and share the N x Dh chunks in the L2 (dealt out over the XCDs: 3 to 9 % slower, with the other two kernels of its kind).  The N x N operand is read exactly once.
 // As in k_attn_tn the N x Dh operand sits on the M side: a lane ends up with one output row j and runs of four d.
 //
 // RS: groups of four waves that share out the workgroup's chunks (group g takes chunks g, g + RS, ...), each with LDS buffers
@@ -1103,7 +1136,7 @@ template <int DT, bool WIDE_CODED, int RS> struct TcCfg {
     static constexpr int kJW = 256;                        // columns of the N x N operand per workgroup
     static constexpr int kNt = kJW;                        // threads of a group: a wave per 64 columns (two blocks of 32)
     static constexpr int kJB = 2;
-    static constexpr int kCR = 16;                         // rows per chunk (N is a multiple of 16: no ragged chunk)
+    static constexpr int kCR = 16;                         // rows per chunk
     static constexpr int kAhead = WIDE_CODED ? 2 : 1;      // chunks in registers ahead of the one in LDS: the codes' chunks are
                                                            // half the bytes, and it is bytes in flight that hide the latency
     static constexpr int kWideEb = WIDE_CODED ? 1 : 2;
@@ -1119,7 +1152,7 @@ template <int DT, bool WIDE_CODED, int RS> struct TcCfg {
     static constexpr int kWaves = RS > 1 ? RS : 2;         // per SIMD, for the register budget
 };
 
-template <int DT, bool WIDE_CODED, int RS, typename ET>
+template <int DT, bool WIDE_CODED, int RS, bool ANY, typename ET>
 __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED, RS>::kNt * RS), (TcCfg<DT, WIDE_CODED, RS>::kWaves)) void k_attn_tn_cols(const void *__restrict__ wide_, const void *__restrict__ narrow_,
                                                               _Float16 *__restrict__ out, int N, int heads, int tiles_j, float scale,
                                                               const float *__restrict__ alpha, const float *__restrict__ beta)
@@ -1131,38 +1164,66 @@ __global__ __launch_bounds__((TcCfg<DT, WIDE_CODED, RS>::kNt * RS), (TcCfg<DT, W
     const int tid = RS > 1 ? int(threadIdx.x) % C::kNt : int(threadIdx.x);   // within the group
     const int lane = tid & 63, wave = tid >> 6;
     unsigned char *lds_tc = lds_all + group * 2 * C::kStage;
-    const int64_t bh = blockIdx.x / unsigned(tiles_j);
-    const int j0 = int(blockIdx.x % unsigned(tiles_j)) * C::kJW;
+    const unsigned bid = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t bh = bid / unsigned(tiles_j);
+    const int j0 = int(bid % unsigned(tiles_j)) * C::kJW;
+    const bool last_head = ANY && bid + unsigned(tiles_j) >= gridDim.x;
     const unsigned char *wide = static_cast<const unsigned char *>(wide_) + (bh * N * int64_t(N) + j0) * C::kWideEb;
     const unsigned char *narrow = static_cast<const unsigned char *>(narrow_) + bh * N * int64_t(Dh) * (WIDE_CODED ? 2 : 1);
     const int fl = lane & 31, half = lane >> 5, blk = lane >> 4, sl = lane & 15;
-    const int nchunks = N / C::kCR;
-    const int cols = N - j0 < C::kJW ? N - j0 : C::kJW;    // columns of this tile that exist (a multiple of 16)
+    const int nchunks = (N + C::kCR - 1) / C::kCR;         // ANY: the last one may be ragged
+    const int cols = N - j0 < C::kJW ? N - j0 : C::kJW;    // columns of this tile that exist (a multiple of 16, or any number)
 
     // ---- staging: a thread's vectors sit at the same place of every chunk ---------------------------------------------
     u32x4 wv[C::kAhead][C::kWideVecs], nv[C::kAhead][C::kNarrowVecs];
-    int w_src[C::kWideVecs], w_dst[C::kWideVecs];          // byte offsets from the chunk's first row: in memory (-1: past N), in LDS
+    int w_src[C::kWideVecs], w_dst[C::kWideVecs];          // byte offsets from the chunk's first row: in memory, in LDS
+    constexpr int kV = 16 / C::kWideEb;
 #pragma unroll
     for (int k = 0; k < C::kWideVecs; ++k) {
         const int v = tid + k * C::kNt, r = v / C::kVecRowW, cv = v % C::kVecRowW;
-        w_src[k] = cv * 16 < cols * C::kWideEb ? r * N * C::kWideEb + cv * 16 : -1;
+        // (a vector past the row's end: the row's first one; and one that the row ends in reads on into the next: columns past N
+        // only reach sums that are never written)
+        w_src[k] = (r * N + (cv * kV < cols ? cv * kV : -j0)) * C::kWideEb;
         w_dst[k] = r * C::kPitchW + cv * 16;
     }
     auto load_chunk = [&](int c, auto set_) {
         constexpr int S = decltype(set_)::value;
-        const int rows = c < nchunks ? C::kCR : 0;         // a chunk past the end (RS > 1): zeros
+        const int left = N - c * C::kCR;                   // rows from the chunk's first one to the head's end
         const unsigned char *src = wide + int64_t(c) * C::kCR * N * C::kWideEb;
+        const u32x4 *nsrc = reinterpret_cast<const u32x4 *>(narrow + int64_t(c) * C::kCR * Dh * (WIDE_CODED ? 2 : 1));
+        if (left > C::kCR || (left == C::kCR && !last_head)) {   // uniform: the tensor goes on behind the chunk
+#pragma unroll
+            for (int k = 0; k < C::kWideVecs; ++k) {
+                if constexpr (ANY) __builtin_memcpy(&wv[S][k], src + w_src[k], 16);
+                else wv[S][k] = *reinterpret_cast<const u32x4 *>(src + w_src[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < C::kNarrowVecs; ++k) {
+                const int v = tid + k * C::kNt;
+                nv[S][k] = nsrc[v < C::kCR * C::kVecRowN ? v : 0];
+            }
+            return;
+        }
+        // rows past the end, and chunks past the end (RS > 1): zeros
 #pragma unroll
         for (int k = 0; k < C::kWideVecs; ++k) {
-            const int r = (tid + k * C::kNt) / C::kVecRowW;
-            wv[S][k] = u32x4{0u, 0u, 0u, 0u};              // columns past N, rows past the end: zeros
-            if (w_src[k] >= 0 && r < rows) wv[S][k] = *reinterpret_cast<const u32x4 *>(src + w_src[k]);
+            const int v = tid + k * C::kNt, r = v / C::kVecRowW, cv = v % C::kVecRowW;
+            // (the vector that the tensor ends in: the tensor's last 16 bytes, moved to where they belong)
+            const int over = ANY && r == left - 1 && cv * kV < cols && cv * kV + kV > cols ? (cv * kV + kV - cols) * C::kWideEb : 0;
+            wv[S][k] = u32x4{0u, 0u, 0u, 0u};
+            if (r < left) {
+                if constexpr (ANY) {
+                    __builtin_memcpy(&wv[S][k], src + w_src[k] - over, 16);
+                    wv[S][k] = move_down(wv[S][k], over);
+                } else {
+                    wv[S][k] = *reinterpret_cast<const u32x4 *>(src + w_src[k]);
+                }
+            }
         }
-        const u32x4 *nsrc = reinterpret_cast<const u32x4 *>(narrow + int64_t(c) * C::kCR * Dh * (WIDE_CODED ? 2 : 1));
 #pragma unroll
         for (int k = 0; k < C::kNarrowVecs; ++k) {
             const int v = tid + k * C::kNt;
-            nv[S][k] = v < rows * C::kVecRowN ? nsrc[v] : u32x4{0u, 0u, 0u, 0u};
+            nv[S][k] = v < (left < C::kCR ? left : C::kCR) * C::kVecRowN ? nsrc[v] : u32x4{0u, 0u, 0u, 0u};
         }
     };
     auto store_chunk = [&](int b, auto set_) {
@@ -1454,9 +1515,9 @@ __global__ __launch_bounds__(NnCfg<DT>::kNt, 3) void k_attn_nn(const _Float16 *_
     }
 }
 
-// ---- dQ for long sequences (N a multiple of 8): a workgroup takes 64 rows i of one head and walks along the columns ----
+// ---- dQ by tiles of rows: a workgroup takes 64 rows i of one head and walks along the columns ----
 // j in chunks of 64 (larger chunks cost workgroups per CU, which cost more than the shorter row segments): per chunk 64
-// row segments of dS (aligned 16-byte vectors) and the chunk's rows of K codes, both in LDS row by row, the next two
+// row segments of dS (16-byte vectors, from any element) and the chunk's rows of K codes, both in LDS row by row, the next two
 // chunks' vectors waiting in registers (two LDS buffers, one barrier per chunk).  Wave w takes rows 32 (w & 1) ..+31 and the d tiles of parity w >> 1.  A lane's dS fragment (its row, eight
 // consecutive j) is one aligned 16-byte LDS read; the codes come through the byte-transposing read.  Codes on the M
 // side as in k_attn_nn: a lane ends up with one row i and runs of four consecutive d.  dS is read exactly once.
@@ -1465,7 +1526,7 @@ template <int DT> struct NrCfg {
     static constexpr int kJC = 64;                         // columns per chunk
     static constexpr int kPitchS = kJC * 2 + 16;           // bytes per staged row segment of dS: 16 (mod 128), eight rows' reads on different banks
     static constexpr int kRowK = Dh + 32;                  // bytes per staged code row
-    static constexpr int kTiles = DT >= 2 ? DT / 2 : 1;
+    static constexpr int kTiles = (DT + 1) / 2;
     static constexpr int kVecRowS = kJC / 8, kVecRowK = Dh / 16;
     static constexpr int kSVecs = 64 * kVecRowS / kThreads, kKVecs = (kJC * kVecRowK + kThreads - 1) / kThreads;
     static constexpr int kStage = 64 * kPitchS + kJC * kRowK;
@@ -1473,7 +1534,7 @@ template <int DT> struct NrCfg {
     static constexpr int kAhead = 2;                       // chunks in registers ahead of the one in LDS
 };
 
-template <int DT, typename ET>
+template <int DT, bool ANY, typename ET>
 __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__restrict__ dS, const int8_t *__restrict__ kq,
                                                               _Float16 *__restrict__ dQ, int N, int heads, int tiles_i, float scale,
                                                               const float *__restrict__ alpha_k, const float *__restrict__ beta_k)
@@ -1482,8 +1543,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
     __shared__ __attribute__((aligned(16))) unsigned char lds_nr[C::kLds];
     constexpr int Dh = C::Dh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t bh = blockIdx.x / unsigned(tiles_i);
-    const int i0 = int(blockIdx.x % unsigned(tiles_i)) * 64;
+    const unsigned bid = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t bh = bid / unsigned(tiles_i);
+    const int i0 = int(bid % unsigned(tiles_i)) * 64;
     const int rows = N - i0 < 64 ? N - i0 : 64;
     const int fl = lane & 31, half = lane >> 5, blk = lane >> 4, sl = lane & 15;
     const int nchunks = (N + C::kJC - 1) / C::kJC;
@@ -1491,15 +1553,37 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
     const unsigned char *krow = reinterpret_cast<const unsigned char *>(kq + bh * N * int64_t(Dh));
 
     u32x4 sv[C::kAhead][C::kSVecs], kv[C::kAhead][C::kKVecs];
+    int s_src[C::kSVecs];                                  // byte offsets from the chunk's first column; rows past the end repeat the last one
+#pragma unroll
+    for (int k = 0; k < C::kSVecs; ++k) {
+        const int v = tid + k * kThreads, r = v / C::kVecRowS;
+        s_src[k] = ((r < rows ? r : rows - 1) * N + (v % C::kVecRowS) * 8) * 2;
+    }
     auto load_chunk = [&](int c, auto set_) {
         constexpr int S = decltype(set_)::value;
         const int j0 = c * C::kJC;
-        const int cols = N - j0 < C::kJC ? N - j0 : C::kJC;   // a multiple of 8
+        const int cols = N - j0 < C::kJC ? N - j0 : C::kJC;   // a multiple of 8, or (ANY) any number
+        const unsigned char *src = srow + int64_t(j0) * 2;
+        if (cols == C::kJC) {                              // uniform
 #pragma unroll
-        for (int k = 0; k < C::kSVecs; ++k) {
-            const int v = tid + k * kThreads, r = v / C::kVecRowS, cv = v % C::kVecRowS;
-            sv[S][k] = u32x4{0u, 0u, 0u, 0u};           // columns past N meet codes of zero weight: zeros; rows past the end are never written
-            if (r < rows && cv * 8 < cols) sv[S][k] = *reinterpret_cast<const u32x4 *>(srow + (int64_t(r) * N + j0 + cv * 8) * 2);
+            for (int k = 0; k < C::kSVecs; ++k) {
+                if constexpr (ANY) __builtin_memcpy(&sv[S][k], src + s_src[k], 16);
+                else sv[S][k] = *reinterpret_cast<const u32x4 *>(src + s_src[k]);
+            }
+        } else {
+            // columns past N: zeros
+#pragma unroll
+            for (int k = 0; k < C::kSVecs; ++k) {
+                const int cv = (tid + k * kThreads) % C::kVecRowS, some = cols - cv * 8;
+                sv[S][k] = u32x4{0u, 0u, 0u, 0u};
+                if (some >= 8) {
+                    if constexpr (ANY) __builtin_memcpy(&sv[S][k], src + s_src[k], 16);
+                    else sv[S][k] = *reinterpret_cast<const u32x4 *>(src + s_src[k]);
+                } else if (ANY && some > 0) {              // the row's last 16 bytes, moved to where they belong
+                    __builtin_memcpy(&sv[S][k], src + s_src[k] - (8 - some) * 2, 16);
+                    sv[S][k] = move_down(sv[S][k], (8 - some) * 2);
+                }
+            }
         }
         const u32x4 *ksrc = reinterpret_cast<const u32x4 *>(krow + int64_t(j0) * Dh);
 #pragma unroll
@@ -1552,6 +1636,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
             for (int q = 0; q < 8; q += 2) rsum = BmNum<ET>::dot_ones(fs[q], fs[q + 1], rsum);
 #pragma unroll
             for (int t = 0; t < C::kTiles; ++t) {
+                if (DT % 2 == 1 && DT > 1 && tpar + 2 * t >= DT) break;   // uniform per wave
                 const bm_v8h fc = BmNum<ET>::codes8(__builtin_amdgcn_ds_read_tr8_b64_v2i32(BM_LDS3(bm_v2i, lk + k_at + ks * 16 * C::kRowK + t * 64)));
                 acc[t] = BmNum<ET>::mfma(fc, fs, acc[t]);
             }
@@ -1575,6 +1660,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
         for (int t = 0; t < C::kTiles; ++t)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
+                if (DT % 2 == 1 && DT > 1 && tpar + 2 * t >= DT) break;
                 bm_v4h o;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) o[k] = BmNum<ET>::round(scale * fmaf(s, acc[t][4 * g + k], add));
@@ -1585,8 +1671,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
 
 static bool nn_rows_fits(int64_t batches, int64_t N, int64_t Dh)
 {
-    if (Dh != 32 && Dh != 64 && Dh != 128) return false;
-    return N % 8 == 0 && N >= 64 && batches * ceil_div(N, 64) < (int64_t(1) << 31);
+    if (Dh != 32 && Dh != 64 && Dh != 96 && Dh != 128) return false;
+    return N >= 64 && batches * ceil_div(N, 64) < (int64_t(1) << 31);
 }
 
 template <typename ET>
@@ -1595,9 +1681,15 @@ static void launch_nn_rows(const _Float16 *dS, const int8_t *kq, _Float16 *dQ, i
 {
     const int tiles_i = int(ceil_div(N, 64));
     const dim3 grid(unsigned(batches * tiles_i));
-    if (Dh == 32) hipLaunchKernelGGL((k_attn_nn_rows<1, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, scale, alpha_k, beta_k);
-    else if (Dh == 64) hipLaunchKernelGGL((k_attn_nn_rows<2, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, scale, alpha_k, beta_k);
-    else hipLaunchKernelGGL((k_attn_nn_rows<4, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, scale, alpha_k, beta_k);
+#define MESA_LAUNCH_NR(DT_, ANY_) \
+    hipLaunchKernelGGL((k_attn_nn_rows<DT_, ANY_, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, scale, alpha_k, beta_k)
+#define MESA_LAUNCH_NR_A(DT_) do { if (N % 8 == 0) MESA_LAUNCH_NR(DT_, false); else MESA_LAUNCH_NR(DT_, true); } while (0)
+    if (Dh == 32) MESA_LAUNCH_NR_A(1);
+    else if (Dh == 64) MESA_LAUNCH_NR_A(2);
+    else if (Dh == 96) MESA_LAUNCH_NR_A(3);
+    else MESA_LAUNCH_NR_A(4);
+#undef MESA_LAUNCH_NR_A
+#undef MESA_LAUNCH_NR
 }
 
 // whether k_attn_da can take the shape, and in which mode
@@ -1664,12 +1756,12 @@ static void launch_tn(const void *wide, const void *narrow, _Float16 *out, int64
 }
 
 // whether k_attn_nn can take the shape: a 64-row chunk of dS within kMaxVecs vectors per thread, LDS within 64 KiB
-// long sequences: k_attn_da_cols
+// by tiles: k_attn_da_cols
 static bool da_cols_fits(int64_t batches, int64_t N, int64_t Dh)
 {
-    if (Dh != 32 && Dh != 64 && Dh != 128) return false;
+    if (Dh != 32 && Dh != 64 && Dh != 96 && Dh != 128) return false;
     // from 64 on: below, at most one of a workgroup's four waves has columns (N = 48: 0.28 against 0.24 ms for N = 49 through k_attn_da)
-    return N % 8 == 0 && N >= 64 && batches * ceil_div(N, 256) * ceil_div(N, 64) < (int64_t(1) << 31);   // 64: the fewest rows a workgroup takes
+    return N >= 64 && batches * ceil_div(N, 256) * ceil_div(N, 64) < (int64_t(1) << 31);   // 64: the fewest rows a workgroup takes
 }
 
 template <typename ET>
@@ -1679,20 +1771,22 @@ static void launch_da_cols(const _Float16 *dO, const int8_t *vq, _Float16 *dA, i
 #define MESA_LAUNCH_DC(KS_) \
     do { \
         const int tiles_j = int(ceil_div(N, 256)), tiles_i = int(ceil_div(N, DcCfg<KS_>::kRows)); \
-        hipLaunchKernelGGL((k_attn_da_cols<KS_, ET>), dim3(unsigned(batches * tiles_j * tiles_i)), dim3(kThreads), 0, s, dO, vq, dA, N, heads, \
-                           tiles_j, tiles_i, alpha_v, beta_v); \
+        const dim3 grid(unsigned(batches * tiles_j * tiles_i)); \
+        if (N % 8 == 0) hipLaunchKernelGGL((k_attn_da_cols<KS_, false, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, alpha_v, beta_v); \
+        else hipLaunchKernelGGL((k_attn_da_cols<KS_, true, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, alpha_v, beta_v); \
     } while (0)
     if (Dh == 32) MESA_LAUNCH_DC(2);
     else if (Dh == 64) MESA_LAUNCH_DC(4);
+    else if (Dh == 96) MESA_LAUNCH_DC(6);
     else MESA_LAUNCH_DC(8);
 #undef MESA_LAUNCH_DC
 }
 
-// long sequences: k_attn_tn_cols
+// by tiles: k_attn_tn_cols
 static bool tn_cols_fits(int64_t batches, int64_t N, int64_t Dh)
 {
-    if (Dh != 32 && Dh != 64 && Dh != 128) return false;
-    return N % 16 == 0 && N >= 64 && batches * ceil_div(N, 256) < (int64_t(1) << 31);
+    if (Dh != 32 && Dh != 64 && Dh != 96 && Dh != 128) return false;
+    return N >= 64 && batches * ceil_div(N, 256) < (int64_t(1) << 31);
 }
 
 template <bool WIDE_CODED, typename ET>
@@ -1707,10 +1801,14 @@ static void launch_tn_cols(const void *wide, const void *narrow, _Float16 *out, 
     // 192: 61.0 / 57.9 / 60.7
     const int rs = wgs > 512 ? 1 : wgs <= 256 && N >= 1024 && Dh <= 64 ? 4 : 2;
 #define MESA_LAUNCH_TC(DT_, RS_) \
-    hipLaunchKernelGGL((k_attn_tn_cols<DT_, WIDE_CODED, RS_, ET>), dim3(unsigned(wgs)), dim3(TcCfg<DT_, WIDE_CODED, RS_>::kNt * (RS_)), 0, s, wide, narrow, \
-                       out, N, heads, tiles_j, scale, alpha, beta)
+    do { \
+        const dim3 grid{unsigned(wgs)}, block(TcCfg<DT_, WIDE_CODED, RS_>::kNt * (RS_)); \
+        if (N % 16 == 0) hipLaunchKernelGGL((k_attn_tn_cols<DT_, WIDE_CODED, RS_, false, ET>), grid, block, 0, s, wide, narrow, out, N, heads, tiles_j, scale, alpha, beta); \
+        else hipLaunchKernelGGL((k_attn_tn_cols<DT_, WIDE_CODED, RS_, true, ET>), grid, block, 0, s, wide, narrow, out, N, heads, tiles_j, scale, alpha, beta); \
+    } while (0)
     if (Dh == 32) { if (rs == 4) MESA_LAUNCH_TC(1, 4); else if (rs == 2) MESA_LAUNCH_TC(1, 2); else MESA_LAUNCH_TC(1, 1); }
     else if (Dh == 64) { if (rs == 4) MESA_LAUNCH_TC(2, 4); else if (rs == 2) MESA_LAUNCH_TC(2, 2); else MESA_LAUNCH_TC(2, 1); }
+    else if (Dh == 96) { if (rs == 2) MESA_LAUNCH_TC(3, 2); else MESA_LAUNCH_TC(3, 1); }
     else { if (rs == 2) MESA_LAUNCH_TC(4, 2); else MESA_LAUNCH_TC(4, 1); }
 #undef MESA_LAUNCH_TC
 }
@@ -1729,6 +1827,54 @@ template <int DT, typename ET> static void launch_nn(const _Float16 *dS, const i
     typedef NnCfg<DT> C;
     hipLaunchKernelGGL((k_attn_nn<DT, ET>), dim3(unsigned(batches)), dim3(C::kNt), C::lds_bytes(N), s, dS, kq, dQ, N, heads, scale,
                        alpha_k, beta_k, int(C::ds_bytes(N)), batches * N * int64_t(N));
+}
+
+// Which kernel a product of 16-bit tensors takes: the general one, the one that goes by tiles of columns or rows, or the one that keeps a
+// head's rows or codes whole.  The lines lie where two hundred shapes put them (3 to 1536 heads, 50 to 1024 tokens); us of the product
+// alone, by the general kernel / by tiles / whole, where a path exists.  What decides is how many workgroups a way of cutting leaves: the
+// general kernel has a workgroup per 64 x 64 results and its loads are its own, the others share what they read.
+enum AttnWay { kWayGeneral, kWayTiles, kWayWhole };
+
+// dA.  Whole: 32 x N results in LDS.  Aligned rows by tiles once these give every CU a workgroup ((192, 256, 64) -4.1 us against
+// the general kernel, (16, 576, 64) -1.3, (64, 64, 64) +0.5), else whole, but not where N is a multiple of 32, whose rows meet on the same banks
+// ((192, 256, 64): +15).  Unaligned ones whole up to 448 tokens ((192, 301, 64) -6.6 by tiles, -9.1 whole; (192, 420, 64) -17.0 and -17.7; (192, 577, 64)
+// 4 us behind), unless heads are few and long ((3, 420, 64) +0.9).
+static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
+{
+    const bool whole = (Dh == 32 && da_fits<2>(batches, N)) || (Dh == 64 && da_fits<4>(batches, N)) || (Dh == 96 && da_fits<6>(batches, N)) ||
+                       (Dh == 128 && da_fits<8>(batches, N));
+    const int64_t per_head = ceil_div(N, 256) * ceil_div(N, Dh <= 64 ? 128 : 64);
+    const bool tiles = da_cols_fits(batches, N, Dh) && batches >= ceil_div(N % 8 == 0 ? 256 : 384, per_head);
+    if (N % 8 == 0 && N >= 64) return tiles ? kWayTiles : whole && N % 32 != 0 ? kWayWhole : kWayGeneral;
+    if (whole && (N <= 256 || (N <= 448 && batches >= ceil_div(128, ceil_div(N, 32))))) return kWayWhole;
+    return tiles ? kWayTiles : kWayGeneral;
+}
+
+// dV and dK.  Both other ways give a workgroup all the rows of a head, so they want heads: from some hundred columns per CU on at Dh = 64, which the
+// general kernel's tiles fit exactly, sooner at other sizes.  dV by tiles: (64, 301, 64) +1.3, (64, 577, 64) -3.2, (64, 919, 64) -18,
+// (192, 197, 64) -1.9, (1536, 197, 96) -83; (3, 601, 64) +5.  Whole (a few percent ahead) below 128 tokens: (1536, 71, 64) dK -1.2 by tiles, -3.0
+// whole; (1536, 131, 64) -11.6 and -11.1.
+template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
+{
+    if (batches < ceil_div(Dh == 64 ? 28672 : 20480, N)) return kWayGeneral;
+    const bool whole = tn_fits<WIDE_CODED>(N, Dh) && batches < (int64_t(1) << 31);
+    if (tn_cols_fits(batches, N, Dh) && (N >= 128 || N % 16 == 0 || !whole)) return kWayTiles;
+    return whole ? kWayWhole : kWayGeneral;
+}
+
+// dQ.  Whole, a workgroup per head, for many short heads whose rows do not meet on the same banks: (768, 197, 64) -3.8 by tiles, -4.4 whole;
+// (3072, 100, 64) -1.3, -4.1 (with dK behind it, (768, 100, 64) 22.7 by the general kernel, 22.2); (1536, 100, 32) -1.6, -2.6; (1536, 150, 32) -4.1, -1.1; (768, 150, 128) -9, -14; (768, 197,
+// 128) -24, -19; (8, 197, 64) 0 and +7.  By tiles from 192 workgroups on ((192, 301, 96) -11, (24, 919, 96) -3.5, (8, 919, 96) +2.9), short heads only
+// where the general kernel's 64 x 64 tiles do not fit Dh; always at Dh = 32, half such a tile ((64, 601, 32) -3.7, (192, 74, 32) -0.7).
+static AttnWay nn_way(int64_t batches, int64_t N, int64_t Dh)
+{
+    if (nn_fits(N, Dh) && batches < (int64_t(1) << 31)) {
+        const bool many = Dh == 32 ? N < 144 && batches >= 1024 : batches >= 640 && (Dh == 64 || N < 192);
+        if (N < 64 || (N % 32 != 0 && many)) return kWayWhole;
+    }
+    if (!nn_rows_fits(batches, N, Dh)) return kWayGeneral;
+    const bool tiles = Dh == 32 || (batches >= ceil_div(192, ceil_div(N, 64)) && (Dh == 64 ? N >= 192 : Dh == 96 || N >= 128 || batches >= 384));
+    return tiles ? kWayTiles : kWayGeneral;
 }
 
 static mesa_status check_attn(int64_t B, int64_t H, int64_t N, int64_t Dh, mesa_dtype dt)
@@ -1779,17 +1925,15 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         launch_bmm_plain<true>(a, batches, dt, s);
         return launch_status();
     }
-    // aligned rows (N a multiple of 8): the column-tile kernel, at every length -- k_attn_da keeps its 32 x N block at a
-    // pitch of N elements, and for N a multiple of 32 its lanes' rows fall on the same LDS banks (N = 256: 0.73 against
-    // 0.48 ms for the four products).  Else k_attn_da if its block fits the 64 KiB of LDS a kernel gets by default.
 #define MESA_AV_DA(ET) \
     do { \
-        if (da_cols_fits(batches, N, Dh)) launch_da_cols<ET>(a.x, vq, a.c, batches, int(N), int(Dh), int(H), alpha_v, beta_v, s); \
-        else if (Dh == 32 && da_fits<2>(batches, N)) launch_da<2, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
-        else if (Dh == 64 && da_fits<4>(batches, N)) launch_da<4, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
-        else if (Dh == 96 && da_fits<6>(batches, N)) launch_da<6, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
-        else if (Dh == 128 && da_fits<8>(batches, N)) launch_da<8, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
-        else launch_bmm<false, true, true, ET>(a, batches, s); \
+        const AttnWay way = da_way(batches, N, Dh); \
+        if (way == kWayTiles) launch_da_cols<ET>(a.x, vq, a.c, batches, int(N), int(Dh), int(H), alpha_v, beta_v, s); \
+        else if (way == kWayGeneral) launch_bmm<false, true, true, ET>(a, batches, s); \
+        else if (Dh == 32) launch_da<2, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
+        else if (Dh == 64) launch_da<4, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
+        else if (Dh == 96) launch_da<6, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
+        else launch_da<8, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
     } while (0)
     if (dt == MESA_F32) launch_bmm<false, true, true, float>(a, batches, s);
     else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
@@ -1800,16 +1944,12 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     a.R = int(N); a.Cn = int(Dh); a.Tn = int(N);
     a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
     a.alpha = alpha_a; a.beta = beta_a;
-    // aligned rows (N a multiple of 16): the column-tile kernel at every length (k_attn_tn's gathers, a row apart at a
-    // pitch of N elements, meet on the same banks when N is a multiple of 32)
 #define MESA_AV_DV(ET) \
     do { \
-        if (tn_cols_fits(batches, N, Dh)) \
-            launch_tn_cols<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
-        else if (tn_fits<true>(N, Dh) && batches < (int64_t(1) << 31)) \
-            launch_tn<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
-        else \
-            launch_bmm<true, false, false, ET>(a, batches, s); \
+        const AttnWay way = tn_way<true>(batches, N, Dh); \
+        if (way == kWayTiles) launch_tn_cols<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
+        else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
+        else launch_bmm<true, false, false, ET>(a, batches, s); \
     } while (0)
     if (dt == MESA_F32) launch_bmm<true, false, false, float>(a, batches, s);
     else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
@@ -1850,19 +1990,14 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
         launch_bmm_plain<false>(a, batches, dt, s);
         return launch_status();
     }
-    // k_attn_nn (K codes resident) where it fits, except for N a multiple of 32 (its rows' reads meet on the same banks)
 #define MESA_QK_DQ(ET) \
     do { \
-        if (nn_rows_fits(batches, N, Dh) && (N % 32 == 0 || !nn_fits(N, Dh))) \
-            launch_nn_rows<ET>(a.x, kq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_k, beta_k, s); \
-        else if (nn_fits(N, Dh) && batches < (int64_t(1) << 31)) { \
-            if (Dh == 32) launch_nn<1, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
-            else if (Dh == 64) launch_nn<2, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
-            else launch_nn<4, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
-        } else if (nn_rows_fits(batches, N, Dh)) \
-            launch_nn_rows<ET>(a.x, kq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_k, beta_k, s); \
-        else \
-            launch_bmm<false, true, false, ET>(a, batches, s); \
+        const AttnWay way = nn_way(batches, N, Dh); \
+        if (way == kWayTiles) launch_nn_rows<ET>(a.x, kq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_k, beta_k, s); \
+        else if (way == kWayGeneral) launch_bmm<false, true, false, ET>(a, batches, s); \
+        else if (Dh == 32) launch_nn<1, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
+        else if (Dh == 64) launch_nn<2, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
+        else launch_nn<4, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
     } while (0)
     if (dt == MESA_F32) launch_bmm<false, true, false, float>(a, batches, s);
     else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
@@ -1873,12 +2008,10 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
     a.alpha = alpha_q; a.beta = beta_q;
 #define MESA_QK_DK(ET) \
     do { \
-        if (tn_cols_fits(batches, N, Dh)) \
-            launch_tn_cols<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
-        else if (tn_fits<false>(N, Dh) && batches < (int64_t(1) << 31)) \
-            launch_tn<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
-        else \
-            launch_bmm<false, false, false, ET>(a, batches, s); \
+        const AttnWay way = tn_way<false>(batches, N, Dh); \
+        if (way == kWayTiles) launch_tn_cols<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
+        else if (way == kWayWhole) launch_tn<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
+        else launch_bmm<false, false, false, ET>(a, batches, s); \
     } while (0)
     if (dt == MESA_F32) launch_bmm<false, false, false, float>(a, batches, s);
     else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
