@@ -735,6 +735,174 @@ __global__ __launch_bounds__(kThreads, 2) void k_dw_cut(const int8_t *__restrict
     }
 }
 
+// ---- small matrices: a 32 x 32 tile per workgroup, its sixteen waves share out the rows ----------------------------
+// A small matrix is latency: one or a few stages through LDS with a barrier each, then a second launch for the slices' sums.
+// Here a wave takes every sixteenth block of 32 rows straight from memory -- a lane's operand is eight rows of one column,
+// and a load of one row by 32 lanes is a whole line or half of one, so nothing needs transposing --, all 32 loads of a block are
+// in flight together, no wave waits for another before the end, and the sixteen tiles are added in LDS, in a fixed order.
+// One launch; every operand is read (and dy cut) N / 32 or K / 32 times, which is what ends its range: see dw_waves.  394 x (192 -> 768):
+// 13.4 -> 6.0 us in binary32, 10.1 -> 6.0 in 16 bits, of which 4.2 are the launch and one block's loads.
+// What is contracted is what the tiles above contract: the signed code, x_bar for bfloat16; a wave's chain of sums ends after a
+// sixteenth of the rows.
+
+template <typename E> struct DwWaveElem {
+    typedef E operand;
+    static constexpr bool SIGNED = std::is_same<E, _Float16>::value;
+    static constexpr int PARTS = 1;
+};
+template <> struct DwWaveElem<float> {
+    typedef __bf16 operand;
+    static constexpr bool SIGNED = true;
+    static constexpr int PARTS = 3;
+};
+
+template <typename E, int NW>
+__global__ __launch_bounds__(NW * 64) void k_dw_waves(const int8_t *__restrict__ xq, const E *__restrict__ dy, int M, int K, int N,
+                                                            int tiles_n, int tiles_k, DwDirect out)
+{
+    typedef DwWaveElem<E> W;
+    typedef typename W::operand Op;
+    typedef typename std::conditional<std::is_same<E, float>::value, float, uint16_t>::type Raw;
+    __shared__ float sums[NW][16][64];              // accumulator register v of a wave's lane
+    __shared__ float sums0[NW][64];                 // row sums: column lane % 32 of dy, its half of the rows
+    __shared__ int large[NW];                       // the wave met a value that is too large to be cut
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int logical = int(blockIdx.x % kDwXcd) * int(gridDim.x / kDwXcd) + int(blockIdx.x / kDwXcd);   // the grid is a multiple of 8
+    if (logical >= tiles_n * tiles_k) return;             // uniform, before any barrier
+    const int tn = logical / tiles_k, tk = logical - tn * tiles_k;
+    const int n0 = tn * 32, k0 = tk * 32;
+    // columns outside N or K are read from column 0: they only reach results that are never written
+    const uint32_t col_a = n0 + l32 < N ? n0 + l32 : 0, col_b = k0 + l32 < K ? k0 + l32 : 0;
+
+    v16f acc;
+    float s0 = 0.0f, most = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+
+    // 32 rows from row m; CHECK: rows behind the last one are read from it and count as zeros of dy
+    auto block = [&](int m, auto check) __attribute__((always_inline)) {
+        constexpr bool CHECK = decltype(check)::value;
+        Raw a[2][8];
+        int b[2][8];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (CHECK) {
+                    const int r = m + s * 16 + half * 8 + j, in = r < M ? r : M - 1;
+                    const Raw v = reinterpret_cast<const Raw *>(dy)[int64_t(in) * N + col_a];
+                    a[s][j] = r < M ? v : Raw(0);
+                    b[s][j] = xq[int64_t(in) * K + col_b];
+                } else {                                  // a uniform base and one offset per lane
+                    a[s][j] = (reinterpret_cast<const Raw *>(dy) + int64_t(m + s * 16 + j) * N)[uint32_t(half) * 8u * uint32_t(N) + col_a];
+                    b[s][j] = (xq + int64_t(m + s * 16 + j) * K)[uint32_t(half) * 8u * uint32_t(K) + col_b];
+                }
+            }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            v4s bo[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float f[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] = float(W::SIGNED ? b[s][4 * h + j] : b[s][4 * h + j] + 128);
+                if constexpr (std::is_same<Op, _Float16>::value) {
+                    const v2i w = {__builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(f[0], f[1])), __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]))};
+                    bo[h] = __builtin_bit_cast(v4s, w);
+                } else {
+                    const v2i w = {int(__builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u)),
+                                   int(__builtin_amdgcn_perm(__float_as_uint(f[3]), __float_as_uint(f[2]), 0x07060302u))};
+                    bo[h] = __builtin_bit_cast(v4s, w);
+                }
+            }
+            v4s ao[W::PARTS][2];
+            if constexpr (W::PARTS == 3) {
+                uint32_t p[3][8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cut_f32(a[s][j], p[0][j], p[1][j], p[2][j]);
+                s0 += ((a[s][0] + a[s][1]) + (a[s][2] + a[s][3])) + ((a[s][4] + a[s][5]) + (a[s][6] + a[s][7]));
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) most = max_magnitude(most, a[s][j], a[s][j + 1]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const v2i w = {int(__builtin_amdgcn_perm(p[q][4 * h + 1], p[q][4 * h], 0x07060302u)),
+                                       int(__builtin_amdgcn_perm(p[q][4 * h + 3], p[q][4 * h + 2], 0x07060302u))};
+                        ao[q][h] = __builtin_bit_cast(v4s, w);
+                    }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const v2i w = {int(uint32_t(a[s][4 * h]) | uint32_t(a[s][4 * h + 1]) << 16),
+                                   int(uint32_t(a[s][4 * h + 2]) | uint32_t(a[s][4 * h + 3]) << 16)};
+                    ao[0][h] = __builtin_bit_cast(v4s, w);
+                    s0 = DwElem<Op>::dot_ones(uint32_t(w[0]), s0);
+                    s0 = DwElem<Op>::dot_ones(uint32_t(w[1]), s0);
+                }
+            }
+#pragma unroll
+            for (int q = W::PARTS - 1; q >= 0; --q) acc = DwElem<Op>::mfma(ao[q][0], ao[q][1], bo[0], bo[1], acc);   // the smallest parts first
+        }
+    };
+    for (int m = wave * 32; m < M; m += NW * 32) {
+        if (m + 32 <= M) block(m, std::false_type());
+        else block(m, std::true_type());
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sums[wave][v][lane] = acc[v];
+    sums0[wave][lane] = s0;
+    float down = 1.0f;
+    if constexpr (W::PARTS == 3) {
+        const bool mine = __any(too_large(most));
+        if (lane == 0) large[wave] = mine;
+    }
+    __syncthreads();
+    if constexpr (W::PARTS == 3) {
+        down = kCutDown;
+        if (__any(large[lane % NW])) {              // the same in every wave: its rows again with binary32 products
+            down = 1.0f;
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+            for (int m = wave * 32; m < M; m += NW * 32) {
+                for (int r = m; r < m + 32 && r < M; r += 2) {
+                    const int row = r + half, in = row < M ? row : M - 1;
+                    const float av = dy[int64_t(in) * N + col_a];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(row < M ? av : 0.0f, float(int(xq[int64_t(in) * K + col_b])), acc, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sums[wave][v][lane] = acc[v];
+            __syncthreads();
+        }
+    }
+
+    // a wave takes every NW-th register v of the tile: row 8 * (v / 4) + 4 * (lane / 32) + v % 4, column lane % 32
+    const int kk = k0 + l32;
+    const uint32_t g = fastdiv(uint32_t(kk < K ? kk : 0), out.div_per);
+    const float sg = out.alpha[g] / 255.0f, off = fmaf(W::SIGNED ? 128.0f : 0.0f, sg, out.beta[g]);
+#pragma unroll
+    for (int v = wave; v < 16; v += NW) {
+        const int r = (v >> 2) * 8 + half * 4 + (v & 3), n = n0 + r;
+        float t0 = l32 < 2 * NW ? sums0[l32 / 2 % NW][(l32 & 1) * 32 + r] : 0.0f;   // a row sum's parts: one per lane of the half wave
+#pragma unroll
+        for (int x = 16; x > 0; x >>= 1) t0 += __shfl_xor(t0, x, 64);
+        float p[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) p[w] = sums[w][v][lane];
+#pragma unroll
+        for (int w = NW / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int i = 0; i < w; ++i) p[i] += p[i + w];
+        if (n < N && kk < K) {
+            out.dW[int64_t(n) * K + kk] = fmaf(sg, p[0] * down, off * t0);
+            if (out.db && kk == 0) out.db[n] = t0;
+        }
+    }
+}
+
 // The plain path: 32x32x2 binary32 MFMA, operands straight from global memory, one element at a time (a lane
 // needs a single value per operand, so no transposition and no alignment is involved).  Kept simple: it serves
 // widths that the vector loads of the kernels above cannot take (K not a multiple of 16, N not a multiple of 8, of 4
@@ -978,6 +1146,19 @@ static DwPlan dw_plan(int64_t M, int64_t K, int64_t N, mesa_dtype dt, int64_t ro
     return p;
 }
 
+// Waves of k_dw_waves's workgroups where it is the faster kernel, else 0.  Its time is a round of workgroups: sixteen waves fill a CU's
+// registers for one workgroup (76 to 97 a lane), so up to 256 tiles; eight waves leave room for two or three, up to 640 tiles; beyond, the
+// operands that every tile reads for itself take over.  In f32 / 16 bit, plan of tiles and slices -> this one: 394 x (192 -> 768)
+// 13.4 -> 6.0 / 10.1 -> 6.0 us; 1130 x (832 -> 280) 18.1 -> 8.6; 918 x (192 -> 1152) 12.6 -> 7.5; eight waves: 395 x (288 -> 1200) 15.2 -> 7.8,
+// 510 x (512 -> 864) 11.3 -> 7.7, 197 x (384 -> 1536) 8.4 -> 7.1, 1610 x (1024 -> 560) 26.5 -> 23; sixteen waves there 10.7, 11.0, 11.7, 27;
+// 306 x (1344 -> 1752) 21 and 43.  Long chains of blocks lose: 3650 x (384 -> 104) 15.2 and 16.3, 3260 x (512 -> 64) 11.1 and 12.2, and up to 2048
+// rows the error against 64 bits was no larger in any of 190 shapes (f32 1.1e-7 -> 1.0e-7, f16 9e-8 -> 7e-8; chains of 256 rows at most).
+static int dw_waves(int64_t M, int64_t K, int64_t N)
+{
+    const int64_t tiles = ceil_div(N, 32) * ceil_div(K, 32);
+    return M > 2048 || tiles > 640 ? 0 : tiles <= 256 ? 16 : 8;
+}
+
 static size_t dw_slice_bytes(int64_t K, int64_t N) { return (size_t(N) * size_t(K) + size_t(N)) * sizeof(float); }
 
 size_t linear_dw_ws_bytes(int64_t M, int64_t K, int64_t N, mesa_dtype dt)
@@ -1013,6 +1194,21 @@ extern "C" MESA_EXPORT mesa_status mesa_linear_dw_q(const int8_t *xq, int64_t M,
     const int Ki = int(K), Ni = int(N_out);
     float centre = 128.0f;
     const FastDiv dper = make_fastdiv(uint32_t(K / G));
+    if (const int waves = p.variant >= 3 ? dw_waves(M, K, N_out) : 0) {
+        const int tn = int(ceil_div(N_out, 32)), tk = int(ceil_div(K, 32));
+        const DwDirect out = {alpha, beta, dper, dW, db};
+        const dim3 grid(unsigned(ceil_div(int64_t(tn) * tk, kDwXcd) * kDwXcd));
+#define MESA_LAUNCH_WAVES(E) \
+    do { \
+        if (waves == 16) hipLaunchKernelGGL((k_dw_waves<E, 16>), grid, dim3(1024), 0, s, xq, static_cast<const E *>(dy), int(M), Ki, Ni, tn, tk, out); \
+        else hipLaunchKernelGGL((k_dw_waves<E, 8>), grid, dim3(512), 0, s, xq, static_cast<const E *>(dy), int(M), Ki, Ni, tn, tk, out); \
+    } while (0)
+        if (dt == MESA_F32) MESA_LAUNCH_WAVES(float);
+        else if (dt == MESA_F16) MESA_LAUNCH_WAVES(_Float16);
+        else MESA_LAUNCH_WAVES(__bf16);
+#undef MESA_LAUNCH_WAVES
+        return launch_status();
+    }
     const bool one = p.splits == 1 && p.variant >= 3;    // the others leave their sums to the second kernel
     const DwDirect direct = {alpha, beta, dper, one ? dW : nullptr, db};
 #define MESA_LAUNCH_DW(E, BN_, BK_, SUMS_) \
