@@ -403,7 +403,7 @@ __device__ __forceinline__ void bmm_plain_sums(const BmmArgs &a, uint32_t b, int
 // of its own; their sums are added through LDS at the end, in group order.  A stage behind the last one is all zeros
 // (BmOperand::store).  For few workgroups with many stages: one workgroup's next stage is all that a CU has on its way.
 template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET, int RS>
-__global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value || RS == 4 ? 4 : 6)) void k_bmm_q(BmmArgs a)
+__global__ __launch_bounds__(kThreads * RS, (std::is_same<ET, float>::value ? 4 : 6)) void k_bmm_q(BmmArgs a)
 {
     typedef BmOperand<P_CODED, P_TFAST, ET> OP;
     typedef BmOperand<!P_CODED, Q_TFAST, ET> OQ;
@@ -537,14 +537,203 @@ static void launch_bmm(BmmArgs a, int64_t batches, hipStream_t s)
         const int64_t nb = batches - b0 < 65535 ? batches - b0 : 65535;
         const dim3 grid(unsigned(a.tiles_c), unsigned(a.tiles_r), unsigned(nb));
         const int64_t wgs = int64_t(a.tiles_c) * a.tiles_r * nb;
-        // groups per workgroup: whole attention backward with 1 / 2 / 4 of them, by the workgroups of dV, dQ and dK: (1, 4, 919,
-        // 32), 60: 90 / 67 / 58 us; (1, 3, 856, 96), 84: 72 / 56 / 56; (4, 8, 577, 64), 320: 76 / 67 / 82; (34, 4, 378, 64),
-        // 816: 93 / 102 / 119; binary32 (1, 12, 324, 64), 72: 63 / 51 / 54
-        const int rs = a.Tn < 128 || wgs > 512 ? 1 : wgs <= 64 && a.Tn >= 512 ? 4 : 2;
-        if (rs == 4) hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 4>), grid, dim3(kThreads * 4), 0, s, a);
-        else if (rs == 2) hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 2>), grid, dim3(kThreads * 2), 0, s, a);
+        // groups per workgroup: whole attention backward with 1 / 2 of them, by the workgroups of dV, dQ and dK: (4, 8, 577, 64), 320: 76 / 67 us;
+        // (34, 4, 378, 64), 816: 93 / 102
+        const int rs = a.Tn < 128 || wgs > 512 ? 1 : 2;
+        if (rs == 2) hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 2>), grid, dim3(kThreads * 2), 0, s, a);
         else hipLaunchKernelGGL((k_bmm_q<P_CODED, P_TFAST, Q_TFAST, ET, 1>), grid, dim3(kThreads), 0, s, a);
     }
+}
+
+// ---- few heads: a 32 x 32 tile per workgroup, its waves share out the contraction -----------------------------------
+// The same product where all of it is a fraction of a round of workgroups, so that its time is latency: the stages of k_bmm_q, each
+// with a trip to memory and two barriers, one after the other.  Here a wave takes every NW-th block of 16 contraction steps straight from
+// memory (a lane: eight steps of one line -- a vector where they lie side by side, else eight loads that 32 lanes make whole
+// lines of), all of them on their way at once, and the waves' tiles are added in LDS in a fixed order.  The sums of the
+// plain operand are added by the lanes that hold it.  Same contracted values as k_bmm_q.  See bmm_waves for its range.
+template <bool CODED, bool TFAST, typename ET> struct BmLane {
+    typedef BmElem<CODED, ET> Elem;
+    typedef typename Elem::global_t E;
+    typedef typename std::conditional<sizeof(E) == 4, uint32_t, typename std::conditional<sizeof(E) == 2, uint16_t, uint8_t>::type>::type U;
+    typename Elem::raw_t raw;
+
+    // steps t .. t + 7 of the line; WHOLE: they all exist, else those from tn on read as zeros
+    template <bool WHOLE> __device__ __forceinline__ void load(const E *base, int64_t line_stride, int64_t t_stride, int line, int t, int tn)
+    {
+        if (TFAST && WHOLE) {
+            __builtin_memcpy(&raw, base + int64_t(line) * line_stride + t, 8 * sizeof(E));
+            return;
+        }
+        const U *at = reinterpret_cast<const U *>(base) + int64_t(line) * (TFAST ? line_stride : 1);
+        U e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int tj = WHOLE || t + j < tn ? t + j : tn - 1;
+            const U v = at[int64_t(tj) * (TFAST ? 1 : t_stride)];
+            e[j] = WHOLE || t + j < tn ? v : U(0);
+        }
+        uint32_t w[sizeof(raw) / 4];
+        constexpr int per = 4 / sizeof(E);
+#pragma unroll
+        for (int k = 0; k < int(sizeof(raw) / 4); ++k) {
+            w[k] = uint32_t(e[per * k]);
+#pragma unroll
+            for (int j = 1; j < per; ++j) w[k] |= uint32_t(e[per * k + j]) << (32 / per * j);
+        }
+        __builtin_memcpy(&raw, w, sizeof(raw));
+    }
+};
+
+template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET, int NW>
+__global__ __launch_bounds__(64 * NW) void k_bmm_waves(BmmArgs a)
+{
+    typedef typename BmElem<false, ET>::global_t X;
+    constexpr bool kCut = std::is_same<ET, float>::value;
+    constexpr int kPlanes = BmElem<false, ET>::kPlanes;
+    __shared__ float sums[NW][16][64];                    // accumulator register v of a wave's lane
+    // sums of the plain operand's line lane % 32, this half's steps: the matrix cores added sixteen values with one rounding, eight binary32
+    // values one by one do not (dA of 32-wide heads 6.3e-8 -> 6.9e-8), hence binary64
+    typedef typename std::conditional<kCut, double, float>::type Sum;
+    __shared__ Sum sums1[NW][64];
+    __shared__ int large[NW];                             // the wave met a value that is too large to be cut
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), half = lane >> 5, l32 = lane & 31;
+    const uint32_t block = xcd_block(blockIdx.x, gridDim.x), tiles = uint32_t(a.tiles_r) * uint32_t(a.tiles_c);
+    const uint32_t b = block / tiles, tile = block - b * tiles, tr = tile / uint32_t(a.tiles_c);
+    const int r0 = int(tr) * 32, c0 = int(tile - tr * uint32_t(a.tiles_c)) * 32;
+    const uint32_t h = b % uint32_t(a.heads);
+    const X *xb = reinterpret_cast<const X *>(a.x) + int64_t(b) * a.x_batch;
+    const int8_t *yb = a.y + int64_t(b) * a.y_batch;
+    // lines beyond the extents are the last one again: they only reach results that are never written
+    const int r = r0 + l32 < a.R ? r0 + l32 : a.R - 1, c = c0 + l32 < a.Cn ? c0 + l32 : a.Cn - 1;
+
+    bm_v16f acc;
+    Sum sum = 0;
+    float most = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    auto block16 = [&](int t0, auto whole) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        BmLane<P_CODED, P_TFAST, ET> p;
+        BmLane<!P_CODED, Q_TFAST, ET> q;
+        if constexpr (P_CODED) {
+            p.template load<WHOLE>(yb, a.p_rs, a.p_ts, r, t0 + half * 8, a.Tn);
+            q.template load<WHOLE>(xb, a.q_cs, a.q_ts, c, t0 + half * 8, a.Tn);
+        } else {
+            p.template load<WHOLE>(xb, a.p_rs, a.p_ts, r, t0 + half * 8, a.Tn);
+            q.template load<WHOLE>(yb, a.q_cs, a.q_ts, c, t0 + half * 8, a.Tn);
+        }
+        const auto &plain = [&]() -> const auto & { if constexpr (P_CODED) return q.raw; else return p.raw; }();
+        const auto &code = [&]() -> const auto & { if constexpr (P_CODED) return p.raw; else return q.raw; }();
+        const bm_v8h coded = BmNum<ET>::codes8(bm_v2i{int(code[0]), int(code[1])});
+        u32x4 part[kPlanes];
+        BmElem<false, ET>::cut(plain, part);
+        if constexpr (kCut) {
+            float x[8];
+            __builtin_memcpy(x, &plain, 32);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum += double(x[j]);
+            most = BmElem<false, float>::most(most, plain);
+        } else {
+            const bm_v8h x = __builtin_bit_cast(bm_v8h, part[0]);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) sum = BmNum<ET>::dot_ones(x[j], x[j + 1], sum);
+        }
+#pragma unroll
+        for (int k = kPlanes - 1; k >= 0; --k) {          // the smallest parts first
+            const bm_v8h x = __builtin_bit_cast(bm_v8h, part[k]);
+            acc = BmNum<ET>::mfma(P_CODED ? coded : x, P_CODED ? x : coded, acc);
+        }
+    };
+    for (int t0 = wave * 16; t0 < a.Tn; t0 += NW * 16) {
+        if (t0 + 16 <= a.Tn) block16(t0, std::true_type());
+        else block16(t0, std::false_type());
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sums[wave][v][lane] = acc[v];
+    sums1[wave][lane] = sum;
+    if constexpr (kCut) {
+        const bool mine = __any(too_large(most));
+        if (lane == 0) large[wave] = mine;
+    }
+    __syncthreads();
+    float down = 1.0f;
+    if constexpr (kCut) {
+        down = kCutDown;
+        if (__any(large[lane % NW])) {                    // the same in every wave: its steps again with binary32 products
+            down = 1.0f;
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+            for (int t0 = wave * 16; t0 < a.Tn; t0 += NW * 16)
+                for (int t2 = t0; t2 < t0 + 16 && t2 < a.Tn; t2 += 2) {
+                    const int t = t2 + half < a.Tn ? t2 + half : a.Tn - 1;
+                    const int64_t po = int64_t(r) * a.p_rs + int64_t(t) * a.p_ts, qo = int64_t(t) * a.q_ts + int64_t(c) * a.q_cs;
+                    const float code = float(int(yb[P_CODED ? po : qo])), x = t2 + half < a.Tn ? float(xb[P_CODED ? qo : po]) : 0.0f;
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(P_CODED ? code : x, P_CODED ? x : code, acc, 0, 0, 0);
+                }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sums[wave][v][lane] = acc[v];
+            __syncthreads();
+        }
+    }
+
+    // a wave takes every NW-th register v of the tile: row 8 * (v / 4) + 4 * (lane / 32) + v % 4, column lane % 32
+    const float s = a.alpha[h] / 255.0f, off = fmaf(BmNum<ET>::kCentre, s, a.beta[h]);
+    X *cb = reinterpret_cast<X *>(a.c) + int64_t(b) * a.c_batch;
+    const int col = c0 + l32;
+    Sum of_col = 0;                                       // the sum of the plain operand's column
+    if constexpr (P_CODED) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) of_col += sums1[w][l32] + sums1[w][32 + l32];
+    }
+#pragma unroll
+    for (int v = wave; v < 16; v += NW) {
+        const int rl = (v >> 2) * 8 + half * 4 + (v & 3);
+        Sum t1 = of_col;
+        if constexpr (!P_CODED) {                         // of its row: a part per lane of the half wave
+            t1 = l32 < 2 * NW ? sums1[l32 / 2 % NW][(l32 & 1) * 32 + rl] : Sum(0);
+#pragma unroll
+            for (int x = 16; x > 0; x >>= 1) t1 += __shfl_xor(t1, x, 64);
+        }
+        float p[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) p[w] = sums[w][v][lane];
+#pragma unroll
+        for (int w = NW / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int i = 0; i < w; ++i) p[i] += p[i + w];
+        if (r0 + rl < a.R && col < a.Cn)
+            cb[uint32_t(r0 + rl) * uint32_t(a.Cn) + uint32_t(col)] = BmNum<ET>::round(a.scale * fmaf(s, p[0] * down, off * float(t1)));
+    }
+}
+
+// Waves of k_bmm_waves's workgroups where it is the faster kernel, else 0: no more than there are blocks of steps, and as many
+// workgroups as run at once (binary32, whose other kernel is the general one alone: half as many again, or twice).  Two products, kernels chosen
+// by da_way, tn_way and nn_way -> this one, dA and dV / dQ and dK: (6, 197, 64) f16 9.3 -> 8.4 / 11.0 -> 9.1 us, f32 12.2 -> 9.1 / 17.3 -> 9.3; (3, 1005, 32) f16
+// - / 22.8 -> 15.2; (6, 574, 64) - / 17.1 -> 10.8; (6, 426, 64) f32 16.3 -> 11.8 / 24.0 -> 11.2; lines, in 16 bits: (6, 1015, 64), 384 tiles of dV, 30.3 -> 23.0 and
+// (12, 498, 96), 576, 17.7 -> 17.9, (48, 108, 96), 576, 10.0 -> 12.3; dA with four waves (24, 199, 64), 1176 tiles, +0.3, (32, 248, 64), 2048, +3; with eight
+// (32, 147, 96), 800, +0.8.  binary32: (12, 783, 64), 600, 43 -> 32; (16, 746, 40), 768, 39 -> 34; (16, 1000, 40), 1024, 46 -> 52.
+template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t Cn, int64_t Tn)
+{
+    constexpr bool kWide = std::is_same<ET, float>::value;
+    const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
+    if (tiles <= 256 && Tn > 128) return 16;
+    if (Tn > 64) return tiles <= (kWide ? 800 : 512) ? 8 : 0;
+    return tiles <= (kWide ? 2048 : 1024) ? 4 : 0;
+}
+
+template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET>
+static bool launch_bmm_waves(BmmArgs a, int64_t batches, hipStream_t s)
+{
+    const int nw = bmm_waves<ET>(batches, a.R, a.Cn, a.Tn);
+    if (nw == 0) return false;
+    a.tiles_r = int(ceil_div(a.R, 32));
+    a.tiles_c = int(ceil_div(a.Cn, 32));
+    const dim3 grid(unsigned(batches * a.tiles_r * a.tiles_c));
+    if (nw == 16) hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 16>), grid, dim3(1024), 0, s, a);
+    else if (nw == 8) hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 4>), grid, dim3(256), 0, s, a);
+    return true;
 }
 
 // The plain kernel: bmm_plain_sums alone.  Kept simple: it serves extents shorter than one load vector.  T: the tensors'
@@ -1927,6 +2116,7 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     }
 #define MESA_AV_DA(ET) \
     do { \
+        if (launch_bmm_waves<false, true, true, ET>(a, batches, s)) break; \
         const AttnWay way = da_way(batches, N, Dh); \
         if (way == kWayTiles) launch_da_cols<ET>(a.x, vq, a.c, batches, int(N), int(Dh), int(H), alpha_v, beta_v, s); \
         else if (way == kWayGeneral) launch_bmm<false, true, true, ET>(a, batches, s); \
@@ -1935,8 +2125,9 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         else if (Dh == 96) launch_da<6, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
         else launch_da<8, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
     } while (0)
-    if (dt == MESA_F32) launch_bmm<false, true, true, float>(a, batches, s);
-    else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
+    if (dt == MESA_F32) {
+        if (!launch_bmm_waves<false, true, true, float>(a, batches, s)) launch_bmm<false, true, true, float>(a, batches, s);
+    } else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
 #undef MESA_AV_DA
     // dV[j,d] = sum_i A_hat[i,j] * dO[i,d]:  P = A (r = j, t = i),  Q = dO (t = i, c = d)
     a.y = aq; a.c = static_cast<_Float16 *>(dV);
@@ -1946,13 +2137,15 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     a.alpha = alpha_a; a.beta = beta_a;
 #define MESA_AV_DV(ET) \
     do { \
+        if (launch_bmm_waves<true, false, false, ET>(a, batches, s)) break; \
         const AttnWay way = tn_way<true>(batches, N, Dh); \
         if (way == kWayTiles) launch_tn_cols<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
         else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
         else launch_bmm<true, false, false, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_F32) launch_bmm<true, false, false, float>(a, batches, s);
-    else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
+    if (dt == MESA_F32) {
+        if (!launch_bmm_waves<true, false, false, float>(a, batches, s)) launch_bmm<true, false, false, float>(a, batches, s);
+    } else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
 #undef MESA_AV_DV
     return launch_status();
 }
@@ -1992,6 +2185,7 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
     }
 #define MESA_QK_DQ(ET) \
     do { \
+        if (launch_bmm_waves<false, true, false, ET>(a, batches, s)) break; \
         const AttnWay way = nn_way(batches, N, Dh); \
         if (way == kWayTiles) launch_nn_rows<ET>(a.x, kq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_k, beta_k, s); \
         else if (way == kWayGeneral) launch_bmm<false, true, false, ET>(a, batches, s); \
@@ -1999,8 +2193,9 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
         else if (Dh == 64) launch_nn<2, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
         else launch_nn<4, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
     } while (0)
-    if (dt == MESA_F32) launch_bmm<false, true, false, float>(a, batches, s);
-    else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
+    if (dt == MESA_F32) {
+        if (!launch_bmm_waves<false, true, false, float>(a, batches, s)) launch_bmm<false, true, false, float>(a, batches, s);
+    } else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
 #undef MESA_QK_DQ
     // dK[j,d] = scale * sum_i dS[i,j] * Q_hat[i,d]:  P = dS (r = j, t = i),  Q = Q codes (t = i, c = d)
     a.y = qq; a.c = static_cast<_Float16 *>(dK);
@@ -2008,13 +2203,15 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
     a.alpha = alpha_q; a.beta = beta_q;
 #define MESA_QK_DK(ET) \
     do { \
+        if (launch_bmm_waves<false, false, false, ET>(a, batches, s)) break; \
         const AttnWay way = tn_way<false>(batches, N, Dh); \
         if (way == kWayTiles) launch_tn_cols<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
         else if (way == kWayWhole) launch_tn<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
         else launch_bmm<false, false, false, ET>(a, batches, s); \
     } while (0)
-    if (dt == MESA_F32) launch_bmm<false, false, false, float>(a, batches, s);
-    else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
+    if (dt == MESA_F32) {
+        if (!launch_bmm_waves<false, false, false, float>(a, batches, s)) launch_bmm<false, false, false, float>(a, batches, s);
+    } else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
 #undef MESA_QK_DK
     return launch_status();
 }
