@@ -584,20 +584,33 @@ template <bool CODED, bool TFAST, typename ET> struct BmLane {
     }
 };
 
-template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET, int NW>
-__global__ __launch_bounds__(64 * NW) void k_bmm_waves(BmmArgs a)
-{
-    typedef typename BmElem<false, ET>::global_t X;
-    constexpr bool kCut = std::is_same<ET, float>::value;
-    constexpr int kPlanes = BmElem<false, ET>::kPlanes;
-    __shared__ float sums[NW][16][64];                    // accumulator register v of a wave's lane
+template <typename ET, int NW> struct BmWavesLds {
     // sums of the plain operand's line lane % 32, this half's steps: the matrix cores added sixteen values with one rounding, eight binary32
     // values one by one do not (dA of 32-wide heads 6.3e-8 -> 6.9e-8), hence binary64
-    typedef typename std::conditional<kCut, double, float>::type Sum;
-    __shared__ Sum sums1[NW][64];
-    __shared__ int large[NW];                             // the wave met a value that is too large to be cut
+    typedef typename std::conditional<std::is_same<ET, float>::value, double, float>::type Sum;
+    float sums[NW][16][64];                               // accumulator register v of a wave's lane
+    Sum sums1[NW][64];
+    int large[NW];                                        // the wave met a value that is too large to be cut
+};
+
+// what a product is: which operand is coded, and whose unit-stride index the contraction is
+template <bool P_CODED_, bool P_TFAST_, bool Q_TFAST_> struct BmProduct {
+    static constexpr bool P_CODED = P_CODED_, P_TFAST = P_TFAST_, Q_TFAST = Q_TFAST_;
+};
+
+template <typename PR, typename ET, int NW>
+__device__ __forceinline__ void bmm_waves_tile(const BmmArgs &a, uint32_t block, BmWavesLds<ET, NW> &lds)
+{
+    constexpr bool P_CODED = PR::P_CODED, P_TFAST = PR::P_TFAST, Q_TFAST = PR::Q_TFAST;
+    typedef typename BmElem<false, ET>::global_t X;
+    typedef typename BmWavesLds<ET, NW>::Sum Sum;
+    constexpr bool kCut = std::is_same<ET, float>::value;
+    constexpr int kPlanes = BmElem<false, ET>::kPlanes;
+    auto &sums = lds.sums;
+    auto &sums1 = lds.sums1;
+    auto &large = lds.large;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), half = lane >> 5, l32 = lane & 31;
-    const uint32_t block = xcd_block(blockIdx.x, gridDim.x), tiles = uint32_t(a.tiles_r) * uint32_t(a.tiles_c);
+    const uint32_t tiles = uint32_t(a.tiles_r) * uint32_t(a.tiles_c);
     const uint32_t b = block / tiles, tile = block - b * tiles, tr = tile / uint32_t(a.tiles_c);
     const int r0 = int(tr) * 32, c0 = int(tile - tr * uint32_t(a.tiles_c)) * 32;
     const uint32_t h = b % uint32_t(a.heads);
@@ -707,11 +720,28 @@ __global__ __launch_bounds__(64 * NW) void k_bmm_waves(BmmArgs a)
     }
 }
 
+template <typename PR, typename ET, int NW>
+__global__ __launch_bounds__(64 * NW) void k_bmm_waves(BmmArgs a)
+{
+    __shared__ BmWavesLds<ET, NW> lds;
+    bmm_waves_tile<PR>(a, xcd_block(blockIdx.x, gridDim.x), lds);
+}
+
+// Two products of one call in one launch, the first one's tiles first: neither waits for the other, and a launch costs the host 3.7 us.
+template <typename PR1, typename PR2, typename ET, int NW>
+__global__ __launch_bounds__(64 * NW) void k_bmm_waves_two(BmmArgs a, BmmArgs b, uint32_t first)
+{
+    __shared__ BmWavesLds<ET, NW> lds;
+    const uint32_t block = xcd_block(blockIdx.x, gridDim.x);
+    if (block < first) bmm_waves_tile<PR1>(a, block, lds);   // uniform
+    else bmm_waves_tile<PR2>(b, block - first, lds);
+}
+
 // Waves of k_bmm_waves's workgroups where it is the faster kernel, else 0: no more than there are blocks of steps, and as many
 // workgroups as run at once (binary32, whose other kernel is the general one alone: half as many again, or twice).  Two products, kernels chosen
 // by da_way, tn_way and nn_way -> this one, dA and dV / dQ and dK: (6, 197, 64) f16 9.3 -> 8.4 / 11.0 -> 9.1 us, f32 12.2 -> 9.1 / 17.3 -> 9.3; (3, 1005, 32) f16
 // - / 22.8 -> 15.2; (6, 574, 64) - / 17.1 -> 10.8; (6, 426, 64) f32 16.3 -> 11.8 / 24.0 -> 11.2; lines, in 16 bits: (6, 1015, 64), 384 tiles of dV, 30.3 -> 23.0 and
-// (12, 498, 96), 576, 17.7 -> 17.9, (48, 108, 96), 576, 10.0 -> 12.3; dA with four waves (24, 199, 64), 1176 tiles, +0.3, (32, 248, 64), 2048, +3; with eight
+// (12, 498, 96), 576, 17.7 -> 17.9, (48, 108, 96), 576, 10.0 -> 12.3; dA with four waves (16, 195, 64), 784 tiles, -0.2, (24, 165, 64), 864, +0.5, (32, 248, 64), 2048, +3; with eight
 // (32, 147, 96), 800, +0.8.  binary32: (12, 783, 64), 600, 43 -> 32; (16, 746, 40), 768, 39 -> 34; (16, 1000, 40), 1024, 46 -> 52.
 template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t Cn, int64_t Tn)
 {
@@ -719,21 +749,54 @@ template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t 
     const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
     if (tiles <= 256 && Tn > 128) return 16;
     if (Tn > 64) return tiles <= (kWide ? 800 : 512) ? 8 : 0;
-    return tiles <= (kWide ? 2048 : 1024) ? 4 : 0;
+    return tiles <= (kWide ? 2048 : 800) ? 4 : 0;
+}
+
+static int64_t bmm_waves_tiles(BmmArgs &a, int64_t batches)
+{
+    a.tiles_r = int(ceil_div(a.R, 32));
+    a.tiles_c = int(ceil_div(a.Cn, 32));
+    return batches * a.tiles_r * a.tiles_c;
 }
 
 template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET>
 static bool launch_bmm_waves(BmmArgs a, int64_t batches, hipStream_t s)
 {
+    typedef BmProduct<P_CODED, P_TFAST, Q_TFAST> PR;
     const int nw = bmm_waves<ET>(batches, a.R, a.Cn, a.Tn);
     if (nw == 0) return false;
-    a.tiles_r = int(ceil_div(a.R, 32));
-    a.tiles_c = int(ceil_div(a.Cn, 32));
-    const dim3 grid(unsigned(batches * a.tiles_r * a.tiles_c));
-    if (nw == 16) hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 16>), grid, dim3(1024), 0, s, a);
-    else if (nw == 8) hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 8>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_bmm_waves<P_CODED, P_TFAST, Q_TFAST, ET, 4>), grid, dim3(256), 0, s, a);
+    const dim3 grid{unsigned(bmm_waves_tiles(a, batches))};
+    if (nw == 16) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 16>), grid, dim3(1024), 0, s, a);
+    else if (nw == 8) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_bmm_waves<PR, ET, 4>), grid, dim3(256), 0, s, a);
     return true;
+}
+
+// Both products, where both of them would go that way; with different numbers of steps the shorter one's spare waves keep others from running,
+// and two launches are the better ones from some 850 tiles on.  dA and dV / dQ and dK, two launches -> one: (6, 197, 64) f16 8.3 -> 5.0 / 9.1 -> 5.0 us, f32
+// 9.0 -> 5.4 / 9.4 -> 5.2; (24, 97, 64) 7.3 -> 6.0 / 7.4 -> 5.0; dA and dV (12, 219, 64), 756 tiles, 8.9 -> 7.3, (16, 195, 64), 1008, 9.1 -> 8.4, (6, 330, 64) f32, 858, 10.3 -> 11.1,
+// (9, 293, 64), 1080, 9.6 -> 10.2, (6, 398, 64) f32, 2340, 17 -> 26; dQ and dK (32, 248, 64), 1024, 10.5 -> 9.5.
+template <typename PR1, typename PR2, typename ET>
+static bool launch_bmm_waves_two(BmmArgs a, BmmArgs b, int64_t batches, hipStream_t s)
+{
+    const int na = bmm_waves<ET>(batches, a.R, a.Cn, a.Tn), nb = bmm_waves<ET>(batches, b.R, b.Cn, b.Tn);
+    if (na == 0 || nb == 0) return false;
+    const int64_t first = bmm_waves_tiles(a, batches), all = first + bmm_waves_tiles(b, batches);
+    if (a.Tn != b.Tn && all > 850) return false;
+    const int most = na > nb ? na : nb, nw = most == 16 && all > 256 ? 8 : most;
+    const dim3 grid{unsigned(all)};
+    if (nw == 16) hipLaunchKernelGGL((k_bmm_waves_two<PR1, PR2, ET, 16>), grid, dim3(1024), 0, s, a, b, uint32_t(first));
+    else if (nw == 8) hipLaunchKernelGGL((k_bmm_waves_two<PR1, PR2, ET, 8>), grid, dim3(512), 0, s, a, b, uint32_t(first));
+    else hipLaunchKernelGGL((k_bmm_waves_two<PR1, PR2, ET, 4>), grid, dim3(256), 0, s, a, b, uint32_t(first));
+    return true;
+}
+
+template <typename PR1, typename PR2>
+static bool launch_bmm_waves_two(BmmArgs a, BmmArgs b, int64_t batches, mesa_dtype dt, hipStream_t s)
+{
+    if (dt == MESA_F32) return launch_bmm_waves_two<PR1, PR2, float>(a, b, batches, s);
+    if (dt == MESA_BF16) return launch_bmm_waves_two<PR1, PR2, __bf16>(a, b, batches, s);
+    return launch_bmm_waves_two<PR1, PR2, _Float16>(a, b, batches, s);
 }
 
 // The plain kernel: bmm_plain_sums alone.  Kept simple: it serves extents shorter than one load vector.  T: the tensors'
@@ -2104,16 +2167,19 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     a.R = int(N); a.Cn = int(N); a.Tn = int(Dh);
     a.p_rs = Dh; a.p_ts = 1; a.q_ts = 1; a.q_cs = Dh;
     a.alpha = alpha_v; a.beta = beta_v;
+    // dV[j,d] = sum_i A_hat[i,j] * dO[i,d]:  P = A (r = j, t = i),  Q = dO (t = i, c = d)
+    BmmArgs v = a;
+    v.y = aq; v.c = static_cast<_Float16 *>(dV);
+    v.y_batch = N * N; v.c_batch = N * Dh;
+    v.R = int(N); v.Cn = int(Dh); v.Tn = int(N);
+    v.p_rs = 1; v.p_ts = N; v.q_ts = Dh; v.q_cs = 1;
+    v.alpha = alpha_a; v.beta = beta_a;
     if (N < 8 || Dh < 8) {   // an extent shorter than one load vector: the plain kernel
         launch_bmm_plain<false>(a, batches, dt, s);
-        a.y = aq; a.c = static_cast<_Float16 *>(dV);
-        a.y_batch = N * N; a.c_batch = N * Dh;
-        a.R = int(N); a.Cn = int(Dh); a.Tn = int(N);
-        a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
-        a.alpha = alpha_a; a.beta = beta_a;
-        launch_bmm_plain<true>(a, batches, dt, s);
+        launch_bmm_plain<true>(v, batches, dt, s);
         return launch_status();
     }
+    if (launch_bmm_waves_two<BmProduct<false, true, true>, BmProduct<true, false, false>>(a, v, batches, dt, s)) return launch_status();
 #define MESA_AV_DA(ET) \
     do { \
         if (launch_bmm_waves<false, true, true, ET>(a, batches, s)) break; \
@@ -2129,22 +2195,16 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         if (!launch_bmm_waves<false, true, true, float>(a, batches, s)) launch_bmm<false, true, true, float>(a, batches, s);
     } else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
 #undef MESA_AV_DA
-    // dV[j,d] = sum_i A_hat[i,j] * dO[i,d]:  P = A (r = j, t = i),  Q = dO (t = i, c = d)
-    a.y = aq; a.c = static_cast<_Float16 *>(dV);
-    a.y_batch = N * N; a.c_batch = N * Dh;
-    a.R = int(N); a.Cn = int(Dh); a.Tn = int(N);
-    a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
-    a.alpha = alpha_a; a.beta = beta_a;
 #define MESA_AV_DV(ET) \
     do { \
-        if (launch_bmm_waves<true, false, false, ET>(a, batches, s)) break; \
+        if (launch_bmm_waves<true, false, false, ET>(v, batches, s)) break; \
         const AttnWay way = tn_way<true>(batches, N, Dh); \
-        if (way == kWayTiles) launch_tn_cols<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
-        else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, a.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
-        else launch_bmm<true, false, false, ET>(a, batches, s); \
+        if (way == kWayTiles) launch_tn_cols<true, ET>(aq, dO, v.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
+        else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, v.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
+        else launch_bmm<true, false, false, ET>(v, batches, s); \
     } while (0)
     if (dt == MESA_F32) {
-        if (!launch_bmm_waves<true, false, false, float>(a, batches, s)) launch_bmm<true, false, false, float>(a, batches, s);
+        if (!launch_bmm_waves<true, false, false, float>(v, batches, s)) launch_bmm<true, false, false, float>(v, batches, s);
     } else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
 #undef MESA_AV_DV
     return launch_status();
@@ -2175,17 +2235,19 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
     a.y = kq; a.c = static_cast<_Float16 *>(dQ);
     a.p_rs = N; a.p_ts = 1; a.q_ts = Dh; a.q_cs = 1;
     a.alpha = alpha_k; a.beta = beta_k;
+    // dK[j,d] = scale * sum_i dS[i,j] * Q_hat[i,d]:  P = dS (r = j, t = i),  Q = Q codes (t = i, c = d)
+    BmmArgs k = a;
+    k.y = qq; k.c = static_cast<_Float16 *>(dK);
+    k.p_rs = 1; k.p_ts = N; k.q_ts = Dh; k.q_cs = 1;
+    k.alpha = alpha_q; k.beta = beta_q;
     if (N < 8 || Dh < 8) {
         launch_bmm_plain<false>(a, batches, dt, s);
-        a.y = qq; a.c = static_cast<_Float16 *>(dK);
-        a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
-        a.alpha = alpha_q; a.beta = beta_q;
-        launch_bmm_plain<false>(a, batches, dt, s);
+        launch_bmm_plain<false>(k, batches, dt, s);
         return launch_status();
     }
+    if (launch_bmm_waves_two<BmProduct<false, true, false>, BmProduct<false, false, false>>(a, k, batches, dt, s)) return launch_status();
 #define MESA_QK_DQ(ET) \
     do { \
-        if (launch_bmm_waves<false, true, false, ET>(a, batches, s)) break; \
         const AttnWay way = nn_way(batches, N, Dh); \
         if (way == kWayTiles) launch_nn_rows<ET>(a.x, kq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_k, beta_k, s); \
         else if (way == kWayGeneral) launch_bmm<false, true, false, ET>(a, batches, s); \
@@ -2193,25 +2255,18 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
         else if (Dh == 64) launch_nn<2, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
         else launch_nn<4, ET>(a.x, kq, a.c, batches, int(N), int(H), scale, alpha_k, beta_k, s); \
     } while (0)
-    if (dt == MESA_F32) {
-        if (!launch_bmm_waves<false, true, false, float>(a, batches, s)) launch_bmm<false, true, false, float>(a, batches, s);
-    } else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
+    if (dt == MESA_F32) launch_bmm<false, true, false, float>(a, batches, s);
+    else if (dt == MESA_BF16) MESA_QK_DQ(__bf16); else MESA_QK_DQ(_Float16);
 #undef MESA_QK_DQ
-    // dK[j,d] = scale * sum_i dS[i,j] * Q_hat[i,d]:  P = dS (r = j, t = i),  Q = Q codes (t = i, c = d)
-    a.y = qq; a.c = static_cast<_Float16 *>(dK);
-    a.p_rs = 1; a.p_ts = N; a.q_ts = Dh; a.q_cs = 1;
-    a.alpha = alpha_q; a.beta = beta_q;
 #define MESA_QK_DK(ET) \
     do { \
-        if (launch_bmm_waves<false, false, false, ET>(a, batches, s)) break; \
         const AttnWay way = tn_way<false>(batches, N, Dh); \
-        if (way == kWayTiles) launch_tn_cols<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
-        else if (way == kWayWhole) launch_tn<false, ET>(dS, qq, a.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
-        else launch_bmm<false, false, false, ET>(a, batches, s); \
+        if (way == kWayTiles) launch_tn_cols<false, ET>(dS, qq, k.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
+        else if (way == kWayWhole) launch_tn<false, ET>(dS, qq, k.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
+        else launch_bmm<false, false, false, ET>(k, batches, s); \
     } while (0)
-    if (dt == MESA_F32) {
-        if (!launch_bmm_waves<false, false, false, float>(a, batches, s)) launch_bmm<false, false, false, float>(a, batches, s);
-    } else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
+    if (dt == MESA_F32) launch_bmm<false, false, false, float>(k, batches, s);
+    else if (dt == MESA_BF16) MESA_QK_DK(__bf16); else MESA_QK_DK(_Float16);
 #undef MESA_QK_DK
     return launch_status();
 }

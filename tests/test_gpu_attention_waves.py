@@ -53,7 +53,8 @@ def run(M, B, H, N, Dh, dtype, large):
 @pytest.mark.parametrize("B,H,N,Dh", [
     (1, 1, 8, 8), (1, 3, 15, 24), (2, 1, 17, 64), (1, 2, 31, 65), (3, 1, 33, 33), (1, 2, 64, 96), (2, 2, 65, 64), (1, 1, 127, 128), (1, 2, 128, 130), (1, 3, 129, 40),
     (2, 3, 197, 64), (1, 1, 257, 64), (1, 2, 513, 32), (1, 1, 1031, 64),
-    (16, 4, 128, 64), (13, 5, 127, 64), (16, 2, 256, 64), (16, 1, 256, 64), (17, 1, 255, 64),       # 512, 1024 and 256 tiles, and more
-    (10, 10, 128, 64), (21, 5, 120, 64), (8, 4, 250, 64), (9, 12, 197, 64)])                         # 800 and 2048, and more; beyond them all
+    (16, 4, 128, 64), (13, 5, 127, 64), (16, 2, 256, 64), (16, 1, 256, 64), (17, 1, 255, 64),       # 512 and 256 tiles, and more
+    (10, 10, 128, 64), (21, 5, 120, 64), (8, 4, 250, 64), (9, 12, 197, 64),                          # 800 and more; beyond them all
+    (53, 4, 64, 32), (17, 3, 128, 64), (9, 4, 150, 32)])
 def test_attention_products_with_few_heads(M, B, H, N, Dh, dtype, large):
     run(M, B, H, N, Dh, dtype, large)
