@@ -2191,9 +2191,11 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         else if (Dh == 96) launch_da<6, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
         else launch_da<8, ET>(a.x, vq, a.c, batches, int(N), int(H), alpha_v, beta_v, s); \
     } while (0)
-    if (dt == MESA_F32) {
-        if (!launch_bmm_waves<false, true, true, float>(a, batches, s)) launch_bmm<false, true, true, float>(a, batches, s);
-    } else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
+    auto da = [&]() {
+        if (dt == MESA_F32) {
+            if (!launch_bmm_waves<false, true, true, float>(a, batches, s)) launch_bmm<false, true, true, float>(a, batches, s);
+        } else if (dt == MESA_BF16) MESA_AV_DA(__bf16); else MESA_AV_DA(_Float16);
+    };
 #undef MESA_AV_DA
 #define MESA_AV_DV(ET) \
     do { \
@@ -2203,10 +2205,23 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, v.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
         else launch_bmm<true, false, false, ET>(v, batches, s); \
     } while (0)
-    if (dt == MESA_F32) {
-        if (!launch_bmm_waves<true, false, false, float>(v, batches, s)) launch_bmm<true, false, false, float>(v, batches, s);
-    } else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
+    auto dv = [&]() {
+        if (dt == MESA_F32) {
+            if (!launch_bmm_waves<true, false, false, float>(v, batches, s)) launch_bmm<true, false, false, float>(v, batches, s);
+        } else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
+    };
 #undef MESA_AV_DV
+    // A dA that is larger than the memory-side cache (256 MB) is still leaving it while the next kernel reads: dV, bound by its reads, goes first
+    // then.  (1, 16, 4096, 64) bfloat16, 537 MB: dV 100 -> 70 us, softmax behind dA 191 -> 211, the whole attention backward 623 -> 595; (1, 8, 4096, 64), 268 MB,
+    // 350 -> 330; (16, 12, 1024, 64), 403 MB, 504 -> 486; (32, 12, 577, 64), 256 MB, 417 -> 405.  A smaller one had better stay for softmax: (8, 12, 1024, 64),
+    // 201 MB, 250 -> 256.  Whole-head dA (sequences of 197: 862 -> 866) and binary32 (634 -> 644) are bound by other things.
+    if (dt != MESA_F32 && batches * N * N > (int64_t(1) << 27) && da_way(batches, N, Dh) == kWayTiles) {
+        dv();
+        da();
+    } else {
+        da();
+        dv();
+    }
     return launch_status();
 }
 

@@ -55,3 +55,9 @@ def test_attention_products_with_many_heads(M, B, H, N, Dh, dtype):
         assert err <= BOUND[dtype], (name, err)
         assert intact(frame_), name
         del r
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+def test_attention_products_with_a_map_larger_than_the_memory_side_cache(M, dtype):
+    """dV before dA."""
+    test_attention_products_with_many_heads(M, 1, 33, 2049, 32, dtype)
