@@ -20,7 +20,8 @@
 // is multiplied.  binary16 or bfloat16 tensors (every kernel here takes the number type as a parameter);
 // binary32 tensors run the general kernel on three bfloat16 parts.
 //
-// That general kernel (k_bmm_q) serves every shape; dedicated kernels take over where there is work enough for them (da_way, tn_way,
+// That general kernel (k_bmm_q) serves every shape; few heads go to k_bmm_waves (bmm_waves), a launch with both of a call's products;
+// dedicated kernels take over where there is work enough for them (da_way, tn_way,
 // nn_way): k_attn_da, k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths
 // included, and k_attn_da_cols, k_attn_tn_cols, k_attn_nn_rows, by tiles, for sequences of any length from 64 on (a pitch of N elements
 // with N a multiple of 32 puts the first three kernels' lanes on the same LDS banks).  The tile kernels' rows may start at any
