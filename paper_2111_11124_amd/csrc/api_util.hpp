@@ -51,23 +51,28 @@ inline mesa_status launch_status()
     return hipGetLastError() == hipSuccess ? MESA_OK : MESA_ERR_LAUNCH;
 }
 
+// The number of workgroups of `per_wg_iter` elements each whose multiples make a grid step a whole number of rows of `row` elements;
+// 1 where that is too many, or there are no rows.
+inline int64_t row_multiple(int64_t per_wg_iter, int64_t row)
+{
+    if (row <= 0) return 1;
+    int64_t a = per_wg_iter, b = row;
+    while (b) { int64_t t = a % b; a = b; b = t; }
+    return row / a <= 64 ? row / a : 1;
+}
+
 // Number of workgroups for a grid-stride streaming kernel in which every workgroup moves
-// `per_wg_iter` elements per iteration: at most `cap` workgroups, iterations spread evenly, and --
-// when it costs little -- a count that makes one grid step a whole number of rows of `row`
-// elements, so that a thread keeps meeting the same channel group.
+// `per_wg_iter` elements per iteration: at most `cap` workgroups, iterations spread evenly, and then --
+// when it costs little -- rounded up, by 63 at most and beyond `cap` too, to a count that makes one grid step a whole number of rows of
+// `row` elements, so that a thread keeps meeting the same channel group.
 inline int plan_grid(int64_t numel, int64_t per_wg_iter, int cap, int64_t row)
 {
     int64_t wgs_needed = ceil_div(numel, per_wg_iter);
     if (wgs_needed < 1) wgs_needed = 1;
     int64_t iters = ceil_div(wgs_needed, cap);
     int64_t n = ceil_div(wgs_needed, iters);
-    if (row > 0) {
-        int64_t a = per_wg_iter, b = row;
-        while (b) { int64_t t = a % b; a = b; b = t; }
-        int64_t mult = row / a;  // grid must be a multiple of this
-        if (mult > 1 && mult <= 64) n = ceil_div(n, mult) * mult;
-    }
-    return int(n);
+    const int64_t mult = row_multiple(per_wg_iter, row);
+    return int(ceil_div(n, mult) * mult);
 }
 
 }  // namespace mesa

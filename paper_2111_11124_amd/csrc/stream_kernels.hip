@@ -1101,7 +1101,12 @@ static int minmax_grid(const mesa_layout &L, int unroll = kMmU, int grid_cap = k
     }
     if (max_wgs > 0 && cap > max_wgs) cap = max_wgs;
     const int64_t chunk = int64_t(kThreads) * unroll * kVec;
-    int n = plan_grid(numel, chunk, cap, L.groups > 1 ? L.groups * L.inner : 0);
+    const int64_t cycle = L.groups > 1 ? L.groups * L.inner : 0;
+    int n = plan_grid(numel, chunk, cap, cycle);
+    if (max_wgs > 0 && n > max_wgs) {              // rounded up beyond what there is room for: the largest multiple that fits, or all of it
+        const int mult = int(row_multiple(chunk, cycle));
+        n = mult <= max_wgs ? max_wgs / mult * mult : max_wgs;
+    }
     // Long slabs (head-wise tensors): a thread hands its extrema to LDS whenever its group changes,
     // so pick a grid whose step is a whole number of group cycles plus a small remainder -- then a
     // thread stays with one head for many iterations instead of meeting a new one every time.

@@ -59,11 +59,18 @@ def report(x): print("REPORT " + json.dumps(x))
 '''
 
 
-def run(body):
-    """What `body` hands to report(), run after PRELUDE."""
+# for `also`: the device and its scratch array, for calls that ask the runtime where the library's own array lies
+ONE_DEVICE = r'''
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipGetSymbolAddress(void **p, const void *symbol) { *p = (void *)0x100000; return 0; }
+'''
+
+
+def run(body, also=""):
+    """What `body` hands to report(), run after PRELUDE; `also`: further functions of the runtime, in C."""
     with tempfile.TemporaryDirectory() as d:
         so = os.path.join(d, "recorder.so")
-        open(os.path.join(d, "recorder.c"), "w").write(SOURCE)
+        open(os.path.join(d, "recorder.c"), "w").write(SOURCE + also)
         subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", os.path.join(d, "recorder.c"), "-o", so], check=True)
         out = subprocess.run([sys.executable, "-c", PRELUDE + body, so, ROOT], capture_output=True, text=True, timeout=600)
         assert out.returncode == 0, out.stderr[-3000:]
