@@ -2050,9 +2050,10 @@ static void launch_tn_cols(const void *wide, const void *narrow, _Float16 *out, 
     const int64_t wgs = batches * tiles_j;
     // groups per workgroup, by the workgroups there are: (1, 16, 4096, 64), 256 of them, 759 / 644 / 630 us for the whole
     // attention backward with 1 / 2 / 4 groups; (2, 16, 4096, 64), 512: 1269 / 1235 / 1251; (8, 12, 1024, 64), 384:
-    // 261 / 254 / 265; (16, 12, 576, 64), 576: 188 / 200 / 210; short columns pay the adding sooner: (16, 12, 256, 64),
-    // 192: 61.0 / 57.9 / 60.7
-    const int rs = wgs > 512 ? 1 : wgs <= 256 && N >= 1024 && Dh <= 64 ? 4 : 2;
+    // 261 / 254 / 265; (16, 12, 576, 64), 576: 188 / 200 / 210.  At heads of 96 and 128 two groups fill a CU's registers, and more workgroups than CUs take a
+    // second round: dA and dV with two groups -> one, (275, 256, 96) 35.3 -> 30.2 us, (313, 140, 96) 26.7 -> 20.8, (374, 64, 128) 18.8 -> 12.0.  Below 128 rows a
+    // group has four chunks or fewer and the adding costs more than it saves: (366, 112, 64) 15.3 -> 14.2, dQ and dK 14.0 -> 13.0.
+    const int rs = N < 128 || wgs > (Dh <= 64 ? 512 : 256) ? 1 : wgs <= 256 && N >= 1024 && Dh <= 64 ? 4 : 2;
 #define MESA_LAUNCH_TC(DT_, RS_) \
     do { \
         const dim3 grid{unsigned(wgs)}, block(TcCfg<DT_, WIDE_CODED, RS_>::kNt * (RS_)); \

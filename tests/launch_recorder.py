@@ -17,6 +17,8 @@ static size_t shared;
 static void *stream;
 static int last;
 static unsigned log_[64][6];
+static const void *kernel_[64];
+static unsigned shared_[64];
 static int count;
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, void *s) { grid = g; block = b; shared = sh; stream = s; return 0; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, void **s) { *g = grid; *b = block; *sh = shared; *s = stream; return 0; }
@@ -29,6 +31,8 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh, void 
     if (count < 64) {
         const unsigned v[6] = {g.x, g.y, g.z, b.x, b.y, b.z};
         for (int i = 0; i < 6; ++i) log_[count][i] = v[i];
+        kernel_[count] = f;
+        shared_[count] = (unsigned)sh;
     }
     ++count;
     return 0;
@@ -55,9 +59,41 @@ def launches():
     out = (C.c_uint * (64 * 6))()
     n = rec.recorded(out)
     return [tuple(out[i * 6:i * 6 + 6]) for i in range(n)]
+def kernels():
+    """(name, template arguments as they are mangled, workgroups, threads of one, dynamic LDS) per launch, with NAMES"""
+    import math, re
+    rec.recorded_kernel.restype = C.c_char_p
+    names = [(rec.recorded_kernel(i).decode(), rec.recorded_shared(i)) for i in range(64)]
+    out = []
+    for k, (mangled, lds) in zip(launches(), names):
+        n = re.match(r"_ZN4mesa(\d+)", mangled)
+        at = n.end() + int(n.group(1))
+        args = mangled[at + 1:mangled.index("EEv", at)] if mangled[at] == "I" else ""
+        out.append((mangled[n.end():at], args, math.prod(k[:3]), math.prod(k[3:]), lds))
+    return out
 def report(x): print("REPORT " + json.dumps(x))
 '''
 
+
+# for `also`: the kernels' names, which the library hands to the runtime as it is loaded (kept from it here: nothing is launched)
+NAMES = r'''
+#include <stdlib.h>
+#include <string.h>
+static struct { const void *f; char *name; } *known;
+static int known_n;
+void __hipRegisterFunction(void **modules, const void *f, char *device, const char *name, unsigned limit, void *a, void *b, void *c, void *d, int *e)
+{
+    known = realloc(known, (known_n + 1) * sizeof(*known));
+    known[known_n].f = f;
+    known[known_n++].name = strdup(name);
+}
+const char *recorded_kernel(int i)
+{
+    for (int k = 0; k < known_n; ++k) if (known[k].f == kernel_[i]) return known[k].name;
+    return "";
+}
+unsigned recorded_shared(int i) { return shared_[i]; }
+'''
 
 # for `also`: the device and its scratch array, for calls that ask the runtime where the library's own array lies
 ONE_DEVICE = r'''
