@@ -2104,13 +2104,15 @@ static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
     return tiles ? kWayTiles : kWayGeneral;
 }
 
-// dV and dK.  Both other ways give a workgroup all the rows of a head, so they want heads: from some hundred columns per CU on at Dh = 64, which the
-// general kernel's tiles fit exactly, sooner at other sizes.  dV by tiles: (64, 301, 64) +1.3, (64, 577, 64) -3.2, (64, 919, 64) -18,
-// (192, 197, 64) -1.9, (1536, 197, 96) -83; (3, 601, 64) +5.  Whole (a few percent ahead) below 128 tokens: (1536, 71, 64) dK -1.2 by tiles, -3.0
-// whole; (1536, 131, 64) -11.6 and -11.1.
+// dV and dK.  Both other ways give a workgroup all the rows of a head, so they want columns, some hundred per CU at Dh = 64, which the general
+// kernel's tiles fit exactly, fewer at other sizes; a head of less than 32 rows costs what one of 32 does.  dV by tiles: (64, 301, 64) +1.3, (64, 577, 64) -3.2,
+// (64, 919, 64) -18, (192, 197, 64) -1.9, (1536, 197, 96) -83; (3, 601, 64) +5.  Whole (a few percent ahead) below 128 tokens: (1536, 71, 64) dK -1.2 by tiles, -3.0
+// whole; (1536, 131, 64) -11.6 and -11.1.  Whole against general, dK: (2048, 8, 128) 17.0 -> 11.8, (1536, 10, 128) -3.9, (1536, 12, 32) -2.1, (571, 33, 32) -0.7,
+// (200, 23, 96) +0.1; dV of (275, 71, 32) -0.5, by tiles of (14, 1392, 32) -3.0, (29, 575, 32) -1.8.
 template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
 {
-    if (batches < ceil_div(Dh == 64 ? 28672 : 20480, N)) return kWayGeneral;
+    const int64_t columns = Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 16384 : 20480;
+    if (batches < ceil_div(columns, N < 32 ? 32 : N)) return kWayGeneral;
     const bool whole = tn_fits<WIDE_CODED>(N, Dh) && batches < (int64_t(1) << 31);
     if (tn_cols_fits(batches, N, Dh) && (N >= 128 || N % 16 == 0 || !whole)) return kWayTiles;
     return whole ? kWayWhole : kWayGeneral;

@@ -38,3 +38,31 @@ def test_groups_of_waves_per_workgroup_of_the_column_tiles():
             (1, 300, 200, 64, "f16"): 2, (1, 300, 200, 32, "bf16"): 2, (1, 512, 112, 64, "f16"): 1, (1, 16, 4096, 64, "bf16"): 4, (1, 600, 200, 64, "f16"): 1}
     for shape, calls in routes(list(want)).items():
         assert [by_tiles(c) for c in calls] == [want[shape]] * 2, (shape, calls)
+
+
+KINDS = {"k_attn_da": "whole", "k_attn_tn": "whole", "k_attn_nn": "whole", "k_attn_da_cols": "tiles", "k_attn_tn_cols": "tiles", "k_attn_nn_rows": "tiles",
+         "k_bmm_q": "general", "k_bmm_waves": "waves", "k_bmm_waves_two": "waves", "k_bmm_plain": "plain"}
+
+
+def ways(shapes):
+    """{shape: {product: way}}; a launch of two products stands for both"""
+    out = {}
+    for shape, calls in routes(shapes).items():
+        w = {}
+        for call, names in zip(calls, (("dA", "dV"), ("dQ", "dK"))):
+            kinds = [KINDS[k[0]] for k in call]
+            if len(kinds) == 1:
+                kinds *= 2
+            elif call[0][0] in ("k_attn_tn_cols", "k_attn_tn") or call[0][1].startswith("Lb1"):   # dV, whose first operand is coded, before dA
+                kinds.reverse()
+            w.update(zip(names, kinds))
+        out[shape] = w
+    return out
+
+
+def test_short_heads_keep_a_workgroup_per_head():
+    """dV and dK of very many heads of a few rows, and of fewer heads at a head size of 32."""
+    want = {(1, 2048, 8, 128, "f16"): "whole", (1, 1536, 10, 128, "bf16"): "whole", (1, 1536, 12, 32, "f16"): "whole", (1, 571, 33, 32, "bf16"): "whole",
+            (1, 650, 23, 96, "f16"): "whole", (1, 275, 71, 32, "f16"): "whole", (1, 28, 600, 32, "f16"): "tiles", (1, 200, 33, 96, "f16"): "general", (1, 300, 72, 64, "f16"): "general"}
+    for shape, w in ways(list(want)).items():
+        assert w["dV"] == w["dK"] == want[shape], (shape, w)
