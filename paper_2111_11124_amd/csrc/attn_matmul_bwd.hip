@@ -2089,19 +2089,23 @@ template <int DT, typename ET> static void launch_nn(const _Float16 *dS, const i
 // general kernel has a workgroup per 64 x 64 results and its loads are its own, the others share what they read.
 enum AttnWay { kWayGeneral, kWayTiles, kWayWhole };
 
-// dA.  Whole: 32 x N results in LDS.  Aligned rows by tiles once these give every CU a workgroup ((192, 256, 64) -4.1 us against
-// the general kernel, (16, 576, 64) -1.3, (64, 64, 64) +0.5), else whole, but not where N is a multiple of 32, whose rows meet on the same banks
-// ((192, 256, 64): +15).  Unaligned ones whole up to 448 tokens ((192, 301, 64) -6.6 by tiles, -9.1 whole; (192, 420, 64) -17.0 and -17.7; (192, 577, 64)
-// 4 us behind), unless heads are few and long ((3, 420, 64) +0.9).
+// dA.  Whole: 32 x N results in LDS.  Aligned rows by tiles once these give the CUs enough workgroups -- the more of a tile's 256 columns exist, the fewer
+// will do: general / by tiles / whole, calls of dA and dV, (118, 224, 64), 236 workgroups, 16.5 / 14.5 / 19.5, (12, 760, 64), 216, 18.4 / 17.0 / 18.8, (6, 728, 128), 108,
+// 16.6 / 14.5 / 17.0, (64, 64, 64) +0.5 by tiles --, else whole, but not where N is a multiple of 32, whose rows meet on the same banks
+// ((192, 256, 64): +15).  Wide heads of less than 96 rows whole: (403, 80, 96) 22.5 / 20.7 / 18.3, (822, 72, 96) 30.0 / 27.4 / 24.3.  Unaligned rows whole up to 704 tokens ((192, 301, 64)
+// -6.6 by tiles, -9.1 whole; (192, 420, 64) -17.0 and -17.7; (27, 553, 64) 20.5 / 21.3 / 18.2, (42, 463, 128) 34.1 / 31.7 / 28.2), unless heads are few and
+// long ((3, 420, 64) +0.9), or many and longer than 448 ((192, 577, 64) 4 us behind).
 static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
 {
     const bool whole = (Dh == 32 && da_fits<2>(batches, N)) || (Dh == 64 && da_fits<4>(batches, N)) || (Dh == 96 && da_fits<6>(batches, N)) ||
                        (Dh == 128 && da_fits<8>(batches, N));
     const int64_t per_head = ceil_div(N, 256) * ceil_div(N, Dh <= 64 ? 128 : 64);
-    const bool tiles = da_cols_fits(batches, N, Dh) && batches >= ceil_div(N % 8 == 0 ? 256 : 384, per_head);
-    if (N % 8 == 0 && N >= 64) return tiles ? kWayTiles : whole && N % 32 != 0 ? kWayWhole : kWayGeneral;
-    if (whole && (N <= 256 || (N <= 448 && batches >= ceil_div(128, ceil_div(N, 32))))) return kWayWhole;
-    return tiles ? kWayTiles : kWayGeneral;
+    const bool aligned = N % 8 == 0 && N >= 64;
+    if (whole && aligned && N < 96 && N % 32 != 0 && Dh > 64) return kWayWhole;
+    if (whole && !aligned && (N <= 256 || (batches >= ceil_div(128, ceil_div(N, 32)) && (N <= 448 || (N <= 704 && batches < ceil_div(2048, per_head))))))
+        return kWayWhole;
+    if (da_cols_fits(batches, N, Dh) && batches >= ceil_div(!aligned ? 384 : N > 256 ? 96 : N >= 192 ? 160 : 256, per_head)) return kWayTiles;
+    return whole && aligned && N % 32 != 0 ? kWayWhole : kWayGeneral;
 }
 
 // dV and dK.  Both other ways give a workgroup all the rows of a head, so they want columns, some hundred per CU at Dh = 64, which the general
