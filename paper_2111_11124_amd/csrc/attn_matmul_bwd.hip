@@ -2124,16 +2124,19 @@ template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int
 
 // dQ.  Whole, a workgroup per head, for many short heads whose rows do not meet on the same banks: (768, 197, 64) -3.8 by tiles, -4.4 whole;
 // (3072, 100, 64) -1.3, -4.1 (with dK behind it, (768, 100, 64) 22.7 by the general kernel, 22.2); (1536, 100, 32) -1.6, -2.6; (1536, 150, 32) -4.1, -1.1; (768, 150, 128) -9, -14; (768, 197,
-// 128) -24, -19; (8, 197, 64) 0 and +7.  By tiles from 192 workgroups on ((192, 301, 96) -11, (24, 919, 96) -3.5, (8, 919, 96) +2.9), short heads only
-// where the general kernel's 64 x 64 tiles do not fit Dh; always at Dh = 32, half such a tile ((64, 601, 32) -3.7, (192, 74, 32) -0.7).
+// 128) -24, -19; (8, 197, 64) 0 and +7; against tiles, (949, 125, 32) -1.9, (750, 118, 32) -1.7, (516, 97, 128) -3.0, aligned (1550, 80, 32) +5.9.  By tiles from 192 workgroups on ((192, 301, 96)
+// -11, (24, 919, 96) -3.5, (8, 919, 96) +2.9), short heads only where the general kernel's 64 x 64 tiles do not fit Dh; always at Dh = 32, half such a tile ((64, 601, 32) -3.7, (192, 74, 32)
+// -0.7).  Long heads fill the general kernel's workgroups well, so by tiles later: (16, 888, 96), 224 workgroups, +3.0, (11, 1126, 128), 198, +3.9, (14, 1426, 64), 322, +2.2, (19, 1356,
+// 64), 418, +2.3.
 static AttnWay nn_way(int64_t batches, int64_t N, int64_t Dh)
 {
     if (nn_fits(N, Dh) && batches < (int64_t(1) << 31)) {
-        const bool many = Dh == 32 ? N < 144 && batches >= 1024 : batches >= 640 && (Dh == 64 || N < 192);
+        const bool many = Dh == 32 ? N % 8 != 0 && N < 144 && batches >= 640 : Dh == 64 ? batches >= 640 : N < 192 && batches >= 512;
         if (N < 64 || (N % 32 != 0 && many)) return kWayWhole;
     }
     if (!nn_rows_fits(batches, N, Dh)) return kWayGeneral;
-    const bool tiles = Dh == 32 || (batches >= ceil_div(192, ceil_div(N, 64)) && (Dh == 64 ? N >= 192 : Dh == 96 || N >= 128 || batches >= 384));
+    const int64_t enough = ceil_div(N <= 448 ? 192 : Dh == 64 ? 448 : 320, ceil_div(N, 64));
+    const bool tiles = Dh == 32 || (batches >= enough && (Dh == 64 ? N >= 192 : Dh == 96 || N >= 128 || batches >= 384));
     return tiles ? kWayTiles : kWayGeneral;
 }
 

@@ -76,3 +76,12 @@ def test_da_of_medium_and_long_heads():
             (1, 403, 96, 96, "f16"): "tiles", (1, 403, 72, 64, "f16"): "tiles"}
     for shape, w in ways(list(want)).items():
         assert w["dA"] == want[shape], (shape, w)
+
+
+def test_dq_of_many_short_and_of_long_heads():
+    """dQ whole of many unaligned short heads, by tiles of long ones only once there are workgroups for it."""
+    want = {(1, 949, 125, 32, "f16"): "whole", (1, 750, 118, 32, "f16"): "whole", (1, 1550, 80, 32, "bf16"): "tiles", (1, 516, 97, 128, "f16"): "whole", (1, 16, 888, 96, "bf16"): "general",
+            (1, 11, 1126, 128, "bf16"): "general", (1, 14, 1426, 64, "bf16"): "general", (1, 19, 1356, 64, "f16"): "general", (1, 16, 4096, 64, "bf16"): "tiles", (1, 60, 919, 64, "f16"): "tiles",
+            (1, 192, 301, 96, "f16"): "tiles", (1, 768, 197, 64, "f16"): "whole", (1, 64, 601, 32, "f16"): "tiles", (1, 24, 919, 96, "f16"): "tiles"}
+    for shape, w in ways(list(want)).items():
+        assert w["dQ"] == want[shape], (shape, w)
