@@ -738,19 +738,33 @@ __global__ __launch_bounds__(64 * NW) void k_bmm_waves_two(BmmArgs a, BmmArgs b,
     else bmm_waves_tile<PR2>(b, block - first, lds);
 }
 
-// Waves of k_bmm_waves's workgroups where it is the faster kernel, else 0: no more than there are blocks of steps, and as many
-// workgroups as run at once (binary32, whose other kernel is the general one alone: half as many again, or twice).  Two products, kernels chosen
-// by da_way, tn_way and nn_way -> this one, dA and dV / dQ and dK: (6, 197, 64) f16 9.3 -> 8.4 / 11.0 -> 9.1 us, f32 12.2 -> 9.1 / 17.3 -> 9.3; (3, 1005, 32) f16
-// - / 22.8 -> 15.2; (6, 574, 64) - / 17.1 -> 10.8; (6, 426, 64) f32 16.3 -> 11.8 / 24.0 -> 11.2; lines, in 16 bits: (6, 1015, 64), 384 tiles of dV, 30.3 -> 23.0 and
-// (12, 498, 96), 576, 17.7 -> 17.9, (48, 108, 96), 576, 10.0 -> 12.3; dA with four waves (16, 195, 64), 784 tiles, -0.2, (24, 165, 64), 864, +0.5, (32, 248, 64), 2048, +3; with eight
-// (32, 147, 96), 800, +0.8.  binary32: (12, 783, 64), 600, 43 -> 32; (16, 746, 40), 768, 39 -> 34; (16, 1000, 40), 1024, 46 -> 52.
+// Waves of k_bmm_waves's workgroups where it is the faster kernel for both products of a call, in one launch, else 0: no more than there are blocks of steps, and
+// as many workgroups as run at once (binary32, whose other kernel is the general one alone: half as many again, or twice).  Two launches of the kernels chosen by
+// da_way, tn_way and nn_way -> one of this kernel, dQ and dK: 16 bits (3, 436, 64) 14.0 -> 5.2, 400 to 512 tiles of eight waves -2.5, 700 to 800 of four -0.3; (1, 4096, 64) 96 -> 30,
+// (2, 4100, 32) 91 -> 41, (4, 2048, 64) 54 -> 31, (1, 8192, 64) 185 -> 106.  binary32: (12, 783, 64), 600 tiles, 43 -> 32; (65, 112, 96), 780, 13.8 -> 10.9, (10, 1248, 64), 780, 47.0 -> 45.2.
+// Four waves in binary32, heads of at most 32 columns, half a tile of the general kernel, (1653, 20, 32) 16.0 -> 12.5, (1951, 13, 32) 16.8 -> 13.7, (936, 35, 32), 1872, -0.4, others
+// (290, 39, 64), 1160 tiles, 12.0 -> 10.6, (313, 22, 128), 1252, -0.1, (334, 57, 64), 1336, +0.5, (490, 53, 64), 1960, 12.8 -> 15.8, (464, 24, 128), 1856, 10.9 -> 14.4.
 template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t Cn, int64_t Tn)
 {
     constexpr bool kWide = std::is_same<ET, float>::value;
     const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
     if (tiles <= 256 && Tn > 128) return 16;
     if (Tn > 64) return tiles <= (kWide ? 800 : 512) ? 8 : 0;
-    return tiles <= (kWide ? 2048 : 800) ? 4 : 0;
+    return tiles <= (!kWide ? 800 : Cn <= 32 ? 2048 : 1248) ? 4 : 0;
+}
+
+// The same for a product in a launch of its own (dA or dV).  16 bits: four waves gain nothing there (dA +0.1 to +0.5 us, (78, 65, 64) 7.3 -> 8.5; dV -0.3 to +0.2), eight for dA up to 256
+// tiles (-0.5; 512: +0.5).  binary32: dA with four, 256 tiles -0.5, 512 0.0, 1024 +1.6, (490, 53, 64), 1960, +5.6 of 11.6, but -0.3 on average up to 2048 where a head is one tile; dV
+// with four 1152 tiles -0.1, 1290 +1.0; with eight (65, 112, 96), 780, -0.6, long ones (2, 5311, 64), 664, -21 of 167, (2, 5648, 64), 708, +5, (3, 4100, 64), 774, +8 of 135, (10, 1248, 64),
+// 780, +6 of 43.
+template <typename ET> static int bmm_waves_alone(int64_t batches, int64_t R, int64_t Cn, int64_t Tn, bool da)
+{
+    constexpr bool kWide = std::is_same<ET, float>::value;
+    const int nw = bmm_waves<ET>(batches, R, Cn, Tn);
+    const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
+    if (nw == 4) return kWide && tiles <= (R <= 32 && Cn <= 32 ? 2048 : da ? 512 : 1248) ? 4 : 0;
+    if (nw == 8 && tiles > (kWide ? Tn >= 1024 ? 700 : 800 : da ? 256 : 512)) return 0;
+    return nw;
 }
 
 static int64_t bmm_waves_tiles(BmmArgs &a, int64_t batches)
@@ -764,7 +778,7 @@ template <bool P_CODED, bool P_TFAST, bool Q_TFAST, typename ET>
 static bool launch_bmm_waves(BmmArgs a, int64_t batches, hipStream_t s)
 {
     typedef BmProduct<P_CODED, P_TFAST, Q_TFAST> PR;
-    const int nw = bmm_waves<ET>(batches, a.R, a.Cn, a.Tn);
+    const int nw = bmm_waves_alone<ET>(batches, a.R, a.Cn, a.Tn, P_TFAST && Q_TFAST);
     if (nw == 0) return false;
     const dim3 grid{unsigned(bmm_waves_tiles(a, batches))};
     if (nw == 16) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 16>), grid, dim3(1024), 0, s, a);
@@ -776,7 +790,7 @@ static bool launch_bmm_waves(BmmArgs a, int64_t batches, hipStream_t s)
 // Both products, where both of them would go that way; with different numbers of steps the shorter one's spare waves keep others from running,
 // and two launches are the better ones from some 850 tiles on.  dA and dV / dQ and dK, two launches -> one: (6, 197, 64) f16 8.3 -> 5.0 / 9.1 -> 5.0 us, f32
 // 9.0 -> 5.4 / 9.4 -> 5.2; (24, 97, 64) 7.3 -> 6.0 / 7.4 -> 5.0; dA and dV (12, 219, 64), 756 tiles, 8.9 -> 7.3, (16, 195, 64), 1008, 9.1 -> 8.4, (6, 330, 64) f32, 858, 10.3 -> 11.1,
-// (9, 293, 64), 1080, 9.6 -> 10.2, (6, 398, 64) f32, 2340, 17 -> 26; dQ and dK (32, 248, 64), 1024, 10.5 -> 9.5.
+// (9, 293, 64), 1080, 9.6 -> 10.2, (12, 398, 64) f32, 2340, 17 -> 26; dQ and dK (32, 248, 64), 1024, 10.5 -> 9.5.
 template <typename PR1, typename PR2, typename ET>
 static bool launch_bmm_waves_two(BmmArgs a, BmmArgs b, int64_t batches, hipStream_t s)
 {

@@ -85,3 +85,15 @@ def test_dq_of_many_short_and_of_long_heads():
             (1, 192, 301, 96, "f16"): "tiles", (1, 768, 197, 64, "f16"): "whole", (1, 64, 601, 32, "f16"): "tiles", (1, 24, 919, 96, "f16"): "tiles"}
     for shape, w in ways(list(want)).items():
         assert w["dQ"] == want[shape], (shape, w)
+
+
+def test_few_heads_by_waves_only_where_that_is_faster():
+    """Both products in one launch, one alone, and neither; in binary32 with four waves by how the tiles compare with the general kernel's."""
+    want = {(1, 6, 197, 64, "f32"): ("waves", "waves", "waves"), (1, 490, 53, 64, "f32"): ("general", "general", "general"), (1, 391, 60, 64, "f32"): ("general", "general", "general"),
+            (1, 290, 39, 64, "f32"): ("general", "waves", "waves"), (1, 1653, 20, 32, "f32"): ("waves", "waves", "waves"), (1, 464, 24, 128, "f32"): ("waves", "general", "general"),
+            (1, 10, 1248, 64, "f32"): ("general", "general", "waves"), (1, 12, 783, 64, "f32"): ("general", "waves", "waves"), (1, 128, 120, 64, "f32"): ("general", "general", "general"),
+            (1, 261, 92, 16, "f32"): ("general", "waves", "waves"), (1, 65, 112, 96, "f32"): ("general", "waves", "waves"), (1, 696, 43, 32, "f32"): ("general", "general", "waves"),
+            (1, 78, 65, 64, "f16"): ("whole", "waves", "waves"), (1, 156, 44, 64, "f16"): ("whole", "general", "waves"), (1, 4, 2048, 64, "f16"): ("tiles", "waves", "waves"),
+            (1, 3, 436, 64, "bf16"): ("waves", "waves", "waves"), (1, 1, 8192, 64, "bf16"): ("tiles", "waves", "waves")}
+    for shape, w in ways(list(want)).items():
+        assert (w["dA"], w["dV"], w["dK"]) == want[shape] and (w["dQ"] == "waves") == (w["dK"] == "waves"), (shape, w)
