@@ -753,17 +753,18 @@ template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t 
     return tiles <= (!kWide ? 800 : Cn <= 32 ? 2048 : 1248) ? 4 : 0;
 }
 
-// The same for a product in a launch of its own (dA or dV).  16 bits: four waves gain nothing there (dA +0.1 to +0.5 us, (78, 65, 64) 7.3 -> 8.5; dV -0.3 to +0.2), eight for dA up to 256
-// tiles (-0.5; 512: +0.5).  binary32: dA with four, 256 tiles -0.5, 512 0.0, 1024 +1.6, (490, 53, 64), 1960, +5.6 of 11.6, but -0.3 on average up to 2048 where a head is one tile; dV
-// with four 1152 tiles -0.1, 1290 +1.0; with eight (65, 112, 96), 780, -0.6, long ones (2, 5311, 64), 664, -21 of 167, (2, 5648, 64), 708, +5, (3, 4100, 64), 774, +8 of 135, (10, 1248, 64),
-// 780, +6 of 43.
+// The same for a product in a launch of its own (dA or dV).  16 bits: four waves gain nothing there (dA +0.1 to +0.5 us, (78, 65, 64) 7.3 -> 8.5; dV -0.3 to +0.2), eight for dA
+// -0.5 to 0 up to 512 tiles, but +0.5 from 257 on where two of them or fewer are one of the general kernel's and Dh has kernels of its own ((272, 27, 80) -0.6).  binary32: dA with four, 256 tiles -0.5, 512 0.0, 1024 +1.6, (490, 53, 64), 1960, +5.6 of 11.6, but -0.3 on average up to 2048 where a head is one tile; dV
+// with four 1152 tiles -0.1, 1290 +1.0; with eight (65, 112, 96), 780, -0.6, long ones (2, 5311, 64), 664, -21 of 167, (6, 2047, 64), 768, -5 of 69,
+// aligned (2, 5648, 64), 708, +5, (10, 1248, 64), 780, +6 of 43, but (3, 8192, 32), 768, -32.
 template <typename ET> static int bmm_waves_alone(int64_t batches, int64_t R, int64_t Cn, int64_t Tn, bool da)
 {
     constexpr bool kWide = std::is_same<ET, float>::value;
     const int nw = bmm_waves<ET>(batches, R, Cn, Tn);
-    const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
+    const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32), general = batches * ceil_div(R, 64) * ceil_div(Cn, 64);
     if (nw == 4) return kWide && tiles <= (R <= 32 && Cn <= 32 ? 2048 : da ? 512 : 1248) ? 4 : 0;
-    if (nw == 8 && tiles > (kWide ? Tn >= 1024 ? 700 : 800 : da ? 256 : 512)) return 0;
+    if (nw == 8 && kWide && Tn >= 1024 && Tn % 16 == 0 && Cn > 32 && tiles > 700) return 0;
+    if (nw == 8 && !kWide && da && Tn % 32 == 0 && 2 * tiles < 5 * general && tiles > 256) return 0;
     return nw;
 }
 
@@ -2104,11 +2105,12 @@ template <int DT, typename ET> static void launch_nn(const _Float16 *dS, const i
 enum AttnWay { kWayGeneral, kWayTiles, kWayWhole };
 
 // dA.  Whole: 32 x N results in LDS.  Aligned rows by tiles once these give the CUs enough workgroups -- the more of a tile's 256 columns exist, the fewer
-// will do: general / by tiles / whole, calls of dA and dV, (118, 224, 64), 236 workgroups, 16.5 / 14.5 / 19.5, (12, 760, 64), 216, 18.4 / 17.0 / 18.8, (6, 728, 128), 108,
-// 16.6 / 14.5 / 17.0, (64, 64, 64) +0.5 by tiles --, else whole, but not where N is a multiple of 32, whose rows meet on the same banks
-// ((192, 256, 64): +15).  Wide heads of less than 96 rows whole: (403, 80, 96) 22.5 / 20.7 / 18.3, (822, 72, 96) 30.0 / 27.4 / 24.3.  Unaligned rows whole up to 704 tokens ((192, 301, 64)
-// -6.6 by tiles, -9.1 whole; (192, 420, 64) -17.0 and -17.7; (27, 553, 64) 20.5 / 21.3 / 18.2, (42, 463, 128) 34.1 / 31.7 / 28.2), unless heads are few and
-// long ((3, 420, 64) +0.9), or many and longer than 448 ((192, 577, 64) 4 us behind).
+// will do: general / by tiles / whole, calls of dA and dV, (118, 224, 64), 236 workgroups, 16.5 / 14.5 / 19.5, (12, 760, 64), 216, 18.4 / 17.0 / 18.8, (6, 728, 128), 216,
+// 16.6 / 14.5 / 17.0, (9, 544, 64), 135, +1.0 by tiles, (64, 64, 64) +0.5 --, else whole, but not where N is a multiple of 32, whose rows meet on the same banks
+// ((192, 256, 64): +15).  Wide heads of less than 96 rows whole: (403, 80, 96) 22.5 / 20.7 / 18.3, (822, 72, 96) 30.0 / 27.4 / 24.3.  Unaligned rows whole up to 800 tokens ((192, 301, 64)
+// -6.6 by tiles, -9.1 whole; (192, 420, 64) -17.0 and -17.7; (27, 553, 64) 20.5 / 21.3 / 18.2, (42, 463, 128) 34.1 / 31.7 / 28.2, (44, 524, 64) - / 25.7 / 22.7, (18, 733, 64) - / 23.5 /
+// 21.9), unless heads are few and long ((3, 420, 64) +0.9, (8, 511, 64) +0.4), or, beyond 448 tokens, many and the tiles well filled ((192, 577, 64) 4 us behind, (38, 687, 64) +1.1 of
+// 31, (24, 765, 64) +1.6 of 27), or 96 wide (0 to +2: (37, 741, 96), (41, 655, 96)).
 static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
 {
     const bool whole = (Dh == 32 && da_fits<2>(batches, N)) || (Dh == 64 && da_fits<4>(batches, N)) || (Dh == 96 && da_fits<6>(batches, N)) ||
@@ -2116,9 +2118,13 @@ static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
     const int64_t per_head = ceil_div(N, 256) * ceil_div(N, Dh <= 64 ? 128 : 64);
     const bool aligned = N % 8 == 0 && N >= 64;
     if (whole && aligned && N < 96 && N % 32 != 0 && Dh > 64) return kWayWhole;
-    if (whole && !aligned && (N <= 256 || (batches >= ceil_div(128, ceil_div(N, 32)) && (N <= 448 || (N <= 704 && batches < ceil_div(2048, per_head))))))
-        return kWayWhole;
-    if (da_cols_fits(batches, N, Dh) && batches >= ceil_div(!aligned ? 384 : N > 256 ? 96 : N >= 192 ? 160 : 256, per_head)) return kWayTiles;
+    if (whole && !aligned) {
+        if (N <= 256 || (N <= 448 && batches >= ceil_div(128, ceil_div(N, 32)))) return kWayWhole;
+        const bool filled = 4 * N >= 3 * 256 * ceil_div(N, 256);   // the tiles' columns, three quarters of them
+        const int64_t many = N > 704 ? 352 : Dh == 64 && filled ? 640 : 2048;
+        if (N > 448 && N <= 800 && Dh != 96 && batches >= ceil_div(192, ceil_div(N, 32)) && batches < ceil_div(many, per_head)) return kWayWhole;
+    }
+    if (da_cols_fits(batches, N, Dh) && batches >= ceil_div(!aligned ? 384 : N > 448 ? 144 : N >= 192 ? 160 : 256, per_head)) return kWayTiles;
     return whole && aligned && N % 32 != 0 ? kWayWhole : kWayGeneral;
 }
 
@@ -2126,10 +2132,11 @@ static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
 // kernel's tiles fit exactly, fewer at other sizes; a head of less than 32 rows costs what one of 32 does.  dV by tiles: (64, 301, 64) +1.3, (64, 577, 64) -3.2,
 // (64, 919, 64) -18, (192, 197, 64) -1.9, (1536, 197, 96) -83; (3, 601, 64) +5.  Whole (a few percent ahead) below 128 tokens: (1536, 71, 64) dK -1.2 by tiles, -3.0
 // whole; (1536, 131, 64) -11.6 and -11.1.  Whole against general, dK: (2048, 8, 128) 17.0 -> 11.8, (1536, 10, 128) -3.9, (1536, 12, 32) -2.1, (571, 33, 32) -0.7,
-// (200, 23, 96) +0.1; dV of (275, 71, 32) -0.5, by tiles of (14, 1392, 32) -3.0, (29, 575, 32) -1.8.
+// (200, 23, 96) +0.1; dV of (275, 71, 32) -0.5, by tiles of (14, 1392, 32) -3.0, (29, 575, 32) -1.8, (132, 128, 96),
+// 16896 columns, +1.7 of 11.1.
 template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
 {
-    const int64_t columns = Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 16384 : 20480;
+    const int64_t columns = Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 18432 : 20480;
     if (batches < ceil_div(columns, N < 32 ? 32 : N)) return kWayGeneral;
     const bool whole = tn_fits<WIDE_CODED>(N, Dh) && batches < (int64_t(1) << 31);
     if (tn_cols_fits(batches, N, Dh) && (N >= 128 || N % 16 == 0 || !whole)) return kWayTiles;
@@ -2138,18 +2145,18 @@ template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int
 
 // dQ.  Whole, a workgroup per head, for many short heads whose rows do not meet on the same banks: (768, 197, 64) -3.8 by tiles, -4.4 whole;
 // (3072, 100, 64) -1.3, -4.1 (with dK behind it, (768, 100, 64) 22.7 by the general kernel, 22.2); (1536, 100, 32) -1.6, -2.6; (1536, 150, 32) -4.1, -1.1; (768, 150, 128) -9, -14; (768, 197,
-// 128) -24, -19; (8, 197, 64) 0 and +7; against tiles, (949, 125, 32) -1.9, (750, 118, 32) -1.7, (516, 97, 128) -3.0, aligned (1550, 80, 32) +5.9.  By tiles from 192 workgroups on ((192, 301, 96)
+// 128) -24, -19; (8, 197, 64) 0 and +7; against tiles, (949, 125, 32) -1.9, (750, 118, 32) -1.7, (516, 97, 128) -3.0, aligned (1550, 80, 32) +5.9, (526, 144, 128) +5.7.  By tiles from 192 workgroups on ((192, 301, 96)
 // -11, (24, 919, 96) -3.5, (8, 919, 96) +2.9), short heads only where the general kernel's 64 x 64 tiles do not fit Dh; always at Dh = 32, half such a tile ((64, 601, 32) -3.7, (192, 74, 32)
 // -0.7).  Long heads fill the general kernel's workgroups well, so by tiles later: (16, 888, 96), 224 workgroups, +3.0, (11, 1126, 128), 198, +3.9, (14, 1426, 64), 322, +2.2, (19, 1356,
-// 64), 418, +2.3.
+// 64), 418, +2.3; (55, 512, 64), 440, -1.0, (15, 1168, 128), 285, -2.1.
 static AttnWay nn_way(int64_t batches, int64_t N, int64_t Dh)
 {
     if (nn_fits(N, Dh) && batches < (int64_t(1) << 31)) {
-        const bool many = Dh == 32 ? N % 8 != 0 && N < 144 && batches >= 640 : Dh == 64 ? batches >= 640 : N < 192 && batches >= 512;
+        const bool many = Dh == 32 ? N % 8 != 0 && N < 144 && batches >= 640 : Dh == 64 ? batches >= 640 : N < 192 && batches >= (N % 8 != 0 ? 512 : 640);
         if (N < 64 || (N % 32 != 0 && many)) return kWayWhole;
     }
     if (!nn_rows_fits(batches, N, Dh)) return kWayGeneral;
-    const int64_t enough = ceil_div(N <= 448 ? 192 : Dh == 64 ? 448 : 320, ceil_div(N, 64));
+    const int64_t enough = ceil_div(Dh == 64 ? (N < 704 ? 192 : 448) : N <= 448 ? 192 : 256, ceil_div(N, 64));
     const bool tiles = Dh == 32 || (batches >= enough && (Dh == 64 ? N >= 192 : Dh == 96 || N >= 128 || batches >= 384));
     return tiles ? kWayTiles : kWayGeneral;
 }

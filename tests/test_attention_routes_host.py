@@ -63,7 +63,7 @@ def ways(shapes):
 def test_short_heads_keep_a_workgroup_per_head():
     """dV and dK of very many heads of a few rows, and of fewer heads at a head size of 32."""
     want = {(1, 2048, 8, 128, "f16"): "whole", (1, 1536, 10, 128, "bf16"): "whole", (1, 1536, 12, 32, "f16"): "whole", (1, 571, 33, 32, "bf16"): "whole",
-            (1, 650, 23, 96, "f16"): "whole", (1, 275, 71, 32, "f16"): "whole", (1, 28, 600, 32, "f16"): "tiles", (1, 200, 33, 96, "f16"): "general", (1, 300, 72, 64, "f16"): "general"}
+            (1, 650, 23, 96, "f16"): "whole", (1, 275, 71, 32, "f16"): "whole", (1, 28, 600, 32, "f16"): "tiles", (1, 200, 33, 96, "f16"): "general", (1, 300, 72, 64, "f16"): "general", (1, 132, 128, 96, "bf16"): "general", (1, 145, 128, 96, "bf16"): "tiles"}
     for shape, w in ways(list(want)).items():
         assert w["dV"] == w["dK"] == want[shape], (shape, w)
 
@@ -73,7 +73,8 @@ def test_da_of_medium_and_long_heads():
     want = {(1, 118, 224, 64, "f16"): "tiles", (1, 12, 760, 64, "bf16"): "tiles", (1, 12, 728, 128, "f16"): "tiles", (1, 250, 64, 64, "f16"): "general", (1, 403, 80, 96, "bf16"): "whole",
             (1, 822, 72, 96, "f16"): "whole", (1, 400, 88, 128, "f16"): "whole", (1, 27, 553, 64, "f16"): "whole", (1, 42, 463, 128, "f16"): "whole", (1, 28, 610, 32, "bf16"): "whole",
             (1, 192, 577, 64, "f16"): "tiles", (1, 192, 420, 64, "f16"): "whole", (1, 60, 919, 64, "f16"): "tiles", (1, 16, 4096, 64, "bf16"): "tiles", (1, 768, 197, 64, "f16"): "whole",
-            (1, 403, 96, 96, "f16"): "tiles", (1, 403, 72, 64, "f16"): "tiles"}
+            (1, 403, 96, 96, "f16"): "tiles", (1, 403, 72, 64, "f16"): "tiles", (1, 11, 511, 64, "f16"): "general", (1, 38, 687, 64, "bf16"): "tiles", (1, 38, 687, 128, "bf16"): "whole", (1, 18, 733, 64, "bf16"): "whole",
+            (1, 9, 544, 64, "f16"): "general", (1, 44, 524, 64, "f16"): "whole", (1, 24, 765, 64, "f16"): "tiles", (1, 41, 655, 96, "f16"): "tiles"}
     for shape, w in ways(list(want)).items():
         assert w["dA"] == want[shape], (shape, w)
 
@@ -82,7 +83,7 @@ def test_dq_of_many_short_and_of_long_heads():
     """dQ whole of many unaligned short heads, by tiles of long ones only once there are workgroups for it."""
     want = {(1, 949, 125, 32, "f16"): "whole", (1, 750, 118, 32, "f16"): "whole", (1, 1550, 80, 32, "bf16"): "tiles", (1, 516, 97, 128, "f16"): "whole", (1, 16, 888, 96, "bf16"): "general",
             (1, 11, 1126, 128, "bf16"): "general", (1, 14, 1426, 64, "bf16"): "general", (1, 19, 1356, 64, "f16"): "general", (1, 16, 4096, 64, "bf16"): "tiles", (1, 60, 919, 64, "f16"): "tiles",
-            (1, 192, 301, 96, "f16"): "tiles", (1, 768, 197, 64, "f16"): "whole", (1, 64, 601, 32, "f16"): "tiles", (1, 24, 919, 96, "f16"): "tiles"}
+            (1, 192, 301, 96, "f16"): "tiles", (1, 768, 197, 64, "f16"): "whole", (1, 64, 601, 32, "f16"): "tiles", (1, 24, 919, 96, "f16"): "tiles", (1, 55, 512, 64, "f16"): "tiles", (1, 15, 1168, 128, "bf16"): "tiles", (1, 526, 144, 128, "f16"): "tiles"}
     for shape, w in ways(list(want)).items():
         assert w["dQ"] == want[shape], (shape, w)
 
@@ -94,6 +95,7 @@ def test_few_heads_by_waves_only_where_that_is_faster():
             (1, 10, 1248, 64, "f32"): ("general", "general", "waves"), (1, 12, 783, 64, "f32"): ("general", "waves", "waves"), (1, 128, 120, 64, "f32"): ("general", "general", "general"),
             (1, 261, 92, 16, "f32"): ("general", "waves", "waves"), (1, 65, 112, 96, "f32"): ("general", "waves", "waves"), (1, 696, 43, 32, "f32"): ("general", "general", "waves"),
             (1, 78, 65, 64, "f16"): ("whole", "waves", "waves"), (1, 156, 44, 64, "f16"): ("whole", "general", "waves"), (1, 4, 2048, 64, "f16"): ("tiles", "waves", "waves"),
-            (1, 3, 436, 64, "bf16"): ("waves", "waves", "waves"), (1, 1, 8192, 64, "bf16"): ("tiles", "waves", "waves")}
+            (1, 3, 436, 64, "bf16"): ("waves", "waves", "waves"), (1, 1, 8192, 64, "bf16"): ("tiles", "waves", "waves"),
+            (1, 3, 8192, 32, "f32"): ("general", "waves", "waves"), (1, 6, 2047, 64, "f32"): ("general", "waves", "waves"), (1, 272, 27, 80, "f16"): ("waves", "general", "general")}
     for shape, w in ways(list(want)).items():
         assert (w["dA"], w["dV"], w["dK"]) == want[shape] and (w["dQ"] == "waves") == (w["dK"] == "waves"), (shape, w)
