@@ -34,11 +34,18 @@ constexpr int kU = 2;                            // vectors per thread and itera
 constexpr int kGridCap = 1 << 20;                // one chunk per workgroup up to 2^32 elements: the workgroups in flight then sweep the tensor as one compact window (a grid-stride loop has them at 2^12-element pieces spread over the whole tensor, measured 15 % slower at 2^31 elements)
 constexpr int kMmU = 4;                          // the same two numbers for the min/max scan
 constexpr int kMmGridCap = 1024;
-// Up to 2^24 elements the scan's threads hold two vectors as well: twice the workgroups (as many as the single-pass kernel has, for
-// which the workspace is sized), and half the vectors to hand to LDS at the end.  Whole call, four -> two vectors: (394, 3, 256)
-// in binary32 6.2 -> 5.5 us, (4096, 3, 64) 5.7 -> 5.4, (6304, 6, 64) in binary32 7.8 -> 7.4, (25216, 6, 64) 9.2 -> 9.0; beyond,
-// (50432, 12, 64) 17.2 -> 19.0, (25216, 6, 256) 16.7 -> 17.4.
+// Slabs that are no whole vectors, whose elements a thread looks at one by one: up to 2^24 elements the scan's threads hold two vectors as
+// well, so that twice the workgroups (as many as the single-pass kernel has, for which the workspace is sized) share that out.  Whole call, four
+// -> two vectors: (1542, 4, 49) 13.8 -> 8.5 us, (8, 768, 49) 14.8 -> 10.1, (17001, 2, 20) 8.3 -> 6.3, (26330, 8, 49) 20 -> 17, in binary32 (1, 2048, 441) 23.8 -> 17.2; whole vectors only
+// pay for more partial extrema: (25855, 16, 32) 9.4 -> 11.0, (619, 48, 256) 9.5 -> 11.4, in binary32 (22583, 4, 64) 7.6 -> 9.7, (24, 4096, 96) 35 -> 59 (up to some 2^20 elements it is the same).  So do
+// unaligned slabs of one group, (1, 1, 5.4e6) 7.3 -> 9.0 in binary32, and of very many: (3, 8192, 49) 42 -> 61.  Hundreds of slabs that come once each, up to
+// 2^20 elements, gain too: (1, 768, 1056) 10.8 -> 9.1, (1, 2048, 424) 13.6 -> 11.8, (1, 768, 256) 7.9 -> 7.0.
 constexpr int64_t kMmSmall = int64_t(1) << 24;
+static bool minmax_two_vectors(const mesa_layout &L)
+{
+    if (L.inner % kVec == 0) return L.outer == 1 && L.groups > 256 && L.groups <= 2048 && layout_numel(L) <= kMmSmall / 16;
+    return L.groups > 1 && L.groups <= 4096 && layout_numel(L) <= kMmSmall;
+}
 constexpr int kMmFew = 8;                        // groups for which a thread can hold every group's extrema
 constexpr int kFuU = 2;                          // and for the single-pass quantize + min/max
 constexpr int kFuGridCap = 2048;
@@ -1185,7 +1192,7 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
     if (variant != kEmaScaleOnly && (!beta || !aligned4(beta))) return MESA_ERR_INVALID_ARG;
     int grid = minmax_grid(L, kMmU, kMmGridCap, max_wgs);
     const bool few = minmax_few_groups(L, grid, kMmU);
-    const int unroll = !few && numel <= kMmSmall ? kFuU : kMmU;
+    const int unroll = !few && minmax_two_vectors(L) ? kFuU : kMmU;
     if (unroll != kMmU) grid = minmax_grid(L, unroll, kFuGridCap, max_wgs);
     const size_t need = max_wgs > 0 ? size_t(grid) * 2 * size_t(L.groups) * sizeof(float) : update_ws_bytes(L.outer, L.groups, L.inner);
     if (!ws || !aligned16(ws) || ws_bytes < need) return MESA_ERR_WORKSPACE;
