@@ -39,11 +39,11 @@ constexpr int kMmGridCap = 1024;
 // -> two vectors: (1542, 4, 49) 13.8 -> 8.5 us, (8, 768, 49) 14.8 -> 10.1, (17001, 2, 20) 8.3 -> 6.3, (26330, 8, 49) 20 -> 17, in binary32 (1, 2048, 441) 23.8 -> 17.2; whole vectors only
 // pay for more partial extrema: (25855, 16, 32) 9.4 -> 11.0, (619, 48, 256) 9.5 -> 11.4, in binary32 (22583, 4, 64) 7.6 -> 9.7, (24, 4096, 96) 35 -> 59 (up to some 2^20 elements it is the same).  So do
 // unaligned slabs of one group, (1, 1, 5.4e6) 7.3 -> 9.0 in binary32, and of very many: (3, 8192, 49) 42 -> 61.  Hundreds of slabs that come once each, up to
-// 2^20 elements, gain too: (1, 768, 1056) 10.8 -> 9.1, (1, 2048, 424) 13.6 -> 11.8, (1, 768, 256) 7.9 -> 7.0.
+// 2^22 elements, gain too: (1, 768, 1056) 10.8 -> 9.1, (1, 2048, 424) 13.6 -> 11.8, (1, 768, 256) 7.9 -> 7.0, in binary32 (1, 2048, 2024) 43 -> 27.
 constexpr int64_t kMmSmall = int64_t(1) << 24;
 static bool minmax_two_vectors(const mesa_layout &L)
 {
-    if (L.inner % kVec == 0) return L.outer == 1 && L.groups > 256 && L.groups <= 2048 && layout_numel(L) <= kMmSmall / 16;
+    if (L.inner % kVec == 0) return L.outer == 1 && L.groups > 256 && L.groups <= 2048 && layout_numel(L) <= kMmSmall / 4;
     return L.groups > 1 && L.groups <= 4096 && layout_numel(L) <= kMmSmall;
 }
 constexpr int kMmFew = 8;                        // groups for which a thread can hold every group's extrema
@@ -191,8 +191,13 @@ template <> struct MinMax<_Float16> {
 // same few words, and same-address atomics are served one after the other (some 32 clocks each): with few groups the tables come four
 // times, a lane takes its quarter, and they are folded as they leave.  Sixteen tables measured the same.  Whole
 // call of the two-launch update with one table -> four: (25216, 6, 256) 19.8 -> 16.7 us, (128, 6, 38809) 17.6 -> 15.7,
-// (394, 3, 256) in binary32 6.8 -> 6.2, single-pass GELU forward (2000, 12, 256) 15.5 -> 13.9; within 0.1 us at 600 to 10^5 elements.
-__host__ __device__ __forceinline__ uint32_t extrema_tables(uint32_t groups) { return groups <= 256 ? 4u : 1u; }
+// (394, 3, 256) in binary32 6.8 -> 6.2, (619, 48, 256) 14.2 -> 9.5, (1117, 96, 128) 12.5 -> 11.4, single-pass GELU forward (2000, 12, 256) 15.5 -> 13.9; within 0.1 us at 600 to 10^5
+// elements.  Short slabs of many groups meet less and pay for the clearing and the folding: (964, 128, 32) 7.6 -> 7.9, (991, 256, 16) 7.5 -> 8.2, binary32 (964, 256, 8) 7.0 -> 7.7, and so do
+// long ones of more than 128 groups ((n, 256, 1225) and up in the single-pass kernel +2 to +5 %).
+__host__ __device__ __forceinline__ uint32_t extrema_tables(const GroupGeom &gg)
+{
+    return gg.groups <= 32 || (gg.groups <= 128 && gg.inner >= 96) ? 4u : 1u;
+}
 
 __device__ __forceinline__ void clear_tables(int *lmn, int *lmx, uint32_t words)
 {
@@ -201,23 +206,27 @@ __device__ __forceinline__ void clear_tables(int *lmn, int *lmx, uint32_t words)
         lmx[k] = order_key(-__builtin_inff());
     }
 }
-__device__ __forceinline__ int quad_min(int v, bool whole)   // of four neighbouring lanes, or the lane's own
+__device__ __forceinline__ int quad_min(int v)     // of four neighbouring lanes
 {
-    if (whole) {
-        int w = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
-        v = w < v ? w : v;
-        w = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);       // quad_perm [2,3,0,1]
-        v = w < v ? w : v;
-    }
-    return v;
+    int w = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+    v = w < v ? w : v;
+    w = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);       // quad_perm [2,3,0,1]
+    return w < v ? w : v;
 }
 // the tables, complete behind a barrier, to this workgroup's row of the partial extrema: minima, then maxima
 __device__ __forceinline__ void store_tables(const int *lmn, const int *lmx, uint32_t groups, uint32_t tables, float *__restrict__ part)
 {
     float *out = part + int64_t(blockIdx.x) * 2 * groups;
-    for (uint32_t k = threadIdx.x; k < groups * tables; k += kThreads) {   // a group's four words in neighbouring lanes: k's last quad is whole
-        const uint32_t g = tables == 4u ? k >> 2 : k, t = tables == 4u ? k & 3u : 0u;
-        const int lo = quad_min(lmn[t * groups + g], tables == 4u), hi = ~quad_min(~lmx[t * groups + g], tables == 4u);
+    if (tables == 1u) {                            // uniform
+        for (uint32_t g = threadIdx.x; g < groups; g += kThreads) {
+            out[g] = order_val(lmn[g]);
+            out[groups + g] = order_val(lmx[g]);
+        }
+        return;
+    }
+    for (uint32_t k = threadIdx.x; k < groups * 4u; k += kThreads) {   // a group's four words in neighbouring lanes: k's last quad is whole
+        const uint32_t g = k >> 2, t = k & 3u;
+        const int lo = quad_min(lmn[t * groups + g]), hi = ~quad_min(~lmx[t * groups + g]);
         if (t == 0) {
             out[g] = order_val(lo);
             out[groups + g] = order_val(hi);
@@ -316,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial(const void *__restr
                                                              float *__restrict__ part)
 {
     extern __shared__ int lds_mm[];
-    const uint32_t tables = extrema_tables(gg.groups), own = (threadIdx.x & (tables - 1)) * gg.groups;
+    const uint32_t tables = extrema_tables(gg), own = (threadIdx.x & (tables - 1)) * gg.groups;
     int *all_mn = lds_mm, *all_mx = lds_mm + tables * gg.groups;
     int *lmn = all_mn + own, *lmx = all_mx + own;
     clear_tables(all_mn, all_mx, tables * gg.groups);
@@ -743,7 +752,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_minmax(const void *__rest
                                                               float *__restrict__ part, void *__restrict__ y = nullptr)
 {
     extern __shared__ float2 lds_tab[];
-    const uint32_t tables = extrema_tables(gg.groups), own = (threadIdx.x & (tables - 1)) * gg.groups;
+    const uint32_t tables = extrema_tables(gg), own = (threadIdx.x & (tables - 1)) * gg.groups;
     int *all_mn = reinterpret_cast<int *>(lds_tab + gg.groups), *all_mx = all_mn + tables * gg.groups;
     int *lmn = all_mn + own, *lmx = all_mx + own;
     clear_tables(all_mn, all_mx, tables * gg.groups);
@@ -1220,7 +1229,7 @@ static mesa_status update_running_params(const void *x, mesa_dtype dt, mesa_layo
         return launch_status();
     }
     GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * unroll * kVec);
-    const size_t lds = size_t(2) * gg.groups * (few ? 1 : extrema_tables(gg.groups)) * sizeof(int);
+    const size_t lds = size_t(2) * gg.groups * (few ? 1 : extrema_tables(gg)) * sizeof(int);
     float *part = static_cast<float *>(ws);
     if (few) {
 #define MESA_LAUNCH_FEW(T, GM) \
@@ -1382,7 +1391,7 @@ static mesa_status quantize_update_fused(const void *x, mesa_dtype dt, mesa_layo
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int grid = minmax_grid(L, kFuU, kFuGridCap);
     GroupGeom gg = make_geom(L.groups, L.inner, int64_t(grid) * kThreads * kFuU * kVec);
-    const size_t lds = size_t(gg.groups) * (sizeof(float2) + 2 * extrema_tables(gg.groups) * sizeof(int));
+    const size_t lds = size_t(gg.groups) * (sizeof(float2) + 2 * extrema_tables(gg) * sizeof(int));
     float *part = static_cast<float *>(ws);
     const bool sr = mode == MESA_ROUND_STOCHASTIC;
     // parameter table and extrema of every group live in LDS, 16 bytes a group where there are many: beyond the 64 KiB a launch gets by default

@@ -31,3 +31,9 @@ def test_extrema_of_either_number_of_tables(M, layout, dtype):
     a, b, q = torch.full((groups,), 3.0, device="cuda"), torch.full((groups,), -1.0, device="cuda"), torch.empty(x.numel(), dtype=torch.int8, device="cuda")
     M.mesa_quantize_update_fused(x, layout, a, b, 0.9, q, ws_for(M, M.OP_UPDATE_RUNNING_PARAMS, *layout, dt=dtype), M.ROUND_NEAREST_EVEN, 1, 0)
     assert np.array_equal(npy(a) + np.float32(0), ra + np.float32(0)) and np.array_equal(npy(b) + np.float32(0), rb + np.float32(0))
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
+@pytest.mark.parametrize("layout", [(900, 32, 40), (900, 33, 40), (400, 33, 96), (400, 128, 96), (400, 128, 88), (400, 129, 96), (500, 128, 97), (2000, 40, 20), (1, 768, 256)])
+def test_extrema_on_either_side_of_the_tables_lines(M, layout, dtype):
+    test_extrema_of_either_number_of_tables(M, layout, dtype)
