@@ -784,7 +784,7 @@ static bool launch_bmm_waves(BmmArgs a, int64_t batches, hipStream_t s)
     const dim3 grid{unsigned(bmm_waves_tiles(a, batches))};
     if (nw == 16) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 16>), grid, dim3(1024), 0, s, a);
     else if (nw == 8) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 8>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_bmm_waves<PR, ET, 4>), grid, dim3(256), 0, s, a);
+    else if constexpr (std::is_same<ET, float>::value) hipLaunchKernelGGL((k_bmm_waves<PR, ET, 4>), grid, dim3(256), 0, s, a);
     return true;
 }
 
@@ -1177,8 +1177,8 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
 // fragment of the N x N operand -- lane l: column j = l%32, the eight rows 8*(l/32) ..+7 of a 16-row step --
 // is gathered from LDS with eight 2-byte (1-byte) reads a row apart; the fragment of the other operand comes
 // from transposing reads.  The MFMA runs with the N x Dh operand on the M side, so a lane ends up with one
-// output row j and runs of four consecutive d.  Dh == 32 * DT; N <= 128 * JB (JB blocks of j per wave).
-template <int DT, int JB, bool WIDE_CODED, int NW> struct TnCfg {
+// output row j and runs of four consecutive d.  Dh == 32 * DT; N <= 32 * NW (a block of j per wave): below 128, longer heads go by tiles (tn_way).
+template <int DT, bool WIDE_CODED, int NW> struct TnCfg {
     static constexpr int kNt = 64 * NW;                     // threads of a workgroup (NW waves)
     // WIDE_CODED: the N x N operand is the coded one (dV: A codes, dO plain); else dK: dS plain, Q codes
     static constexpr int Dh = 32 * DT;
@@ -1191,19 +1191,16 @@ template <int DT, int JB, bool WIDE_CODED, int NW> struct TnCfg {
     static size_t lds_bytes(int64_t N) { return 2 * (wide_bytes(N) + narrow_bytes()); }
 };
 
-// waves per SIMD the register budget is set for (the accumulators are 16 * DT * JB registers)
-template <int DT, int JB, int NW> constexpr int tn_waves_per_simd()
-{
-    return (NW < 4 ? DT <= 2 : DT * JB <= 4 && DT < 4) ? 3 : DT * JB <= 6 ? 2 : 1;
-}
+// waves per SIMD the register budget is set for (the accumulators are 16 * DT registers)
+template <int DT, int NW> constexpr int tn_waves_per_simd() { return (NW < 4 ? DT <= 2 : DT < 4) ? 3 : 2; }
 
-template <int DT, int JB, bool WIDE_CODED, int NW, typename ET>
-__global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_attn_tn(const void *__restrict__ wide_, const void *__restrict__ narrow_,
+template <int DT, bool WIDE_CODED, int NW, typename ET>
+__global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, NW>())) void k_attn_tn(const void *__restrict__ wide_, const void *__restrict__ narrow_,
                                                          _Float16 *__restrict__ out, int N, int heads, float scale,
                                                          const float *__restrict__ alpha, const float *__restrict__ beta,
                                                          int wide_bytes, int64_t wide_elems)
 {
-    typedef TnCfg<DT, JB, WIDE_CODED, NW> C;
+    typedef TnCfg<DT, WIDE_CODED, NW> C;
     constexpr int kNt = C::kNt;
     typedef typename BmElem<WIDE_CODED, ET>::global_t WideT;       // element of the N x N operand
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_tn[];
@@ -1274,18 +1271,15 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
         }
     };
 
-    // ---- accumulators: wave w takes the blocks j = 32 * (w + NW * jb) ----------------------------------
-    bm_v16f acc[JB][DT];
+    // ---- accumulators: wave w takes the block j = 32 * w ----------------------------------
+    const int j0 = wave * 32;
+    bm_v16f acc[DT];
     bm_v16f acc1[WIDE_CODED ? DT : 1];                     // dV: column sums of dO per d, from MFMAs against ones
-    float csum[JB];                                        // dK: column sums of dS per j, per lane
+    float csum = 0.0f;                                     // dK: column sums of dS per j, per lane
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb) {
-        csum[jb] = 0.0f;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[jb][dt][v] = 0.0f;
-    }
+        for (int v = 0; v < 16; ++v) acc[dt][v] = 0.0f;
 #pragma unroll
     for (int dt = 0; dt < (WIDE_CODED ? DT : 1); ++dt)
 #pragma unroll
@@ -1324,10 +1318,7 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
                     fn[dt] = BmNum<ET>::codes8(__builtin_amdgcn_ds_read_tr8_b64_v2i32(BM_LDS3(bm_v2i, p)));
                 }
             }
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb) {
-                const int j0 = (wave + NW * jb) * 32;
-                if (j0 >= N) break;                        // uniform per wave
+            if (j0 < N) {                                  // uniform per wave
                 const int j = j0 + fl < N ? j0 + fl : N - 1;   // columns past the end repeat the last one; never written
                 const int at = mis_c + (ks * 16 + half * 8) * N + j;
                 bm_v8h fw;
@@ -1351,10 +1342,10 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
                     }
 #pragma unroll
                     for (int k = 0; k < 8; k += 2)
-                        csum[jb] = BmNum<ET>::dot_ones(fw[k], fw[k + 1], csum[jb]);
+                        csum = BmNum<ET>::dot_ones(fw[k], fw[k + 1], csum);
                 }
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) acc[jb][dt] = BmNum<ET>::mfma(fn[dt], fw, acc[jb][dt]);
+                for (int dt = 0; dt < DT; ++dt) acc[dt] = BmNum<ET>::mfma(fn[dt], fw, acc[dt]);
             }
         }
     }
@@ -1363,26 +1354,23 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, JB, NW>())) void k_
     const int h = int(bh % heads);
     const float s = alpha[h] / 255.0f;
     const float off = fmaf(BmNum<ET>::kCentre, s, beta[h]);
+    const int j = j0 + fl;
+    if (j >= N) return;
+    float cs = 0.0f;
+    if (!WIDE_CODED) cs = off * (csum + __shfl_xor(csum, 32));
+    _Float16 *po = out + (bh * N + j) * int64_t(Dh) + half * 4;
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb) {
-        const int j = (wave + NW * jb) * 32 + fl;
-        if (j >= N) continue;
-        float cs = 0.0f;
-        if (!WIDE_CODED) cs = off * (csum[jb] + __shfl_xor(csum[jb], 32));
-        _Float16 *po = out + (bh * N + j) * int64_t(Dh) + half * 4;
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int g = 0; g < 4; ++g) {
+            bm_v4h o;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bm_v4h o;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float add = WIDE_CODED ? off * acc1[dt][4 * g + k] : cs;
-                    o[k] = BmNum<ET>::round(scale * fmaf(s, acc[jb][dt][4 * g + k], add));
-                }
-                *reinterpret_cast<bm_v4h *>(po + dt * 32 + g * 8) = o;
+            for (int k = 0; k < 4; ++k) {
+                const float add = WIDE_CODED ? off * acc1[dt][4 * g + k] : cs;
+                o[k] = BmNum<ET>::round(scale * fmaf(s, acc[dt][4 * g + k], add));
             }
-    }
+            *reinterpret_cast<bm_v4h *>(po + dt * 32 + g * 8) = o;
+        }
 }
 
 // ---- the same two products by tiles of columns -----
@@ -1983,24 +1971,16 @@ template <int KS, typename ET> static void launch_da(const _Float16 *dO, const i
     }
 }
 
-// whether k_attn_tn can take the shape: the chunk of 32 rows of the N x N operand within kMaxWideVecs vectors per
-// thread, at most 2 blocks of j per wave, LDS within the 64 KiB a kernel gets by default
-template <bool WIDE_CODED> static bool tn_fits(int64_t N, int64_t Dh)
-{
-    if (Dh != 32 && Dh != 64 && Dh != 96 && Dh != 128) return false;
-    const int64_t eb = WIDE_CODED ? 1 : 2, per_vec = 16 / eb;
-    if ((32 * N + 2 * (per_vec - 1)) / per_vec + 1 > int64_t(4) * kThreads) return false;
-    if (N > 256) return false;
-    const int64_t wide = (32 * N * eb + 16 + 64 + 15) / 16 * 16, narrow = 32 * (WIDE_CODED ? 2 * Dh + 32 : Dh + 32);
-    return 2 * (wide + narrow) <= 65536;
-}
+// whether k_attn_tn can take the shape; a chunk of 32 rows is then within kMaxWideVecs vectors per thread, and all of it within the 64 KiB of LDS
+// that a kernel gets by default
+static bool tn_fits(int64_t N, int64_t Dh) { return (Dh == 32 || Dh == 64 || Dh == 96 || Dh == 128) && N < 128; }
 
-template <int DT, int JB, bool WIDE_CODED, int NW, typename ET>
+template <int DT, bool WIDE_CODED, int NW, typename ET>
 static void launch_tn_one(const void *wide, const void *narrow, _Float16 *out, int64_t batches, int N, int heads, float scale,
                           const float *alpha, const float *beta, hipStream_t s)
 {
-    typedef TnCfg<DT, JB, WIDE_CODED, NW> C;
-    hipLaunchKernelGGL((k_attn_tn<DT, JB, WIDE_CODED, NW, ET>), dim3(unsigned(batches)), dim3(C::kNt), C::lds_bytes(N), s, wide, narrow,
+    typedef TnCfg<DT, WIDE_CODED, NW> C;
+    hipLaunchKernelGGL((k_attn_tn<DT, WIDE_CODED, NW, ET>), dim3(unsigned(batches)), dim3(C::kNt), C::lds_bytes(N), s, wide, narrow,
                        out, N, heads, scale, alpha, beta, int(C::wide_bytes(N)), batches * N * int64_t(N));
 }
 
@@ -2008,13 +1988,12 @@ template <bool WIDE_CODED, typename ET>
 static void launch_tn(const void *wide, const void *narrow, _Float16 *out, int64_t batches, int N, int Dh, int heads, float scale,
                       const float *alpha, const float *beta, hipStream_t s)
 {
-    // waves per workgroup and blocks of j per wave, so that no wave is left without a block
+    // a wave per block of 32 rows j
 #define MESA_TN(DT_) \
     do { \
-        if (N <= 32) launch_tn_one<DT_, 1, WIDE_CODED, 1, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
-        else if (N <= 64) launch_tn_one<DT_, 1, WIDE_CODED, 2, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
-        else if (N <= 128) launch_tn_one<DT_, 1, WIDE_CODED, 4, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
-        else launch_tn_one<DT_, 2, WIDE_CODED, 4, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
+        if (N <= 32) launch_tn_one<DT_, WIDE_CODED, 1, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
+        else if (N <= 64) launch_tn_one<DT_, WIDE_CODED, 2, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
+        else launch_tn_one<DT_, WIDE_CODED, 4, ET>(wide, narrow, out, batches, N, heads, scale, alpha, beta, s); \
     } while (0)
     if (Dh == 32) MESA_TN(1);
     else if (Dh == 64) MESA_TN(2);
@@ -2134,11 +2113,11 @@ static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
 // whole; (1536, 131, 64) -11.6 and -11.1.  Whole against general, dK: (2048, 8, 128) 17.0 -> 11.8, (1536, 10, 128) -3.9, (1536, 12, 32) -2.1, (571, 33, 32) -0.7,
 // (200, 23, 96) +0.1; dV of (275, 71, 32) -0.5, by tiles of (14, 1392, 32) -3.0, (29, 575, 32) -1.8, (132, 128, 96),
 // 16896 columns, +1.7 of 11.1.
-template <bool WIDE_CODED> static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
+static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
 {
     const int64_t columns = Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 18432 : 20480;
     if (batches < ceil_div(columns, N < 32 ? 32 : N)) return kWayGeneral;
-    const bool whole = tn_fits<WIDE_CODED>(N, Dh) && batches < (int64_t(1) << 31);
+    const bool whole = tn_fits(N, Dh) && batches < (int64_t(1) << 31);
     if (tn_cols_fits(batches, N, Dh) && (N >= 128 || N % 16 == 0 || !whole)) return kWayTiles;
     return whole ? kWayWhole : kWayGeneral;
 }
@@ -2232,7 +2211,7 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
 #define MESA_AV_DV(ET) \
     do { \
         if (launch_bmm_waves<true, false, false, ET>(v, batches, s)) break; \
-        const AttnWay way = tn_way<true>(batches, N, Dh); \
+        const AttnWay way = tn_way(batches, N, Dh); \
         if (way == kWayTiles) launch_tn_cols<true, ET>(aq, dO, v.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
         else if (way == kWayWhole) launch_tn<true, ET>(aq, dO, v.c, batches, int(N), int(Dh), int(H), 1.0f, alpha_a, beta_a, s); \
         else launch_bmm<true, false, false, ET>(v, batches, s); \
@@ -2307,7 +2286,7 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_qk_bwd_q(const int8_t *qq, const in
 #undef MESA_QK_DQ
 #define MESA_QK_DK(ET) \
     do { \
-        const AttnWay way = tn_way<false>(batches, N, Dh); \
+        const AttnWay way = tn_way(batches, N, Dh); \
         if (way == kWayTiles) launch_tn_cols<false, ET>(dS, qq, k.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
         else if (way == kWayWhole) launch_tn<false, ET>(dS, qq, k.c, batches, int(N), int(Dh), int(H), scale, alpha_q, beta_q, s); \
         else launch_bmm<false, false, false, ET>(k, batches, s); \
