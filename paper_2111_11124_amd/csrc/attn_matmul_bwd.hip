@@ -2222,11 +2222,13 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
         } else if (dt == MESA_BF16) MESA_AV_DV(__bf16); else MESA_AV_DV(_Float16);
     };
 #undef MESA_AV_DV
-    // A dA that is larger than the memory-side cache (256 MB) is still leaving it while the next kernel reads: dV, bound by its reads, goes first
-    // then.  (1, 16, 4096, 64) bfloat16, 537 MB: dV 100 -> 70 us, softmax behind dA 191 -> 211, the whole attention backward 623 -> 595; (1, 8, 4096, 64), 268 MB,
-    // 350 -> 330; (16, 12, 1024, 64), 403 MB, 504 -> 486; (32, 12, 577, 64), 256 MB, 417 -> 405.  A smaller one had better stay for softmax: (8, 12, 1024, 64),
-    // 201 MB, 250 -> 256.  Whole-head dA (sequences of 197: 862 -> 866) and binary32 (634 -> 644) are bound by other things.
-    if (dt != MESA_F32 && batches * N * N > (int64_t(1) << 27) && da_way(batches, N, Dh) == kWayTiles) {
+    // dV, bound by its reads, goes first where dA is about as large as the memory-side cache (256 MB) and more: a dA just written is still leaving that cache
+    // while the next kernel reads, and softmax behind it, which would find a smaller one there, finds little of this one.  The whole attention backward, dA first ->
+    // dV first: (1, 7, 4096, 64) bfloat16, 235 MB, 310 -> 293 us, (1, 8, 4096, 64), 268 MB, 334 -> 315, (1, 16, 4096, 64), 537 MB, 626 -> 602 (dV alone 100 -> 70, softmax 191 -> 211), (16, 12, 1024,
+    // 64), 403 MB, 492 -> 470, (32, 12, 577, 64), 256 MB, 411 -> 402, (256, 12, 250, 64), 384 MB, 635 -> 626, (512, 12, 197, 64), 477 MB, 847 -> 846, (1, 16, 4096, 128), 757 -> 763.  Below it goes either
+    // way: (24, 12, 577, 64), 192 MB, 292 -> 283, (1, 6, 4096, 64), 201 MB, 288 -> 292, (8, 12, 1024, 64), 201 MB, binary16 245 -> 248.  binary32 too, at any size: (4, 12, 1024, 64), 201 MB, 285 ->
+    // 292, (1, 6, 4096, 64), 403 MB, 588 -> 582.
+    if (dt != MESA_F32 && batches * N * N >= 115000000) {
         dv();
         da();
     } else {
