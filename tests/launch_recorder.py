@@ -64,13 +64,18 @@ def kernels():
     import math, re
     rec.recorded_kernel.restype = C.c_char_p
     names = [(rec.recorded_kernel(i).decode(), rec.recorded_shared(i)) for i in range(64)]
+    return [(*parts(mangled), math.prod(k[:3]), math.prod(k[3:]), lds) for k, (mangled, lds) in zip(launches(), names)]
+def parts(mangled):
+    import re
+    n = re.match(r"_ZN4mesa(\d+)", mangled)
+    at = n.end() + int(n.group(1))
+    return mangled[n.end():at], mangled[at + 1:mangled.index("EEv", at)] if mangled[at] == "I" else ""
+def all_kernels():
+    """(name, template arguments) of every kernel in the library, with NAMES"""
+    rec.known_kernel.restype = C.c_char_p
     out = []
-    for k, (mangled, lds) in zip(launches(), names):
-        n = re.match(r"_ZN4mesa(\d+)", mangled)
-        at = n.end() + int(n.group(1))
-        args = mangled[at + 1:mangled.index("EEv", at)] if mangled[at] == "I" else ""
-        out.append((mangled[n.end():at], args, math.prod(k[:3]), math.prod(k[3:]), lds))
-    return out
+    while rec.known_kernel(len(out)): out.append(rec.known_kernel(len(out)).decode())
+    return [parts(m) for m in out]
 def report(x): print("REPORT " + json.dumps(x))
 '''
 
@@ -83,6 +88,7 @@ static struct { const void *f; char *name; } *known;
 static int known_n;
 void __hipRegisterFunction(void **modules, const void *f, char *device, const char *name, unsigned limit, void *a, void *b, void *c, void *d, int *e)
 {
+    if (strncmp(name, "_ZN4mesa", 8)) return;
     known = realloc(known, (known_n + 1) * sizeof(*known));
     known[known_n].f = f;
     known[known_n++].name = strdup(name);
@@ -93,6 +99,7 @@ const char *recorded_kernel(int i)
     return "";
 }
 unsigned recorded_shared(int i) { return shared_[i]; }
+const char *known_kernel(int i) { return i < known_n ? known[i].name : 0; }
 '''
 
 # for `also`: the device and its scratch array, for calls that ask the runtime where the library's own array lies

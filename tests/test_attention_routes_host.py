@@ -107,3 +107,17 @@ def test_dv_goes_first_beside_a_da_as_large_as_the_memory_side_cache():
     for shape, (av, _) in routes(list(first)).items():
         got = "dV" if av[0][0] == "k_attn_tn_cols" or av[0][1].startswith("Lb1") else "dA"
         assert len(av) == 2 and got == first[shape], (shape, av)
+
+
+def test_the_gpu_tests_reach_every_kernel_of_the_products():
+    """and no kernel is there that no call reaches."""
+    from tests.test_gpu_attention_kernels import SIXTEEN, WIDE
+    shapes = [(*s, t) for s in SIXTEEN for t in ("f16", "bf16")] + [(*s, "f32") for s in WIDE]
+    reached = {k[:2] for calls in routes(shapes).values() for call in calls for k in call}
+    there = {tuple(k) for k in run("report(all_kernels())", NAMES) if k[0] in KINDS}
+    assert there and there == reached, there ^ reached
+
+
+def test_heads_over_the_range_of_binary32_go_to_the_general_kernel():
+    w = ways([(1, 22, 600, 64, "f32")])[(1, 22, 600, 64, "f32")]
+    assert set(w.values()) == {"general"}, w
