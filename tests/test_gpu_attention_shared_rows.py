@@ -1,6 +1,5 @@
-"""Attention products where groups of waves share a contraction: dK and dV of aligned sequences, whose rows a workgroup's groups
-share out, and the general kernel with its stages; chunk counts that the groups do and do not divide, every head size, against
-the CPU oracle (the bounds of the other attention tests)."""
+"""Attention products of one or two heads, every head size, against the CPU oracle (the bounds of the other attention tests): the waves of a workgroup share out the
+contraction (k_bmm_waves), whose blocks they do and do not divide.  Kernels whose groups of waves share rows or stages take more heads: test_gpu_attention_kernels.py."""
 import pytest
 import torch
 
@@ -27,5 +26,5 @@ def test_attention_products_rows_shared_among_wave_groups(M, B, H, N, Dh, dtype)
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16], ids=["f32", "f16", "bf16"])
 @pytest.mark.parametrize("B,H,N,Dh", [(1, 1, 129, 40), (1, 2, 257, 64), (1, 1, 289, 96), (1, 1, 511, 64), (1, 1, 513, 64), (1, 1, 545, 32), (1, 1, 577, 72)])
 def test_attention_products_stages_shared_among_wave_groups(M, B, H, N, Dh, dtype):
-    """The general kernel: contractions of stages that two and four groups do and do not divide, ragged last ones."""
+    """Unaligned rows, head sizes without kernels of their own."""
     _attention_case(M, B, H, N, Dh, dtype)

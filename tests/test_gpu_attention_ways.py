@@ -28,7 +28,7 @@ def bmm(x, y):
     return torch.bmm(x.reshape(n, *x.shape[2:]).contiguous(), y.reshape(n, *y.shape[2:]).contiguous()).view(*x.shape[:3], y.shape[3])
 
 
-# heads: more than the 20480 (or 28672) columns that the tiles ask for; 800 for the whole-head dQ; one image of many heads and many of few
+# heads: more than the 12288 to 28672 columns that the tiles ask for; 800 for the whole-head dQ; one image of many heads and many of few
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("B,H,N,Dh", [(160, 3, 64, 64), (107, 3, 65, 96), (100, 3, 71, 128), (450, 1, 64, 32), (133, 6, 49, 64), (270, 3, 101, 64), (80, 3, 127, 32),
                                       (80, 3, 128, 64), (75, 3, 129, 64), (41, 5, 143, 96), (35, 4, 209, 128), (267, 3, 197, 64), (40, 3, 255, 64), (28, 4, 256, 64),

@@ -46,8 +46,8 @@ def _dw(M, Mr, K, N, few=False, spoil=None):
 @pytest.mark.parametrize("Mr,K,N", [(1, 16, 4), (31, 112, 124), (32, 128, 128), (33, 144, 132), (63, 16, 260), (64, 256, 4), (65, 272, 12),
                                     (129, 48, 128), (1000, 192, 576), (4099, 80, 136)])
 def test_linear_dw_binary32_edges(M, Mr, K, N):
-    """Slices of one and two stages, ragged last rows, tiles that end inside, at and behind N and K; per row of dW, since
-    the rows' magnitudes differ by sixty binades."""
+    """Ragged last rows, tiles that end inside, at and behind N and K; per row of dW, since the rows' magnitudes differ by sixty binades.  (All but the
+    last are small enough for k_dw_waves; the tiles and slices of k_dw_cut: test_gpu_linear_dw_cut.py.)"""
     dW, db, (rW, rb) = _dw(M, Mr, K, N)
     assert (np.abs(dW - rW).max(1) / np.abs(rW).max(1)).max() <= 1e-5
     # a column sum of dy can cancel; the bound is on its terms' magnitude, which the largest entry of the row carries
@@ -74,7 +74,7 @@ def test_linear_dw_binary32_extreme_values_stay_in_their_row(M, spoil):
 @pytest.mark.parametrize("B,H,N,Dh", [(1, 1, 8, 8), (2, 3, 19, 24), (1, 2, 32, 64), (1, 1, 63, 40), (1, 2, 64, 64), (1, 1, 65, 72), (1, 2, 128, 96),
                                       (1, 1, 129, 128), (1, 3, 197, 64), (1, 1, 300, 33)])
 def test_attention_products_binary32(M, B, H, N, Dh):
-    """Tiles and stages that end inside, at and behind the extents."""
+    """Tiles and blocks of steps that end inside, at and behind the extents."""
     _attention_case(M, B, H, N, Dh, torch.float32)
 
 

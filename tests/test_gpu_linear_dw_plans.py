@@ -48,7 +48,7 @@ def test_linear_dw_tiles_and_slices(M, Mr, K, N, G, dtype):
                                                 (4097, 768, 264, 12, 4097), (129, 128, 120, 2, 129)])
 def test_linear_dw_of_small_matrices_in_the_workspace_there_is(M, Mr, K, N, G, sized_for, dtype):
     """The small tile in a workspace sized for more rows, which holds fewer slices than it would take, in one of a single slice (None)
-    and in its own.  1e-5 of the largest result, the binary32 bound: every product is exact in binary32, and the sums are of
+    and in its own; matrices that k_dw_waves takes need none of it.  1e-5 of the largest result, the binary32 bound: every product is exact in binary32, and the sums are of
     centred codes or in short chains (contracting 1024 + code, as the large binary16 tiles do, misses it)."""
     g = torch.Generator(device="cuda").manual_seed(Mr + K)
     q = torch.randint(-128, 128, (Mr, K), dtype=torch.int8, device="cuda", generator=g)

@@ -387,7 +387,7 @@ def test_attention_matmul_backward_against_the_oracle(M, B, H, N, Dh):
                                       (2, 4, 64, 32), (1, 2, 300, 128), (3, 2, 40, 64), (1, 2, 24, 128), (1, 1, 255, 128), (1, 2, 223, 32),
                                       (2, 1, 224, 64), (1, 1, 256, 96)])
 def test_attention_matmul_backward_bfloat16(M, B, H, N, Dh):
-    """The same products on bfloat16 tensors: every kernel variant and the general kernel."""
+    """The same products on bfloat16 tensors."""
     _attention_case(M, B, H, N, Dh, torch.bfloat16)
 
 
@@ -395,15 +395,13 @@ def test_attention_matmul_backward_bfloat16(M, B, H, N, Dh):
 @pytest.mark.parametrize("B,H,N,Dh", [(1, 2, 272, 64), (1, 1, 512, 32), (1, 2, 528, 128), (1, 1, 1024, 64), (2, 1, 304, 64), (1, 3, 288, 32),
                                       (1, 1, 784, 128), (1, 2, 264, 64), (1, 1, 328, 32)])
 def test_attention_matmul_backward_long_sequences(M, B, H, N, Dh, dtype):
-    """Sequences beyond one workgroup per head, multiples of 16: the column-tile kernels -- a ragged last column tile
-    (272, 304, 528, 784), a last chunk of 16 rows (272, 304, 528, 784), several whole tiles (512, 1024), every head size;
-    264 and 328 are multiples of 8 only (dA by column tiles, the rest by the general kernel)."""
+    """Long aligned sequences of one to three heads (the kernel for few heads; with more heads these lengths go by tiles: test_gpu_attention_kernels.py)."""
     _attention_case(M, B, H, N, Dh, dtype)
 
 
 @pytest.mark.parametrize("B,H,N,Dh", [(2, 3, 19, 8), (2, 3, 197, 64), (1, 2, 65, 40), (2, 2, 49, 32)])
 def test_attention_matmul_backward_binary32(M, B, H, N, Dh):
-    """The same products on binary32 tensors (the general kernel on three bfloat16 parts), to the binary32 bound."""
+    """The same products on binary32 tensors (three bfloat16 parts of each value), to the binary32 bound."""
     _attention_case(M, B, H, N, Dh, torch.float32)
 
 
