@@ -18,11 +18,11 @@
 // kept in the operand's own orientation; where that is not the orientation the MFMA wants, the
 // fragments come from the LDS transpose reads.  The next stage's loads are in flight while a stage
 // is multiplied.  binary16 or bfloat16 tensors (every kernel here takes the number type as a parameter);
-// binary32 tensors run the general kernel on three bfloat16 parts.
+// binary32 tensors run the general kernel, or the one for few heads, on three bfloat16 parts.
 //
 // That general kernel (k_bmm_q) serves every shape; few heads go to k_bmm_waves (bmm_waves), a launch with both of a call's products;
 // dedicated kernels take over where there is work enough for them (da_way, tn_way,
-// nn_way): k_attn_da, k_attn_tn, k_attn_nn for sequences one workgroup per head (or per 32 rows) can hold, odd lengths
+// nn_way): k_attn_da, k_attn_tn, k_attn_nn for sequences that one workgroup per head (or per 32 rows) holds, odd lengths
 // included, and k_attn_da_cols, k_attn_tn_cols, k_attn_nn_rows, by tiles, for sequences of any length from 64 on (a pitch of N elements
 // with N a multiple of 32 puts the first three kernels' lanes on the same LDS banks).  The tile kernels' rows may start at any
 // element (ANY): a vector that is not aligned touches one cache line more, and from LDS on everything is aligned.  Whole backward (four
@@ -1374,9 +1374,9 @@ __global__ __launch_bounds__(64 * NW, (tn_waves_per_simd<DT, NW>())) void k_attn
 }
 
 // ---- the same two products by tiles of columns -----
-// A workgroup takes 256 columns j of one head and walks down ALL rows i in chunks of 32: per chunk 32 row segments of
+// A workgroup takes 256 columns j of one head and walks down ALL rows i in chunks of 16: per chunk 16 row segments of
 // 256 elements of the N x N operand (512 contiguous bytes of dS, 256 of the A codes: 16-byte vectors, aligned where N is
-// a multiple of 16) and the chunk's 32 rows of the N x Dh operand.  Both lie in LDS row by row, with a
+// a multiple of 16) and the chunk's 16 rows of the N x Dh operand.  Both lie in LDS row by row, with a
 // pitch that keeps the transposing reads of sixteen lanes on different banks; every MFMA operand is one or two
 // transposing reads (lane: column j or d, eight consecutive rows i).  The next chunk's vectors wait in registers
 // while a chunk is multiplied (two LDS buffers, one barrier per chunk).  Wave w takes columns 64 w ..+63 of the tile.

@@ -19,7 +19,8 @@
 // are combined in a fixed order by a second kernel that also applies the affine map (a small tile's
 // only slice applies it itself).
 // Workgroups are numbered so that those sharing a slice of m run on the same XCD (same L2).
-// Small matrices of any type take none of this: k_dw_waves, a 32 x 32 tile per workgroup and one launch.
+// Small matrices of any type, of widths that these vector loads can take, take none of this: k_dw_waves, a 32 x 32 tile per workgroup and one launch.  (Other widths
+// run the plain path at any size.)
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

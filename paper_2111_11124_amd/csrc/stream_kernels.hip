@@ -37,12 +37,14 @@ constexpr int kMmGridCap = 1024;
 // Slabs that are no whole vectors, whose elements a thread looks at one by one: up to 2^24 elements the scan's threads hold two vectors as
 // well, so that twice the workgroups (as many as the single-pass kernel has, for which the workspace is sized) share that out.  Whole call, four
 // -> two vectors: (1542, 4, 49) 13.8 -> 8.5 us, (8, 768, 49) 14.8 -> 10.1, (17001, 2, 20) 8.3 -> 6.3, (26330, 8, 49) 20 -> 17, in binary32 (1, 2048, 441) 23.8 -> 17.2; whole vectors only
-// pay for more partial extrema: (25855, 16, 32) 9.4 -> 11.0, (619, 48, 256) 9.5 -> 11.4, in binary32 (22583, 4, 64) 7.6 -> 9.7, (24, 4096, 96) 35 -> 59 (up to some 2^20 elements it is the same).  So do
+// pay for more partial extrema: (25855, 16, 32) 9.4 -> 11.0, (619, 48, 256) 9.5 -> 11.4, in binary32 (22583, 4, 64) 7.6 -> 9.7, (24, 4096, 96) 35 -> 59.  So do
 // unaligned slabs of one group, (1, 1, 5.4e6) 7.3 -> 9.0 in binary32, and of very many: (3, 8192, 49) 42 -> 61.  Hundreds of slabs that come once each, up to
-// 2^22 elements, gain too: (1, 768, 1056) 10.8 -> 9.1, (1, 2048, 424) 13.6 -> 11.8, (1, 768, 256) 7.9 -> 7.0, in binary32 (1, 2048, 2024) 43 -> 27.
+// 2^22 elements, gain too: (1, 768, 1056) 10.8 -> 9.1, (1, 2048, 424) 13.6 -> 11.8, (1, 768, 256) 7.9 -> 7.0, in binary32 (1, 2048, 2024) 43 -> 27;
+// and up to 2^19 elements of up to 1024 groups, where the call is bound by its launches, the scan itself does: (394, 3, 256) in binary32 4.3 -> 3.7.
 constexpr int64_t kMmSmall = int64_t(1) << 24;
 static bool minmax_two_vectors(const mesa_layout &L)
 {
+    if (L.groups <= 1024 && layout_numel(L) <= kMmSmall / 32) return true;
     if (L.inner % kVec == 0) return L.outer == 1 && L.groups > 256 && L.groups <= 2048 && layout_numel(L) <= kMmSmall / 4;
     return L.groups > 1 && L.groups <= 4096 && layout_numel(L) <= kMmSmall;
 }

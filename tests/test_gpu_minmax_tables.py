@@ -34,6 +34,6 @@ def test_extrema_of_either_number_of_tables(M, layout, dtype):
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=DTYPE_IDS)
-@pytest.mark.parametrize("layout", [(900, 32, 40), (900, 33, 40), (400, 33, 96), (400, 128, 96), (400, 128, 88), (400, 129, 96), (500, 128, 97), (2000, 40, 20), (1, 768, 256)])
+@pytest.mark.parametrize("layout", [(900, 32, 40), (900, 33, 40), (400, 33, 96), (400, 128, 96), (400, 128, 88), (400, 129, 96), (500, 128, 97), (2000, 40, 20), (1, 768, 256), (600, 8, 96), (700, 8, 96)])
 def test_extrema_on_either_side_of_the_tables_lines(M, layout, dtype):
     test_extrema_of_either_number_of_tables(M, layout, dtype)

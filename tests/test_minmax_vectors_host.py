@@ -12,8 +12,8 @@ def scan(layout, dt):
 
 
 def test_vectors_per_thread():
-    whole = [(25855, 16, 32), (619, 48, 256), (22583, 4, 64), (24, 4096, 96), (16, 8192, 64), (27276, 1, 196), (3, 8192, 49), (25216, 6, 64), (200000, 12, 49), (2, 2048, 424), (1, 2048, 4088)]
-    parts = [(8, 768, 49), (17001, 2, 20), (1, 2048, 441), (26330, 8, 49), (1358, 12, 49), (1, 4096, 49), (1, 768, 256), (1, 2048, 424), (1, 2048, 2024)]
+    whole = [(25855, 16, 32), (619, 48, 256), (22583, 4, 64), (24, 4096, 96), (16, 8192, 64), (27276, 1, 196), (700, 8, 96), (7, 2048, 24), (3, 8192, 49), (25216, 6, 64), (200000, 12, 49), (2, 2048, 424), (1, 2048, 4088)]
+    parts = [(8, 768, 49), (17001, 2, 20), (1, 2048, 441), (26330, 8, 49), (1358, 12, 49), (394, 3, 256), (600, 8, 96), (1, 4096, 49), (1, 768, 256), (1, 2048, 424), (1, 2048, 2024)]
     got = run(BODY + f"report([[(l, scan(l, dt)) for l in ls for dt in (M.F16, M.F32)] for ls in ({whole}, {parts})])", NAMES)
     assert all(how[0] == 4 and how[1] <= 1024 + 64 for _, how in got[0]), got[0]
     assert all(how[0] == 2 for _, how in got[1]), got[1]
