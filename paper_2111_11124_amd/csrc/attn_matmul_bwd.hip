@@ -26,7 +26,7 @@
 // included, and k_attn_da_cols, k_attn_tn_cols, k_attn_nn_rows, by tiles, for sequences of any length from 64 on (a pitch of N elements
 // with N a multiple of 32 puts the first three kernels' lanes on the same LDS banks).  The tile kernels' rows may start at any
 // element (ANY): a vector that is not aligned touches one cache line more, and from LDS on everything is aligned.  Whole backward (four
-// products), general kernel -> by tiles: (16, 12, 577, 64) 204 -> 150 us, (8, 8, 919, 64) 162 -> 110, (64, 6, 301, 96) 188 -> 129.
+// products), general kernel -> by tiles: (16, 12, 577, 64) 182 -> 129 us, (8, 8, 919, 64) 151 -> 101, (64, 6, 301, 96) 182 -> 105.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
