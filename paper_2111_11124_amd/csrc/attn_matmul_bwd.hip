@@ -2078,7 +2078,7 @@ template <int DT, typename ET> static void launch_nn(const _Float16 *dS, const i
 }
 
 // Which kernel a product of 16-bit tensors takes: the general one, the one that goes by tiles of columns or rows, or the one that keeps a
-// head's rows or codes whole.  The lines lie where two hundred shapes put them (3 to 1536 heads, 50 to 1024 tokens); us of the product
+// head's rows or codes whole.  The lines lie where some thousands of shapes put them (1 to 2500 heads, 8 to 9000 tokens); us of the product
 // alone, by the general kernel / by tiles / whole, where a path exists.  What decides is how many workgroups a way of cutting leaves: the
 // general kernel has a workgroup per 64 x 64 results and its loads are its own, the others share what they read.
 enum AttnWay { kWayGeneral, kWayTiles, kWayWhole };

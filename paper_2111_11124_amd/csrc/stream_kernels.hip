@@ -1170,7 +1170,10 @@ static int64_t slab_vectors(int64_t inner) { return inner / kVec + (inner % kVec
 // the vectors at their ends ((100000, 12, 20): 22 and 35), longer ones keep a lane's group as it is.
 // Beyond four million elements it takes slabs that are not even multiples of four elements, or a tensor that is large
 // enough: (11184, 2, 1500) 17.7 and 18.5, (82241, 3, 68) 14.9 and 16.3, (15420, 8, 68) in binary32 14.4 and 17.6.  The lines were
-// fitted to 2300 shapes in both types, of one to 8192 groups; both scans have become faster since, the one by group by more.
+// fitted to 2300 shapes in both types, of one to 8192 groups, before both scans became faster, the one by group by more, and lie on the safe side since: of 2500 random layouts of
+// 2^11 to 2^26 elements the 899 that go by group are 1.9 times as fast for it in the geometric mean (four 2 to 6 % slower), but it would also be the faster way for whole slabs of 64 elements and more,
+// 512 to 4095 of a group, 513 to 4095 groups, (23, 520, 64) 7.6 and 5.1, for short whole slabs of two groups and more up to 2^17 elements in all, (1336, 8, 8) 5.4 and 4.2, and beyond four million elements for
+// most of what is no whole vectors, (11426, 12, 74) 15.9 and 12.5, (7208, 4, 1708) 27.3 and 23.2, though not for all: in binary32 (151058, 4, 68) 40.7 and 42.2.
 enum MinmaxScan { kByPosition, kByGroup, kByGroupInPieces };
 
 static MinmaxScan minmax_scan(int64_t outer, int64_t groups, int64_t inner)

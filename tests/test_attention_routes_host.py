@@ -69,7 +69,7 @@ def test_short_heads_keep_a_workgroup_per_head():
 
 
 def test_da_of_medium_and_long_heads():
-    """dA by tiles of aligned rows as soon as there are workgroups for it, of wide short heads and of unaligned rows up to 704 tokens whole."""
+    """dA by tiles of aligned rows as soon as there are workgroups for it, of wide short heads and of unaligned rows up to 800 tokens whole."""
     want = {(1, 118, 224, 64, "f16"): "tiles", (1, 12, 760, 64, "bf16"): "tiles", (1, 12, 728, 128, "f16"): "tiles", (1, 250, 64, 64, "f16"): "general", (1, 403, 80, 96, "bf16"): "whole",
             (1, 822, 72, 96, "f16"): "whole", (1, 400, 88, 128, "f16"): "whole", (1, 27, 553, 64, "f16"): "whole", (1, 42, 463, 128, "f16"): "whole", (1, 28, 610, 32, "bf16"): "whole",
             (1, 192, 577, 64, "f16"): "tiles", (1, 192, 420, 64, "f16"): "whole", (1, 60, 919, 64, "f16"): "tiles", (1, 16, 4096, 64, "bf16"): "tiles", (1, 768, 197, 64, "f16"): "whole",
