@@ -740,7 +740,7 @@ __global__ __launch_bounds__(64 * NW) void k_bmm_waves_two(BmmArgs a, BmmArgs b,
 
 // Waves of k_bmm_waves's workgroups where it is the faster kernel for both products of a call, in one launch, else 0: no more than there are blocks of steps, and
 // as many workgroups as run at once (binary32, whose other kernel is the general one alone: half as many again, or twice).  Two launches of the kernels chosen by
-// da_way, tn_way and nn_way -> one of this kernel, dQ and dK: 16 bits (3, 436, 64) 14.0 -> 5.2, 400 to 512 tiles of eight waves -2.5, 700 to 800 of four -0.3; (1, 4096, 64) 96 -> 30,
+// da_way, tn_way and nn_way -> one of this kernel, dQ and dK: 16 bits (3, 436, 64) 14.0 -> 5.2, 400 to 512 tiles of eight waves -2.5, of four up to 450 -1.3 to -2, 512 to 610 -0.4 to +0.2, 720 +0.3 to +0.8; (1, 4096, 64) 96 -> 30,
 // (2, 4100, 32) 91 -> 41, (4, 2048, 64) 54 -> 31, (1, 8192, 64) 185 -> 106.  binary32: (12, 783, 64), 600 tiles, 43 -> 32; (65, 112, 96), 780, 13.8 -> 10.9, (10, 1248, 64), 780, 47.0 -> 45.2.
 // Four waves in binary32, heads of at most 32 columns, half a tile of the general kernel, (1653, 20, 32) 16.0 -> 12.5, (1951, 13, 32) 16.8 -> 13.7, (936, 35, 32), 1872, -0.4, others
 // (290, 39, 64), 1160 tiles, 12.0 -> 10.6, (313, 22, 128), 1252, -0.1, (334, 57, 64), 1336, +0.5, (490, 53, 64), 1960, 12.8 -> 15.8, (464, 24, 128), 1856, 10.9 -> 14.4.
@@ -750,7 +750,7 @@ template <typename ET> static int bmm_waves(int64_t batches, int64_t R, int64_t 
     const int64_t tiles = batches * ceil_div(R, 32) * ceil_div(Cn, 32);
     if (tiles <= 256 && Tn > 128) return 16;
     if (Tn > 64) return tiles <= (kWide ? 800 : 512) ? 8 : 0;
-    return tiles <= (!kWide ? 800 : Cn <= 32 ? 2048 : 1248) ? 4 : 0;
+    return tiles <= (!kWide ? 640 : Cn <= 32 ? 2048 : 1248) ? 4 : 0;
 }
 
 // The same for a product in a launch of its own (dA or dV).  16 bits: four waves gain nothing there (dA +0.1 to +0.5 us, (78, 65, 64) 7.3 -> 8.5; dV -0.3 to +0.2), eight for dA
@@ -2112,12 +2112,13 @@ static AttnWay da_way(int64_t batches, int64_t N, int64_t Dh)
 // (64, 919, 64) -18, (192, 197, 64) -1.9, (1536, 197, 96) -83; (3, 601, 64) +5.  Whole (a few percent ahead) below 128 tokens: (1536, 71, 64) dK -1.2 by tiles, -3.0
 // whole; (1536, 131, 64) -11.6 and -11.1.  Whole against general, dK: (2048, 8, 128) 17.0 -> 11.8, (1536, 10, 128) -3.9, (1536, 12, 32) -2.1, (571, 33, 32) -0.7,
 // (200, 23, 96) +0.1; dV of (275, 71, 32) -0.5, by tiles of (14, 1392, 32) -3.0, (29, 575, 32) -1.8, (132, 128, 96),
-// 16896 columns, +1.7 of 11.1.
+// 16896 columns, +1.7 of 11.1.  Heads of up to 32 rows are a wave each, of which some hundred do: calls of dQ and dK by the general kernel / whole, (582, 8, 128) 8.9 / 7.7, (450, 13, 96)
+// 9.5 / 8.4, (733, 8, 64) 7.9 / 7.2, 256 heads of 64 or 96 -0.1 to -0.4, dA and dV -0.1 to +0.1 there, at heads of 128 +0.4 with 256 and 0.0 with 360.
 static AttnWay tn_way(int64_t batches, int64_t N, int64_t Dh)
 {
-    const int64_t columns = Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 18432 : 20480;
-    if (batches < ceil_div(columns, N < 32 ? 32 : N)) return kWayGeneral;
     const bool whole = tn_fits(N, Dh) && batches < (int64_t(1) << 31);
+    const int64_t columns = N <= 32 && whole ? (Dh == 128 ? 11520 : 8192) : Dh == 32 ? 12288 : Dh == 64 ? 28672 : Dh == 96 ? 18432 : 20480;
+    if (batches < ceil_div(columns, N < 32 ? 32 : N)) return kWayGeneral;
     if (tn_cols_fits(batches, N, Dh) && (N >= 128 || N % 16 == 0 || !whole)) return kWayTiles;
     return whole ? kWayWhole : kWayGeneral;
 }

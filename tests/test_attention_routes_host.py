@@ -68,6 +68,16 @@ def test_short_heads_keep_a_workgroup_per_head():
         assert w["dV"] == w["dK"] == want[shape], (shape, w)
 
 
+def test_heads_of_one_block_of_rows_keep_a_workgroup_each():
+    """dV and dK of up to 32 rows, a wave per head, from a few hundred heads on; both products of dQ and dK by waves only up to 640 tiles in 16 bits."""
+    want = {(1, 410, 16, 96, "f16"): "whole", (1, 450, 13, 96, "bf16"): "whole", (1, 582, 8, 128, "f16"): "whole", (1, 487, 32, 96, "f16"): "whole", (1, 733, 8, 64, "bf16"): "whole", (1, 340, 11, 64, "f16"): "whole",
+            (1, 410, 33, 96, "f16"): "general", (1, 350, 8, 128, "f16"): "general", (1, 360, 8, 128, "f16"): "whole", (1, 641, 25, 32, "bf16"): "whole"}
+    for shape, w in ways(list(want)).items():
+        assert w["dK"] == w["dV"] == want[shape] and w["dQ"] != "waves", (shape, w)
+    for shape, w in ways([(1, 640, 25, 32, "bf16"), (1, 320, 11, 64, "f16"), (1, 160, 44, 64, "f16")]).items():
+        assert w["dQ"] == w["dK"] == "waves", (shape, w)
+
+
 def test_da_of_medium_and_long_heads():
     """dA by tiles of aligned rows as soon as there are workgroups for it, of wide short heads and of unaligned rows up to 800 tokens whole."""
     want = {(1, 118, 224, 64, "f16"): "tiles", (1, 12, 760, 64, "bf16"): "tiles", (1, 12, 728, 128, "f16"): "tiles", (1, 250, 64, 64, "f16"): "general", (1, 403, 80, 96, "bf16"): "whole",
