@@ -251,6 +251,26 @@ template <> struct Nt<float> {
     }
 };
 
+// A span of memory with the hardware's bounds check: what a lane loads from beyond it is zero and is not fetched, what it stores there is
+// dropped.  So a lane without an element takes offset kNowhere and no branch: where paths with and without an access in flight
+// meet, the compiler waits for everything that was requested after the value it needs, stores included.
+constexpr uint32_t kNowhere = 0xFFFFFF00u;
+struct Span {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Span(const void *p, uint32_t bytes) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, int(bytes), 0x00027000)) {}
+    // streaming accesses (kNt: the non-temporal bit), byte offsets
+    static constexpr int kNt = 2;
+    __device__ __forceinline__ u32x4 load16(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b128(r, int(at), 0, kNt); }
+    __device__ __forceinline__ u32x2 load8(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b64(r, int(at), 0, kNt); }
+    __device__ __forceinline__ float load_f32(uint32_t at) const { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, int(at), 0, 0)); }
+    __device__ __forceinline__ void store16(uint32_t at, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, int(at), 0, kNt); }
+    // eight elements of type T, at: the offset of the first one
+    __device__ __forceinline__ void load(uint32_t at, u32x4 &v) const { v = load16(at); }
+    __device__ __forceinline__ void load(uint32_t at, Store<float>::raw_t &v) const { v.lo = load16(at); v.hi = load16(at == kNowhere ? at : at + 16); }
+    __device__ __forceinline__ void store(uint32_t at, u32x4 v) const { store16(at, v); }
+    __device__ __forceinline__ void store(uint32_t at, Store<float>::raw_t v) const { store16(at, v.lo); store16(at == kNowhere ? at : at + 16, v.hi); }
+};
+
 // 8 codes (int8, q = x_bar - 128) <-> 8 floats holding x_bar in [0, 255]
 __device__ __forceinline__ u32x2 load_codes8(const int8_t *q, int64_t e)
 {

@@ -85,46 +85,45 @@ __global__ __launch_bounds__(kThreads, ln_rows_wg_per_cu(sizeof(T), VPL)) void k
         }
     }
 
-    // One block of rows is in registers while the previous one is worked on: the loads of block
-    // i+1 are issued before the arithmetic, the lane-group sums and the stores of block i.
-    // Lanes without a row or a vector work on zeros: dy = 0 adds nothing to any sum, and only the
-    // loads and the stores are predicated.
+    // One block of rows is on its way while the previous one is worked on, in two register sets that take turns.  Nothing in the loop is
+    // conditional: lanes without a vector and rows past the end are out of their span's bounds, load zeros (dy = 0 adds nothing to
+    // any sum) and store nothing, and so does a whole block past the end.  (With a branch around each access the wait for a block was a
+    // wait for the stores of the block before it, and for the next block's loads: 50432 x 768 binary16, new inputs each time, 44.9 -> 40.8 us
+    // for the call, 100000 x 512 55.0 -> 51.7, 25000 x 640 26.5 -> 24.4, 200000 x 128 31.4 -> 29.2; 100000 x 1024 1 % behind.  Waiting for the stores by
+    // hand gives the former times.)  What bounds it now is HBM: 194 MB in 37 us and the dependent launch.
     struct Block {
         u32x2 cq[U][VPL];
         typename Store<T>::raw_t cd[U][VPL];
         float mu[U], rs[U];
     };
-    const typename Store<T>::raw_t zero_d = Store<T>::pack((const float[8]){0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f});
-    auto load_block = [&](int64_t base, Block &blk) {
+    constexpr uint32_t kEb = sizeof(T);
+    uint32_t at[U][VPL], row_at[U];                      // of this lane in a block: elements of its vectors, row
+#pragma unroll
+    for (int p = 0; p < U; ++p) {
+        row_at[p] = (p * kWaves + wave) * RPW + sub;
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) at[p][k] = act[k] ? row_at[p] * D + col[k] : kNowhere;
+    }
+    auto rows_of = [&](int64_t row0) { return row0 >= M ? 0u : M - row0 < kBlockRows ? uint32_t(M - row0) : uint32_t(kBlockRows); };
+    auto load_block = [&](int64_t row0, Block &blk) __attribute__((always_inline)) {
+        const uint32_t rows = rows_of(row0);
+        const Span sq(xq + row0 * D, rows * D), sd(static_cast<const char *>(dy) + row0 * D * kEb, rows * D * kEb), sm(mean + row0, rows * 4), sr(rstd + row0, rows * 4);
 #pragma unroll
         for (int p = 0; p < U; ++p) {
-            const int64_t row = base + int64_t((p * kWaves + wave) * RPW + sub);
-            const bool ok = row < M;
-            blk.mu[p] = 0.0f;
-            blk.rs[p] = 0.0f;
-            if (ok) { blk.mu[p] = mean[row]; blk.rs[p] = rstd[row]; }
+            blk.mu[p] = sm.load_f32(row_at[p] * 4);
+            blk.rs[p] = sr.load_f32(row_at[p] * 4);
 #pragma unroll
             for (int k = 0; k < VPL; ++k) {
-                blk.cq[p][k] = u32x2{0u, 0u};
-                blk.cd[p][k] = zero_d;
-                if (ok && act[k]) {
-                    const int64_t e = row * D + col[k];
-                    blk.cq[p][k] = nt_load<u32x2>(xq + e);
-                    blk.cd[p][k] = Nt<T>::load(dy, e);
-                }
+                blk.cq[p][k] = sq.load8(at[p][k]);
+                sd.load(act[k] ? at[p][k] * kEb : kNowhere, blk.cd[p][k]);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);                 // requested before the other block is worked on
     };
-    const int64_t stride = int64_t(gridDim.x) * kBlockRows;
-    int64_t base = int64_t(blockIdx.x) * kBlockRows;
-    Block cur, nxt;
-    if (base < M) load_block(base, cur);
-    for (; base < M; base += stride) {
-        load_block(base + stride, nxt);    // past the last block: every row fails its check, nothing is read
+    auto work = [&](int64_t row0, const Block &cur) __attribute__((always_inline)) {
+        const Span sx(static_cast<char *>(dx) + row0 * D * kEb, rows_of(row0) * D * kEb);
 #pragma unroll
         for (int p = 0; p < U; ++p) {
-            const int64_t row = base + int64_t((p * kWaves + wave) * RPW + sub);
-            const bool ok = row < M;
             float xn[VPL][8], gg[VPL][8];
             float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
@@ -149,11 +148,21 @@ __global__ __launch_bounds__(kThreads, ln_rows_wg_per_cu(sizeof(T), VPL)) void k
                 float o[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] = cur.rs[p] * (gg[k][j] - c1 - xn[k][j] * c2);
-                if (ok && act[k]) Nt<T>::store(dx, row * D + col[k], Store<T>::pack(o));
+                sx.store(act[k] ? at[p][k] * kEb : kNowhere, Store<T>::pack(o));
             }
         }
-        cur = nxt;
+    };
+    const int64_t stride = int64_t(gridDim.x) * kBlockRows;
+    int64_t row0 = int64_t(blockIdx.x) * kBlockRows;
+    Block even, odd;
+    load_block(row0, even);
+    for (; row0 + stride < M; row0 += 2 * stride) {
+        load_block(row0 + stride, odd);
+        work(row0, even);
+        load_block(row0 + 2 * stride, even);
+        work(row0 + stride, odd);
     }
+    if (row0 < M) work(row0, even);
 
     // column sums of this workgroup: slot (wave, sub) holds what its lanes gathered
 #pragma unroll
