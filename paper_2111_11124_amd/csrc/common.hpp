@@ -264,6 +264,8 @@ struct Span {
     __device__ __forceinline__ u32x2 load8(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b64(r, int(at), 0, kNt); }
     __device__ __forceinline__ float load_f32(uint32_t at) const { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, int(at), 0, 0)); }
     __device__ __forceinline__ void store16(uint32_t at, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, int(at), 0, kNt); }
+    __device__ __forceinline__ void store8(uint32_t at, u32x2 v) const { __builtin_amdgcn_raw_buffer_store_b64(v, r, int(at), 0, kNt); }
+    __device__ __forceinline__ void store_f32(uint32_t at, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, int(at), 0, 0); }
     // eight elements of type T, at: the offset of the first one
     __device__ __forceinline__ void load(uint32_t at, u32x4 &v) const { v = load16(at); }
     __device__ __forceinline__ void load(uint32_t at, Store<float>::raw_t &v) const { v.lo = load16(at); v.hi = load16(at == kNowhere ? at : at + 16); }
