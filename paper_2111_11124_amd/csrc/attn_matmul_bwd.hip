@@ -1097,6 +1097,12 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
     const float s = alpha_v[h] / 255.0f;
     const float off = fmaf(BmNum<ET>::kCentre, s, beta_v[h]);
     unsigned char *lout = lds_dc + C::kOutAt + wave * (32 * C::kRowOut);
+    // Rows that start on half lines leave non-temporally: their pieces are whole lines, or halves of one, that nobody of this launch reads, and kept
+    // in the L2 like other lines they pushed the operands out and left it, some at a time, during the kernels that follow.  The whole attention backward of
+    // (1, 16, 4096, 64) bfloat16 617 -> 564 us, of (64, 1, 2048, 32) 590 -> 562, of (355, 1, 288, 64) 117 -> 109, of (96, 1, 1024, 64) 249 -> 243; 28 of 40 shapes faster, the slowest 1.5 % behind.
+    // Other rows' pieces are parts of lines at both ends: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
+    const bool on_lines = N % 32 == 0;
+    const Span lines(dA + (bh * N + i0) * int64_t(N), uint32_t(rows) * uint32_t(N) * 2u);
     auto wave_sync = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1151,7 +1157,8 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
                     _Float16 *to = dA + (bh * N + i0 + rb * 32 + r) * int64_t(N) + j0 + wave * 64 + cv * 8;
                     const u32x4 w = *reinterpret_cast<const u32x4 *>(lout + r * C::kRowOut + cv * 16);
                     if constexpr (!ANY) {
-                        *reinterpret_cast<u32x4 *>(to) = w;
+                        if (on_lines) lines.store16(uint32_t((rb * 32 + r) * N + j0 + wave * 64 + cv * 8) * 2u, w);
+                        else *reinterpret_cast<u32x4 *>(to) = w;
                     } else if (wave * 64 + cv * 8 + 8 <= cols) {
                         __builtin_memcpy(to, &w, 16);      // rows start at any element
                     } else {
