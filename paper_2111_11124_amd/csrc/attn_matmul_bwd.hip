@@ -1098,10 +1098,12 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
     const float off = fmaf(BmNum<ET>::kCentre, s, beta_v[h]);
     unsigned char *lout = lds_dc + C::kOutAt + wave * (32 * C::kRowOut);
     // Rows that start on half lines leave non-temporally: their pieces are whole lines, or halves of one, that nobody of this launch reads, and kept
-    // in the L2 like other lines they pushed the operands out and left it, some at a time, during the kernels that follow.  The whole attention backward of
-    // (1, 16, 4096, 64) bfloat16 617 -> 564 us, of (64, 1, 2048, 32) 590 -> 562, of (355, 1, 288, 64) 117 -> 109, of (96, 1, 1024, 64) 249 -> 243; 28 of 40 shapes faster, the slowest 1.5 % behind.
-    // Other rows' pieces are parts of lines at both ends: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
-    const bool on_lines = N % 32 == 0;
+    // like other lines they pushed the operands out of the L2 and left it, some at a time, during the kernels that follow.  The whole attention backward of
+    // (1, 16, 4096, 64) bfloat16 617 -> 564 us, of (1, 12, 4096, 64) 478 -> 457, of (355, 1, 288, 64) 117 -> 109, of (400, 1, 320, 32) 113 -> 110.  Rows of a multiple of 128 elements
+    // meet on the same memory channels, and a dA that the memory-side cache would take in wants to go there: up to 130 MB (32, 1, 1024, 64) 101 -> 108,
+    // (500, 1, 256, 64) 107 -> 116, (8, 1, 2048, 64) 126 -> 131, from 200 MB on (96, 1, 1024, 64) 249 -> 242, (100, 1, 1536, 64) 587 -> 546.
+    // Rows that start elsewhere end in parts of lines: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
+    const bool on_lines = N % 32 == 0 && (N % 128 != 0 || int64_t(gridDim.x) * (C::kRows * 256) >= 100000000);
     const Span lines(dA + (bh * N + i0) * int64_t(N), uint32_t(rows) * uint32_t(N) * 2u);
     auto wave_sync = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
