@@ -317,6 +317,24 @@ __device__ __forceinline__ void minmax_finish(MinMaxState<T> (&st)[U], int *lmn,
     store_tables(all_mn, all_mx, groups, tables, part);
 }
 
+// The vectors of a chunk of x for the scan of its extrema.  A tensor that a fraction of the memory-side cache (256 MB) holds is loaded like any
+// data, so that the quantizer, which reads it next, finds it there; a larger one with the non-temporal hint (one of the two as a span: the compiler makes one of two
+// loads that differ in the hint only).  Both calls, on new inputs each time, non-temporal -> so: (25216, 6, 64) binary16 19.6 -> 18.0 us, (128, 6, 38809) 37.3 -> 35.1, (50432, 12, 64)
+// 44.0 -> 41.1, (8192, 3, 2401), 118 MB, 63.4 -> 61.8, (10000, 8, 128) binary32 27.1 -> 24.4; larger ones: 123 to 169 MB +-1 %, (256, 12, 38809), 238 MB, 109 and 113.
+constexpr int64_t kScanKeepBytes = 120000000;
+template <typename T, int U>
+__device__ __forceinline__ void scan_load(const void *__restrict__ x, int64_t base, bool keep, typename Store<T>::raw_t (&v)[U])
+{
+    if (keep) {                                    // uniform
+        const Span sx(static_cast<const char *>(x) + base * int64_t(sizeof(T)), uint32_t(kThreads * U * kVec * sizeof(T)));
+#pragma unroll
+        for (int u = 0; u < U; ++u) sx.load_kept((u * kThreads + threadIdx.x) * uint32_t(kVec * sizeof(T)), v[u]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = Nt<T>::load(x, base + (u * kThreads + int(threadIdx.x)) * kVec);
+    }
+}
+
 // Partial extrema of each workgroup: part[wg][0..G) = min, part[wg][G..2G) = max.  (Letting the last
 // workgroup to finish do the final step in the same launch was tried and dropped, twice: the device-scope
 // fence it needs flushes the per-XCD L2 once per workgroup, and without a fence, every partial and a flag per workgroup
@@ -342,16 +360,18 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial(const void *__restr
     constexpr int kChunk = kThreads * U * kVec;
     const int64_t stride = int64_t(gridDim.x) * kChunk;
     const int64_t toff = int64_t(threadIdx.x) * kVec;
+    const bool keep = numel * int64_t(sizeof(T)) <= kScanKeepBytes;
     // CHECK = false: the chunk lies wholly inside the tensor, no per-vector bounds test
     auto chunk = [&](int64_t base, auto check) {
         constexpr bool CHECK = decltype(check)::value;
         typename Store<T>::raw_t v[U];
         bool full[U];
+        if (!CHECK) scan_load<T, U>(x, base, keep, v);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t e = base + u * (kThreads * kVec) + toff;
             full[u] = !CHECK || e + kVec <= numel;
-            if (full[u]) v[u] = Nt<T>::load(x, e);
+            if (CHECK && full[u]) v[u] = Store<T>::load(x, e);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -417,15 +437,17 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial_few(const void *__r
     constexpr int kChunk = kThreads * U * kVec;
     const int64_t stride = int64_t(gridDim.x) * kChunk;
     const int64_t toff = int64_t(threadIdx.x) * kVec;
+    const bool keep = numel * int64_t(sizeof(T)) <= kScanKeepBytes;
     auto chunk = [&](int64_t base, auto check) {
         constexpr bool CHECK = decltype(check)::value;
         typename Store<T>::raw_t v[U];
         bool full[U];
+        if (!CHECK) scan_load<T, U>(x, base, keep, v);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t e = base + u * (kThreads * kVec) + toff;
             full[u] = !CHECK || e + kVec <= numel;
-            if (full[u]) v[u] = Nt<T>::load(x, e);
+            if (CHECK && full[u]) v[u] = Store<T>::load(x, e);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
