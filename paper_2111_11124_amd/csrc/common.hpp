@@ -269,6 +269,8 @@ struct Span {
     // without the hint
     __device__ __forceinline__ void load_kept(uint32_t at, u32x4 &v) const { v = __builtin_amdgcn_raw_buffer_load_b128(r, int(at), 0, 0); }
     __device__ __forceinline__ void load_kept(uint32_t at, Store<float>::raw_t &v) const { load_kept(at, v.lo); load_kept(at + 16, v.hi); }
+    __device__ __forceinline__ void keep(uint32_t at, u32x4 v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, int(at), 0, 0); }
+    __device__ __forceinline__ void keep(uint32_t at, Store<float>::raw_t v) const { keep(at, v.lo); keep(at + 16, v.hi); }
     // eight elements of type T, at: the offset of the first one
     __device__ __forceinline__ void load(uint32_t at, u32x4 &v) const { v = load16(at); }
     __device__ __forceinline__ void load(uint32_t at, Store<float>::raw_t &v) const { v.lo = load16(at); v.hi = load16(at == kNowhere ? at : at + 16); }

@@ -291,6 +291,12 @@ __global__ __launch_bounds__(kThreads, kSmWgPerCu) void k_softmax_bwd(const int8
 // and dx is written back over dy in LDS, from where it leaves as aligned vectors.  dx may be dy (in place): a
 // tile's dy is in LDS before any of its dx is stored, and tiles do not overlap.
 // ---------------------------------------------------------------------------------------------
+// A dx that a fraction of the memory-side cache (256 MB) holds is stored like any data, so that the product that reads it next finds it there; a larger one
+// non-temporally (one of the two as a span: the compiler makes one of two stores that differ in the hint only).  The whole attention backward, non-temporal ->
+// so: (768, 1, 197, 64) binary16, 60 MB, 122.4 -> 120.7 us, (500, 1, 250, 64) 117.2 -> 115.6, (60, 1, 577, 64) 90.1 -> 87.0; the call alone (64, 6, 197) binary32, 60 MB, 37.9 -> 32.8.
+// (16, 12, 577), 128 MB, 58.2 and 60.2; (1000, 1, 100, 64), 20 MB, whose lines would leave the L2s at the kernel's end, 61.8 and 63.1.
+constexpr int64_t kSbKeepLeast = 30000000, kSbKeepMost = 100000000;
+__device__ __forceinline__ bool sb_keep(int64_t bytes) { return bytes >= kSbKeepLeast && bytes <= kSbKeepMost; }
 constexpr int kSbRowWaves = 4;      // waves per SIMD the row kernel's register budget is set for
 
 template <typename T, int LPR, int EPL, bool TIGHT>
@@ -334,6 +340,7 @@ __global__ __launch_bounds__(kThreads, kSbRowWaves) void k_softmax_bwd_rows(cons
             }
         }
     };
+    const bool keep = sb_keep(total_rows * cols * kB);
     const int64_t tile_step = int64_t(gridDim.x) * kWaves;
     int64_t tile = int64_t(blockIdx.x) * kWaves + wave;
     if (tile < tiles) fetch(tile);
@@ -391,10 +398,20 @@ __global__ __launch_bounds__(kThreads, kSbRowWaves) void k_softmax_bwd_rows(cons
         }
         team_sync<64>();
 
+        if (keep) {                                      // uniform
+            const uint64_t at = __builtin_amdgcn_readfirstlane(uint32_t(e0)) | uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(uint64_t(e0) >> 32)))) << 32;
+            const Span sx(static_cast<char *>(dx) + at * kB, uint32_t(__builtin_amdgcn_readfirstlane(nfull)) * uint32_t(kVec * kB));   // the wave's: the same for all its lanes
 #pragma unroll
-        for (int u = 0; u < kSrFlat; ++u) {
-            const uint32_t v = u * 64 + lane;
-            if (v < nfull) Nt<T>::store(dx, e0 + v * kVec, Store<T>::load(gs, int64_t(v) * kVec));
+            for (int u = 0; u < kSrFlat; ++u) {
+                const uint32_t v = u * 64 + lane;
+                if (v < nfull) sx.keep(v * uint32_t(kVec * kB), Store<T>::load(gs, int64_t(v) * kVec));
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kSrFlat; ++u) {
+                const uint32_t v = u * 64 + lane;
+                if (v < nfull) Nt<T>::store(dx, e0 + v * kVec, Store<T>::load(gs, int64_t(v) * kVec));
+            }
         }
         if (lane < tail) {
             const uint32_t le = nfull * kVec + lane;
@@ -492,7 +509,12 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
     }
     __syncthreads();
 
-    for (uint32_t v = tid; v < nfull; v += nt) Nt<T>::store(dx, e0 + int64_t(v) * kVec, Store<T>::load(gs, int64_t(v) * kVec));
+    if (sb_keep(total_rows * cols * kB)) {              // uniform
+        const Span sx(static_cast<char *>(dx) + e0 * kB, nfull * uint32_t(kVec * kB));
+        for (uint32_t v = tid; v < nfull; v += nt) sx.keep(v * uint32_t(kVec * kB), Store<T>::load(gs, int64_t(v) * kVec));
+    } else {
+        for (uint32_t v = tid; v < nfull; v += nt) Nt<T>::store(dx, e0 + int64_t(v) * kVec, Store<T>::load(gs, int64_t(v) * kVec));
+    }
     if (tid < tail) {
         const uint32_t le = nfull * kVec + tid;
         Store<T>::store1(dx, e0 + le, LdsElem<T>::get(gs + le * kB));        // exact: the value is already of type T
