@@ -571,6 +571,13 @@ __global__ __launch_bounds__(kThreads, 4) void k_softmax_bwd_wave(const int8_t *
     // the unpacked values are rebuilt from the packed ones: holding them would halve the waves in flight
 #pragma unroll
     for (int u = 0; u < NV; ++u) opaque(rawq[u], raw[u]);
+    // As in the tiled kernels; rows that need no LDS gain at every size up to 180 MB, but those of a multiple of 128 elements below 30 MB.  The whole attention
+    // backward, non-temporal -> so: (12, 1, 1616, 64) 124 -> 114 us, (250, 1, 456, 64), 104 MB, 170 -> 158, (700, 1, 296, 64), 123 MB, 233 -> 221, (8, 1, 2048, 64) 124 -> 117,
+    // (100, 1, 296, 64), 18 MB, 55.2 -> 53.2, the call alone (16, 12, 400), 61 MB, 39.8 -> 32.0, (40, 12, 400), 154 MB,
+    // 93.6 -> 76.2, (16, 12, 560), 120 MB, 59.6 -> 52.5, (20, 6, 512) +-1 %.
+    const int64_t bytes = total_rows * cols * int64_t(sizeof(T));
+    const bool keep = bytes <= 180000000 && (cols % 128 != 0 || bytes >= kSbKeepLeast);
+    const Span sx(static_cast<char *>(dx) + (int64_t(blockIdx.x) * (kThreads / 64) + wave) * RPW * int64_t(cols) * int64_t(sizeof(T)), uint32_t(RPW * cols * sizeof(T)));
 #pragma unroll
     for (int u = 0; u < NV; ++u)
         if (live && u * LPR + lr < nvec) {
@@ -579,7 +586,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_softmax_bwd_wave(const int8_t *
             codes_to_float(rawq[u], y);
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = fmaf(y[j], s, b) * (g[j] - d);
-            Nt<T>::store(dx, e0 + int64_t(u * LPR + lr) * kVec, Store<T>::pack(o));
+            if (keep) sx.keep((sub * cols + (u * LPR + lr) * kVec) * uint32_t(sizeof(T)), Store<T>::pack(o));
+            else Nt<T>::store(dx, e0 + int64_t(u * LPR + lr) * kVec, Store<T>::pack(o));
         }
 }
 
