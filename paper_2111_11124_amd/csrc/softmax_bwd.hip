@@ -293,7 +293,8 @@ __global__ __launch_bounds__(kThreads, kSmWgPerCu) void k_softmax_bwd(const int8
 // ---------------------------------------------------------------------------------------------
 // A dx that a fraction of the memory-side cache (256 MB) holds is stored like any data, so that the product that reads it next finds it there; a larger one
 // non-temporally (one of the two as a span: the compiler makes one of two stores that differ in the hint only).  The whole attention backward, non-temporal ->
-// so: (768, 1, 197, 64) binary16, 60 MB, 122.4 -> 120.7 us, (500, 1, 250, 64) 117.2 -> 115.6, (60, 1, 577, 64) 90.1 -> 87.0; the call alone (64, 6, 197) binary32, 60 MB, 37.9 -> 32.8.
+// so: (60, 1, 577, 64) 90.1 -> 87.0 us; the call alone (64, 6, 197) binary32, 60 MB, 37.9 -> 32.8.  16-bit rows of up to 256 elements stay non-temporal: (768, 1, 197, 64) 122.4 -> 120.7
+// with the same buffers again and again, but 117.9 -> 118.9-120.2 among other work, (500, 1, 250, 64) 117.2 -> 115.6.
 // (16, 12, 577), 128 MB, 58.2 and 60.2; (1000, 1, 100, 64), 20 MB, whose lines would leave the L2s at the kernel's end, 61.8 and 63.1.
 constexpr int64_t kSbKeepLeast = 30000000, kSbKeepMost = 100000000;
 __device__ __forceinline__ bool sb_keep(int64_t bytes) { return bytes >= kSbKeepLeast && bytes <= kSbKeepMost; }
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(kThreads, kSbRowWaves) void k_softmax_bwd_rows(cons
             }
         }
     };
-    const bool keep = sb_keep(total_rows * cols * kB);
+    const bool keep = sizeof(T) == 4 && sb_keep(total_rows * cols * kB);
     const int64_t tile_step = int64_t(gridDim.x) * kWaves;
     int64_t tile = int64_t(blockIdx.x) * kWaves + wave;
     if (tile < tiles) fetch(tile);
