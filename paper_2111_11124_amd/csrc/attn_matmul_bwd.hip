@@ -1824,10 +1824,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
         const int v = tid + k * kThreads, r = v / C::kVecRowS;
         s_src[k] = ((r < rows ? r : rows - 1) * N + (v % C::kVecRowS) * 8) * 2;
     }
-    // Where the chunks are whole ones, every workgroup starts at a place of its own and comes round to it: rows of a power of two (and its
-    // multiples) put the same columns of all rows on the same memory channels, and workgroups in step met there.  dQ and dK of (16, 1, 4096, 64) bfloat16
-    // 194 -> 188 us, the whole attention backward 557 -> 537, of (64, 1, 2048, 32) 548 -> 536; at 1024 and 576 tokens no difference.
-    const int start = N % C::kJC == 0 ? int(bid % 16u) * nchunks / 16 : 0;
+    // Rows of a multiple of 2 KB put the same columns of all rows on the same memory channels, where workgroups in step met; so the row tiles of a head start
+    // at sixteen places and come round (by the tile and not the workgroup: a head's sums are taken in the same order wherever it stands in the batch).  dQ and dK on new
+    // inputs each time, (16, 1, 4096, 64) 215 -> 194 us, (36, 1, 2048, 64) 139 -> 128, of 32 127 -> 112, (9, 1, 4096, 128) 188 -> 184, (16, 1, 3072, 64) 119 -> 116, (7, 1, 6144, 64)
+    // 218 -> 212; (29, 1, 3072, 64) 230 -> 232.  Rows of other multiples of 64, and of 1024, gain nothing: 1088 to 2112 -1 to +1 %, shorter ones up to 2 % behind.
+    const int start = N % 1024 == 0 && N >= 2048 ? i0 / 64 % 16 * nchunks / 16 : 0;
     auto load_chunk = [&](int c, auto set_) {
         constexpr int S = decltype(set_)::value;
         c += start;
