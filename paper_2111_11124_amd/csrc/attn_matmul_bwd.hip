@@ -1061,7 +1061,7 @@ template <int KS> struct DcCfg {
 template <int KS, bool ANY, typename ET>
 __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(const _Float16 *__restrict__ dO, const int8_t *__restrict__ vq,
                                                                             _Float16 *__restrict__ dA, int N, int heads, int tiles_j,
-                                                                            int tiles_i, const float *__restrict__ alpha_v,
+                                                                            int tiles_i, int on_lines, const float *__restrict__ alpha_v,
                                                                             const float *__restrict__ beta_v)
 {
     typedef DcCfg<KS> C;
@@ -1097,13 +1097,7 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 3 : 2) void k_attn_da_cols(cons
     const float s = alpha_v[h] / 255.0f;
     const float off = fmaf(BmNum<ET>::kCentre, s, beta_v[h]);
     unsigned char *lout = lds_dc + C::kOutAt + wave * (32 * C::kRowOut);
-    // Rows that start on half lines leave non-temporally: their pieces are whole lines, or halves of one, that nobody of this launch reads, and kept
-    // like other lines they pushed the operands out of the L2 and left it, some at a time, during the kernels that follow.  The whole attention backward of
-    // (1, 16, 4096, 64) bfloat16 617 -> 564 us, of (1, 12, 4096, 64) 478 -> 457, of (355, 1, 288, 64) 117 -> 109, of (400, 1, 320, 32) 113 -> 110.  Rows of a multiple of 128 elements
-    // meet on the same memory channels, and a dA that the memory-side cache would take in wants to go there: up to 130 MB (32, 1, 1024, 64) 101 -> 108,
-    // (500, 1, 256, 64) 107 -> 116, (8, 1, 2048, 64) 126 -> 131, from 200 MB on (96, 1, 1024, 64) 249 -> 242, (100, 1, 1536, 64) 587 -> 546.
-    // Rows that start elsewhere end in parts of lines: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
-    const bool on_lines = N % 32 == 0 && (N % 128 != 0 || int64_t(gridDim.x) * (C::kRows * 256) >= 100000000);
+    // on_lines (da_streams): the pieces of a row are whole lines, or halves of one, that nobody of this launch reads, and leave non-temporally
     const Span lines(dA + (bh * N + i0) * int64_t(N), uint32_t(rows) * uint32_t(N) * 2u);
     auto wave_sync = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2027,16 +2021,38 @@ static bool da_cols_fits(int64_t batches, int64_t N, int64_t Dh)
     return N >= 64 && batches * ceil_div(N, 256) * ceil_div(N, 64) < (int64_t(1) << 31);   // 64: the fewest rows a workgroup takes
 }
 
+// Whether a dA by tiles leaves non-temporally.  Kept like other lines it pushes the operands out of the L2s and leaves these, some at a time, during the kernels
+// that follow; but one that the memory-side cache would take in wants to go there.  The whole attention backward on new inputs each time, kept -> non-temporal us:
+// Rows of a multiple of 128 elements, which meet on the same memory channels: (458, 256, 64) 98.8 -> 102.1, (114, 512, 64) 94.2 -> 96.5, (203, 384, 96) 123.7 -> 127.1, at 100 to 130 MB
+// (3072, 128, 64) and (122, 640, 64) +-1 %, (992, 256, 64) 195 -> 198, (62, 896, 64) 182 -> 185; above (4578, 128, 64) 308 -> 301, (509, 384, 64) 210 -> 206, (183, 640, 64) 213 -> 206,
+// (93, 896, 64) 200 -> 197.  Longer ones (62, 1024, 64) 168.2 -> 170.5, 151 to 185 MB (72, 1024, 64) 203.8 and 203.6, (81, 1024, 64) 226 -> 221, (88, 1024, 64) 234 -> 238, (18, 2048, 64) 204 -> 209,
+// (22, 2048, 64) 227 -> 230; above (24, 2048, 64) 238 -> 237, (31, 2048, 64) 291 -> 286, (124, 1024, 64) 303 -> 297, dV, dA and
+// softmax of (16, 4096, 64) 407 -> 363.
+// Rows on half lines: (62, 448, 64) 53.4 -> 51.7, (101, 352, 64) 60.0 -> 57.4, (122, 320, 32) 49.1 -> 46.6, (541, 608, 64) 565 -> 538, (179, 1056, 64) 516 -> 488; shorter ones
+// (399, 224, 64) 78.7 -> 81.6, (1562, 160, 64) 162.5 -> 167.3, (2170, 96, 64) 114.7 -> 117.3.  About half of the memory-side cache is better kept: 115 to 145 MB
+// (120, 736, 64) 182 -> 187, (74, 992, 64) 203 -> 209, (65, 1056, 64) 205 -> 209, (282, 480, 32) 169 -> 174, (29, 1568, 64) 192 -> 198; at 100 and 160 MB (51, 992, 64) 149 and 149, (81, 992, 64)
+// 221 -> 218, of longer rows still (18, 2080, 64) 212 -> 219, (14, 2528, 64), 179 MB, 241 -> 246, at 190 MB (22, 2080, 64) 249 -> 243; but not at up to 448 elements ((324, 448, 64)
+// 189 -> 183, (562, 320, 32) 152 -> 150) or wider heads ((131, 704, 96) 213 -> 207, (166, 576, 128) 219 and 220).
+// Rows that start elsewhere end in parts of lines: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
+static bool da_streams(int64_t batches, int64_t N, int64_t Dh)
+{
+    const int64_t bytes = batches * N * N * 2;
+    if (N % 128 == 0) return bytes >= (N < 1024 ? 135000000 : 200000000);
+    if (N % 32 != 0 || N < 256) return false;
+    return Dh > 64 || N <= 448 || bytes <= 105000000 || bytes >= (N < 1536 ? 155000000 : 180000000);
+}
+
 template <typename ET>
 static void launch_da_cols(const _Float16 *dO, const int8_t *vq, _Float16 *dA, int64_t batches, int N, int Dh, int heads,
                            const float *alpha_v, const float *beta_v, hipStream_t s)
 {
+    const int streams = da_streams(batches, N, Dh);
 #define MESA_LAUNCH_DC(KS_) \
     do { \
         const int tiles_j = int(ceil_div(N, 256)), tiles_i = int(ceil_div(N, DcCfg<KS_>::kRows)); \
         const dim3 grid(unsigned(batches * tiles_j * tiles_i)); \
-        if (N % 8 == 0) hipLaunchKernelGGL((k_attn_da_cols<KS_, false, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, alpha_v, beta_v); \
-        else hipLaunchKernelGGL((k_attn_da_cols<KS_, true, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, alpha_v, beta_v); \
+        if (N % 8 == 0) hipLaunchKernelGGL((k_attn_da_cols<KS_, false, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, streams, alpha_v, beta_v); \
+        else hipLaunchKernelGGL((k_attn_da_cols<KS_, true, ET>), grid, dim3(kThreads), 0, s, dO, vq, dA, N, heads, tiles_j, tiles_i, streams, alpha_v, beta_v); \
     } while (0)
     if (Dh == 32) MESA_LAUNCH_DC(2);
     else if (Dh == 64) MESA_LAUNCH_DC(4);

@@ -20,6 +20,7 @@ static unsigned log_[64][6];
 static const void *kernel_[64];
 static unsigned shared_[64];
 static int count;
+void launched(int at, const void *f, void **args) __attribute__((weak));   /* of `also` */
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, void *s) { grid = g; block = b; shared = sh; stream = s; return 0; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, void **s) { *g = grid; *b = block; *sh = shared; *s = stream; return 0; }
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh, void *s)
@@ -33,6 +34,7 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh, void 
         for (int i = 0; i < 6; ++i) log_[count][i] = v[i];
         kernel_[count] = f;
         shared_[count] = (unsigned)sh;
+        if (launched) launched(count, f, args);
     }
     ++count;
     return 0;

@@ -119,6 +119,36 @@ def test_dv_goes_first_beside_a_da_as_large_as_the_memory_side_cache():
         assert len(av) == 2 and got == first[shape], (shape, av)
 
 
+# for `also`: whether a launch of k_attn_da_cols stores non-temporally, its eighth argument
+STREAMS = r'''
+static int streams_[64];
+void launched(int at, const void *f, void **args)
+{
+    streams_[at] = -1;
+    for (int k = 0; k < known_n; ++k)
+        if (known[k].f == f && strstr(known[k].name, "14k_attn_da_cols")) streams_[at] = *(int *)args[7];
+}
+int recorded_streams(int i) { return streams_[i]; }
+'''
+
+
+def test_da_by_tiles_leaves_past_the_caches_by_its_real_size():
+    """Rows of a multiple of 128 elements from 135 MB on, long ones from 200 MB, whatever part of their last tile exists; rows on half lines from 256 elements on, but not
+    those of more than 448 in heads of up to 64 that take about half of the memory-side cache; never rows that start elsewhere."""
+    want = {(3072, 128, 64): 0, (4119, 128, 64): 0, (4120, 128, 64): 1, (457, 384, 64): 0, (458, 384, 128): 1, (1029, 256, 64): 0, (1030, 256, 32): 1, (95, 1024, 64): 0, (96, 1024, 64): 1,
+            (5, 4096, 64): 0, (6, 4096, 64): 1, (78, 1152, 64): 1, (75, 1152, 64): 0, (2170, 96, 64): 0, (10851, 96, 64): 0, (399, 224, 64): 0, (90, 288, 64): 1, (562, 320, 32): 1, (324, 448, 64): 1,
+            (25, 480, 64): 1, (227, 480, 64): 1, (229, 480, 64): 0, (336, 480, 64): 0, (337, 480, 64): 1, (131, 704, 96): 1, (166, 576, 128): 1, (20, 2016, 64): 0, (23, 2016, 64): 1,
+            (51, 656, 64): 0, (192, 577, 64): 0}
+    got = run(r'''
+out = []
+for b, N, Dh in ''' + repr(list(want)) + r''':
+    assert L.mesa_attn_av_bwd_q(P, P, 1, b, N, Dh, P, P, P, P, P, P, P, M.BF16, None) == M.OK
+    out.append(max(rec.recorded_streams(i) for i in range(len(launches()))))
+report(out)
+''', NAMES + STREAMS)
+    assert dict(zip(want, got)) == want, {s: g for s, g in zip(want, got) if want[s] != g}
+
+
 def test_the_gpu_tests_reach_every_kernel_of_the_products():
     """and no kernel is there that no call reaches."""
     from tests.test_gpu_attention_kernels import SIXTEEN, WIDE
