@@ -2256,12 +2256,12 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
     };
 #undef MESA_AV_DV
     // dV, bound by its reads, goes first where dA is about as large as the memory-side cache (256 MB) and more: a dA just written is still leaving that cache
-    // while the next kernel reads, and softmax behind it, which would find a smaller one there, finds little of this one.  The whole attention backward, dA first ->
-    // dV first: (1, 7, 4096, 64) bfloat16, 235 MB, 310 -> 293 us, (1, 8, 4096, 64), 268 MB, 334 -> 315, (1, 16, 4096, 64), 537 MB, 626 -> 602 (dV alone 100 -> 70, softmax 191 -> 211), (16, 12, 1024,
-    // 64), 403 MB, 492 -> 470, (32, 12, 577, 64), 256 MB, 411 -> 402, (256, 12, 250, 64), 384 MB, 635 -> 626, (512, 12, 197, 64), 477 MB, 847 -> 846, (1, 16, 4096, 128), 757 -> 763.  Below it goes either
-    // way: (24, 12, 577, 64), 192 MB, 292 -> 283, (1, 6, 4096, 64), 201 MB, 288 -> 292, (8, 12, 1024, 64), 201 MB, binary16 245 -> 248.  binary32 too, at any size: (4, 12, 1024, 64), 201 MB, 285 ->
-    // 292, (1, 6, 4096, 64), 403 MB, 588 -> 582.
-    if (dt != MESA_F32 && batches * N * N >= 115000000) {
+    // while the next kernel reads, and softmax behind it, which would find a smaller one there, finds little of this one.  The whole attention backward on new inputs each time,
+    // dA first -> dV first us, kept: (315, 577, 64) 316 -> 305, (102, 1127, 64) 355 -> 337, (1680, 250, 64) 347 -> 342, (2706, 197, 64) 388 -> 386; non-temporally (da_streams):
+    // (8, 4096, 64) 331 -> 319, (14, 4096, 64) 505 -> 482, (124, 1024, 128) 405 -> 380, (405, 544, 64) 361 -> 342, (572, 512, 64) 401 -> 393, (1447, 288, 32) 340 -> 333, but (2411, 288, 64)
+    // +1.5 %, (747, 448, 96) 461 -> 468.  Not where rows of up to 256 elements leave non-temporally: (1831, 256, 96) 417 -> 425, (2518, 256, 64) 473 -> 476, (14648, 128, 64) 913 -> 919.
+    // binary32 either way at any size: (4, 12, 1024, 64), 201 MB, 285 -> 292, (1, 6, 4096, 64), 403 MB, 588 -> 582.
+    if (dt != MESA_F32 && batches * N * N >= 115000000 && (N > 256 || !da_streams(batches, N, Dh))) {
         dv();
         da();
     } else {
