@@ -292,12 +292,14 @@ __global__ __launch_bounds__(kThreads, kSmWgPerCu) void k_softmax_bwd(const int8
 // tile's dy is in LDS before any of its dx is stored, and tiles do not overlap.
 // ---------------------------------------------------------------------------------------------
 // A dx that a fraction of the memory-side cache (256 MB) holds is stored like any data, so that the product that reads it next finds it there; a larger one
-// non-temporally (one of the two as a span: the compiler makes one of two stores that differ in the hint only).  The whole attention backward, non-temporal ->
-// so: (60, 1, 577, 64) 90.1 -> 87.0 us; the call alone (64, 6, 197) binary32, 60 MB, 37.9 -> 32.8.  16-bit rows of up to 256 elements stay non-temporal: (768, 1, 197, 64) 122.4 -> 120.7
-// with the same buffers again and again, but 117.9 -> 118.9-120.2 among other work, (500, 1, 250, 64) 117.2 -> 115.6.
-// (16, 12, 577), 128 MB, 58.2 and 60.2; (1000, 1, 100, 64), 20 MB, whose lines would leave the L2s at the kernel's end, 61.8 and 63.1.
-constexpr int64_t kSbKeepLeast = 30000000, kSbKeepMost = 100000000;
-__device__ __forceinline__ bool sb_keep(int64_t bytes) { return bytes >= kSbKeepLeast && bytes <= kSbKeepMost; }
+// non-temporally (one of the two as a span: the compiler makes one of two stores that differ in the hint only).  On new inputs each time, each side behind itself (a kept dx is written
+// back during what follows, which a call of the other side in between would pay for), non-temporal -> so.  binary32 rows of up to 256 elements, the call alone (64, 6, 197), 60 MB, 37.0 -> 32.6 us,
+// (3000, 3, 49), 86 MB, 52.6 -> 43.0, (100, 6, 197), 93 MB, 55.0 -> 48.1, the whole attention backward (200, 1, 250, 64) 115 -> 109.  16-bit ones stay non-temporal: (768, 1, 197, 64) 117.9 -> 118.9-120.2.
+// 16-bit long rows, the whole attention backward (20, 1, 901, 64), 32 MB, 84.5 -> 81.1, (10, 1, 1127, 64) 82.3 -> 78.8, (50, 1, 577, 64) 79.4 -> 79.6, (90, 1, 577, 64), 60 MB, 120.0 -> 119.2,
+// (218, 1, 321, 64) 100.4 -> 98.2, and the call alone 1 to 4 % behind ((90, 1, 577) 30.4 -> 31.2); at 90 MB the call alone falls 7 to 9 % behind for 1 % of the whole ((135, 1, 577, 64) 42.6 -> 46.3
+// and 152.6 -> 150.6), and at 20 MB 6 to 16 % ((20, 1, 701) 11.0 -> 13.1).
+constexpr int64_t kSbKeepLeast = 30000000, kSbKeepMost = 100000000, kSbKeepMostLong = 75000000;
+__device__ __forceinline__ bool sb_keep(int64_t bytes, int64_t most) { return bytes >= kSbKeepLeast && bytes <= most; }
 constexpr int kSbRowWaves = 4;      // waves per SIMD the row kernel's register budget is set for
 
 template <typename T, int LPR, int EPL, bool TIGHT>
@@ -341,7 +343,7 @@ __global__ __launch_bounds__(kThreads, kSbRowWaves) void k_softmax_bwd_rows(cons
             }
         }
     };
-    const bool keep = sizeof(T) == 4 && sb_keep(total_rows * cols * kB);
+    const bool keep = sizeof(T) == 4 && sb_keep(total_rows * cols * kB, kSbKeepMost);
     const int64_t tile_step = int64_t(gridDim.x) * kWaves;
     int64_t tile = int64_t(blockIdx.x) * kWaves + wave;
     if (tile < tiles) fetch(tile);
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(512, 4) void k_softmax_bwd_long(const int8_t *__res
     }
     __syncthreads();
 
-    if (sb_keep(total_rows * cols * kB)) {              // uniform
+    if (sb_keep(total_rows * cols * kB, kSbKeepMostLong)) {   // uniform
         const Span sx(static_cast<char *>(dx) + e0 * kB, nfull * uint32_t(kVec * kB));
         for (uint32_t v = tid; v < nfull; v += nt) sx.keep(v * uint32_t(kVec * kB), Store<T>::load(gs, int64_t(v) * kVec));
     } else {
@@ -572,12 +574,15 @@ __global__ __launch_bounds__(kThreads, 4) void k_softmax_bwd_wave(const int8_t *
     // the unpacked values are rebuilt from the packed ones: holding them would halve the waves in flight
 #pragma unroll
     for (int u = 0; u < NV; ++u) opaque(rawq[u], raw[u]);
-    // As in the tiled kernels; rows that need no LDS gain at every size up to 180 MB, but those of a multiple of 128 elements below 30 MB.  The whole attention
-    // backward, non-temporal -> so: (12, 1, 1616, 64) 124 -> 114 us, (250, 1, 456, 64), 104 MB, 170 -> 158, (700, 1, 296, 64), 123 MB, 233 -> 221, (8, 1, 2048, 64) 124 -> 117,
-    // (100, 1, 296, 64), 18 MB, 55.2 -> 53.2, the call alone (16, 12, 400), 61 MB, 39.8 -> 32.0, (40, 12, 400), 154 MB,
-    // 93.6 -> 76.2, (16, 12, 560), 120 MB, 59.6 -> 52.5, (20, 6, 512) +-1 %.
+    // As in the tiled kernels, but rows that need no LDS gain from the smallest sizes on, those on odd sixteenths of a line most: the call alone / the whole attention backward
+    // (16, 12, 400) 39.1 -> 31.5 us, (717, 1, 264) 63.9 -> 53.1 and 210 -> 200, (250, 1, 456), 104 MB, 71.2 -> 62.7 and 179 -> 161, (438, 1, 400), 140 MB, 85.6 -> 80.1 and 235 -> 221, (86, 1, 904)
+    // 77.6 -> 78.8 and 215 -> 206; on half lines (362, 1, 288), 60 MB, 30.3 -> 28.6 and 122.6 -> 121.5, (53, 1, 576), 35 MB, 18.3 -> 18.9 and 70.7 -> 69.8, at 100 MB and more, where they gain
+    // as a whole what the call alone loses, (603, 1, 288) 47.8 -> 50.1 and 190 -> 186, (109, 1, 800) 61.9 -> 68.8 and 205 -> 199.  Long ones (7, 1, 1616), 37 MB, 18.1 -> 18.2 and 97.8 -> 90.8,
+    // (3, 1, 3000) 25.6 -> 25.9 and 155 -> 153, from 60 MB on (24, 1, 1120) 26.7 -> 28.1 and 106.8 -> 108.5, (12, 1, 2008) 42.2 -> 45.5 and 162 -> 164.  Whole lines gain only as long ones
+    // around 35 MB: (17, 1, 1024) 75.5 -> 71.7, (7, 1, 1536) 85.8 -> 79.5, (5, 1, 2048) 108 -> 101 of the whole; (119, 1, 384) 65.2 -> 66.2, (51, 1, 640), 42 MB, 76.4 -> 78.2, (9, 1, 2048),
+    // 75 MB, 140 -> 145, (12, 1, 2048) 41.0 -> 44.1 and 155 -> 167, (93, 1, 896), 150 MB, 62.6 -> 69.2 and 199 -> 194.
     const int64_t bytes = total_rows * cols * int64_t(sizeof(T));
-    const bool keep = bytes <= 180000000 && (cols % 128 != 0 || bytes >= kSbKeepLeast);
+    const bool keep = cols % 128 == 0 ? cols >= 768 && bytes >= kSbKeepLeast && bytes <= 45000000 : bytes <= (cols > 1024 ? 45000000 : 180000000);
     const Span sx(static_cast<char *>(dx) + (int64_t(blockIdx.x) * (kThreads / 64) + wave) * RPW * int64_t(cols) * int64_t(sizeof(T)), uint32_t(RPW * cols * sizeof(T)));
 #pragma unroll
     for (int u = 0; u < NV; ++u)
