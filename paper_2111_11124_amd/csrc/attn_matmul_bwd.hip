@@ -2022,22 +2022,22 @@ static bool da_cols_fits(int64_t batches, int64_t N, int64_t Dh)
 }
 
 // Whether a dA by tiles leaves non-temporally.  Kept like other lines it pushes the operands out of the L2s and leaves these, some at a time, during the kernels
-// that follow; but one that the memory-side cache would take in wants to go there.  The whole attention backward on new inputs each time, kept -> non-temporal us:
-// Rows of a multiple of 128 elements, which meet on the same memory channels: (458, 256, 64) 98.8 -> 102.1, (114, 512, 64) 94.2 -> 96.5, (203, 384, 96) 123.7 -> 127.1, at 100 to 130 MB
-// (3072, 128, 64) and (122, 640, 64) +-1 %, (992, 256, 64) 195 -> 198, (62, 896, 64) 182 -> 185; above (4578, 128, 64) 308 -> 301, (509, 384, 64) 210 -> 206, (183, 640, 64) 213 -> 206,
-// (93, 896, 64) 200 -> 197.  Longer ones (62, 1024, 64) 168.2 -> 170.5, 151 to 185 MB (72, 1024, 64) 203.8 and 203.6, (81, 1024, 64) 226 -> 221, (88, 1024, 64) 234 -> 238, (18, 2048, 64) 204 -> 209,
-// (22, 2048, 64) 227 -> 230; above (24, 2048, 64) 238 -> 237, (31, 2048, 64) 291 -> 286, (124, 1024, 64) 303 -> 297, dV, dA and
-// softmax of (16, 4096, 64) 407 -> 363.
-// Rows on half lines: (62, 448, 64) 53.4 -> 51.7, (101, 352, 64) 60.0 -> 57.4, (122, 320, 32) 49.1 -> 46.6, (541, 608, 64) 565 -> 538, (179, 1056, 64) 516 -> 488; shorter ones
-// (399, 224, 64) 78.7 -> 81.6, (1562, 160, 64) 162.5 -> 167.3, (2170, 96, 64) 114.7 -> 117.3.  About half of the memory-side cache is better kept: 115 to 145 MB
-// (120, 736, 64) 182 -> 187, (74, 992, 64) 203 -> 209, (65, 1056, 64) 205 -> 209, (282, 480, 32) 169 -> 174, (29, 1568, 64) 192 -> 198; at 100 and 160 MB (51, 992, 64) 149 and 149, (81, 992, 64)
-// 221 -> 218, of longer rows still (18, 2080, 64) 212 -> 219, (14, 2528, 64), 179 MB, 241 -> 246, at 190 MB (22, 2080, 64) 249 -> 243; but not at up to 448 elements ((324, 448, 64)
-// 189 -> 183, (562, 320, 32) 152 -> 150) or wider heads ((131, 704, 96) 213 -> 207, (166, 576, 128) 219 and 220).
+// that follow; but one that the memory-side cache would take in wants to go there.  The whole attention backward on new inputs each time, each side behind itself (behind
+// a call of the other, a kept result is written back at that one's cost), kept -> non-temporal us:
+// Rows of a multiple of 128 elements, which meet on the same memory channels: (458, 256, 64) 97 -> 101, (114, 512, 64) 91 -> 96, (104, 640, 64) 129 -> 132, (29, 1024, 64) 98 -> 101,
+// at 135 to 165 MB (286, 512, 64) 202 -> 204, (84, 896, 64) 184 -> 187, (72, 1024, 64) 202 -> 204, (79, 1024, 64) 213 -> 216, (183, 640, 64) 208 -> 204, (16, 2048, 64) 182 -> 183, above (1297, 256, 64) 254 -> 250,
+// (576, 384, 64) 256 -> 251, (106, 896, 64) 219 -> 216, (105, 1024, 64) 272 -> 265, (26, 2048, 64) 263 -> 257, dV, dA and softmax of (16, 4096, 64) 407 -> 363; of 128 elements
+// (1831, 128, 64), 60 MB, 131 -> 132, (2594, 128, 64) 176 and 176, (3072, 128, 64), 101 MB, 209 -> 206, (3662, 128, 64) 245 -> 243, (3662, 128, 32) 179 -> 180, (4578, 128, 64) 305 -> 299.
+// Rows on half lines: (62, 448, 64) 53.0 -> 50.7, (101, 352, 64) 58.6 -> 57.0, (122, 320, 32) 48.4 -> 46.4, (541, 608, 64) 559 -> 533, (179, 1056, 64) 507 -> 480; shorter ones
+// (399, 224, 64) 78.7 -> 81.3, (1562, 160, 64) 162 -> 166, (2170, 96, 64) 113 -> 117.  About half of the memory-side cache is better kept: 115 to 145 MB
+// (120, 736, 64) 182 -> 187, (74, 992, 64) 202 -> 210, (65, 1056, 64) 206 -> 211, (282, 480, 32) 168 -> 174, (29, 1568, 64) 192 -> 196; at 100 and 160 MB (51, 992, 64) 148 -> 149, (81, 992, 64)
+// 221 -> 217, of longer rows still (18, 2080, 64) 211 -> 218, (14, 2528, 64), 179 MB, 239 -> 242, at 190 MB (22, 2080, 64) 248 -> 241; but not at up to 448 elements ((324, 448, 64)
+// 189 -> 182, (562, 320, 32) 155 -> 151) or wider heads ((131, 704, 96) 212 -> 206, (166, 576, 128) 219 and 219).
 // Rows that start elsewhere end in parts of lines: (51, 1, 656, 64) 88 -> 95, (428, 1, 176, 32) 52 -> 56.
 static bool da_streams(int64_t batches, int64_t N, int64_t Dh)
 {
     const int64_t bytes = batches * N * N * 2;
-    if (N % 128 == 0) return bytes >= (N < 1024 ? 135000000 : 200000000);
+    if (N % 128 == 0) return bytes >= (N == 128 ? 100000000 : 170000000);
     if (N % 32 != 0 || N < 256) return false;
     return Dh > 64 || N <= 448 || bytes <= 105000000 || bytes >= (N < 1536 ? 155000000 : 180000000);
 }

@@ -134,10 +134,10 @@ int recorded_streams(int i) { return streams_[i]; }
 
 
 def test_da_by_tiles_leaves_past_the_caches_by_its_real_size():
-    """Rows of a multiple of 128 elements from 135 MB on, long ones from 200 MB, whatever part of their last tile exists; rows on half lines from 256 elements on, but not
-    those of more than 448 in heads of up to 64 that take about half of the memory-side cache; never rows that start elsewhere."""
-    want = {(3072, 128, 64): 0, (4119, 128, 64): 0, (4120, 128, 64): 1, (457, 384, 64): 0, (458, 384, 128): 1, (1029, 256, 64): 0, (1030, 256, 32): 1, (95, 1024, 64): 0, (96, 1024, 64): 1,
-            (5, 4096, 64): 0, (6, 4096, 64): 1, (78, 1152, 64): 1, (75, 1152, 64): 0, (2170, 96, 64): 0, (10851, 96, 64): 0, (399, 224, 64): 0, (90, 288, 64): 1, (562, 320, 32): 1, (324, 448, 64): 1,
+    """Rows of a multiple of 128 elements from 170 MB on (of 128 from 100), whatever part of their last tile exists; rows on half lines from 256 elements on, but not those of more
+    than 448 in heads of up to 64 that take about half of the memory-side cache; never rows that start elsewhere."""
+    want = {(3051, 128, 64): 0, (3052, 128, 64): 1, (576, 384, 64): 0, (577, 384, 128): 1, (1296, 256, 64): 0, (1298, 256, 32): 1, (81, 1024, 64): 0, (82, 1024, 64): 1,
+            (5, 4096, 64): 0, (6, 4096, 64): 1, (64, 1152, 64): 0, (65, 1152, 64): 1, (2170, 96, 64): 0, (10851, 96, 64): 0, (399, 224, 64): 0, (90, 288, 64): 1, (562, 320, 32): 1, (324, 448, 64): 1,
             (25, 480, 64): 1, (227, 480, 64): 1, (229, 480, 64): 0, (336, 480, 64): 0, (337, 480, 64): 1, (131, 704, 96): 1, (166, 576, 128): 1, (20, 2016, 64): 0, (23, 2016, 64): 1,
             (51, 656, 64): 0, (192, 577, 64): 0}
     got = run(r'''
