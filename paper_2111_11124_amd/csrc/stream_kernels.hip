@@ -318,10 +318,16 @@ __device__ __forceinline__ void minmax_finish(MinMaxState<T> (&st)[U], int *lmn,
 }
 
 // The vectors of a chunk of x for the scan of its extrema.  A tensor that a fraction of the memory-side cache (256 MB) holds is loaded like any
-// data, so that the quantizer, which reads it next, finds it there; a larger one with the non-temporal hint (one of the two as a span: the compiler makes one of two
-// loads that differ in the hint only).  Both calls, on new inputs each time, non-temporal -> so: (25216, 6, 64) binary16 19.6 -> 18.0 us, (128, 6, 38809) 37.3 -> 35.1, (50432, 12, 64)
-// 44.0 -> 41.1, (8192, 3, 2401), 118 MB, 63.4 -> 61.8, (10000, 8, 128) binary32 27.1 -> 24.4; larger ones: 123 to 169 MB +-1 %, (256, 12, 38809), 238 MB, 109 and 113.
-constexpr int64_t kScanKeepBytes = 120000000;
+// data, so that the quantizer, which reads it next, finds it there; others with the non-temporal hint (one of the two as a span: the compiler makes one of two
+// loads that differ in the hint only).  Both calls, on new inputs each time and each side behind itself, non-temporal -> so: binary32 (4069, 12, 128), 25 MB, 18.6 -> 17.9 us, (8138, 12, 128)
+// 28.6 -> 25.8, (15462, 12, 128) 46.0 -> 40.2, (123, 6, 38809), 115 MB, 53.4 -> 48.1, but (1465, 12, 128), 9 MB, 12.6 -> 13.1; 16 bits (8138, 12, 128), 25 MB, 20.0 -> 19.2, (16276, 12, 128) 28.9 -> 28.4,
+// (4859, 3, 2401), 70 MB, 41.2 -> 40.9, but (2930, 12, 128), 9 MB, 12.9 -> 13.9, (625, 3, 2401) 15.3 -> 16.4, and from 95 MB on (30924, 12, 128) 45.6 -> 46.0, (37435, 12, 128) 53.1 -> 54.1.
+template <typename T>
+__device__ __forceinline__ bool scan_keeps(int64_t numel)
+{
+    const int64_t bytes = numel * int64_t(sizeof(T));
+    return bytes >= 18000000 && bytes <= (sizeof(T) == 4 ? 120000000 : 75000000);
+}
 template <typename T, int U>
 __device__ __forceinline__ void scan_load(const void *__restrict__ x, int64_t base, bool keep, typename Store<T>::raw_t (&v)[U])
 {
@@ -360,7 +366,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial(const void *__restr
     constexpr int kChunk = kThreads * U * kVec;
     const int64_t stride = int64_t(gridDim.x) * kChunk;
     const int64_t toff = int64_t(threadIdx.x) * kVec;
-    const bool keep = numel * int64_t(sizeof(T)) <= kScanKeepBytes;
+    const bool keep = scan_keeps<T>(numel);
     // CHECK = false: the chunk lies wholly inside the tensor, no per-vector bounds test
     auto chunk = [&](int64_t base, auto check) {
         constexpr bool CHECK = decltype(check)::value;
@@ -437,7 +443,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_partial_few(const void *__r
     constexpr int kChunk = kThreads * U * kVec;
     const int64_t stride = int64_t(gridDim.x) * kChunk;
     const int64_t toff = int64_t(threadIdx.x) * kVec;
-    const bool keep = numel * int64_t(sizeof(T)) <= kScanKeepBytes;
+    const bool keep = scan_keeps<T>(numel);
     auto chunk = [&](int64_t base, auto check) {
         constexpr bool CHECK = decltype(check)::value;
         typename Store<T>::raw_t v[U];
