@@ -30,8 +30,8 @@ def test_softmax_backward_kept_or_not(M, cols, whole_mb, part_mb, dtype):  # noq
 
 
 # kept from 18 MB on, up to 75 MB in 16 bits and 120 MB in binary32: the whole beyond the upper line and its half below it, the half beyond the lower line and its half below that
-@pytest.mark.parametrize("outer,groups,inner,dtype", [(30000, 12, 128, torch.float16), (9000, 3, 2401, torch.float16), (500, 6, 38809, torch.bfloat16), (30000, 12, 128, torch.float32),
-                                                      (8000, 12, 128, torch.float16), (200, 3, 38809, torch.bfloat16), (4000, 12, 128, torch.float32), (2500, 3, 2401, torch.float16)])
+@pytest.mark.parametrize("outer,groups,inner,dtype", [(30000, 12, 128, torch.float16), (9000, 3, 2401, torch.float16), (300, 6, 38809, torch.bfloat16), (30000, 12, 128, torch.float32),
+                                                      (8000, 12, 128, torch.float16), (120, 3, 38809, torch.bfloat16), (4000, 12, 128, torch.float32), (2400, 3, 2401, torch.float16)])
 def test_running_estimates_kept_or_not(M, outer, groups, inner, dtype):  # noqa: F811
     """a tensor and its half, on either side of a line, against torch's extrema"""
     g = torch.Generator(device="cuda").manual_seed(outer)
