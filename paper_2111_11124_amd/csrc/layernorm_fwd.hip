@@ -36,55 +36,24 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
     constexpr int kWaves = kThreads / 64;
     constexpr int U = lf_rows(VPL, sizeof(T));
     constexpr int kBlockRows = kWaves * U * RPW;
-    __shared__ int lmn[kLfMaxGroups], lmx[kLfMaxGroups];
-    for (uint32_t g = threadIdx.x; g < groups; g += kThreads) {
-        lmn[g] = order_key(__builtin_inff());
-        lmx[g] = order_key(-__builtin_inff());
-    }
-    __syncthreads();
-
+    typedef typename Store<T>::raw_t Raw;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t sub = lane / LPR, l = lane % LPR;
     const uint32_t vpr = D / kVec;
-
-    // gamma and bias stay in registers for rows of up to 1024 elements; for longer rows they are read again for
-    // every row (a few KB that stay in the cache), which costs less than the registers would
-    constexpr bool kKeep = VPL <= 2 || (VPL == 3 && Store<T>::kBytes == 2);
-    constexpr int kHeld = kKeep ? VPL : 1;
-    uint32_t col[VPL], grp[VPL];
+    uint32_t col[VPL];
     bool act[VPL];
-    float gam[kHeld][8], bia[kHeld][8], mn[VPL], mx[VPL];
-    float2 prm[VPL];                                // (255 / alpha, beta) of the vector's channel group
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
         const uint32_t cv = k * LPR + l;
         act[k] = cv < vpr;
         col[k] = cv * kVec;
-        grp[k] = 0;
-        mn[k] = __builtin_inff();
-        mx[k] = -__builtin_inff();
-        prm[k] = make_float2(0.0f, 0.0f);
-        if (kKeep) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { gam[k % kHeld][j] = 0.0f; bia[k % kHeld][j] = 0.0f; }
-        }
-        if (act[k]) {
-            if (kKeep) {
-                Store<T>::unpack(Store<T>::load(gamma, col[k]), gam[k % kHeld]);
-                Store<T>::unpack(Store<T>::load(bias, col[k]), bia[k % kHeld]);
-            }
-            grp[k] = fastdiv(cv, div_vpg);
-            const float a = alpha[grp[k]];
-            prm[k] = make_float2(a > 0.0f ? 255.0f / a : 0.0f, beta[grp[k]]);
-        }
     }
 
     // One block of rows is on its way while the previous one is worked on, in two register sets that take turns.  No access in the loop is
     // conditional: lanes without a vector and rows past the end are out of their span's bounds (Span), and so is a whole block past the end.  Two rows per
     // lane group, requested and then worked on, with a branch around each access -> this: 50432 x 768 binary16 45.4 -> 44.1 us for the call, 25216 x 384
-    // 19.3 -> 17.7, 100000 x 512 61.1 -> 58.6, 20000 x 2048 binary32 99 -> 84 (with two workgroups per CU instead of three, which four vectors per lane now need).
+    // 19.3 -> 17.7, 100000 x 512 61.1 -> 58.6.
     constexpr uint32_t kEb = sizeof(T);
-    typedef typename Store<T>::raw_t Raw;
     struct Block { Raw raw[U][VPL]; };
     uint32_t at[U][VPL], row_at[U];          // of this lane in a block: elements of its vectors, row
 #pragma unroll
@@ -102,6 +71,60 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
             for (int k = 0; k < VPL; ++k) sx.load(act[k] ? at[p][k] * kEb : kNowhere, blk.raw[p][k]);
         __builtin_amdgcn_sched_barrier(0);                 // requested before the other block is worked on
     };
+    const int64_t stride = int64_t(gridDim.x) * kBlockRows;
+    int64_t row0 = int64_t(blockIdx.x) * kBlockRows;
+    Block even, odd;
+    // ahead of everything else that this workgroup waits for, which with a block or two per workgroup is most of its time: behind the parameters -> ahead of them
+    // 6141 x 1024 binary16 14.5 -> 13.3 us, 18429 x 128 binary32 11.2 -> 10.1, 14742 x 192 13.2 -> 12.7, 9213 x 768 23.1 -> 22.8
+    load_block(row0, even);
+
+    __shared__ int lmn[kLfMaxGroups], lmx[kLfMaxGroups];
+    for (uint32_t g = threadIdx.x; g < groups; g += kThreads) {
+        lmn[g] = order_key(__builtin_inff());
+        lmx[g] = order_key(-__builtin_inff());
+    }
+    // gamma and bias stay in registers, or, where there are too few, in LDS (a lane's vectors as 16-byte pieces, those of neighbouring lanes side by side):
+    // a load from memory beside the rows' own would wait for the next block of rows, which was requested before it.  The call with such loads -> this:
+    // binary32 12285 x 768 24.9 -> 24.6 us, 61437 x 768 95.2 -> 93.2, 18429 x 1280 54.6 -> 51.1, 18429 x 2048 77.7 -> 74.5, 16 bits 18429 x 1600 42.2 -> 36.2, 20000 x 2048 (bfloat16) 55.0 -> 45.0.
+    constexpr bool kKeep = VPL <= 2 || (VPL == 3 && Store<T>::kBytes == 2);
+    constexpr int kHeld = kKeep ? VPL : 1, kPieces = sizeof(Raw) / 16, kSlots = kKeep ? 1 : LPR * VPL;
+    __shared__ u32x4 lgam[kPieces][kSlots], lbia[kPieces][kSlots];
+    if (!kKeep) {
+        for (uint32_t v = threadIdx.x; v < uint32_t(kSlots); v += kThreads) {       // slots past the row's end repeat the first one's
+            const Raw g = Store<T>::load(gamma, v < vpr ? v * kVec : 0), b = Store<T>::load(bias, v < vpr ? v * kVec : 0);
+#pragma unroll
+            for (int i = 0; i < kPieces; ++i) {
+                lgam[i][v] = reinterpret_cast<const u32x4 *>(&g)[i];
+                lbia[i][v] = reinterpret_cast<const u32x4 *>(&b)[i];
+            }
+        }
+    }
+    __syncthreads();
+
+    uint32_t grp[VPL];
+    float gam[kHeld][8], bia[kHeld][8], mn[VPL], mx[VPL];
+    float2 prm[VPL];                                // (255 / alpha, beta) of the vector's channel group
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) {
+        grp[k] = 0;
+        mn[k] = __builtin_inff();
+        mx[k] = -__builtin_inff();
+        prm[k] = make_float2(0.0f, 0.0f);
+        if (kKeep) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { gam[k % kHeld][j] = 0.0f; bia[k % kHeld][j] = 0.0f; }
+        }
+        if (act[k]) {
+            if (kKeep) {
+                Store<T>::unpack(Store<T>::load(gamma, col[k]), gam[k % kHeld]);
+                Store<T>::unpack(Store<T>::load(bias, col[k]), bia[k % kHeld]);
+            }
+            grp[k] = fastdiv(k * LPR + l, div_vpg);
+            const float a = alpha[grp[k]];
+            prm[k] = make_float2(a > 0.0f ? 255.0f / a : 0.0f, beta[grp[k]]);
+        }
+    }
+
     auto work = [&](int64_t row0, const Block &blk) __attribute__((always_inline)) {
         const uint32_t rows = rows_of(row0);
         const Span sy(static_cast<char *>(y) + row0 * D * kEb, rows * D * kEb), sq(q + row0 * D, rows * D), sm(mean + row0, rows * 4), sr(rstd + row0, rows * 4);
@@ -135,8 +158,14 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
             for (int k = 0; k < VPL; ++k) {
                 float o[8], w[8], bits[8];
                 if (!kKeep) {
-                    Store<T>::unpack(Store<T>::load(gamma, act[k] ? col[k] : 0), gam[0]);
-                    Store<T>::unpack(Store<T>::load(bias, act[k] ? col[k] : 0), bia[0]);
+                    Raw g, b;
+#pragma unroll
+                    for (int i = 0; i < kPieces; ++i) {
+                        reinterpret_cast<u32x4 *>(&g)[i] = lgam[i][k * LPR + l];
+                        reinterpret_cast<u32x4 *>(&b)[i] = lbia[i][k * LPR + l];
+                    }
+                    Store<T>::unpack(g, gam[0]);
+                    Store<T>::unpack(b, bia[0]);
                 }
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] = fmaf((f[k][j] - mu) * rs, gam[k % kHeld][j], bia[k % kHeld][j]);
@@ -155,10 +184,6 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
             }
         }
     };
-    const int64_t stride = int64_t(gridDim.x) * kBlockRows;
-    int64_t row0 = int64_t(blockIdx.x) * kBlockRows;
-    Block even, odd;
-    load_block(row0, even);
     for (; row0 + stride < M; row0 += 2 * stride) {
         load_block(row0 + stride, odd);
         work(row0, even);

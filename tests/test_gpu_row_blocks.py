@@ -13,10 +13,12 @@ from tests.test_gpu_parity import DTYPE_IDS, DTYPES, TOL, M, canon, npy, relerr,
 
 pytestmark = pytest.mark.gpu
 
-# rows of a round of workgroups (backward / forward): 65536 / 49152 at 8 columns, 16384 / 12288 at 192 and 256, 8192 / 6144 at 384 and 512,
-# 4096 / 6144 at 768, 4096 / 6144 at 1024, - / 3072 at 1280
-SHAPES = [(65537, 8, 1), (98303, 8, 1), (16385, 192, 3), (12287, 256, 4), (24577, 192, 3), (8193, 384, 6), (12289, 512, 8), (16383, 384, 6), (4097, 768, 12),
-          (12291, 768, 12), (6143, 768, 12), (8195, 1024, 16), (3073, 1280, 5), (6145, 1280, 5)]
+# rows of a round of workgroups (backward / forward): 65536 / 49152 at 8 columns, 16384 / 24576 at 192 and / 12288 at 256, 8192 / 12288 at 384 and / 6144 at 512,
+# 4096 / 6144 at 768 and 1024 (forward in binary32 3072 at 1024), - / 3072 at 1280, - / 2048 beyond 1536.  Below a round the forward of rows that come one per lane
+# group and block (three and four vectors per lane, two in binary32) has two blocks per workgroup already.
+SHAPES = [(65537, 8, 1), (98303, 8, 1), (16385, 192, 3), (12287, 256, 4), (24577, 192, 3), (49153, 192, 3), (73729, 192, 3), (8193, 384, 6), (24593, 384, 6), (36865, 384, 6), (12289, 512, 8),
+          (16383, 384, 6), (4097, 768, 12), (12291, 768, 12), (18433, 768, 12), (6143, 768, 12), (8195, 1024, 16), (9219, 1024, 16), (3073, 1280, 5), (6145, 1280, 5), (9217, 1280, 5), (1025, 2048, 8),
+          (4099, 2048, 8), (4097, 1600, 5), (6145, 1544, 1)]
 
 
 def between(t, fill=3.0):
