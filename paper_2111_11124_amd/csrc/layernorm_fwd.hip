@@ -74,9 +74,11 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
     const int64_t stride = int64_t(gridDim.x) * kBlockRows;
     int64_t row0 = int64_t(blockIdx.x) * kBlockRows;
     Block even, odd;
-    // ahead of everything else that this workgroup waits for, which with a block or two per workgroup is most of its time: behind the parameters -> ahead of them
-    // 6141 x 1024 binary16 14.5 -> 13.3 us, 18429 x 128 binary32 11.2 -> 10.1, 14742 x 192 13.2 -> 12.7, 9213 x 768 23.1 -> 22.8
-    load_block(row0, even);
+    // Ahead of everything else that this workgroup waits for, which with a block or two per workgroup is most of its time: behind the parameters -> ahead of them
+    // 6141 x 1024 binary16 14.4 -> 13.3 us, 25216 x 384 16.9 -> 16.4, 18429 x 128 binary32 11.2 -> 10.1, 14742 x 192 13.2 -> 12.7; with three blocks and more 16-bit rows
+    // lose some tenths (18429 x 1024 25.4 -> 25.8, 50432 x 768 42.7 -> 42.9), binary32 gains still (73725 x 128 23.8 -> 23.5, 50432 x 768 80.8 -> 78.7).
+    const bool ahead = sizeof(T) == 4 || 2 * M < 5 * stride;
+    if (ahead) load_block(row0, even);
 
     __shared__ int lmn[kLfMaxGroups], lmx[kLfMaxGroups];
     for (uint32_t g = threadIdx.x; g < groups; g += kThreads) {
@@ -184,6 +186,7 @@ __global__ __launch_bounds__(kThreads, lf_wg_per_cu(VPL)) void k_layernorm_fwd(c
             }
         }
     };
+    if (!ahead) load_block(row0, even);
     for (; row0 + stride < M; row0 += 2 * stride) {
         load_block(row0 + stride, odd);
         work(row0, even);
