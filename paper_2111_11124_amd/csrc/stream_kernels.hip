@@ -326,7 +326,7 @@ template <typename T>
 __device__ __forceinline__ bool scan_keeps(int64_t numel)
 {
     const int64_t bytes = numel * int64_t(sizeof(T));
-    return bytes >= 18000000 && bytes <= (sizeof(T) == 4 ? 120000000 : 75000000);
+    return bytes >= 18000000 && bytes <= (sizeof(T) == 4 ? 120000000 : 80000000);
 }
 template <typename T, int U>
 __device__ __forceinline__ void scan_load(const void *__restrict__ x, int64_t base, bool keep, typename Store<T>::raw_t (&v)[U])
