@@ -1795,8 +1795,8 @@ template <int DT> struct NrCfg {
 
 template <int DT, bool ANY, typename ET>
 __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__restrict__ dS, const int8_t *__restrict__ kq,
-                                                              _Float16 *__restrict__ dQ, int N, int heads, int tiles_i, float scale,
-                                                              const float *__restrict__ alpha_k, const float *__restrict__ beta_k)
+                                                              _Float16 *__restrict__ dQ, int N, int heads, int tiles_i, int turns,
+                                                              float scale, const float *__restrict__ alpha_k, const float *__restrict__ beta_k)
 {
     typedef NrCfg<DT> C;
     __shared__ __attribute__((aligned(16))) unsigned char lds_nr[C::kLds];
@@ -1818,11 +1818,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_attn_nn_rows(const _Float16 *__
         const int v = tid + k * kThreads, r = v / C::kVecRowS;
         s_src[k] = ((r < rows ? r : rows - 1) * N + (v % C::kVecRowS) * 8) * 2;
     }
-    // Rows of a multiple of 2 KB put the same columns of all rows on the same memory channels, where workgroups in step met; so the row tiles of a head start
-    // at sixteen places and come round (by the tile and not the workgroup: a head's sums are taken in the same order wherever it stands in the batch).  dQ and dK on new
-    // inputs each time, (16, 1, 4096, 64) 215 -> 194 us, (36, 1, 2048, 64) 139 -> 128, of 32 127 -> 112, (9, 1, 4096, 128) 188 -> 184, (16, 1, 3072, 64) 119 -> 116, (7, 1, 6144, 64)
-    // 218 -> 212; (29, 1, 3072, 64) 230 -> 232.  Rows of other multiples of 64, and of 1024, gain nothing: 1088 to 2112 -1 to +1 %, shorter ones up to 2 % behind.
-    const int start = N % 1024 == 0 && N >= 2048 ? i0 / 64 % 16 * nchunks / 16 : 0;
+    // turns (nn_rows_turns): the row tiles of a head start at sixteen places and come round.  By the tile and not the workgroup: a head's sums are taken in the same order wherever
+    // it stands in the batch.
+    const int start = turns ? i0 / 64 % 16 * nchunks / 16 : 0;
     auto load_chunk = [&](int c, auto set_) {
         constexpr int S = decltype(set_)::value;
         c += start;
@@ -1941,14 +1939,21 @@ static bool nn_rows_fits(int64_t batches, int64_t N, int64_t Dh)
     return N >= 64 && batches * ceil_div(N, 64) < (int64_t(1) << 31);
 }
 
+// Whether the row tiles of a head start at different columns.  Rows of a multiple of 2 KB put the same columns of all rows on the same memory channels, where workgroups in
+// step met: dQ and dK on new inputs each time (16, 1, 4096, 64) 215 -> 196 us, (36, 1, 2048, 64) 143 -> 130, (64, 1, 2048, 32) 211 -> 195, the whole attention backward 561 -> 543,
+// 368 -> 356, 557 -> 542, of (7, 1, 6144, 64) 726 -> 718, (16, 1, 3072, 64) 332 -> 331.  A larger dS gains by the memory-side cache what workgroups in step leave there for each other: 670 MB
+// (20, 1, 4096, 64) 265 -> 258, 805 MB (96, 1, 2048, 64) 318 -> 310 and (24, 1, 4096, 64) 314 -> 316, above (32, 1, 4096, 64) 385 -> 392, (128, 1, 2048, 64) 406 -> 413, (128, 1, 4096, 64) 1564 -> 1587.
+// Rows of other multiples of 64, and of 1024, gain nothing: 1088 to 2112 -1 to +1 %, shorter ones up to 2 % behind.
+static bool nn_rows_turns(int64_t batches, int64_t N) { return N % 1024 == 0 && N >= 2048 && batches * N * N * 2 <= 750000000; }
+
 template <typename ET>
 static void launch_nn_rows(const _Float16 *dS, const int8_t *kq, _Float16 *dQ, int64_t batches, int N, int Dh, int heads, float scale,
                            const float *alpha_k, const float *beta_k, hipStream_t s)
 {
-    const int tiles_i = int(ceil_div(N, 64));
+    const int tiles_i = int(ceil_div(N, 64)), turns = nn_rows_turns(batches, N);
     const dim3 grid(unsigned(batches * tiles_i));
 #define MESA_LAUNCH_NR(DT_, ANY_) \
-    hipLaunchKernelGGL((k_attn_nn_rows<DT_, ANY_, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, scale, alpha_k, beta_k)
+    hipLaunchKernelGGL((k_attn_nn_rows<DT_, ANY_, ET>), grid, dim3(kThreads), 0, s, dS, kq, dQ, N, heads, tiles_i, turns, scale, alpha_k, beta_k)
 #define MESA_LAUNCH_NR_A(DT_) do { if (N % 8 == 0) MESA_LAUNCH_NR(DT_, false); else MESA_LAUNCH_NR(DT_, true); } while (0)
     if (Dh == 32) MESA_LAUNCH_NR_A(1);
     else if (Dh == 64) MESA_LAUNCH_NR_A(2);

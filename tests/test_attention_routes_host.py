@@ -120,17 +120,32 @@ def test_dv_goes_first_beside_a_da_as_large_as_the_memory_side_cache():
         assert len(av) == 2 and got == first[shape], (shape, av)
 
 
-# for `also`: whether a launch of k_attn_da_cols stores non-temporally, its eighth argument
-STREAMS = r'''
-static int streams_[64];
+# for `also`: an argument of a launch that says how its kernel goes about the memory: k_attn_da_cols' eighth (stores past the caches), k_attn_nn_rows' seventh (tiles start at
+# different columns); -1 for other kernels
+HOW = r'''
+static int how_[64];
 void launched(int at, const void *f, void **args)
 {
-    streams_[at] = -1;
-    for (int k = 0; k < known_n; ++k)
-        if (known[k].f == f && strstr(known[k].name, "14k_attn_da_cols")) streams_[at] = *(int *)args[7];
+    how_[at] = -1;
+    for (int k = 0; k < known_n; ++k) {
+        if (known[k].f != f) continue;
+        if (strstr(known[k].name, "14k_attn_da_cols")) how_[at] = *(int *)args[7];
+        if (strstr(known[k].name, "14k_attn_nn_rows")) how_[at] = *(int *)args[6];
+    }
 }
-int recorded_streams(int i) { return streams_[i]; }
+int recorded_how(int i) { return how_[i]; }
 '''
+
+
+def how(call, shapes):
+    got = run(r'''
+out = []
+for b, N, Dh in ''' + repr(list(shapes)) + r''':
+    assert (''' + call + r''') == M.OK
+    out.append(max(rec.recorded_how(i) for i in range(len(launches()))))
+report(out)
+''', NAMES + HOW)
+    return dict(zip(shapes, got))
 
 
 def test_da_by_tiles_leaves_past_the_caches_by_its_real_size():
@@ -140,14 +155,16 @@ def test_da_by_tiles_leaves_past_the_caches_by_its_real_size():
             (5, 4096, 64): 0, (6, 4096, 64): 1, (64, 1152, 64): 0, (65, 1152, 64): 1, (2170, 96, 64): 0, (10851, 96, 64): 0, (399, 224, 64): 0, (90, 288, 64): 1, (562, 320, 32): 1, (324, 448, 64): 1,
             (25, 480, 64): 1, (227, 480, 64): 1, (229, 480, 64): 0, (336, 480, 64): 0, (337, 480, 64): 1, (131, 704, 96): 1, (166, 576, 128): 1, (20, 2016, 64): 0, (23, 2016, 64): 1,
             (51, 656, 64): 0, (192, 577, 64): 0}
-    got = run(r'''
-out = []
-for b, N, Dh in ''' + repr(list(want)) + r''':
-    assert L.mesa_attn_av_bwd_q(P, P, 1, b, N, Dh, P, P, P, P, P, P, P, M.BF16, None) == M.OK
-    out.append(max(rec.recorded_streams(i) for i in range(len(launches()))))
-report(out)
-''', NAMES + STREAMS)
-    assert dict(zip(want, got)) == want, {s: g for s, g in zip(want, got) if want[s] != g}
+    got = how("L.mesa_attn_av_bwd_q(P, P, 1, b, N, Dh, P, P, P, P, P, P, P, M.BF16, None)", want)
+    assert got == want, {s: g for s, g in got.items() if want[s] != g}
+
+
+def test_dq_by_tiles_starts_at_different_columns_where_rows_meet_on_the_same_channels():
+    """Rows of a multiple of 1024 elements from 2048 on, of a dS of up to 750 MB."""
+    want = {(16, 4096, 64): 1, (22, 4096, 64): 1, (23, 4096, 64): 0, (128, 4096, 64): 0, (36, 2048, 32): 1, (89, 2048, 64): 1, (90, 2048, 64): 0, (16, 3072, 64): 1, (9, 4096, 128): 1, (10, 5120, 32): 1,
+            (67, 1024, 64): 0, (34, 2112, 64): 0, (17, 1536, 96): 0, (9, 4160, 64): 0, (114, 512, 64): 0, (150, 320, 64): 0, (64, 601, 32): 0}
+    got = how("L.mesa_attn_qk_bwd_q(P, P, 1, b, N, Dh, P, P, P, P, P, 0.2, P, P, M.BF16, None)", want)
+    assert got == want, {s: g for s, g in got.items() if want[s] != g}
 
 
 def test_the_gpu_tests_reach_every_kernel_of_the_products():
