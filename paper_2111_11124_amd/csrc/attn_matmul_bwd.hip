@@ -2262,11 +2262,13 @@ extern "C" MESA_EXPORT mesa_status mesa_attn_av_bwd_q(const int8_t *aq, const in
 #undef MESA_AV_DV
     // dV, bound by its reads, goes first where dA is about as large as the memory-side cache (256 MB) and more: a dA just written is still leaving that cache
     // while the next kernel reads, and softmax behind it, which would find a smaller one there, finds little of this one.  The whole attention backward on new inputs each time,
-    // dA first -> dV first us, kept: (315, 577, 64) 316 -> 305, (102, 1127, 64) 355 -> 337, (1680, 250, 64) 347 -> 342, (2706, 197, 64) 388 -> 386; non-temporally (da_streams):
-    // (8, 4096, 64) 331 -> 319, (14, 4096, 64) 505 -> 482, (124, 1024, 128) 405 -> 380, (405, 544, 64) 361 -> 342, (572, 512, 64) 401 -> 393, (1447, 288, 32) 340 -> 333, but (2411, 288, 64)
-    // +1.5 %, (747, 448, 96) 461 -> 468.  Not where rows of up to 256 elements leave non-temporally: (1831, 256, 96) 417 -> 425, (2518, 256, 64) 473 -> 476, (14648, 128, 64) 913 -> 919.
+    // dA first -> dV first us, kept: (315, 577, 64) 317 -> 306, (102, 1127, 64) 354 -> 337, (1680, 250, 64) 346 -> 341, (2706, 197, 64) 386 -> 385.  One that leaves non-temporally
+    // (da_streams) gains as long as dO and the rest stay in reach, up to some 600000 rows: (8, 4096, 64) 331 -> 319, (16, 4096, 64) 580 -> 560, (66, 4096, 64) 2708 -> 2700,
+    // (124, 1024, 64) 307 -> 297, (477, 1024, 64) 1212 -> 1202, (760, 544, 64) 658 -> 634, (1567, 288, 32) 385 -> 373; with more (1049, 1024, 64) 2692 -> 2715, (1221, 640, 64) 1288 -> 1299,
+    // (2219, 352, 64) 860 -> 880, (3315, 288, 64) 944 -> 960; rows of up to 256 elements never: (1831, 256, 96) 410 -> 417, (6104, 256, 64) 1135 -> 1149, (14648, 128, 64) 905 -> 910.
     // binary32 either way at any size: (4, 12, 1024, 64), 201 MB, 285 -> 292, (1, 6, 4096, 64), 403 MB, 588 -> 582.
-    if (dt != MESA_F32 && batches * N * N >= 115000000 && (N > 256 || !da_streams(batches, N, Dh))) {
+    const bool dv_first = dt != MESA_F32 && batches * N * N >= 115000000 && (!da_streams(batches, N, Dh) || (N > 256 && batches * N <= 600000));
+    if (dv_first) {
         dv();
         da();
     } else {

@@ -114,7 +114,8 @@ def test_few_heads_by_waves_only_where_that_is_faster():
 def test_dv_goes_first_beside_a_da_as_large_as_the_memory_side_cache():
     first = {(1, 7, 4096, 64, "bf16"): "dV", (1, 8, 4096, 64, "bf16"): "dV", (32, 12, 577, 64, "f16"): "dV", (256, 12, 250, 64, "f16"): "dV", (8, 12, 1024, 64, "f16"): "dA",
              (1, 6, 4096, 64, "bf16"): "dA", (1, 16, 4096, 64, "f32"): "dA",
-             (1, 1831, 256, 96, "f16"): "dA", (12, 1221, 128, 64, "bf16"): "dA", (1, 5182, 224, 64, "f16"): "dV", (1, 1447, 288, 32, "f16"): "dV"}   # of up to 256 elements not if dA leaves non-temporally
+             (1, 1831, 256, 96, "f16"): "dA", (12, 1221, 128, 64, "bf16"): "dA", (1, 5182, 224, 64, "f16"): "dV", (1, 1447, 288, 32, "f16"): "dV",   # of up to 256 elements not if dA leaves non-temporally
+             (1, 2219, 352, 64, "f16"): "dA", (1, 549, 640, 64, "bf16"): "dV", (1, 1221, 640, 64, "bf16"): "dA", (1, 128, 4096, 64, "f16"): "dV", (1, 3840, 250, 64, "f16"): "dV"}   # nor of more than 600000
     for shape, (av, _) in routes(list(first)).items():
         got = "dV" if av[0][0] == "k_attn_tn_cols" or av[0][1].startswith("Lb1") else "dA"
         assert len(av) == 2 and got == first[shape], (shape, av)
