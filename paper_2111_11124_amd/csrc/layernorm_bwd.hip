@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads, ln_rows_wg_per_cu(sizeof(T), VPL)) void k
     // conditional: lanes without a vector and rows past the end are out of their span's bounds, load zeros (dy = 0 adds nothing to
     // any sum) and store nothing, and so does a whole block past the end.  (With a branch around each access the wait for a block was a
     // wait for the stores of the block before it, and for the next block's loads: 50432 x 768 binary16, new inputs each time, 44.9 -> 40.8 us
-    // for the call, 100000 x 512 55.0 -> 51.7, 25000 x 640 26.5 -> 24.4, 200000 x 128 31.4 -> 29.2; 100000 x 1024 1 % behind.  Waiting for the stores by
+    // for the call, 100000 x 512 55.0 -> 51.7, 25000 x 640 26.5 -> 24.4, 200000 x 128 31.4 -> 29.2, 100000 x 1024 94.7 -> 93.1.  Waiting for the stores by
     // hand gives the former times.)  What bounds it now is HBM: 194 MB in 37 us and the dependent launch.
     struct Block {
         u32x2 cq[U][VPL];
